@@ -15,7 +15,7 @@ OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnadmm.so")
 
 SOURCES = ["nadmm_api.hip", "nadmm_generic.hip", "nadmm_vec.hip", "nadmm_fused.hip", "nadmm_thin.hip", "nadmm_sliced.hip",
-           "nadmm_admm.hip", "nadmm_sparse.hip"]
+           "nadmm_wide.hip", "nadmm_admm.hip", "nadmm_sparse.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -36,7 +36,7 @@ def _compile(src):
     return src, obj, res
 
 
-def build(verbose=True, jobs=4):
+def build(verbose=True, jobs=8):
     os.makedirs(OBJDIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         results = list(ex.map(_compile, SOURCES))

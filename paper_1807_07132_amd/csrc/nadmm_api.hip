@@ -29,13 +29,15 @@ struct Layout {
   size_t drows, pcache, zx, zp;
   size_t partial, partial2, loss_part, lpart, dotpart, rrpart, headpart, zw;
   size_t pack, win_rows, win_cols;  // sparse storage: packed dense operand, windows of the two views
+  size_t operands;    // wide single pass: the packed operands of a call
   size_t total;       // with the history of directional logits (hist_bufs of them), which comes last
   size_t total_base;  // without it
   size_t hist;
   int hist_bufs;
   int gen_row_blocks, gen_slabs, gen_chunks, gen_rpc;
-  int fused_parts, thin_parts, sliced_parts, sliced_loss;
+  int fused_parts, thin_parts, sliced_parts, sliced_loss, wide_parts;
   bool fused_ok, thin_ok, sliced_ok;
+  bool wide;     // path 4 makes its sweeps with a transpose product in a single pass (nadmm_wide.hip)
   bool mc_auto;  // the matrix-core paths are also the automatic choice (see kAnyStrideMinP)
   bool sparse;
   int nwin_rows, nwin_cols;
@@ -75,7 +77,8 @@ int validate_problem(const nadmm_problem* p, bool need_labels) {
 // side share the compute units; each then keeps the long row ranges per workgroup that amortise a launch).
 // max_cg > 0: room for the directional logits A d_k of that many CG iterations, if the fused single-pass path is the
 // one a solve would take and keeping them is cheaper than the pass over A they replace (see local_newton_enqueue).
-void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg_cap = 0, int max_cg = 0) {
+// no_wide: the two-sweep kernels only (their partial sums take less room).
+void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg_cap = 0, int max_cg = 0, bool no_wide = false) {
   Shape s;
   s.n = p->n;
   s.p = p->p;
@@ -120,7 +123,10 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
     sliced_grid(s, &S2, &sps, &L->sliced_parts);  // partial sums per row group
     L->sliced_loss = sliced_loss_blocks(s);       // partial row losses per workgroup of sweep 1
   }
+  L->wide = L->sliced_ok && !no_wide && wide_supported(s, p->lda, p->d_A);
+  L->wide_parts = L->wide ? wide_num_partials(s, wg_cap) : 0;
   int parts = L->gen_chunks > L->fused_parts ? L->gen_chunks : L->fused_parts;
+  if (L->wide_parts > parts) parts = L->wide_parts;
   if (L->sliced_parts > parts) parts = L->sliced_parts;
   if (L->thin_parts > parts) parts = L->thin_parts;
   L->partial = off; off += align256((size_t)parts * s.d * sizeof(float));
@@ -129,6 +135,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   int lblocks = L->gen_row_blocks > L->fused_parts ? L->gen_row_blocks : L->fused_parts;
   if (L->thin_parts > lblocks) lblocks = L->thin_parts;
   if (L->sliced_loss > lblocks) lblocks = L->sliced_loss;
+  if (L->wide_parts > lblocks) lblocks = L->wide_parts;
   L->loss_part = off; off += hv_only ? 0 : align256((size_t)lblocks * sizeof(double));
   L->lpart = off; off += hv_only ? 0 : align256((size_t)ls_eval_blocks(s.n) * kCandSlots * sizeof(double));
   L->dotpart = off; off += hv_only ? 0 : align256((size_t)2 * reduce_out_blocks(s.d) * sizeof(double));  // two sums per workgroup
@@ -138,6 +145,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->headpart = off; off += hv_only ? 0 : align256((size_t)2 * reduce_out_blocks(s.d) * sizeof(double));
   // the logits [Z | W] of the sparse path
   L->zw = off; off += align256(L->sparse ? (size_t)s.n * 2 * s.NC * sizeof(float) : 0);
+  L->operands = off; off += L->wide ? align256(wide_operand_bytes(s)) : 0;
   L->pack = off;
   L->win_rows = off;
   L->win_cols = off;
@@ -227,8 +235,10 @@ int choose_path(const Layout& L, int* path) {
   return NADMM_OK;
 }
 
-int loss_blocks(const Layout& L, int path) {
-  return path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : (path == 4 ? L.sliced_loss : L.gen_row_blocks));
+// partial row losses that a sweep leaves (with_cols: one that also forms A^T rows)
+int loss_blocks(const Layout& L, int path, bool with_cols) {
+  if (path == 4) return (with_cols && L.wide) ? L.wide_parts : L.sliced_loss;
+  return path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : L.gen_row_blocks);
 }
 
 SparseView row_view(const nadmm_problem* prob) {
@@ -318,6 +328,11 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
     return NADMM_OK;
   }
   if (path == 4) {
+    if (with_cols && L.wide && wide_takes(L.s, ra.B0 != nullptr, ra.B1 != nullptr)) {
+      NADMM_HIP(launch_wide(ra, at<char>(ws, L.operands), at<float>(ws, L.partial), L.wide_parts, st));
+      *nparts = L.wide_parts;
+      return NADMM_OK;
+    }
     NADMM_HIP(launch_sliced_logits(ra, st));
     if (with_cols) {
       NADMM_HIP(launch_sliced_cols(ra, ra.rows_out, at<float>(ws, L.partial), st));
@@ -489,7 +504,7 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
   cu.rr_part = at<double>(ws, L.rrpart);
   cu.d = L.s.d;
   cu.tol = tol;
-  const int parts = path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : (path == 4 ? L.sliced_parts : L.gen_chunks));
+  const int parts = path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : (path == 4 ? (L.wide_parts > L.sliced_parts ? L.wide_parts : L.sliced_parts) : L.gen_chunks));
   if (cg_fused_tail_supported(L.s.d, parts)) {
     int nparts = 0;
     int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, nullptr, nullptr, &ds->cg_active, &nparts, st);
@@ -574,7 +589,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     std::memset(&nh, 0, sizeof(nh));
     nh.st = ds;
     nh.loss_part = at<double>(d_ws, L.loss_part);
-    nh.nblocks = loss_blocks(L, path);
+    nh.nblocks = loss_blocks(L, path, true);
     nh.scale = prob->loss_scale;
     nh.lambda = prob->lambda;
     nh.rho = prob->rho;
@@ -814,7 +829,7 @@ int nadmm_loss_grad(const nadmm_problem* prob, const float* d_X, double* d_loss,
     ReduceArgs rg = reduce_args(prob, L, d_ws, nparts, 1, d_X, d_grad, nullptr, nullptr);
     if (L.s.d <= kReduceFinishMax) {  // short vectors: the objective is finished by a workgroup of the same launch
       rg.lf_loss_part = at<double>(d_ws, L.loss_part);
-      rg.lf_nblocks = loss_blocks(L, path);
+      rg.lf_nblocks = loss_blocks(L, path, true);
       rg.lf_loss_out = d_loss;
       NADMM_HIP(launch_reduce_out(rg, st));
       return NADMM_OK;
@@ -825,7 +840,7 @@ int nadmm_loss_grad(const nadmm_problem* prob, const float* d_X, double* d_loss,
 
   LossFinishArgs lf;
   lf.loss_part = at<double>(d_ws, L.loss_part);
-  lf.nblocks = loss_blocks(L, path);
+  lf.nblocks = loss_blocks(L, path, d_grad != nullptr);
   lf.scale = prob->loss_scale;
   lf.lambda = prob->lambda;
   lf.rho = prob->rho;
@@ -857,10 +872,17 @@ int nadmm_hessvec(const nadmm_problem* prob, const float* d_X, const float* d_V,
 
 size_t nadmm_static_scratch_bytes(void) { return NADMM_STATIC_SCRATCH_BYTES; }
 
+// Scratch of a Hessian-vector product in the built-in buffer: the single-pass kernels for wide rows are left out where
+// only the two-sweep kernels' partial sums fit it.
+static void static_layout(const nadmm_problem* prob, Layout* L) {
+  make_layout(prob, L, true);
+  if (L->wide && L->total > (size_t)NADMM_STATIC_SCRATCH_BYTES) make_layout(prob, L, true, 0, 0, true);
+}
+
 size_t nadmm_hessvec_static_bytes(const nadmm_problem* prob) {
   if (validate_problem(prob, false) != NADMM_OK) return 0;
   Layout L;
-  make_layout(prob, &L, true);
+  static_layout(prob, &L);
   return L.total;
 }
 
@@ -869,7 +891,7 @@ int nadmm_hessvec_static(const nadmm_problem* prob, const float* d_X, const floa
   if (rc != NADMM_OK) return rc;
   if (d_X == nullptr || d_V == nullptr || d_HV == nullptr) return NADMM_EINVAL;
   Layout L;
-  make_layout(prob, &L, true);
+  static_layout(prob, &L);
   if (L.total > (size_t)NADMM_STATIC_SCRATCH_BYTES) return NADMM_ESCRATCH;  // before any device call: host-testable
   int path = 0;
   if ((rc = choose_path(L, &path)) != NADMM_OK) return rc;

@@ -360,6 +360,14 @@ int sliced_loss_blocks(const Shape& s);
 hipError_t launch_sliced_logits(const RowArgs& a, hipStream_t st);
 hipError_t launch_sliced_cols(const RowArgs& a, const float* rows_in, float* partial, hipStream_t st);
 
+// ---- single-pass matrix-core kernel for wide rows (nadmm_wide.hip): the sweeps of that path that form A^T rows ----
+bool wide_supported(const Shape& s, int64_t lda, const void* A);
+bool wide_takes(const Shape& s, bool has_x, bool has_v);  // whether it makes the sweep with these operands (else two sweeps)
+int wide_num_partials(const Shape& s, int wg_cap);   // workgroups, at most wg_cap if that is > 0
+size_t wide_operand_bytes(const Shape& s);
+// packs the operands into `operands` and makes the sweep; partial sums and partial losses as launch_fused
+hipError_t launch_wide(const RowArgs& a, void* operands, float* partial, int nparts, hipStream_t st);
+
 // ---- sparse storage of A (nadmm_sparse.hip) ----
 // compressed rows of an nrows x ncols matrix; used for A (row view) and for A^T (column view of A)
 struct SparseView {

@@ -1,0 +1,616 @@
+// Single-pass matrix-core kernel for wide rows and for 17 to 32 free classes (gfx950): rows pass and transpose product in
+// one sweep over A, where the fused kernel (p <= 960, C-1 <= 16) cannot hold a row's operands and accumulators.
+//
+// What bounds it: the stream of A from memory.  The column-sliced kernels read A twice, because the tile of a row range
+// has to wait for D, which needs the whole row, and they keep a slice's operands in registers.  Here a workgroup of 8 waves
+// owns a range of rows and walks it in tiles of 16 rows, and
+//   * the accumulators of A^T D of ALL columns stay in registers (8 per step of 32 columns, block of 16 classes and wave);
+//   * the tile stays on the chip, as bf16 high and low parts, between the product with [X|V] and the product with D: 2 KB
+//     of LDS per step, and in registers for the steps beyond LS per wave;
+//   * the operands [X|V] are not resident: they are split and laid out once per call (pack_operands_kernel) and stream from
+//     the L2 beside the rows of A.  Loads return in order, so A and operands form ONE stream that runs D steps ahead across
+//     the tiles: a wait for a step's operands never waits for rows that were requested later.
+// Wave w owns a contiguous run of steps in both products.  Per tile: the K-split partials of the logits are exchanged
+// through LDS, every wave adds up all of them and forms the rows of D for itself (it needs all 16 rows as an operand), so
+// that D is never exchanged.  The transposed operand of the second product comes from LDS by transposing reads
+// (ds_read_b64_tr_b16): the rows are written as they are, in 16-byte pieces.
+// With 16 rows a tile half of the K = 32 slots of a matrix instruction would be empty: high and low part of the same rows
+// take one half each, so two instructions give all four terms of (Dhi + Dlo)(Ahi + Alo).
+// The product of a tile with its D is taken together with the conversion of the next tile, step by step, so that the stream
+// only pauses for the K-split exchange and the rows.
+// Measured against two sweeps (with the other kernels of the call): CG iteration on 50000 x 3072, C = 10: 227 -> 162 us (sweep
+// 141 us, 4.4 TB/s), on 75000 x 2048, C = 10 with resident operands: 240 -> 152 us (sweep 112 us, 5.5 TB/s, the rate at which a
+// plain read streams here); 250000 x 2000, C = 20: 772 -> 550 us.  Streamed operands cost 64 bytes per step, class and part
+// from the L2 next to 2 KB of A.
+#include "nadmm_internal.h"
+#include "nadmm_cgstep.h"
+#include "nadmm_mfma.h"
+
+namespace nadmm {
+namespace {
+
+using namespace mfma_detail;
+
+constexpr int kThreads = 512;
+constexpr int kWaves = 8;
+constexpr int kTileRows = 16;
+constexpr int kStepCols = 32;
+constexpr int kSlotBytes = 2048;   // one step of a tile: 16 rows x 32 columns, high plane and low plane
+constexpr int kMaxSteps1 = 96;     // C-1 <= 16: 12 steps per wave
+constexpr int kMaxSteps2 = 64;     // C-1 <= 32: 8 steps per wave
+constexpr int kMaxLdsSlots = 8;    // steps per wave whose tile stays in LDS
+
+struct WideArgs {
+  RowArgs r;
+  const char* op;       // packed operands, see pack_operands_kernel
+  float* partial;       // gridDim.x x (p*NC)
+  int32_t steps;        // ceil(p / 32)
+  int32_t rows_per_wg;
+};
+
+// Columns of a step in the k-slots of the matrix instructions: slot e of k-group kg.  Two pieces of four consecutive
+// columns, so that the four lanes of a row fetch 64 consecutive bytes with one load instruction (with 8 consecutive columns
+// per lane every load instruction touched both halves of 16 cache lines).
+__device__ __forceinline__ int column_of(int kg, int e) { return 16 * (e >> 2) + 4 * kg + (e & 3); }
+
+// The operands of a call as the matrix instructions read them.  Per step of 32 columns, class and part one run of 64 bytes:
+// the 8 columns of each of the four k-groups in bf16.  Order: [step][block of 16 classes][part][class][k-group];
+// parts: X in three (full float32 accuracy of the logits), V in two; columns past p are zero.
+__global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restrict__ X, const float* __restrict__ V, int p, int NC,
+                                                            int steps, char* __restrict__ dst, const int32_t* flag) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int per_step = NC * 4;
+  if (t >= steps * per_step) return;
+  const int s = t / per_step, rest = t - s * per_step;
+  const int cls = rest % NC, kg = rest / NC;   // neighbouring threads read neighbouring classes
+  const int nb = cls >> 4, c = cls & 15;
+  const int ncls = nb == 0 ? (NC < 16 ? NC : 16) : NC - 16;
+  const int parts = (X != nullptr ? 3 : 0) + (V != nullptr ? 2 : 0);
+  float x[8], v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int j = kStepCols * s + column_of(kg, e);
+    const size_t at = (size_t)(j < p ? j : p - 1) * NC + cls;
+    const float xv = X != nullptr ? X[at] : 0.f, vv = V != nullptr ? V[at] : 0.f;
+    x[e] = j < p ? xv : 0.f;
+    v[e] = j < p ? vv : 0.f;
+  }
+  if (flag != nullptr && *flag == 0) return;
+  char* base = dst + ((size_t)s * NC + 16 * nb) * parts * 64 + (size_t)c * 64 + kg * 16;
+  const size_t stride = (size_t)ncls * 64;  // from part to part
+  int k = 0;
+  if (X != nullptr) {
+    u32x4 a, b, d;
+    split8_3(x, a, b, d);
+    *reinterpret_cast<u32x4*>(base) = a;
+    *reinterpret_cast<u32x4*>(base + stride) = b;
+    *reinterpret_cast<u32x4*>(base + 2 * stride) = d;
+    k = 3;
+  }
+  if (V != nullptr) {
+    u32x4 a, b;
+    split8(v, a, b);
+    *reinterpret_cast<u32x4*>(base + k * stride) = a;
+    *reinterpret_cast<u32x4*>(base + (k + 1) * stride) = b;
+  }
+}
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// Transposing read: the 16 lanes of a group name the 8-byte pieces of a block of 4 rows x 16 columns of 16-bit values (lane
+// i: row i / 4, columns 4 (i % 4) ..), lane i receives the 4 rows of column i.
+__device__ __forceinline__ u32x2 read_transposed(char* at) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at));
+}
+
+// The operands of all of a wave's steps stay in registers where they fit beside the accumulators (4 registers per step, class
+// block and part, 8 per step and class block, and two steps of A in flight); else they stream.  The stream costs: at
+// 75000 x 2048, C = 10 a sweep with V took 130 us with streamed operands (C = 3: 110 us, the rate of the memory).
+template <int SPW, int NB, bool HAS0, bool HAS1>
+__host__ __device__ constexpr bool operands_resident() {
+  return 4 * SPW * NB * ((HAS0 ? 3 : 0) + (HAS1 ? 2 : 0)) + 8 * SPW * NB + 8 * (SPW > kMaxLdsSlots ? SPW - kMaxLdsSlots : 0) + 16 <= 176;
+}
+
+// SPW: step slots per wave; D: steps in flight (divides SPW); LS: step slots whose tile stays in LDS; NB: blocks of 16 classes.
+template <int SPW, int D, int NB, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
+__global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
+  static_assert(SPW % D == 0, "the stream's slots repeat with the tiles");
+  const RowArgs& a = wa.r;
+  if (a.flag != nullptr && *a.flag == 0) return;
+  constexpr int LS = SPW < kMaxLdsSlots ? SPW : kMaxLdsSlots;
+  constexpr int RS = SPW - LS;                       // steps of the tile held in registers
+  constexpr int kMats = (HAS0 ? 1 : 0) + (HAS1 ? 1 : 0);
+  constexpr int kQuads = kMats * NB;
+  constexpr int kMatW = HAS0 ? 1 : 0;
+  constexpr int PX = HAS0 ? 3 : 0, PARTS = PX + (HAS1 ? 2 : 0);
+  constexpr bool RES = operands_resident<SPW, NB, HAS0, HAS1>();
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = lane & 15, kg = lane >> 4;
+  const int NC = a.NC, p = a.p;
+  constexpr int kSlots = LS + (RS > 0 ? 1 : 0);      // one more, through which the steps held in registers are transposed
+  char* slots = lds + (size_t)wave * kSlots * kSlotBytes;
+  f32x4* part = reinterpret_cast<f32x4*>(lds + (size_t)kWaves * kSlots * kSlotBytes);  // [wave][matrix, class block][lane]
+
+  // steps of this wave: a contiguous, balanced run
+  const int step0 = (wave * wa.steps) >> 3;
+  const int count = (((wave + 1) * wa.steps) >> 3) - step0;  // SPW - 2 .. SPW
+  const int col_max = ANY ? p - 4 : ((p + 3) & ~3) - 4;  // the last column a 16-byte piece is fetched from
+
+  const int64_t r_begin = (int64_t)blockIdx.x * wa.rows_per_wg;
+  int64_t r_end = r_begin + wa.rows_per_wg;
+  if (r_end > a.n) r_end = a.n;
+
+  f32x4 acc[SPW][2][NB];
+#pragma unroll
+  for (int i = 0; i < SPW; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[i][h][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  double loss_acc = 0.0;
+
+  // ---- the stream: rows of A and operands of one step ----
+  float4 pf[D][2];
+  u32x4 ob[RES ? SPW : D][NB][PARTS];
+  // operand offsets of this lane: padded class lanes read the block's last class again (their logits are never used)
+  const int cls1 = NB == 2 ? NC - 16 : 0;
+  int olane[NB];
+  olane[0] = (m < NC ? m : NC - 1) * 64 + kg * 16;
+  if constexpr (NB == 2) olane[1] = 16 * 64 * PARTS + (m < cls1 ? m : cls1 - 1) * 64 + kg * 16;
+  const int opart[2] = {(NC < 16 ? NC : 16) * 64, cls1 * 64};  // from part to part
+  auto row_ptr = [&](int64_t row0) {
+    int64_t row = row0 + m;
+    row = row < r_end ? row : r_end - 1;
+    return a.A + row * a.lda + kStepCols * step0 + 4 * kg;
+  };
+  // step slots below SPW - 2 exist for every wave and hold whole steps; the others are clamped into the matrix
+  // buffer loads: the lane's offset in a register, everything else (step, part) uniform
+  const __amdgpu_buffer_rsrc_t ops =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wa.op), 0, wa.steps * NC * PARTS * 64, 0x00020000);
+  auto load_operands = [&](int b, int i) {
+    const int s = (i < SPW - 2 || i < count) ? step0 + i : wa.steps - 1;  // uniform
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int k = 0; k < PARTS; ++k)
+        ob[b][nb][k] = __builtin_amdgcn_raw_buffer_load_b128(ops, olane[nb], s * (NC * PARTS * 64) + k * opart[nb], 0);
+  };
+  auto load = [&](int b, int i, const float* rp) {
+    const int s = (i < SPW - 2 || i < count) ? step0 + i : wa.steps - 1;  // uniform
+    if (!RES) load_operands(b, i);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int off = kStepCols * i + 16 * h;
+      if (i >= SPW - 2) {
+        const int c0 = kStepCols * s + 16 * h + 4 * kg;
+        off = (c0 < col_max ? c0 : col_max) - kStepCols * step0 - 4 * kg;
+      }
+      if constexpr (ANY) {
+        const Quad q = *reinterpret_cast<const Quad*>(rp + off);
+        pf[b][h] = float4{q.x, q.y, q.z, q.w};
+      } else {
+        pf[b][h] = *reinterpret_cast<const float4*>(rp + off);
+      }
+    }
+  };
+
+  // A slot holds four blocks of 16 rows x 16 columns (high part: columns 0..15, 16..31; low part likewise), rows of 32 bytes:
+  // a lane writes its two pieces of a part with one instruction, 512 bytes back to back each, and a transposing read of a
+  // block (row 4 kg + i / 4, piece i % 4) covers it back to back as well: no bank conflicts.
+  const int wr_off = m * 32 + kg * 8;
+  const int rd_off = (4 * kg + (m >> 2)) * 32 + (m & 3) * 8;
+  auto write_tile = [&](char* base, u32x4 hi, u32x4 lo) {
+    *reinterpret_cast<u32x2*>(base + wr_off) = u32x2{hi[0], hi[1]};
+    *reinterpret_cast<u32x2*>(base + 512 + wr_off) = u32x2{hi[2], hi[3]};
+    *reinterpret_cast<u32x2*>(base + 1024 + wr_off) = u32x2{lo[0], lo[1]};
+    *reinterpret_cast<u32x2*>(base + 1536 + wr_off) = u32x2{lo[2], lo[3]};
+  };
+
+  bool cv[NB];
+  int cl[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    cv[nb] = 16 * nb + m < NC;
+    cl[nb] = cv[nb] ? 16 * nb + m : NC - 1;
+  }
+
+  u32x4 keep[RS > 0 ? RS : 1][2];
+  u32x4 dhi[NB], dlo[NB];  // D of the previous tile; k-slots of a lane: its four rows against the high part, then against the low part
+  const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int i = 0; i < (RS > 0 ? RS : 1); ++i) keep[i][0] = keep[i][1] = zero4;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) dhi[nb] = dlo[nb] = zero4;
+  // before the first tile: D = 0 meets zeros (the slots are private to the wave)
+#pragma unroll
+  for (int i = 0; i < 2 * kSlots; ++i) *reinterpret_cast<u32x4*>(slots + i * 1024 + lane * 16) = zero4;
+  // step i of the tile whose D is in dhi, dlo: operand of the product with D
+  auto fetch_transposed = [&](int i, u32x4 (&t)[2]) {
+    char* base = slots + (i < LS ? i : LS) * kSlotBytes;
+    if (i >= LS) write_tile(base, keep[i - LS < RS ? i - LS : 0][0], keep[i - LS < RS ? i - LS : 0][1]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {  // LDS operations of a wave execute in order
+      const u32x2 th = read_transposed(base + 512 * h + rd_off);
+      const u32x2 tl = read_transposed(base + 1024 + 512 * h + rd_off);
+      t[h] = u32x4{th[0], th[1], tl[0], tl[1]};
+    }
+  };
+  auto multiply_transposed = [&](int i, const u32x4 (&t)[2], const u32x4 (&dop)[NB]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) acc[i][h][nb] = mfma(dop[nb], t[h], acc[i][h][nb]);
+  };
+  const float* rp = row_ptr(r_begin);
+  if (r_begin < r_end) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) load(i, i, rp);
+  }
+  if constexpr (RES) {
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) load_operands(i, i);
+  }
+
+  for (int64_t row0 = r_begin; row0 < r_end; row0 += kTileRows) {
+    const float* rp_next = row_ptr(row0 + kTileRows);
+    const int left = r_end - row0 < kTileRows ? (int)(r_end - row0) : kTileRows;  // rows of this tile
+    // cached probabilities or labels of rows row0 + 4 kg + e
+    float pin[NB][4];
+    int label[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 4 * kg + e < left ? 4 * kg + e : left - 1;
+      if (KIND == kRowsHv && !HAS0) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) pin[nb][e] = (a.Pin + row0 * NC)[(unsigned)(r * NC + cl[nb])];
+      }
+      if (KIND == kRowsGrad) label[e] = (a.labels + row0)[(unsigned)r];
+    }
+
+    // ---------------- steps: product of the previous tile with its D, logits of this tile ----------------
+    f32x4 accZ[NB], accW[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) accZ[nb] = accW[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      const int b = i % D;
+      const int o = RES ? i : b;
+      const int s = step0 + i;
+      u32x4 told[2];
+      fetch_transposed(i, told);
+      float av[8] = {pf[b][0].x, pf[b][0].y, pf[b][0].z, pf[b][0].w, pf[b][1].x, pf[b][1].y, pf[b][1].z, pf[b][1].w};
+      if (i >= SPW - 2 && kStepCols * (s + 1) > p) {  // uniform: the step that contains column p (or lies past it)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int c0 = kStepCols * s + 16 * h + 4 * kg;
+          if constexpr (ANY) {
+            const int shift = c0 - (c0 < col_max ? c0 : col_max);  // 0: the piece is its own; >= 4: all of it is past p
+            const float q0 = av[4 * h], q1 = av[4 * h + 1], q2 = av[4 * h + 2], q3 = av[4 * h + 3];
+            av[4 * h + 0] = shift == 0 ? q0 : (shift == 1 ? q1 : (shift == 2 ? q2 : (shift == 3 ? q3 : 0.f)));
+            av[4 * h + 1] = shift == 0 ? q1 : (shift == 1 ? q2 : (shift == 2 ? q3 : 0.f));
+            av[4 * h + 2] = shift == 0 ? q2 : (shift == 1 ? q3 : 0.f);
+            av[4 * h + 3] = shift == 0 ? q3 : 0.f;
+          } else {
+            const int nv = c0 <= col_max ? p - c0 : 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) av[4 * h + e] = e < nv ? av[4 * h + e] : 0.f;
+          }
+        }
+      }
+      u32x4 ahi, alo, alo2;
+      if (HAS0) split8_3(av, ahi, alo, alo2);
+      else split8(av, ahi, alo);
+      if (i < SPW - 2 || i < count) {  // uniform
+        // Consecutive instructions work on different accumulators: the product with D (two halves) and the terms of Z
+        // (six) and W (three) take turns.
+        auto term_z = [&](int t) {  // smallest terms first, see mfma6
+          const u32x4 aa = t == 0 ? alo2 : ((t == 1 || t >= 4) ? ahi : alo);
+          const int part_ = t == 1 ? 2 : ((t == 2 || t == 4) ? 1 : 0);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) accZ[nb] = mfma(aa, ob[o][nb][HAS0 ? part_ : 0], accZ[nb]);
+        };
+        auto term_w = [&](int t) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            accW[nb] = mfma(t == 0 ? alo : ahi, ob[o][nb][HAS1 ? PX + (t == 1 ? 1 : 0) : 0], accW[nb]);
+        };
+        if (HAS0) term_z(0);
+        if (HAS1) term_w(0);
+        multiply_transposed(i, told, dlo);
+        if (HAS0) { term_z(1); }
+        if (HAS1) term_w(1);
+        if (HAS0) { term_z(2); }
+        multiply_transposed(i, told, dhi);
+        if (HAS0) { term_z(3); }
+        if (HAS1) term_w(2);
+        if (HAS0) { term_z(4); term_z(5); }
+        if (i < LS) write_tile(slots + i * kSlotBytes, ahi, alo);
+      }
+      if (i >= LS) {
+        keep[i - LS < RS ? i - LS : 0][0] = ahi;
+        keep[i - LS < RS ? i - LS : 0][1] = alo;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // the slot is free again: the step D further on, of this tile or of the next one
+      if (i + D < SPW) load(b, i + D, rp);
+      else load(b, i + D - SPW, rp_next);
+      __builtin_amdgcn_sched_barrier(0);  // steps stay apart: the registers hold D of them, not more
+    }
+    rp = rp_next;
+
+    // ---------------- K-split sums ----------------
+    lds_barrier();  // the previous tile's partials have been read
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      if (HAS0) part[(wave * kQuads + nb) * 64 + lane] = accZ[nb];
+      if (HAS1) part[(wave * kQuads + kMatW * NB + nb) * 64 + lane] = accW[nb];
+    }
+    lds_barrier();
+    f32x4 z[NB], w[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) z[nb] = w[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int RU = kQuads >= 4 ? 1 : (kQuads == 2 ? 2 : 4);  // waves' partials requested together
+#pragma unroll
+    for (int sw0 = 0; sw0 < kWaves; sw0 += RU) {
+      f32x4 pt[RU][kQuads];
+#pragma unroll
+      for (int u = 0; u < RU; ++u)
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q) pt[u][q] = part[((sw0 + u) * kQuads + q) * 64 + lane];
+#pragma unroll
+      for (int u = 0; u < RU; ++u)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          if (HAS0) z[nb] += pt[u][nb];
+          if (HAS1) w[nb] += pt[u][kMatW * NB + nb];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ---------------- rows: lane (m, kg) holds rows row0 + 4 kg + e, classes 16 nb + m ----------------
+    float d[NB][4];
+    // what wave e keeps of row e for the stores and the row loss (selected without branches)
+    float pk[NB], zk[NB], mk = 0.f, ak = 1.f, zbk = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) pk[nb] = zk[nb] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool valid = 4 * kg + e < left;
+      float P[NB], M = 0.f, alpha = 1.f;
+      if (HAS0) {
+        float mx = 0.f;  // the reference class has logit 0
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) mx = fmaxf(mx, cv[nb] ? z[nb][e] : 0.f);
+        M = row16_max(mx);
+        float es = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          P[nb] = cv[nb] ? expf(z[nb][e] - M) : 0.f;
+          es += P[nb];
+        }
+        alpha = row16_sum(es) + expf(-M);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) P[nb] = P[nb] / alpha;
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) P[nb] = cv[nb] ? pin[nb][e] : 0.f;
+      }
+      if (KIND == kRowsHv) {
+        float t = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) t = fmaf(P[nb], cv[nb] ? w[nb][e] : 0.f, t);
+        t = row16_sum(t);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) d[nb][e] = (valid && cv[nb]) ? P[nb] * (w[nb][e] - t) : 0.f;
+      } else {
+        float zb = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const bool mine = cv[nb] && 16 * nb + m == label[e];
+          zb += mine ? z[nb][e] : 0.f;
+          d[nb][e] = (valid && cv[nb]) ? P[nb] - (mine ? 1.f : 0.f) : 0.f;
+        }
+        zbk = wave == e ? zb : zbk;
+        mk = wave == e ? M : mk;
+        ak = wave == e ? alpha : ak;
+      }
+      if (STORES) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          pk[nb] = wave == e ? P[nb] : pk[nb];
+          if (HAS0) zk[nb] = wave == e ? z[nb][e] : zk[nb];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if ((STORES || KIND == kRowsGrad) && wave < 4) {  // uniform: wave e counts and stores the rows 4 kg + e
+      const int r = 4 * kg + wave;
+      if (KIND == kRowsGrad) {
+        const float zb = row16_sum(zbk);
+        if (m == 0 && r < left) loss_acc += (double)mk + (double)logf(ak) - (double)zb;
+      }
+      if (STORES && r < left) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          if (cv[nb]) {
+            const unsigned at = (unsigned)(r * NC + cl[nb]);
+            if (a.Pout) (a.Pout + row0 * NC)[at] = pk[nb];
+            if (HAS0 && a.Z0out) (a.Z0out + row0 * NC)[at] = zk[nb];
+          }
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const unsigned h0 = pack2(d[nb][0], d[nb][1]), h1 = pack2(d[nb][2], d[nb][3]);
+      const unsigned l0 = pack2(d[nb][0] - low_as_float(h0), d[nb][1] - high_as_float(h0));
+      const unsigned l1 = pack2(d[nb][2] - low_as_float(h1), d[nb][3] - high_as_float(h1));
+      dhi[nb] = u32x4{h0, h1, h0, h1};
+      dlo[nb] = u32x4{l0, l1, l0, l1};
+    }
+
+  }
+  // the last tile's product with D
+#pragma unroll
+  for (int i = 0; i < SPW; ++i) {
+    if (i < SPW - 2 || i < count) {  // uniform
+      u32x4 told[2];
+      fetch_transposed(i, told);
+      multiply_transposed(i, told, dlo);
+      multiply_transposed(i, told, dhi);
+    }
+    if (i & 1) __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // ---- this workgroup's partial of A^T D: a step's 32 columns are one run of 32 (C-1) floats, laid out in the wave's own
+  // LDS slots and written in 16-byte pieces (4-byte ones where the partial does not start on a 16-byte boundary) ----
+  float* out = wa.partial + (size_t)blockIdx.x * ((size_t)p * NC);
+  const bool quads_ok = (((int64_t)p * NC) & 3) == 0 && (reinterpret_cast<uintptr_t>(wa.partial) & 15) == 0;
+  float* stage = reinterpret_cast<float*>(slots);  // 32 (C-1) floats: at most 4 KB, two slots
+#pragma unroll
+  for (int i = 0; i < SPW; ++i) {
+    if (i < count) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int c = 16 * nb + 4 * kg + e;
+            if (c < NC) stage[(16 * h + m) * NC + c] = acc[i][h][nb][e];
+          }
+      const int s = step0 + i;
+      const int cols = p - kStepCols * s < kStepCols ? p - kStepCols * s : kStepCols;
+      const int total = cols * NC;
+      float* dst = out + (size_t)kStepCols * s * NC;
+      if (quads_ok) {
+        const int quads = total >> 2;
+#pragma unroll
+        for (int u = 0; u < 4 * NB / 2; ++u) {
+          const int q = lane + 64 * u;
+          if (q < quads) *reinterpret_cast<f32x4*>(dst + 4 * q) = *reinterpret_cast<const f32x4*>(stage + 4 * q);
+        }
+        if (lane < (total & 3)) dst[4 * quads + lane] = stage[4 * quads + lane];
+      } else {
+        for (int q = lane; q < total; q += 64) dst[q] = stage[q];
+      }
+    }
+  }
+  if (KIND == kRowsGrad) {
+    loss_acc = mfma_detail::wave64_sum(loss_acc);
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(part);
+    if (lane == 0) red[wave] = loss_acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int wv = 0; wv < kWaves; ++wv) t += red[wv];
+      a.loss_part[blockIdx.x] = t;
+    }
+  }
+}
+
+int steps_of(int p) { return (p + kStepCols - 1) / kStepCols; }
+
+bool rows_16_byte_aligned(const RowArgs& a) { return (a.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(a.A) & 15) == 0; }
+
+template <int SPW, int D, int NB, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
+hipError_t launch_a(const WideArgs& wa, int grid, hipStream_t st) {
+  constexpr int LS = SPW < kMaxLdsSlots ? SPW : kMaxLdsSlots;
+  constexpr int kMats = (HAS0 ? 1 : 0) + (HAS1 ? 1 : 0);
+  constexpr size_t lds = (size_t)kWaves * (LS + (SPW > LS ? 1 : 0)) * kSlotBytes + (size_t)kWaves * kMats * NB * 64 * 16;
+  static_assert(lds <= 160 * 1024, "LDS of a compute unit");
+  static uint64_t lds_set = 0;  // per device
+  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&wide_kernel<SPW, D, NB, KIND, HAS0, HAS1, STORES, ANY>), &lds_set);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((wide_kernel<SPW, D, NB, KIND, HAS0, HAS1, STORES, ANY>), dim3(grid), dim3(kThreads), lds, st, wa);
+  return hipGetLastError();
+}
+
+template <int SPW, int D, int NB, int KIND, bool HAS0, bool HAS1, bool STORES>
+hipError_t launch_s(const WideArgs& wa, int grid, hipStream_t st) {
+  if (rows_16_byte_aligned(wa.r)) return launch_a<SPW, D, NB, KIND, HAS0, HAS1, STORES, false>(wa, grid, st);
+  return launch_a<SPW, D, NB, KIND, HAS0, HAS1, STORES, true>(wa, grid, st);
+}
+
+// Steps in flight with V, with X and with both (more registers per step).  2, 4 and 8 measured alike at 75000 x 2048.
+template <int SPW, int NB, int DV, int DX, int DXV = 1>
+hipError_t launch_spw(const WideArgs& wa, int grid, hipStream_t st) {
+  const RowArgs& a = wa.r;
+  const bool h0 = a.B0 != nullptr, h1 = a.B1 != nullptr;
+  const bool stores = a.Pout != nullptr || a.Z0out != nullptr;
+  if (a.kind == kRowsHv && h1) {
+    if constexpr (NB == 1) {  // see wide_takes
+      if (h0 && stores) return launch_s<SPW, DXV, NB, kRowsHv, true, true, true>(wa, grid, st);
+      if (h0) return launch_s<SPW, DXV, NB, kRowsHv, true, true, false>(wa, grid, st);
+    }
+    if (h0 || a.Pin == nullptr) return hipErrorInvalidValue;
+    return launch_s<SPW, DV, NB, kRowsHv, false, true, false>(wa, grid, st);
+  }
+  if (a.kind == kRowsGrad && h0 && !h1) {
+    if (a.labels == nullptr || a.loss_part == nullptr) return hipErrorInvalidValue;
+    if (stores) return launch_s<SPW, DX, NB, kRowsGrad, true, false, true>(wa, grid, st);
+    return launch_s<SPW, DX, NB, kRowsGrad, true, false, false>(wa, grid, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// Shapes: the accumulators of all columns have to fit the registers (12 steps per wave, 8 with two blocks of classes).
+bool wide_supported(const Shape& s, int64_t lda, const void* A) {
+  const int steps = steps_of(s.p);
+  if (s.NC > 32 || steps > (s.NC > 16 ? kMaxSteps2 : kMaxSteps1)) return false;
+  // C-1 <= 16: the fewest steps a wave may hold (`count` in the kernel).  C-1 > 16: below 10 steps some waves hold one step
+  // and others two, and 16 rows are too little work for the barriers of a tile (CG at 100000 x 200, C = 20: 574 against
+  // 566 us with two sweeps; at 100000 x 500: 723 against 974 us).
+  if (steps < (s.NC > 16 ? 10 : 17)) return false;
+  if ((reinterpret_cast<uintptr_t>(A) & 3) != 0 || lda < s.p) return false;
+  return true;
+}
+
+// With two blocks of classes X and V together take 40 registers per step in flight: the kernel spills into its stream (a
+// reload waits for every row requested before it), and two sweeps are faster: 250000 x 2000, C = 20: 867 against 1253 us,
+// 50000 x 1500, C = 25: 167 against 183 us, 100000 x 960, C = 20: 177 against 198 us.
+bool wide_takes(const Shape& s, bool has_x, bool has_v) { return s.NC <= 16 || !(has_x && has_v); }
+
+int wide_num_partials(const Shape& s, int wg_cap) {
+  const int64_t tiles = (s.n + kTileRows - 1) / kTileRows;
+  const int64_t most = wg_cap > 0 && wg_cap < 256 ? wg_cap : 256;
+  const int64_t g = tiles < most ? tiles : most;
+  const int64_t rows = (s.n + g - 1) / g;
+  return (int)((s.n + rows - 1) / rows);
+}
+
+size_t wide_operand_bytes(const Shape& s) { return (size_t)steps_of(s.p) * s.NC * 5 * 64; }
+
+hipError_t launch_wide(const RowArgs& a, void* operands, float* partial, int nparts, hipStream_t st) {
+  WideArgs wa;
+  wa.r = a;
+  wa.op = static_cast<const char*>(operands);
+  wa.partial = partial;
+  wa.steps = steps_of(a.p);
+  wa.rows_per_wg = (int)((a.n + nparts - 1) / nparts);
+  const int threads = wa.steps * a.NC * 4;
+  hipLaunchKernelGGL(pack_operands_kernel, dim3((threads + 255) / 256), dim3(256), 0, st, a.B0, a.B1, a.p, a.NC, wa.steps,
+                     static_cast<char*>(operands), a.flag);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int spw = (wa.steps + kWaves - 1) / kWaves;
+  if (a.NC <= 16) {
+    if (spw <= 4) return launch_spw<4, 1, 4, 4, 4>(wa, nparts, st);
+    if (spw <= 6) return launch_spw<6, 1, 3, 3, 3>(wa, nparts, st);
+    if (spw <= 8) return launch_spw<8, 1, 4, 2, 2>(wa, nparts, st);
+    if (spw <= 10) return launch_spw<10, 1, 2, 2, 2>(wa, nparts, st);
+    return launch_spw<12, 1, 3, 2, 2>(wa, nparts, st);
+  }
+  if (spw <= 2) return launch_spw<2, 2, 2, 2>(wa, nparts, st);
+  if (spw <= 4) return launch_spw<4, 2, 4, 2>(wa, nparts, st);
+  if (spw <= 6) return launch_spw<6, 2, 2, 2>(wa, nparts, st);
+  return launch_spw<8, 2, 2, 2>(wa, nparts, st);
+}
+
+}  // namespace nadmm

@@ -544,3 +544,33 @@ def test_two_streams_with_their_own_workspaces_do_not_interfere(cache):
             nadmm.nadmm_local_newton(gp2, X2, params, want_stats=False, stream=s2)
         s1.synchronize(); s2.synchronize()
         assert torch.equal(X1, ref1) and torch.equal(X2, ref2)
+
+
+# Single-pass kernel for wide rows (kernel path 4, sweeps with a transpose product): numbers of column steps at which waves
+# hold different counts (513 = 16 steps and one column; 1024 = 4 steps per wave exactly; 1025; 2049; 3072 = the widest), rows at
+# the edges of a tile of 16 and of the 256 row ranges, rows that are only 4-byte aligned, one and two blocks of classes, and
+# shapes on either side of the limits (3073 and 2049 columns with 25 classes take two sweeps).
+WIDE_SHAPES = [(1, 513, 2), (15, 544, 10), (16, 1024, 17), (17, 1025, 5), (257, 1100, 10), (4096, 640, 3), (4097, 1537, 9),
+               (300, 2049, 10), (129, 2561, 16), (530, 3072, 10), (40, 3071, 2), (35, 3073, 4),
+               (33, 290, 18), (4100, 330, 20), (70, 513, 33), (48, 1025, 25), (31, 2048, 33), (31, 2049, 25)]
+
+
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("n,p,C", WIDE_SHAPES)
+def test_wide_single_pass(n, p, C, pad):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    A = torch.full((n, p + pad), float("nan"), device="cuda")  # what lies between the rows must not matter
+    A[:, :p] = dev(w.A)
+    gp = nadmm.Problem(A[:, :p], dev(w.b), C, w.s, w.lam, w.rho, dev(w.z), dev(w.y))
+    op = oracle_problem(w)
+    force_path(gp, 4)
+    loss, grad = nadmm.nadmm_loss_grad(gp, dev(w.X0))
+    f_ref, g_ref = orc.loss_grad(op, w.X0)
+    # 16-bit products summed in float32: relative error 2^-16 per term, averaged over the sum; TOL_PRIMITIVE is the API's bar
+    assert rel_abs(loss.item(), f_ref) <= TOL_PRIMITIVE and rel_l2(host(grad), g_ref) <= TOL_PRIMITIVE
+    hv = nadmm.nadmm_hessvec(gp, dev(w.X0), dev(w.V))
+    assert rel_l2(host(hv), orc.hessvec(op, w.X0, w.V)) <= TOL_PRIMITIVE
+    assert torch.equal(hv, nadmm.nadmm_hessvec(gp, dev(w.X0), dev(w.V)))
+    p_out, it, _ = nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g_ref.astype(np.float32)), 3, 0.0)  # cached probabilities
+    p_ref, it_ref, _ = orc.cg(op, w.X0, g_ref.astype(np.float32).astype(np.float64), 3, 0.0)
+    assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
