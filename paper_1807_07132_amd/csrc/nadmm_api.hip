@@ -2,6 +2,7 @@
 // drivers that enqueue the kernels of one local x-update (Algorithm 3 with the CG
 // of Section 2.4 and the line search of Algorithm 2).  Nothing here synchronises
 // the device except the final copy of the statistics.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -37,6 +38,9 @@ struct Layout {
   int gen_row_blocks, gen_slabs, gen_chunks, gen_rpc;
   int fused_parts, thin_parts, sliced_parts, sliced_loss, wide_parts;
   bool fused_ok, thin_ok, sliced_ok;
+  bool thin_gen; // thin rows of any alignment (automatic choice only)
+  bool narrow;   // paths 2 and 4 take the kernel for narrow rows (nadmm_narrow.hip) where it supports the sweep
+  int narrow_parts;
   bool wide;     // path 4 makes its sweeps with a transpose product in a single pass (nadmm_wide.hip)
   bool mc_auto;  // the matrix-core paths are also the automatic choice (see kAnyStrideMinP)
   bool sparse;
@@ -44,10 +48,13 @@ struct Layout {
   const float* rho_scale;  // device scalar factor on rho (outer solver with an adaptive penalty), or NULL
 };
 
-// Rows that are not 16-byte aligned take the matrix-core kernels' any-stride variants automatically only from this many
-// columns on: with fewer, most waves of those kernels have no column step and the vector kernels are faster (measured
-// per Hessian-vector product: 1375000 x 29: 260 against 152 us, 200000 x 13: 47 against 37 us, 100000 x 70: 29 against 75 us).
+// Rows that are not 16-byte aligned and have fewer columns than this are reported as path 1, whose vector kernels served them
+// before the kernel for narrow rows did; they still do where that kernel has no room (fewer than 4 columns).
 constexpr int kAnyStrideMinP = 48;
+
+bool aligned_or_long_rows(const nadmm_problem* p) {
+  return ((p->lda & 3) == 0 && (reinterpret_cast<uintptr_t>(p->d_A) & 15) == 0) || p->p >= kAnyStrideMinP;
+}
 
 int validate_problem(const nadmm_problem* p, bool need_labels) {
   if (p == nullptr) return NADMM_EINVAL;
@@ -90,12 +97,17 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->gen_row_blocks = generic_row_blocks(s.n);
   generic_col_grid(s, &L->gen_slabs, &L->gen_chunks, &L->gen_rpc);
   if (L->sparse) L->gen_chunks = 1;  // the column view gives every element of A^T D whole
-  L->mc_auto = L->sparse || (((p->lda & 3) == 0 && (reinterpret_cast<uintptr_t>(p->d_A) & 15) == 0) || s.p >= kAnyStrideMinP);
+  L->narrow = !L->sparse && narrow_supported(s, p->lda, p->d_A) &&
+              (s.NC > 16 || !aligned_or_long_rows(p) || s.n >= narrow_min_rows(s.p));
+  L->narrow_parts = L->narrow ? narrow_num_partials(s) : 0;
+  if (wg_cap > 0 && L->narrow_parts > wg_cap) L->narrow_parts = wg_cap;
+  L->mc_auto = L->sparse || aligned_or_long_rows(p) || L->narrow;
   L->fused_ok = !L->sparse && fused_supported(s, p->lda, p->d_A);
-  L->fused_parts = L->fused_ok ? fused_num_partials(s) : 0;
+  L->fused_parts = L->fused_ok ? (L->narrow ? L->narrow_parts : fused_num_partials(s)) : 0;
   if (wg_cap > 0 && L->fused_parts > wg_cap) L->fused_parts = wg_cap;
   L->thin_ok = !L->sparse && thin_supported(s, p->lda, p->d_A);
-  L->thin_parts = L->thin_ok ? thin_num_partials(s) : 0;
+  L->thin_gen = !L->sparse && !L->thin_ok && thin_general_supported(s, p->lda, p->d_A);
+  L->thin_parts = L->thin_ok || L->thin_gen ? thin_num_partials(s) : 0;
   const size_t vec = hv_only ? 0 : align256((size_t)s.d * sizeof(float));
   const size_t rows = align256((size_t)s.n * s.NC * sizeof(float));
   const size_t rows_solver = hv_only ? 0 : rows;
@@ -127,6 +139,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->wide_parts = L->wide ? wide_num_partials(s, wg_cap) : 0;
   int parts = L->gen_chunks > L->fused_parts ? L->gen_chunks : L->fused_parts;
   if (L->wide_parts > parts) parts = L->wide_parts;
+  if (L->narrow_parts > parts) parts = L->narrow_parts;
   if (L->sliced_parts > parts) parts = L->sliced_parts;
   if (L->thin_parts > parts) parts = L->thin_parts;
   L->partial = off; off += align256((size_t)parts * s.d * sizeof(float));
@@ -136,6 +149,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   if (L->thin_parts > lblocks) lblocks = L->thin_parts;
   if (L->sliced_loss > lblocks) lblocks = L->sliced_loss;
   if (L->wide_parts > lblocks) lblocks = L->wide_parts;
+  if (L->narrow_parts > lblocks) lblocks = L->narrow_parts;
   L->loss_part = off; off += hv_only ? 0 : align256((size_t)lblocks * sizeof(double));
   L->lpart = off; off += hv_only ? 0 : align256((size_t)ls_eval_blocks(s.n) * kCandSlots * sizeof(double));
   L->dotpart = off; off += hv_only ? 0 : align256((size_t)2 * reduce_out_blocks(s.d) * sizeof(double));  // two sums per workgroup
@@ -161,7 +175,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   }
   L->total_base = off;
   // 2 max_cg n (C-1) floats written and read instead of n p floats read: taken with a margin
-  const bool fused_default = L->fused_ok && (g_path == 2 || (g_path == 0 && !L->thin_ok && L->mc_auto));
+  const bool fused_default = L->fused_ok && (g_path == 2 || (g_path == 0 && !L->thin_ok && !L->thin_gen && L->mc_auto));
   L->hist_bufs = (!hv_only && fused_default && max_cg >= 1 && max_cg <= kCgHist && (int64_t)3 * max_cg * s.NC <= s.p) ? max_cg : 0;
   L->hist = off; off += (size_t)L->hist_bufs * rows;
   L->total = off;
@@ -231,13 +245,16 @@ int choose_path(const Layout& L, int* path) {
     *path = 4;
     return NADMM_OK;
   }
-  *path = L.thin_ok ? 3 : (L.fused_ok && L.mc_auto ? 2 : (L.sliced_ok && L.mc_auto ? 4 : 1));
+  *path = L.thin_ok || L.thin_gen ? 3 : (L.fused_ok && L.mc_auto ? 2 : (L.sliced_ok && L.mc_auto ? 4 : 1));
   return NADMM_OK;
 }
 
+// path 4: whether the kernel for narrow rows makes the sweep (more than 16 free classes)
+bool narrow_sweep(const Layout& L, bool has_x, bool has_v) { return L.narrow && L.s.NC > 16 && narrow_takes(L.s, has_x, has_v); }
+
 // partial row losses that a sweep leaves (with_cols: one that also forms A^T rows)
 int loss_blocks(const Layout& L, int path, bool with_cols) {
-  if (path == 4) return (with_cols && L.wide) ? L.wide_parts : L.sliced_loss;
+  if (path == 4) return narrow_sweep(L, true, false) ? L.narrow_parts : (with_cols && L.wide ? L.wide_parts : L.sliced_loss);
   return path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : L.gen_row_blocks);
 }
 
@@ -317,7 +334,8 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
     return NADMM_OK;
   }
   if (path == 2) {
-    NADMM_HIP(launch_fused(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.fused_parts, st, cg));
+    if (L.narrow) NADMM_HIP(launch_narrow(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.fused_parts, st, cg));
+    else NADMM_HIP(launch_fused(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.fused_parts, st, cg));
     *nparts = L.fused_parts;
     return NADMM_OK;
   }
@@ -328,6 +346,11 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
     return NADMM_OK;
   }
   if (path == 4) {
+    if (narrow_sweep(L, ra.B0 != nullptr, ra.B1 != nullptr)) {
+      NADMM_HIP(launch_narrow(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.narrow_parts, st, nullptr));
+      *nparts = L.narrow_parts;
+      return NADMM_OK;
+    }
     if (with_cols && L.wide && wide_takes(L.s, ra.B0 != nullptr, ra.B1 != nullptr)) {
       NADMM_HIP(launch_wide(ra, at<char>(ws, L.operands), at<float>(ws, L.partial), L.wide_parts, st));
       *nparts = L.wide_parts;
@@ -504,7 +527,7 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
   cu.rr_part = at<double>(ws, L.rrpart);
   cu.d = L.s.d;
   cu.tol = tol;
-  const int parts = path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : (path == 4 ? (L.wide_parts > L.sliced_parts ? L.wide_parts : L.sliced_parts) : L.gen_chunks));
+  const int parts = path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : (path == 4 ? std::max(std::max(L.wide_parts, L.sliced_parts), L.narrow_parts) : L.gen_chunks));
   if (cg_fused_tail_supported(L.s.d, parts)) {
     int nparts = 0;
     int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, nullptr, nullptr, &ds->cg_active, &nparts, st);
@@ -613,7 +636,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     if (!head_in_reduce) NADMM_HIP(launch_newton_head(nh, st));
 
     // CG on H p = -g with the probabilities of this iterate
-    const bool thin_def = thin_deferred(path) && params->max_cg >= 1;
+    const bool thin_def = thin_deferred(path) && !L.thin_gen && params->max_cg >= 1;
     const bool hist = use_hist && cg_deferred(path) && params->max_cg >= 1 && params->max_cg <= L.hist_bufs;
     const size_t hist_stride = align256((size_t)L.s.n * L.s.NC * sizeof(float)) / sizeof(float);
     for (int k = 0; k < params->max_cg; ++k) {
@@ -794,7 +817,12 @@ int nadmm_query_kernel_path(const nadmm_problem* prob) {
   make_layout(prob, &L);
   int path = 0;
   rc = choose_path(L, &path);
-  return rc != NADMM_OK ? rc : path;
+  if (rc != NADMM_OK) return rc;
+  if (g_path != 0 || path == 5) return path;
+  // the number names the class of shape: rows that are not 16-byte aligned have 1 below 48 columns, whichever kernel serves them
+  if (L.thin_ok) return 3;
+  if (!aligned_or_long_rows(prob)) return 1;
+  return L.fused_ok ? 2 : (L.sliced_ok ? 4 : 1);
 }
 
 size_t nadmm_workspace_bytes(const nadmm_problem* prob, const nadmm_params* params) {

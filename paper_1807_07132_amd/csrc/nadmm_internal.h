@@ -345,6 +345,7 @@ hipError_t launch_cg_pending_finish(const CgPend& c, hipStream_t st);
 
 // ---- thin-data single-pass path (nadmm_thin.hip): p <= 32, p % 4 == 0, C-1 <= 3, lda == p ----
 bool thin_supported(const Shape& s, int64_t lda, const void* A);
+bool thin_general_supported(const Shape& s, int64_t lda, const void* A);  // the same kernel for other rows of up to 32 columns, without cg
 int thin_num_partials(const Shape& s);
 // cg, prev (both or neither): the sweep first applies the pending CG update, forming q = H d from the previous sweep's
 // partial sums prev->partial (prev also carries scale, lambda, rho of the linear terms); see ThinArgs in nadmm_thin.hip
@@ -359,6 +360,13 @@ void sliced_grid(const Shape& s, int* nslices, int* steps_per_slice, int* row_gr
 int sliced_loss_blocks(const Shape& s);
 hipError_t launch_sliced_logits(const RowArgs& a, hipStream_t st);
 hipError_t launch_sliced_cols(const RowArgs& a, const float* rows_in, float* partial, hipStream_t st);
+
+// ---- matrix-core kernel for narrow rows (nadmm_narrow.hip), on the paths of the fused (C-1 <= 16) and the column-sliced kernels ----
+bool narrow_supported(const Shape& s, int64_t lda, const void* A);
+bool narrow_takes(const Shape& s, bool has_x, bool has_v);  // whether it makes the sweep with these operands
+int64_t narrow_min_rows(int32_t p);                         // C-1 <= 16: fewer rows are faster on the fused kernel, where that takes them
+int narrow_num_partials(const Shape& s);
+hipError_t launch_narrow(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg);  // as launch_fused
 
 // ---- single-pass matrix-core kernel for wide rows (nadmm_wide.hip): the sweeps of that path that form A^T rows ----
 bool wide_supported(const Shape& s, int64_t lda, const void* A);

@@ -138,5 +138,15 @@ __device__ __forceinline__ int cm_offset(int q, int ck) {
   return qs * 64 + ((ck ^ g) << 4);
 }
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// Transposing read: the 16 lanes of a group name the 8-byte pieces of a block of 4 rows x 16 columns of 16-bit values (lane
+// i: row i / 4, columns 4 (i % 4) ..), lane i receives the 4 rows of column i.
+__device__ __forceinline__ u32x2 read_transposed(char* at) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at));
+}
+
 }  // namespace mfma_detail
 }  // namespace nadmm

@@ -44,8 +44,15 @@ struct ThinArgs {
 };
 
 // NQ = p / 4: float4 per row, which is also the float4 per lane in a chunk of 256 rows
-template <int NQ, int NC, bool CG>
+// GEN: rows that are no whole number of 16-byte pieces, or not 16-byte aligned (p odd, a few columns of padding, A 4-byte
+// aligned).  256 consecutive rows are still one contiguous block of memory: it is copied to LDS as it lies, in 16-byte pieces
+// (NQ = ceil(lda / 4) per lane, rounded up; lda = p or the few elements of padding more), and the lanes read their rows back
+// in 4-byte pieces, free of bank conflicts where lda is odd.  Such rows went through the two-pass vector kernels before
+// (1375000 x 29, C = 2, objective and gradient: 192 us) or would go through the matrix-core kernel for narrow rows, where
+// one lane in 16 has work in the rows stage (103 us).
+template <int NQ, int NC, bool CG, bool GEN>
 __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
+  static_assert(!(CG && GEN), "the deferred CG update reads the partial sums in whole quads");
   constexpr int PP = 4 * NQ;
   constexpr int kMaxQuads = NQ;
   constexpr int nquads = NQ;
@@ -54,7 +61,7 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
   extern __shared__ __attribute__((aligned(16))) float tile[];  // 256 x lds_stride floats
   __shared__ double red[4];
   const int t = threadIdx.x;
-  constexpr int p = PP;
+  const int p = GEN ? a.p : PP;
   constexpr int PS = (PP % 8 == 0) ? PP + 4 : PP;  // LDS row stride, off the bank period
   const bool has0 = !CG && a.B0 != nullptr;
   const bool has1 = CG || a.B1 != nullptr;
@@ -132,8 +139,9 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
     for (int j = 0; j < PP; ++j)
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        xs[j][c] = has0 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B0[j * NC + c]))) : 0.f;
-        vs[j][c] = has1 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B1[j * NC + c]))) : 0.f;
+        const int jc = GEN ? (j < p ? j : p - 1) : j;  // columns past p meet zeros of the row
+        xs[j][c] = has0 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B0[jc * NC + c]))) : 0.f;
+        vs[j][c] = has1 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B1[jc * NC + c]))) : 0.f;
       }
   }
 
@@ -163,7 +171,19 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
   // wait for exactly the chunk it needs.
   f32x4 pf[2][kMaxQuads];
   const int64_t own_last4 = (r_end > r_begin ? r_end : r_begin + 1) * nquads - 1;
+  const int ld = (int)a.lda;                                          // GEN: <= 32
+  const int64_t last_el = GEN ? (a.n - 1) * a.lda + a.p - 4 : 0;      // GEN: where the matrix's last 16 bytes start
   auto load_chunk = [&](int b, int64_t row0) {
+    if constexpr (GEN) {
+      const int64_t rc = row0 < a.n ? row0 : a.n - 1;
+#pragma unroll
+      for (int k = 0; k < kMaxQuads; ++k) {
+        const int64_t e0 = rc * ld + 4 * (t + k * kThinThreads);
+        const Quad q = *reinterpret_cast<const Quad*>(a.A + (e0 < last_el ? e0 : last_el));
+        pf[b][k] = f32x4{q.x, q.y, q.z, q.w};
+      }
+      return;
+    }
     const int64_t base4 = row0 * nquads + t;
 #pragma unroll
     for (int k = 0; k < kMaxQuads; ++k) {
@@ -176,14 +196,37 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
   auto process = [&](int b, int64_t row0) {
     __syncthreads();  // rows of the previous chunk have been read
 #pragma unroll
-    for (int k = 0; k < kMaxQuads; ++k)
-      *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[prow[k] * PS + pcol[k]], 16)) = pf[b][k];
+    for (int k = 0; k < kMaxQuads; ++k) {
+      if constexpr (GEN) {
+        const int at = 4 * (t + k * kThinThreads);  // the tile holds 4 NQ 256 floats
+        f32x4 v = pf[b][k];
+        if (row0 + kThinThreads >= a.n) {  // uniform: the last rows; a piece fetched from the matrix's end holds its elements further up
+          const int64_t over = row0 * ld + at - last_el;
+          const int sh = over <= 0 ? 0 : (over < 4 ? (int)over : 4);
+          const f32x4 u = v;
+          v[0] = sh == 0 ? u[0] : (sh == 1 ? u[1] : (sh == 2 ? u[2] : (sh == 3 ? u[3] : 0.f)));
+          v[1] = sh == 0 ? u[1] : (sh == 1 ? u[2] : (sh == 2 ? u[3] : 0.f));
+          v[2] = sh == 0 ? u[2] : (sh == 1 ? u[3] : 0.f);
+          v[3] = sh == 0 ? u[3] : 0.f;
+        }
+        *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[at], 16)) = v;
+      } else {
+        *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[prow[k] * PS + pcol[k]], 16)) = pf[b][k];
+      }
+    }
     load_chunk(b, row0 + 2 * kThinThreads);
     __syncthreads();
 
     const int64_t row = row0 + t;
     const bool valid = row < r_end;
     float av[PP];
+    if constexpr (GEN) {
+#pragma unroll
+      for (int j = 0; j < PP; ++j) {
+        const float v = tile[t * ld + j];  // at most 255 ld + PP - 1 < 256 PP
+        av[j] = (j < PP - 4 || j < p) ? v : 0.f;  // p > PP - 4
+      }
+    } else
 #pragma unroll
     for (int q = 0; q < PP / 4; ++q) {
       const f32x4 v = *reinterpret_cast<const f32x4*>(__builtin_assume_aligned(&tile[t * PS + 4 * q], 16));
@@ -303,19 +346,21 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
 int lds_stride_of(int p) { return (p % 8 == 0) ? p + 4 : p; }
 
 template <int NQ, int NC>
-hipError_t launch_thin_t(const ThinArgs& ta, int grid, bool cg, hipStream_t st) {
+hipError_t launch_thin_t(const ThinArgs& ta, int grid, bool cg, bool gen, hipStream_t st) {
   const size_t lds = (size_t)kThinThreads * ta.lds_stride * sizeof(float);
-  if (cg) hipLaunchKernelGGL((thin_kernel<NQ, NC, true>), dim3(grid), dim3(kThinThreads), lds, st, ta);
-  else hipLaunchKernelGGL((thin_kernel<NQ, NC, false>), dim3(grid), dim3(kThinThreads), lds, st, ta);
+  if (gen && cg) return hipErrorInvalidValue;
+  if (gen) hipLaunchKernelGGL((thin_kernel<NQ, NC, false, true>), dim3(grid), dim3(kThinThreads), (size_t)kThinThreads * 4 * NQ * sizeof(float), st, ta);
+  else if (cg) hipLaunchKernelGGL((thin_kernel<NQ, NC, true, false>), dim3(grid), dim3(kThinThreads), lds, st, ta);
+  else hipLaunchKernelGGL((thin_kernel<NQ, NC, false, false>), dim3(grid), dim3(kThinThreads), lds, st, ta);
   return hipGetLastError();
 }
 
 template <int NQ>
-hipError_t launch_thin_nq(const ThinArgs& ta, int grid, bool cg, hipStream_t st) {
+hipError_t launch_thin_nq(const ThinArgs& ta, int grid, bool cg, bool gen, hipStream_t st) {
   switch (ta.r.NC) {
-    case 1: return launch_thin_t<NQ, 1>(ta, grid, cg, st);
-    case 2: return launch_thin_t<NQ, 2>(ta, grid, cg, st);
-    case 3: return launch_thin_t<NQ, 3>(ta, grid, cg, st);
+    case 1: return launch_thin_t<NQ, 1>(ta, grid, cg, gen, st);
+    case 2: return launch_thin_t<NQ, 2>(ta, grid, cg, gen, st);
+    case 3: return launch_thin_t<NQ, 3>(ta, grid, cg, gen, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -326,6 +371,14 @@ bool thin_supported(const Shape& s, int64_t lda, const void* A) {
   if (s.p > 32 || (s.p & 3) != 0 || s.NC > 3 || s.p * s.NC > 64) return false;
   if (lda != s.p || (reinterpret_cast<uintptr_t>(A) & 15) != 0) return false;
   return true;
+}
+
+// Any other rows of up to 32 columns (instantiations with GEN): at most 3 elements of padding, so that 256 rows are one
+// block of about 256 p floats; the accumulators of the padded row fit the registers.
+bool thin_general_supported(const Shape& s, int64_t lda, const void* A) {
+  const int64_t pp = (lda + 3) / 4 * 4;
+  if (lda < s.p || lda > 32 || s.NC > 3 || pp * s.NC > 64 || s.p <= pp - 4) return false;
+  return s.n * lda >= 8 && (s.n - 1) * lda + s.p >= 4 && (reinterpret_cast<uintptr_t>(A) & 3) == 0;
 }
 
 int thin_num_partials(const Shape& s) {
@@ -362,15 +415,16 @@ hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t
     ta.rho = prev->rho;
     ta.rho_scale = prev->rho_scale;
   }
-  switch (a.p >> 2) {
-    case 1: return launch_thin_nq<1>(ta, nparts, with_cg, st);
-    case 2: return launch_thin_nq<2>(ta, nparts, with_cg, st);
-    case 3: return launch_thin_nq<3>(ta, nparts, with_cg, st);
-    case 4: return launch_thin_nq<4>(ta, nparts, with_cg, st);
-    case 5: return launch_thin_nq<5>(ta, nparts, with_cg, st);
-    case 6: return launch_thin_nq<6>(ta, nparts, with_cg, st);
-    case 7: return launch_thin_nq<7>(ta, nparts, with_cg, st);
-    case 8: return launch_thin_nq<8>(ta, nparts, with_cg, st);
+  const bool gen = !thin_supported(Shape{a.n, a.p, a.NC, (int64_t)a.p * a.NC}, a.lda, a.A);
+  switch (gen ? (int)((a.lda + 3) >> 2) : a.p >> 2) {
+    case 1: return launch_thin_nq<1>(ta, nparts, with_cg, gen, st);
+    case 2: return launch_thin_nq<2>(ta, nparts, with_cg, gen, st);
+    case 3: return launch_thin_nq<3>(ta, nparts, with_cg, gen, st);
+    case 4: return launch_thin_nq<4>(ta, nparts, with_cg, gen, st);
+    case 5: return launch_thin_nq<5>(ta, nparts, with_cg, gen, st);
+    case 6: return launch_thin_nq<6>(ta, nparts, with_cg, gen, st);
+    case 7: return launch_thin_nq<7>(ta, nparts, with_cg, gen, st);
+    case 8: return launch_thin_nq<8>(ta, nparts, with_cg, gen, st);
     default: return hipErrorInvalidValue;
   }
 }

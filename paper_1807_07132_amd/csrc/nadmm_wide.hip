@@ -95,16 +95,6 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restr
   }
 }
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-// Transposing read: the 16 lanes of a group name the 8-byte pieces of a block of 4 rows x 16 columns of 16-bit values (lane
-// i: row i / 4, columns 4 (i % 4) ..), lane i receives the 4 rows of column i.
-__device__ __forceinline__ u32x2 read_transposed(char* at) {
-  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)at));
-}
-
 // The operands of all of a wave's steps stay in registers where they fit beside the accumulators (4 registers per step, class
 // block and part, 8 per step and class block, and two steps of A in flight); else they stream.  The stream costs: at
 // 75000 x 2048, C = 10 a sweep with V took 130 us with streamed operands (C = 3: 110 us, the rate of the memory).

@@ -574,3 +574,43 @@ def test_wide_single_pass(n, p, C, pad):
     p_out, it, _ = nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g_ref.astype(np.float32)), 3, 0.0)  # cached probabilities
     p_ref, it_ref, _ = orc.cg(op, w.X0, g_ref.astype(np.float32).astype(np.float64), 3, 0.0)
     assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
+
+
+# Rows of up to 128 columns: the kernel for narrow rows (1 to 4 column steps, one and two blocks of classes, tiles of 16, 32 and
+# 64 rows with remainders, more rows than one round of 512 workgroups) and the thin-data kernel on rows that are no whole number
+# of 16-byte pieces (lda = p odd, a few elements of padding, one row, the last piece of the matrix at every offset).
+NARROW_SHAPES = [(1, 5, 6), (17, 31, 7), (65, 4, 17), (130, 33, 5), (2049, 47, 16), (33000, 36, 10), (50001, 97, 4), (49152, 128, 17),
+                 (40000, 64, 2), (63, 32, 33), (1000, 65, 20), (500, 96, 33), (33001, 45, 18),
+                 (1, 8, 2), (2, 3, 2), (255, 29, 2), (256, 30, 3), (257, 31, 2), (1025, 13, 4), (70001, 21, 3), (3, 32, 2), (40, 1, 2)]
+
+
+@pytest.mark.parametrize("pad", [0, 1, 3])
+@pytest.mark.parametrize("n,p,C", NARROW_SHAPES)
+def test_narrow_rows(n, p, C, pad):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    # ends with the last row (16-byte aligned rows: up to three elements later, as the header asks); NaN between the rows
+    flat = torch.full(((n - 1) * (p + pad) + (p if (p + pad) % 4 else (p + 3) // 4 * 4),), float("nan"), device="cuda")
+    A = flat.as_strided((n, p), (p + pad, 1))
+    A.copy_(dev(w.A))
+    gp = nadmm.Problem(A, dev(w.b), C, w.s, w.lam, w.rho, dev(w.z), dev(w.y))
+    op = oracle_problem(w)
+    X, V = dev(w.X0), dev(w.V)
+    loss, grad = nadmm.nadmm_loss_grad(gp, X)
+    loss_only, _ = nadmm.nadmm_loss_grad(gp, X, want_grad=False)
+    f_ref, g_ref = orc.loss_grad(op, w.X0)
+    # products of full float32 accuracy summed in float32: some 2^-22 of the terms' absolute sum; the API's bar is 1e-4
+    assert rel_abs(loss.item(), f_ref) <= 1e-6 and rel_abs(loss_only.item(), f_ref) <= 1e-6
+    assert rel_l2(host(grad), g_ref) <= TOL_PRIMITIVE
+    hv = nadmm.nadmm_hessvec(gp, X, V)
+    assert rel_l2(host(hv), orc.hessvec(op, w.X0, w.V)) <= TOL_PRIMITIVE
+    assert torch.equal(hv, nadmm.nadmm_hessvec(gp, X, V))
+    g32 = g_ref.astype(np.float32)
+    k = min(3, p * (C - 1))
+    p_out, it, _ = nadmm.nadmm_cg_solve(gp, X, dev(g32), k, 0.0)
+    p_ref, it_ref, _ = orc.cg(op, w.X0, g32.astype(np.float64), k, 0.0)
+    assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
+    Xn = X.clone()
+    st = nadmm.nadmm_local_newton(gp, Xn, nadmm.make_params(2, k, 10))
+    w.max_newton, w.max_cg = 2, k
+    X_ref, _, _ = oracle_newton_following(op, w.X0, w, st["alpha"])
+    assert rel_l2(host(Xn), X_ref) <= TOL_ITERATE
