@@ -20,7 +20,7 @@
 // only pauses for the K-split exchange and the rows.
 // Measured against two sweeps (with the other kernels of the call): CG iteration on 50000 x 3072, C = 10: 227 -> 162 us (sweep
 // 141 us, 4.4 TB/s), on 75000 x 2048, C = 10 with resident operands: 240 -> 152 us (sweep 112 us, 5.5 TB/s, the rate at which a
-// plain read streams here); 250000 x 2000, C = 20: 772 -> 550 us.  Streamed operands cost 64 bytes per step, class and part
+// plain read streams here); 250000 x 2000, C = 20: 772 -> 545 us.  Streamed operands cost 64 bytes per step, class and part
 // from the L2 next to 2 KB of A.
 #include "nadmm_internal.h"
 #include "nadmm_cgstep.h"
@@ -38,6 +38,8 @@ constexpr int kStepCols = 32;
 constexpr int kSlotBytes = 2048;   // one step of a tile: 16 rows x 32 columns, high plane and low plane
 constexpr int kMaxSteps1 = 96;     // C-1 <= 16: 12 steps per wave
 constexpr int kMaxSteps2 = 64;     // C-1 <= 32: 8 steps per wave
+constexpr int kExtra = 3;          // free classes beyond 16 that need no second block of classes (EX)
+constexpr int kExtraGroups = 5;    // steps whose extra classes share an accumulator: 5 x 3 of its 16 class rows
 constexpr int kMaxLdsSlots = 8;    // steps per wave whose tile stays in LDS
 
 struct WideArgs {
@@ -56,28 +58,44 @@ __device__ __forceinline__ int column_of(int kg, int e) { return 16 * (e >> 2) +
 // The operands of a call as the matrix instructions read them.  Per step of 32 columns, class and part one run of 64 bytes:
 // the 8 columns of each of the four k-groups in bf16.  Order: [step][block of 16 classes][part][class][k-group];
 // parts: X in three (full float32 accuracy of the logits), V in two; columns past p are zero.
+// ex: the classes from 16 on (at most kExtra) go into one block of 16 columns behind the step's 16 classes instead, all parts of
+// them side by side: column kExtra * part + class - 16.
 __global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restrict__ X, const float* __restrict__ V, int p, int NC,
-                                                            int steps, char* __restrict__ dst, const int32_t* flag) {
+                                                            int steps, int ex, char* __restrict__ dst, const int32_t* flag) {
   const int t = blockIdx.x * 256 + threadIdx.x;
-  const int per_step = NC * 4;
+  const int cols = ex ? 16 + kExtra : NC;       // ex: the missing extra classes are written as zeros
+  const int per_step = cols * 4;
   if (t >= steps * per_step) return;
   const int s = t / per_step, rest = t - s * per_step;
-  const int cls = rest % NC, kg = rest / NC;   // neighbouring threads read neighbouring classes
-  const int nb = cls >> 4, c = cls & 15;
-  const int ncls = nb == 0 ? (NC < 16 ? NC : 16) : NC - 16;
+  const int cls = rest % cols, kg = rest / cols;  // neighbouring threads read neighbouring classes
   const int parts = (X != nullptr ? 3 : 0) + (V != nullptr ? 2 : 0);
+  const int clc = cls < NC ? cls : NC - 1;
   float x[8], v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int j = kStepCols * s + column_of(kg, e);
-    const size_t at = (size_t)(j < p ? j : p - 1) * NC + cls;
+    const size_t at = (size_t)(j < p ? j : p - 1) * NC + clc;
     const float xv = X != nullptr ? X[at] : 0.f, vv = V != nullptr ? V[at] : 0.f;
-    x[e] = j < p ? xv : 0.f;
-    v[e] = j < p ? vv : 0.f;
+    const bool ok = j < p && cls < NC;
+    x[e] = ok ? xv : 0.f;
+    v[e] = ok ? vv : 0.f;
   }
   if (flag != nullptr && *flag == 0) return;
-  char* base = dst + ((size_t)s * NC + 16 * nb) * parts * 64 + (size_t)c * 64 + kg * 16;
-  const size_t stride = (size_t)ncls * 64;  // from part to part
+  char* base;
+  size_t stride;  // from part to part
+  if (ex) {
+    char* step = dst + (size_t)s * (16 * 64 * parts + 1024);
+    base = cls < 16 ? step + (size_t)cls * 64 + kg * 16 : step + 16 * 64 * parts + (size_t)(cls - 16) * 64 + kg * 16;
+    stride = cls < 16 ? 16 * 64 : kExtra * 64;
+    if (cls == 16 + kExtra - 1) {  // the block's columns that hold nothing
+      for (int c = kExtra * parts; c < 16; ++c) *reinterpret_cast<u32x4*>(step + 16 * 64 * parts + (size_t)c * 64 + kg * 16) = u32x4{0u, 0u, 0u, 0u};
+    }
+  } else {
+    const int nb = cls >> 4, c = cls & 15;
+    const int ncls = nb == 0 ? (NC < 16 ? NC : 16) : NC - 16;
+    base = dst + ((size_t)s * NC + 16 * nb) * parts * 64 + (size_t)c * 64 + kg * 16;
+    stride = (size_t)ncls * 64;
+  }
   int k = 0;
   if (X != nullptr) {
     u32x4 a, b, d;
@@ -95,16 +113,27 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restr
   }
 }
 
-// The operands of all of a wave's steps stay in registers where they fit beside the accumulators (4 registers per step, class
-// block and part, 8 per step and class block, and two steps of A in flight); else they stream.  The stream costs: at
-// 75000 x 2048, C = 10 a sweep with V took 130 us with streamed operands (C = 3: 110 us, the rate of the memory).
-template <int SPW, int NB, bool HAS0, bool HAS1>
-__host__ __device__ constexpr bool operands_resident() {
-  return 4 * SPW * NB * ((HAS0 ? 3 : 0) + (HAS1 ? 2 : 0)) + 8 * SPW * NB + 8 * (SPW > kMaxLdsSlots ? SPW - kMaxLdsSlots : 0) + 16 <= 176;
+// Steps of a wave whose operands stay in registers for the whole kernel; those of the others stream with the rows.  As many as
+// fit beside the accumulators and two steps in flight: the stream costs.  At 75000 x 2048, C = 10 a sweep with V took 130 us with
+// streamed and 112 us with resident operands (C = 3, where there is little to stream: 110 us, the rate of the memory); at
+// 250000 x 2000 a sweep with V takes 380 us with 9 free classes (all resident) and 540 us with 19 (all streamed).
+template <int SPW, int NB, bool HAS0, bool HAS1, bool EX>
+__host__ __device__ constexpr int resident_steps() {
+  constexpr int op = 4 * (NB * ((HAS0 ? 3 : 0) + (HAS1 ? 2 : 0)) + (EX ? 1 : 0));
+  constexpr int fixed = 8 * SPW * NB + (EX ? 8 * ((SPW + kExtraGroups - 1) / kExtraGroups) : 0) +
+                        8 * (SPW > kMaxLdsSlots ? SPW - kMaxLdsSlots : 0) + 16;
+  constexpr int room = 176 + (HAS0 ? 0 : 12);   // what the rest of the kernel leaves of 256 registers
+  if (fixed + op * SPW <= room) return SPW;
+  constexpr int some = (room - (EX ? 26 : 0) - fixed - 2 * op) / op;
+  return some > 0 ? some : 0;
 }
 
 // SPW: step slots per wave; D: steps in flight (divides SPW); LS: step slots whose tile stays in LDS; NB: blocks of 16 classes.
-template <int SPW, int D, int NB, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
+// EX: 17 to 19 free classes with one block of 16 and up to three extra classes on the side.  A second block of classes would
+// double accumulators and operands for 3 of its 16 columns.  The parts of the extra classes' operands (3 classes, 5 parts)
+// share one block of 16 columns, and the sums of five steps share one accumulator: the extra classes' D stands in the class
+// rows 3 g .. 3 g + 2 of the operand for step 5 j + g and zeros in the others.
+template <int SPW, int D, int NB, bool EX, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
 __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
   static_assert(SPW % D == 0, "the stream's slots repeat with the tiles");
   const RowArgs& a = wa.r;
@@ -112,10 +141,14 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
   constexpr int LS = SPW < kMaxLdsSlots ? SPW : kMaxLdsSlots;
   constexpr int RS = SPW - LS;                       // steps of the tile held in registers
   constexpr int kMats = (HAS0 ? 1 : 0) + (HAS1 ? 1 : 0);
-  constexpr int kQuads = kMats * NB;
+  static_assert(!EX || NB == 1, "extra classes go with one block");
+  constexpr int kQuads = kMats * NB + (EX ? 1 : 0);
+  constexpr int kQuadE = kMats * NB;   // the extra classes' sums
+  constexpr int AX = EX ? (SPW + kExtraGroups - 1) / kExtraGroups : 1;
   constexpr int kMatW = HAS0 ? 1 : 0;
   constexpr int PX = HAS0 ? 3 : 0, PARTS = PX + (HAS1 ? 2 : 0);
-  constexpr bool RES = operands_resident<SPW, NB, HAS0, HAS1>();
+  constexpr int RN = resident_steps<SPW, NB, HAS0, HAS1, EX>();
+  constexpr bool RES = RN == SPW;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -141,11 +174,17 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[i][h][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 accx[AX][2];
+#pragma unroll
+  for (int j = 0; j < AX; ++j) accx[j][0] = accx[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4* scratch = part + (size_t)kWaves * kQuads * 64 + wave * 64;  // EX: this wave's 1 KB
   double loss_acc = 0.0;
 
   // ---- the stream: rows of A and operands of one step ----
   float4 pf[D][2];
-  u32x4 ob[RES ? SPW : D][NB][PARTS];
+  constexpr int OB = RN + (RES ? 0 : D);   // operands held: the resident steps, then the stream's slots
+  u32x4 ob[OB][NB][PARTS];
+  u32x4 oe[EX ? OB : 1];
   // operand offsets of this lane: padded class lanes read the block's last class again (their logits are never used)
   const int cls1 = NB == 2 ? NC - 16 : 0;
   int olane[NB];
@@ -158,20 +197,22 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
     return a.A + row * a.lda + kStepCols * step0 + 4 * kg;
   };
   // step slots below SPW - 2 exist for every wave and hold whole steps; the others are clamped into the matrix
+  const int step_bytes = EX ? 16 * 64 * PARTS + 1024 : NC * PARTS * 64;
   // buffer loads: the lane's offset in a register, everything else (step, part) uniform
   const __amdgpu_buffer_rsrc_t ops =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wa.op), 0, wa.steps * NC * PARTS * 64, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wa.op), 0, wa.steps * step_bytes, 0x00020000);
   auto load_operands = [&](int b, int i) {
     const int s = (i < SPW - 2 || i < count) ? step0 + i : wa.steps - 1;  // uniform
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int k = 0; k < PARTS; ++k)
-        ob[b][nb][k] = __builtin_amdgcn_raw_buffer_load_b128(ops, olane[nb], s * (NC * PARTS * 64) + k * opart[nb], 0);
+        ob[b][nb][k] = __builtin_amdgcn_raw_buffer_load_b128(ops, olane[nb], s * step_bytes + k * opart[nb], 0);
+    if (EX) oe[EX ? b : 0] = __builtin_amdgcn_raw_buffer_load_b128(ops, m * 64 + kg * 16, s * step_bytes + 16 * 64 * PARTS, 0);
   };
   auto load = [&](int b, int i, const float* rp) {
     const int s = (i < SPW - 2 || i < count) ? step0 + i : wa.steps - 1;  // uniform
-    if (!RES) load_operands(b, i);
+    if (i >= RN) load_operands(RN + b, i);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       int off = kStepCols * i + 16 * h;
@@ -208,9 +249,16 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
     cl[nb] = cv[nb] ? 16 * nb + m : NC - 1;
   }
 
+  // EX: lane m holds the extra class 16 + m % 3 as well (lanes 0..14; the same value in all five groups); lanes 0..2 count it
+  const int xc = m % kExtra, xg = m / kExtra;
+  const bool xv = EX && xg < kExtraGroups && 16 + xc < NC;
+  const bool xone = xv && xg == 0;
+  const int xcl = 16 + xc < NC ? 16 + xc : NC - 1;
+
   u32x4 keep[RS > 0 ? RS : 1][2];
   u32x4 dhi[NB], dlo[NB];  // D of the previous tile; k-slots of a lane: its four rows against the high part, then against the low part
   const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
+  unsigned xh[2] = {0u, 0u}, xl[2] = {0u, 0u};  // D of the extra classes
 #pragma unroll
   for (int i = 0; i < (RS > 0 ? RS : 1); ++i) keep[i][0] = keep[i][1] = zero4;
 #pragma unroll
@@ -229,27 +277,32 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
       t[h] = u32x4{th[0], th[1], tl[0], tl[1]};
     }
   };
-  auto multiply_transposed = [&](int i, const u32x4 (&t)[2], const u32x4 (&dop)[NB]) {
+  auto multiply_transposed = [&](int i, const u32x4 (&t)[2], const u32x4 (&dop)[NB], const unsigned (&xop)[2]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[i][h][nb] = mfma(dop[nb], t[h], acc[i][h][nb]);
+    if constexpr (EX) {
+      const bool here = xg == i % kExtraGroups;
+      const unsigned a0 = here ? xop[0] : 0u, a1 = here ? xop[1] : 0u;
+      const u32x4 q = u32x4{a0, a1, a0, a1};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) accx[i / kExtraGroups][h] = mfma(q, t[h], accx[i / kExtraGroups][h]);
+    }
   };
   const float* rp = row_ptr(r_begin);
   if (r_begin < r_end) {
 #pragma unroll
     for (int i = 0; i < D; ++i) load(i, i, rp);
   }
-  if constexpr (RES) {
 #pragma unroll
-    for (int i = 0; i < SPW; ++i) load_operands(i, i);
-  }
+  for (int i = 0; i < RN; ++i) load_operands(i, i);
 
   for (int64_t row0 = r_begin; row0 < r_end; row0 += kTileRows) {
     const float* rp_next = row_ptr(row0 + kTileRows);
     const int left = r_end - row0 < kTileRows ? (int)(r_end - row0) : kTileRows;  // rows of this tile
     // cached probabilities or labels of rows row0 + 4 kg + e
-    float pin[NB][4];
+    float pin[NB][4], pinx[4];
     int label[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -257,18 +310,19 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
       if (KIND == kRowsHv && !HAS0) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) pin[nb][e] = (a.Pin + row0 * NC)[(unsigned)(r * NC + cl[nb])];
+        if (EX) pinx[e] = (a.Pin + row0 * NC)[(unsigned)(r * NC + xcl)];
       }
       if (KIND == kRowsGrad) label[e] = (a.labels + row0)[(unsigned)r];
     }
 
     // ---------------- steps: product of the previous tile with its D, logits of this tile ----------------
-    f32x4 accZ[NB], accW[NB];
+    f32x4 accZ[NB], accW[NB], accE = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) accZ[nb] = accW[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < SPW; ++i) {
       const int b = i % D;
-      const int o = RES ? i : b;
+      const int o = i < RN ? i : RN + b;
       const int s = step0 + i;
       u32x4 told[2];
       fetch_transposed(i, told);
@@ -308,13 +362,17 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
           for (int nb = 0; nb < NB; ++nb)
             accW[nb] = mfma(t == 0 ? alo : ahi, ob[o][nb][HAS1 ? PX + (t == 1 ? 1 : 0) : 0], accW[nb]);
         };
+        const u32x4 ext = oe[EX ? o : 0];
         if (HAS0) term_z(0);
+        if (EX && HAS0) accE = mfma(alo2, ext, accE);
         if (HAS1) term_w(0);
-        multiply_transposed(i, told, dlo);
+        multiply_transposed(i, told, dlo, xl);
+        if (EX) accE = mfma(alo, ext, accE);
         if (HAS0) { term_z(1); }
         if (HAS1) term_w(1);
         if (HAS0) { term_z(2); }
-        multiply_transposed(i, told, dhi);
+        multiply_transposed(i, told, dhi, xh);
+        if (EX) accE = mfma(ahi, ext, accE);
         if (HAS0) { term_z(3); }
         if (HAS1) term_w(2);
         if (HAS0) { term_z(4); term_z(5); }
@@ -339,11 +397,12 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
       if (HAS0) part[(wave * kQuads + nb) * 64 + lane] = accZ[nb];
       if (HAS1) part[(wave * kQuads + kMatW * NB + nb) * 64 + lane] = accW[nb];
     }
+    if (EX) part[(wave * kQuads + kQuadE) * 64 + lane] = accE;
     lds_barrier();
-    f32x4 z[NB], w[NB];
+    f32x4 z[NB], w[NB], zx = f32x4{0.f, 0.f, 0.f, 0.f}, wx = zx, ex = zx;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) z[nb] = w[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int RU = kQuads >= 4 ? 1 : (kQuads == 2 ? 2 : 4);  // waves' partials requested together
+    constexpr int RU = kQuads >= 3 ? 1 : (kQuads == 2 ? 2 : 4);  // waves' partials requested together
 #pragma unroll
     for (int sw0 = 0; sw0 < kWaves; sw0 += RU) {
       f32x4 pt[RU][kQuads];
@@ -357,22 +416,29 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
         for (int nb = 0; nb < NB; ++nb) {
           if (HAS0) z[nb] += pt[u][nb];
           if (HAS1) w[nb] += pt[u][kMatW * NB + nb];
+          if (EX) ex += pt[u][EX ? kQuadE : 0];
         }
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (EX) {  // the parts of a class lie in different lanes: through the wave's scratch (in order, no barrier)
+      scratch[lane] = ex;
+      const f32x4* col = scratch + 16 * kg + xc;
+      if (HAS0) zx = (col[0] + col[kExtra]) + col[2 * kExtra];
+      if (HAS1) wx = col[PX * kExtra] + col[(PX + 1) * kExtra];
     }
 
     // ---------------- rows: lane (m, kg) holds rows row0 + 4 kg + e, classes 16 nb + m ----------------
     float d[NB][4];
     // what wave e keeps of row e for the stores and the row loss (selected without branches)
-    float pk[NB], zk[NB], mk = 0.f, ak = 1.f, zbk = 0.f;
+    float pk[NB], zk[NB], mk = 0.f, ak = 1.f, zbk = 0.f, dx[4], pkx = 0.f, zkx = 0.f;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) pk[nb] = zk[nb] = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool valid = 4 * kg + e < left;
-      float P[NB], M = 0.f, alpha = 1.f;
+      float P[NB], Px = 0.f, M = 0.f, alpha = 1.f;
       if (HAS0) {
-        float mx = 0.f;  // the reference class has logit 0
+        float mx = xv ? fmaxf(zx[e], 0.f) : 0.f;  // the reference class has logit 0
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) mx = fmaxf(mx, cv[nb] ? z[nb][e] : 0.f);
         M = row16_max(mx);
@@ -382,20 +448,28 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
           P[nb] = cv[nb] ? expf(z[nb][e] - M) : 0.f;
           es += P[nb];
         }
+        if (EX) {
+          Px = xv ? expf(zx[e] - M) : 0.f;
+          es += xone ? Px : 0.f;
+        }
         alpha = row16_sum(es) + expf(-M);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) P[nb] = P[nb] / alpha;
+        if (EX) Px = Px / alpha;
       } else {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) P[nb] = cv[nb] ? pin[nb][e] : 0.f;
+        if (EX) Px = xv ? pinx[e] : 0.f;
       }
       if (KIND == kRowsHv) {
         float t = 0.f;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) t = fmaf(P[nb], cv[nb] ? w[nb][e] : 0.f, t);
+        if (EX) t = fmaf(xone ? Px : 0.f, xone ? wx[e] : 0.f, t);
         t = row16_sum(t);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) d[nb][e] = (valid && cv[nb]) ? P[nb] * (w[nb][e] - t) : 0.f;
+        if (EX) dx[e] = (valid && xv) ? Px * (wx[e] - t) : 0.f;
       } else {
         float zb = 0.f;
 #pragma unroll
@@ -403,6 +477,11 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
           const bool mine = cv[nb] && 16 * nb + m == label[e];
           zb += mine ? z[nb][e] : 0.f;
           d[nb][e] = (valid && cv[nb]) ? P[nb] - (mine ? 1.f : 0.f) : 0.f;
+        }
+        if (EX) {
+          const bool mine = xv && 16 + xc == label[e];
+          zb += (mine && xone) ? zx[e] : 0.f;
+          dx[e] = (valid && xv) ? Px - (mine ? 1.f : 0.f) : 0.f;
         }
         zbk = wave == e ? zb : zbk;
         mk = wave == e ? M : mk;
@@ -413,6 +492,10 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
         for (int nb = 0; nb < NB; ++nb) {
           pk[nb] = wave == e ? P[nb] : pk[nb];
           if (HAS0) zk[nb] = wave == e ? z[nb][e] : zk[nb];
+        }
+        if (EX) {
+          pkx = wave == e ? Px : pkx;
+          if (HAS0) zkx = wave == e ? zx[e] : zkx;
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -431,6 +514,11 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
             if (a.Pout) (a.Pout + row0 * NC)[at] = pk[nb];
             if (HAS0 && a.Z0out) (a.Z0out + row0 * NC)[at] = zk[nb];
           }
+        if (EX && xone) {
+          const unsigned at = (unsigned)(r * NC + xcl);
+          if (a.Pout) (a.Pout + row0 * NC)[at] = pkx;
+          if (HAS0 && a.Z0out) (a.Z0out + row0 * NC)[at] = zkx;
+        }
       }
     }
 #pragma unroll
@@ -441,6 +529,13 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
       dhi[nb] = u32x4{h0, h1, h0, h1};
       dlo[nb] = u32x4{l0, l1, l0, l1};
     }
+    if constexpr (EX) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        xh[k] = pack2(dx[2 * k], dx[2 * k + 1]);
+        xl[k] = pack2(dx[2 * k] - low_as_float(xh[k]), dx[2 * k + 1] - high_as_float(xh[k]));
+      }
+    }
 
   }
   // the last tile's product with D
@@ -449,8 +544,8 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
     if (i < SPW - 2 || i < count) {  // uniform
       u32x4 told[2];
       fetch_transposed(i, told);
-      multiply_transposed(i, told, dlo);
-      multiply_transposed(i, told, dhi);
+      multiply_transposed(i, told, dlo, xl);
+      multiply_transposed(i, told, dhi, xh);
     }
     if (i & 1) __builtin_amdgcn_sched_barrier(0);
   }
@@ -472,6 +567,15 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
             const int c = 16 * nb + 4 * kg + e;
             if (c < NC) stage[(16 * h + m) * NC + c] = acc[i][h][nb][e];
           }
+      if constexpr (EX) {  // class row r of the shared accumulator: step r / 3 of its five, extra class r % 3
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = 4 * kg + e, c = 16 + r % kExtra;
+            if (r / kExtra == i % kExtraGroups && c < NC) stage[(16 * h + m) * NC + c] = accx[i / kExtraGroups][h][e];
+          }
+      }
       const int s = step0 + i;
       const int cols = p - kStepCols * s < kStepCols ? p - kStepCols * s : kStepCols;
       const int total = cols * NC;
@@ -479,7 +583,7 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
       if (quads_ok) {
         const int quads = total >> 2;
 #pragma unroll
-        for (int u = 0; u < 4 * NB / 2; ++u) {
+        for (int u = 0; u < (EX ? 3 : 2 * NB); ++u) {
           const int q = lane + 64 * u;
           if (q < quads) *reinterpret_cast<f32x4*>(dst + 4 * q) = *reinterpret_cast<const f32x4*>(stage + 4 * q);
         }
@@ -507,43 +611,43 @@ int steps_of(int p) { return (p + kStepCols - 1) / kStepCols; }
 
 bool rows_16_byte_aligned(const RowArgs& a) { return (a.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(a.A) & 15) == 0; }
 
-template <int SPW, int D, int NB, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
+template <int SPW, int D, int NB, bool EX, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
 hipError_t launch_a(const WideArgs& wa, int grid, hipStream_t st) {
   constexpr int LS = SPW < kMaxLdsSlots ? SPW : kMaxLdsSlots;
   constexpr int kMats = (HAS0 ? 1 : 0) + (HAS1 ? 1 : 0);
-  constexpr size_t lds = (size_t)kWaves * (LS + (SPW > LS ? 1 : 0)) * kSlotBytes + (size_t)kWaves * kMats * NB * 64 * 16;
+  constexpr size_t lds = (size_t)kWaves * (LS + (SPW > LS ? 1 : 0)) * kSlotBytes + (size_t)kWaves * (kMats * NB + (EX ? 2 : 0)) * 64 * 16;
   static_assert(lds <= 160 * 1024, "LDS of a compute unit");
   static uint64_t lds_set = 0;  // per device
-  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&wide_kernel<SPW, D, NB, KIND, HAS0, HAS1, STORES, ANY>), &lds_set);
+  hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&wide_kernel<SPW, D, NB, EX, KIND, HAS0, HAS1, STORES, ANY>), &lds_set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((wide_kernel<SPW, D, NB, KIND, HAS0, HAS1, STORES, ANY>), dim3(grid), dim3(kThreads), lds, st, wa);
+  hipLaunchKernelGGL((wide_kernel<SPW, D, NB, EX, KIND, HAS0, HAS1, STORES, ANY>), dim3(grid), dim3(kThreads), lds, st, wa);
   return hipGetLastError();
 }
 
-template <int SPW, int D, int NB, int KIND, bool HAS0, bool HAS1, bool STORES>
+template <int SPW, int D, int NB, bool EX, int KIND, bool HAS0, bool HAS1, bool STORES>
 hipError_t launch_s(const WideArgs& wa, int grid, hipStream_t st) {
-  if (rows_16_byte_aligned(wa.r)) return launch_a<SPW, D, NB, KIND, HAS0, HAS1, STORES, false>(wa, grid, st);
-  return launch_a<SPW, D, NB, KIND, HAS0, HAS1, STORES, true>(wa, grid, st);
+  if (rows_16_byte_aligned(wa.r)) return launch_a<SPW, D, NB, EX, KIND, HAS0, HAS1, STORES, false>(wa, grid, st);
+  return launch_a<SPW, D, NB, EX, KIND, HAS0, HAS1, STORES, true>(wa, grid, st);
 }
 
 // Steps in flight with V, with X and with both (more registers per step).  2, 4 and 8 measured alike at 75000 x 2048.
-template <int SPW, int NB, int DV, int DX, int DXV = 1>
+template <int SPW, int NB, bool EX, int DV, int DX, int DXV = 1>
 hipError_t launch_spw(const WideArgs& wa, int grid, hipStream_t st) {
   const RowArgs& a = wa.r;
   const bool h0 = a.B0 != nullptr, h1 = a.B1 != nullptr;
   const bool stores = a.Pout != nullptr || a.Z0out != nullptr;
   if (a.kind == kRowsHv && h1) {
     if constexpr (NB == 1) {  // see wide_takes
-      if (h0 && stores) return launch_s<SPW, DXV, NB, kRowsHv, true, true, true>(wa, grid, st);
-      if (h0) return launch_s<SPW, DXV, NB, kRowsHv, true, true, false>(wa, grid, st);
+      if (h0 && stores) return launch_s<SPW, DXV, NB, EX, kRowsHv, true, true, true>(wa, grid, st);
+      if (h0) return launch_s<SPW, DXV, NB, EX, kRowsHv, true, true, false>(wa, grid, st);
     }
     if (h0 || a.Pin == nullptr) return hipErrorInvalidValue;
-    return launch_s<SPW, DV, NB, kRowsHv, false, true, false>(wa, grid, st);
+    return launch_s<SPW, DV, NB, EX, kRowsHv, false, true, false>(wa, grid, st);
   }
   if (a.kind == kRowsGrad && h0 && !h1) {
     if (a.labels == nullptr || a.loss_part == nullptr) return hipErrorInvalidValue;
-    if (stores) return launch_s<SPW, DX, NB, kRowsGrad, true, false, true>(wa, grid, st);
-    return launch_s<SPW, DX, NB, kRowsGrad, true, false, false>(wa, grid, st);
+    if (stores) return launch_s<SPW, DX, NB, EX, kRowsGrad, true, false, true>(wa, grid, st);
+    return launch_s<SPW, DX, NB, EX, kRowsGrad, true, false, false>(wa, grid, st);
   }
   return hipErrorInvalidValue;
 }
@@ -563,9 +667,13 @@ bool wide_supported(const Shape& s, int64_t lda, const void* A) {
 }
 
 // With two blocks of classes X and V together take 40 registers per step in flight: the kernel spills into its stream (a
-// reload waits for every row requested before it), and two sweeps are faster: 250000 x 2000, C = 20: 867 against 1253 us,
-// 50000 x 1500, C = 25: 167 against 183 us, 100000 x 960, C = 20: 177 against 198 us.
-bool wide_takes(const Shape& s, bool has_x, bool has_v) { return s.NC <= 16 || !(has_x && has_v); }
+// reload waits for every row requested before it), and two sweeps are faster: 50000 x 1500, C = 25: 167 against 183 us.  With
+// up to three extra classes they fit (250000 x 2000, C = 20: 869 us with two sweeps, 1253 with two blocks, 760 with the extra
+// classes on the side); below 14 steps the tiles are too small (100000 x 334, C = 19: 88 against 101 us; x 500: 110 : 108).
+bool wide_takes(const Shape& s, bool has_x, bool has_v) {
+  if (s.NC <= 16 || !(has_x && has_v)) return true;
+  return s.NC <= 16 + kExtra && steps_of(s.p) >= 14;
+}
 
 int wide_num_partials(const Shape& s, int wg_cap) {
   const int64_t tiles = (s.n + kTileRows - 1) / kTileRows;
@@ -575,7 +683,7 @@ int wide_num_partials(const Shape& s, int wg_cap) {
   return (int)((s.n + rows - 1) / rows);
 }
 
-size_t wide_operand_bytes(const Shape& s) { return (size_t)steps_of(s.p) * s.NC * 5 * 64; }
+size_t wide_operand_bytes(const Shape& s) { return (size_t)steps_of(s.p) * (s.NC * 5 * 64 + 1024); }  // at most, see pack_operands_kernel
 
 hipError_t launch_wide(const RowArgs& a, void* operands, float* partial, int nparts, hipStream_t st) {
   WideArgs wa;
@@ -584,23 +692,30 @@ hipError_t launch_wide(const RowArgs& a, void* operands, float* partial, int npa
   wa.partial = partial;
   wa.steps = steps_of(a.p);
   wa.rows_per_wg = (int)((a.n + nparts - 1) / nparts);
-  const int threads = wa.steps * a.NC * 4;
-  hipLaunchKernelGGL(pack_operands_kernel, dim3((threads + 255) / 256), dim3(256), 0, st, a.B0, a.B1, a.p, a.NC, wa.steps,
+  const bool extra = a.NC > 16 && a.NC <= 16 + kExtra;
+  const int threads = wa.steps * (extra ? 16 + kExtra : a.NC) * 4;
+  hipLaunchKernelGGL(pack_operands_kernel, dim3((threads + 255) / 256), dim3(256), 0, st, a.B0, a.B1, a.p, a.NC, wa.steps, extra ? 1 : 0,
                      static_cast<char*>(operands), a.flag);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int spw = (wa.steps + kWaves - 1) / kWaves;
   if (a.NC <= 16) {
-    if (spw <= 4) return launch_spw<4, 1, 4, 4, 4>(wa, nparts, st);
-    if (spw <= 6) return launch_spw<6, 1, 3, 3, 3>(wa, nparts, st);
-    if (spw <= 8) return launch_spw<8, 1, 4, 2, 2>(wa, nparts, st);
-    if (spw <= 10) return launch_spw<10, 1, 2, 2, 2>(wa, nparts, st);
-    return launch_spw<12, 1, 3, 2, 2>(wa, nparts, st);
+    if (spw <= 4) return launch_spw<4, 1, false, 4, 4, 4>(wa, nparts, st);
+    if (spw <= 6) return launch_spw<6, 1, false, 3, 3, 3>(wa, nparts, st);
+    if (spw <= 8) return launch_spw<8, 1, false, 4, 2, 2>(wa, nparts, st);
+    if (spw <= 10) return launch_spw<10, 1, false, 2, 2, 2>(wa, nparts, st);
+    return launch_spw<12, 1, false, 2, 2, 2>(wa, nparts, st);
   }
-  if (spw <= 2) return launch_spw<2, 2, 2, 2>(wa, nparts, st);
-  if (spw <= 4) return launch_spw<4, 2, 4, 2>(wa, nparts, st);
-  if (spw <= 6) return launch_spw<6, 2, 2, 2>(wa, nparts, st);
-  return launch_spw<8, 2, 2, 2>(wa, nparts, st);
+  if (extra) {
+    if (spw <= 2) return launch_spw<2, 1, true, 2, 2, 2>(wa, nparts, st);
+    if (spw <= 4) return launch_spw<4, 1, true, 4, 4, 4>(wa, nparts, st);
+    if (spw <= 6) return launch_spw<6, 1, true, 2, 2, 2>(wa, nparts, st);
+    return launch_spw<8, 1, true, 2, 2, 2>(wa, nparts, st);
+  }
+  if (spw <= 2) return launch_spw<2, 2, false, 2, 2>(wa, nparts, st);
+  if (spw <= 4) return launch_spw<4, 2, false, 4, 2>(wa, nparts, st);
+  if (spw <= 6) return launch_spw<6, 2, false, 2, 2>(wa, nparts, st);
+  return launch_spw<8, 2, false, 2, 2>(wa, nparts, st);
 }
 
 }  // namespace nadmm

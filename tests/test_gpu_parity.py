@@ -552,7 +552,7 @@ def test_two_streams_with_their_own_workspaces_do_not_interfere(cache):
 # shapes on either side of the limits (3073 and 2049 columns with 25 classes take two sweeps).
 WIDE_SHAPES = [(1, 513, 2), (15, 544, 10), (16, 1024, 17), (17, 1025, 5), (257, 1100, 10), (4096, 640, 3), (4097, 1537, 9),
                (300, 2049, 10), (129, 2561, 16), (530, 3072, 10), (40, 3071, 2), (35, 3073, 4),
-               (33, 290, 18), (4100, 330, 20), (70, 513, 33), (48, 1025, 25), (31, 2048, 33), (31, 2049, 25)]
+               (33, 290, 18), (129, 2048, 20), (257, 1500, 19), (50, 700, 18), (4100, 330, 20), (70, 513, 33), (48, 1025, 25), (31, 2048, 33), (31, 2049, 25)]
 
 
 @pytest.mark.parametrize("pad", [0, 3])
