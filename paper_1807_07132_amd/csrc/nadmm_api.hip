@@ -541,6 +541,24 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
   return NADMM_OK;
 }
 
+// Small thin problems: all CG iterations in one launch, instead of one or two launches each (nadmm_small.hip).
+bool small_cg(const Layout& L, int path) { return path == 3 && small_cg_supported(L.s); }
+SmallCg small_cg_args(const nadmm_problem* prob, const Layout& L, void* ws, DevState* ds, const float* X, int max_iter, float tol,
+                      float* zp, const int32_t* flag) {
+  SmallCg c;
+  std::memset(&c, 0, sizeof(c));
+  c.A = prob->d_A; c.n = prob->n; c.lda = prob->lda; c.p = prob->p; c.NC = L.s.NC;
+  c.X = X;
+  c.Pin = X != nullptr ? nullptr : at<float>(ws, L.pcache);
+  c.scale = prob->loss_scale; c.lambda = prob->lambda; c.rho = prob->rho; c.rho_scale = L.rho_scale;
+  c.st = ds;
+  c.pdir = at<float>(ws, L.pdir); c.r = at<float>(ws, L.r); c.dvec = at<float>(ws, L.dvec);
+  c.max_iter = max_iter; c.tol = tol;
+  c.zp = zp;
+  c.flag = flag;
+  return c;
+}
+
 void fill_alphas(float* alphas, int ncand, float gamma) {
   double a = 1.0;
   for (int k = 0; k < ncand; ++k) {
@@ -636,10 +654,14 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     if (!head_in_reduce) NADMM_HIP(launch_newton_head(nh, st));
 
     // CG on H p = -g with the probabilities of this iterate
-    const bool thin_def = thin_deferred(path) && !L.thin_gen && params->max_cg >= 1;
+    const bool small = small_cg(L, path) && params->max_cg >= 1;  // CG and the logits A p of the step in one launch
+    const bool thin_def = thin_deferred(path) && !L.thin_gen && !small && params->max_cg >= 1;
     const bool hist = use_hist && cg_deferred(path) && params->max_cg >= 1 && params->max_cg <= L.hist_bufs;
     const size_t hist_stride = align256((size_t)L.s.n * L.s.NC * sizeof(float)) / sizeof(float);
-    for (int k = 0; k < params->max_cg; ++k) {
+    if (small)
+      NADMM_HIP(launch_small_cg(small_cg_args(prob, L, d_ws, ds, nullptr, params->max_cg, params->cg_tol, at<float>(d_ws, L.zp),
+                                              &ds->newton_active), st));
+    for (int k = 0; k < params->max_cg && !small; ++k) {
       float* w_rows = hist ? at<float>(d_ws, L.hist) + (size_t)k * hist_stride : nullptr;
       if ((rc = cg_iteration(prob, L, path, d_ws, ds, nullptr, false, params->cg_tol, k, st, w_rows,
                              (k == 0 && head_in_reduce) ? &nh : nullptr, thin_def)) != NADMM_OK)
@@ -656,7 +678,9 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     rz.Z1out = at<float>(d_ws, L.zp);
     rz.flag = &ds->newton_active;
     const bool eval_finishes = hist && ls_eval_takes_pending(prob->n);  // the row kernel of the line search applies the last update
-    if (hist) {  // A p comes from the history; the last update alone, unless the line search's row kernel takes it along
+    if (small) {
+      // A p is in place
+    } else if (hist) {  // A p comes from the history; the last update alone, unless the line search's row kernel takes it along
       if (!eval_finishes)
         NADMM_HIP(launch_cg_pending_finish(cg_pend(L, d_ws, ds, (params->max_cg - 1) & 1, true, params->cg_tol), st));
     } else if (pend) {
@@ -955,7 +979,9 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   nh.newton_mode = 0;
   NADMM_HIP(launch_newton_head(nh, st));
 
-  for (int k = 0; k < max_iter; ++k) {
+  const bool small = small_cg(L, path) && max_iter >= 1;
+  if (small) NADMM_HIP(launch_small_cg(small_cg_args(prob, L, d_ws, ds, d_X, max_iter, tol, nullptr, nullptr), st));
+  for (int k = 0; k < max_iter && !small; ++k) {
     if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st)) != NADMM_OK) return rc;
   }
   const bool pend = cg_deferred(path) && max_iter > 0;

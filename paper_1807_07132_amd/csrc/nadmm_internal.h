@@ -352,6 +352,27 @@ int thin_num_partials(const Shape& s);
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
                        const ReduceArgs* prev = nullptr);
 
+// ---- all CG iterations of a small thin problem in one launch (nadmm_small.hip) ----
+struct SmallCg {
+  const float* A;
+  int64_t n, lda;
+  int32_t p, NC;
+  const float* X;        // NULL: the cached probabilities Pin are used
+  const float* Pin;      // n x NC
+  float scale, lambda, rho;
+  const float* rho_scale;
+  DevState* st;          // CG as newton_head_kernel started it; left as after the last iteration taken
+  float* pdir;
+  float* r;
+  float* dvec;
+  int32_t max_iter;
+  float tol;
+  float* zp;             // n x NC, optional: the logits A p of the iterate
+  const int32_t* flag;
+};
+bool small_cg_supported(const Shape& s);
+hipError_t launch_small_cg(const SmallCg& c, hipStream_t st);
+
 // ---- column-sliced two-sweep matrix-core path (nadmm_sliced.hip): any p, C-1 <= 32, lda % 4 == 0 ----
 bool sliced_supported(const Shape& s, int64_t lda, const void* A);
 void sliced_grid(const Shape& s, int* nslices, int* steps_per_slice, int* row_groups);

@@ -1,0 +1,227 @@
+// All CG iterations of a small thin problem in one kernel (gfx950): n <= 2048 rows of up to 32 columns, up to 3 free classes.
+//
+// Such a solve is bound by launches: at 1000 x 20, C = 3 every CG iteration was a launch of 7.4 us around less than 1 us of
+// work.  Here one workgroup keeps its rows of A (up to four per thread) and their probabilities in registers for the whole CG
+// solve; an iteration (Section 2.4) is the product with the rows, a sum over the workgroup and the update of vectors of at most
+// 64 elements by one wave, with two barriers.  At the end the kernel has A in hand and also leaves the logits A p of the step
+// for the line search.  One CG iteration takes about 2 us; a Newton iteration of 10 CG iterations at 1000 x 20, C = 3 with its
+// gradient and line search 107 -> 54 us.
+// float32 products and sums over rows, float64 inner products; every sum in a fixed order.
+#include "nadmm_internal.h"
+#include "nadmm_mfma.h"
+
+namespace nadmm {
+namespace {
+
+constexpr int kRowsPerThread = 4;
+
+template <int NQ, int NC, int THREADS>
+__global__ __launch_bounds__(THREADS) void small_cg_kernel(const SmallCg c) {
+  constexpr int PP = 4 * NQ, D = PP * NC;          // padded columns, vector length with them (<= 64)
+  constexpr int R = kRowsPerThread;
+  constexpr int kSums = THREADS / 16;              // rows of 16 lanes
+  if (c.flag != nullptr && *c.flag == 0) return;
+  __shared__ __attribute__((aligned(16))) float vs[D], xs[D];
+  __shared__ float sums[kSums][D];
+  __shared__ int go_sh;
+  const int t = threadIdx.x, lane = t & 63;
+  const int p = c.p, n = (int)c.n, dlen = p * NC;
+  DevState* st = c.st;
+
+  // rows t, t + THREADS, ... (rows past the end are zeros with P = 0)
+  float a[R][PP], P[R][NC];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int row = t + k * THREADS;
+    const bool valid = row < n;
+    const float* src = c.A + (int64_t)(valid ? row : n - 1) * c.lda;
+#pragma unroll
+    for (int j = 0; j < PP; ++j) {
+      const float v = src[j < p ? j : p - 1];
+      a[k][j] = (valid && j < p) ? v : 0.f;
+    }
+  }
+  // wave 0: one element of the vectors per lane, element lane = j NC + class
+  float r = 0.f, pv = 0.f, dv = 0.f;
+  const int le = lane < dlen ? lane : dlen - 1;
+  if (t < 64) {
+    const float r_in = c.r[le], p_in = c.pdir[le], d_in = c.dvec[le];
+    r = lane < dlen ? r_in : 0.f;
+    pv = lane < dlen ? p_in : 0.f;
+    dv = lane < dlen ? d_in : 0.f;
+    if (lane < D) vs[lane] = dv;
+  }
+  const float rho_ = c.rho_scale != nullptr ? c.rho * *c.rho_scale : c.rho;
+  double rr = st->rr;
+  const double bound = (double)c.tol * sqrt(st->gg_cg);
+  int iters = st->cg_iters, active = st->cg_active;
+  if (c.X != nullptr && t < D) xs[t] = t < dlen ? c.X[t] : 0.f;
+  __syncthreads();
+
+  // probabilities: cached ones, or of the logits A X
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int row = t + k * THREADS;
+    const bool valid = row < n;
+    if (c.X != nullptr) {
+      float z[NC];
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        z[q] = 0.f;
+#pragma unroll
+        for (int j = 0; j < PP; ++j) z[q] = fmaf(a[k][j], xs[j * NC + q], z[q]);
+      }
+      float M = 0.f;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) M = fmaxf(M, z[q]);
+      float alpha = expf(-M);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        P[k][q] = expf(z[q] - M);
+        alpha += P[k][q];
+      }
+      const float inv = 1.f / alpha;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) P[k][q] = valid ? P[k][q] * inv : 0.f;
+    } else {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const float v = c.Pin[(int64_t)(valid ? row : n - 1) * NC + q];
+        P[k][q] = valid ? v : 0.f;
+      }
+    }
+  }
+
+  for (int it = 0; it < c.max_iter && active != 0; ++it) {  // uniform
+    // rows of D = P o W - P o rowsum(P o W), W = A v
+    float dk[R][NC];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      float w[NC], s = 0.f;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        w[q] = 0.f;
+#pragma unroll
+        for (int j = 0; j < PP; ++j) w[q] = fmaf(a[k][j], vs[j * NC + q], w[q]);
+        s = fmaf(P[k][q], w[q], s);
+      }
+#pragma unroll
+      for (int q = 0; q < NC; ++q) dk[k][q] = P[k][q] * (w[q] - s);
+    }
+#pragma unroll
+    for (int j = 0; j < PP; ++j)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        float s = a[0][j] * dk[0][q];
+#pragma unroll
+        for (int k = 1; k < R; ++k) s = fmaf(a[k][j], dk[k][q], s);
+        s = mfma_detail::row16_sum(s);
+        if ((lane & 15) == 0) sums[t >> 4][j * NC + q] = s;
+      }
+    __syncthreads();
+    if (t < 64) {
+      float s = 0.f;
+      if (lane < D) {
+        float u[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) u[k & 3] += sums[k][lane];
+        s = (u[0] + u[1]) + (u[2] + u[3]);
+      }
+      const float q = lane < dlen ? fmaf(c.lambda + rho_, dv, c.scale * s) : 0.f;
+      const double dq = mfma_detail::wave64_sum((double)dv * (double)q);
+      int go = 1;
+      if (!(dq > 0.0) || !isfinite(dq)) {  // no positive curvature: keep the current iterate
+        go = 0;
+      } else {
+        const float al = (float)(rr / dq);
+        r = fmaf(-al, q, r);
+        const double rr_new = mfma_detail::wave64_sum((double)r * (double)r);
+        pv = fmaf(al, dv, pv);
+        if (sqrt(rr_new) <= bound) go = 0;
+        else dv = fmaf((float)(rr_new / rr), dv, r);
+        rr = rr_new;
+        iters += 1;
+      }
+      if (lane < D) vs[lane] = dv;
+      if (lane == 0) go_sh = go;
+    }
+    __syncthreads();
+    active = go_sh;
+  }
+
+  if (t < 64) {
+    if (lane < dlen) {
+      c.pdir[lane] = pv;
+      c.r[lane] = r;
+      c.dvec[lane] = dv;
+    }
+    if (lane == 0) {
+      st->rr = rr;
+      st->cg_iters = iters;
+      st->cg_active = active;
+    }
+  }
+  if (c.zp == nullptr) return;
+  __syncthreads();
+  if (t < D) xs[t] = pv;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int row = t + k * THREADS;
+    float w[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      w[q] = 0.f;
+#pragma unroll
+      for (int j = 0; j < PP; ++j) w[q] = fmaf(a[k][j], xs[j * NC + q], w[q]);
+    }
+    if (row < n) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) c.zp[(int64_t)row * NC + q] = w[q];
+    }
+  }
+}
+
+template <int NQ, int NC>
+hipError_t launch_t(const SmallCg& c, hipStream_t st) {
+  if constexpr (4 * NQ * NC <= 64) {
+    if (c.n <= 256 * kRowsPerThread) hipLaunchKernelGGL((small_cg_kernel<NQ, NC, 256>), dim3(1), dim3(256), 0, st, c);
+    else hipLaunchKernelGGL((small_cg_kernel<NQ, NC, 512>), dim3(1), dim3(512), 0, st, c);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int NQ>
+hipError_t launch_nq(const SmallCg& c, hipStream_t st) {
+  switch (c.NC) {
+    case 1: return launch_t<NQ, 1>(c, st);
+    case 2: return launch_t<NQ, 2>(c, st);
+    case 3: return launch_t<NQ, 3>(c, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+// One workgroup of 512 threads with four rows each; the limits on columns and classes are those of the thin-data kernel.
+bool small_cg_supported(const Shape& s) {
+  return s.n <= 512 * kRowsPerThread && s.p <= 32 && s.NC <= 3 && (s.p + 3) / 4 * 4 * s.NC <= 64;
+}
+
+hipError_t launch_small_cg(const SmallCg& c, hipStream_t st) {
+  if (c.max_iter < 1 || c.A == nullptr || (c.X == nullptr && c.Pin == nullptr) || c.n < 1 || c.n > 512 * kRowsPerThread) return hipErrorInvalidValue;
+  switch ((c.p + 3) / 4) {
+    case 1: return launch_nq<1>(c, st);
+    case 2: return launch_nq<2>(c, st);
+    case 3: return launch_nq<3>(c, st);
+    case 4: return launch_nq<4>(c, st);
+    case 5: return launch_nq<5>(c, st);
+    case 6: return launch_nq<6>(c, st);
+    case 7: return launch_nq<7>(c, st);
+    case 8: return launch_nq<8>(c, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace nadmm

@@ -614,3 +614,26 @@ def test_narrow_rows(n, p, C, pad):
     w.max_newton, w.max_cg = 2, k
     X_ref, _, _ = oracle_newton_following(op, w.X0, w, st["alpha"])
     assert rel_l2(host(Xn), X_ref) <= TOL_ITERATE
+
+
+# All CG iterations of a small thin problem in one launch: rows at the limits of one workgroup (4 rows for 256 or 512 threads; 2049
+# rows take the general path), all numbers of classes, columns that are no whole number of 16-byte pieces, CG that stops early.
+@pytest.mark.parametrize("tol", [0.0, 3e-2])
+@pytest.mark.parametrize("n,p,C", [(1, 4, 2), (3, 1, 2), (255, 32, 3), (1000, 20, 3), (1023, 21, 4), (1024, 7, 2), (1025, 16, 4), (2047, 29, 2),
+                                   (2048, 32, 3), (2049, 32, 3)])
+def test_small_cg(n, p, C, tol):
+    w = workloads.generic(n, p, C, seed=n, x_std=0.5 / math.sqrt(p), mean=True)
+    gp, op = nadmm.Problem.from_workload(w), oracle_problem(w)
+    d = p * (C - 1)
+    k = min(10, d)
+    g32 = orc.grad(op, w.X0).astype(np.float32)
+    got, it, relres = nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g32), k, tol)
+    ref, it_ref, rel_ref = orc.cg(op, w.X0, g32.astype(np.float64), k, tol)
+    assert it.item() == it_ref and rel_l2(host(got), ref) <= TOL_ITERATE
+    assert abs(relres.item() - rel_ref) <= 1e-5 + 1e-3 * rel_ref
+    X = dev(w.X0)
+    st = nadmm.nadmm_local_newton(gp, X, nadmm.make_params(2, k, 10, cg_tol=tol))
+    w.max_newton, w.max_cg, w.cg_tol = 2, k, tol
+    X_ref, st_ref, forced = oracle_newton_following(op, w.X0, w, st["alpha"])
+    assert rel_l2(host(X), X_ref) <= TOL_ITERATE
+    assert forced or st["cg_iters"] == [i["cg_iters"] for i in st_ref["iters"]]
