@@ -11,7 +11,12 @@
 //            log-sum-exp / probabilities / D of 4 of the 32 rows with 16-lane DPP
 //            reductions and hands its D entries to the others through LDS;
 //   phase 2  out^T (16 x cols) += D^T A_tile        -- A re-read from a
-//            wave-private, bank-swizzled LDS copy written in phase 1.
+//            wave-private LDS copy written in phase 1 in 16-byte pieces and
+//            transposed by the read (ds_read_b64_tr_b16).  (Interleaving
+//            row pairs in registers and writing 4-byte words took 64
+//            instructions and 48 LDS writes more per tile and wave and the
+//            registers that the any-stride variant with X and V spilled:
+//            60000 x 785, C = 10, Hessian-vector product 67.8 -> 55.3 us.)
 // A is read from HBM exactly once; the p x (C-1) accumulators stay in registers
 // for the whole row range and are written once as a per-workgroup partial.
 //
@@ -43,6 +48,7 @@ struct FusedArgs {
   float* partial;     // gridDim.x x (p*NC) or NULL (no transpose product)
   int32_t steps;      // ceil(p / 32)
   int32_t rows_per_wg;
+  int32_t tile_rows;  // rows per tile, <= 32
   CgPend cg;          // cg.st != NULL: the operand B1 is the result of a pending CG update (kernels without B0 only)
 };
 
@@ -91,6 +97,10 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
   // load goes past element 4 ceil(p/4) of a row, <= lda); ANYSTRIDE: the last piece that lies inside the row
   const int col_max = ANYSTRIDE ? p - 4 : ((p + 3) & ~3) - 4;
 
+  // rows of a tile past its end are not fetched: the loads repeat its last row, and what is computed from them is dropped
+  const int th_rows = fa.tile_rows;
+  auto tile_end = [&](int64_t row0) { return row0 + th_rows < r_end ? row0 + th_rows : r_end; };
+
   // ---- prefetch registers: [step][row block][half of the 8 columns] ----
   // Addresses are clamped into the matrix, so the loads need no branches; rows
   // past the range and columns past p are zeroed when the registers are used.
@@ -102,7 +112,8 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       int64_t row = row0 + m + 16 * rb;
-      row = row < r_end ? row : r_end - 1;
+      const int64_t end = tile_end(row0);
+      row = row < end ? row : end - 1;
       const float* src = a.A + row * a.lda;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -188,11 +199,11 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
   if (deferred) lds_barrier();  // every wave has picked its operands from LDS: the step slots may be overwritten
 
   u32x4 dhi, dlo;  // D of the current tile as MFMA operand
-  for (int64_t row0 = r_begin; row0 < r_end; row0 += kTileRows) {
+  for (int64_t row0 = r_begin; row0 < r_end; row0 += th_rows) {
     // the row this wave handles in the rows stage: e = wave, row = row0 + 4 kg + (e & 3) + 16 (e >> 2)
     const int64_t my_row = row0 + 4 * kg + (wave & 3) + ((wave >> 2) << 4);
-    const bool my_valid = my_row < r_end;
-    const int64_t my_rowc = my_valid ? my_row : r_end - 1;
+    const bool my_valid = my_row < tile_end(row0);
+    const int64_t my_rowc = my_valid ? my_row : tile_end(row0) - 1;
     float aux = 0.f;  // cached probability (Hessian-vector rows without X) or label (gradient / loss rows)
     if (KIND == kRowsHv && !has0) aux = a.Pin[(size_t)my_rowc * NC + mc];
     if (KIND == kRowsGrad || KIND == kRowsLoss) aux = __int_as_float(a.labels[my_rowc]);
@@ -264,18 +275,14 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
           }
         }
         // the registers are free again: prefetch the next tile (past the range the rows clamp to the last row)
-        load_step(i, row0 + kTileRows);
+        load_step(i, row0 + th_rows);
         if (with_cols) {
-          // transposed copy for phase 2: pair (row m, row m+16) of one column per 32-bit word
-          char* base = cmw + i * kStepBytes;
+          // copy for phase 2: blocks of 16 rows x 16 columns (part, row block, column half), 1 KB back to back per instruction
+          char* base = cmw + i * kStepBytes + (kg >> 1) * 512 + m * 32 + (kg & 1) * 16;
 #pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            const unsigned sel = (c & 1) ? 0x07060302u : 0x05040100u;
-            const unsigned hp = __builtin_amdgcn_perm(ahi[1][c >> 1], ahi[0][c >> 1], sel);
-            const unsigned lp = __builtin_amdgcn_perm(alo[1][c >> 1], alo[0][c >> 1], sel);
-            const int off = cm_offset(8 * kg + c, m >> 2) + ((m & 3) << 2);
-            *reinterpret_cast<unsigned*>(base + off) = hp;
-            *reinterpret_cast<unsigned*>(base + 2048 + off) = lp;
+          for (int rb = 0; rb < 2; ++rb) {
+            *reinterpret_cast<u32x4*>(base + 1024 * rb) = ahi[rb];
+            *reinterpret_cast<u32x4*>(base + 2048 + 1024 * rb) = alo[rb];
           }
         }
       }
@@ -354,18 +361,19 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
     // column halves of a step taking turns so that no matrix instruction waits for the one before it.
     u32x4 th[2][2], tl[2][2];
     auto fetch_step = [&](int i, int b) {
-      const char* base = cmw + i * kStepBytes;
+      char* base = cmw + i * kStepBytes + (4 * kg + (m >> 2)) * 32 + (m & 3) * 8;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int off = cm_offset(16 * h + m, kg);
-        th[b][h] = *reinterpret_cast<const u32x4*>(base + off);
-        tl[b][h] = *reinterpret_cast<const u32x4*>(base + 2048 + off);
+      for (int h = 0; h < 2; ++h) {  // k-slots of a lane: rows 4 kg + e, then 16 + 4 kg + e, of column 16 h + m
+        const u32x2 h0 = read_transposed(base + 512 * h), h1 = read_transposed(base + 1024 + 512 * h);
+        const u32x2 l0 = read_transposed(base + 2048 + 512 * h), l1 = read_transposed(base + 3072 + 512 * h);
+        th[b][h] = u32x4{h0[0], h0[1], h1[0], h1[1]};
+        tl[b][h] = u32x4{l0[0], l0[1], l1[0], l1[1]};
       }
     };
     {
       float d0[4], d1[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {  // k-slot pair (2e, 2e+1) = (row 4kg+e, row 16+4kg+e)
+      for (int e = 0; e < 4; ++e) {
         d0[e] = dbuf[e * 64 + lane];
         d1[e] = dbuf[(4 + e) * 64 + lane];
       }
@@ -373,9 +381,10 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
       __builtin_amdgcn_sched_barrier(0);  // keep the requests ahead of the packing below
       unsigned h[4], l[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        h[e] = pack2(d0[e], d1[e]);
-        l[e] = pack2(d0[e] - low_as_float(h[e]), d1[e] - high_as_float(h[e]));
+      for (int e = 0; e < 4; ++e) {  // k-slots 2e, 2e+1
+        const float da = e < 2 ? d0[2 * e] : d1[2 * e - 4], db = e < 2 ? d0[2 * e + 1] : d1[2 * e - 3];
+        h[e] = pack2(da, db);
+        l[e] = pack2(da - low_as_float(h[e]), db - high_as_float(h[e]));
       }
       dhi = u32x4{h[0], h[1], h[2], h[3]};
       dlo = u32x4{l[0], l[1], l[2], l[3]};
@@ -582,6 +591,11 @@ hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_
   fa.steps = steps_of(a.p);
   const int grid = nparts;
   fa.rows_per_wg = (int)((a.n + grid - 1) / grid);
+  // Equal tiles instead of a last one of a few rows, whose stages nothing overlaps: 60000 x 784, C = 10 (234 rows per workgroup, 8
+  // tiles of 30): local solve 4966 -> 4907 us, Hessian-vector product 51.8 -> 51.1 us.  With fewer than 4 tiles there is no
+  // steady state to even out.
+  const int ntiles = (fa.rows_per_wg + kTileRows - 1) / kTileRows;
+  fa.tile_rows = ntiles >= 4 ? (fa.rows_per_wg + ntiles - 1) / ntiles : kTileRows;
   const size_t lds_bytes = (size_t)fa.steps * kStepBytes + kPartBytes + kSumBytes;
   const int spw = (fa.steps + kWaves - 1) / kWaves;
   switch (spw) {
