@@ -249,7 +249,9 @@ int choose_path(const Layout& L, int* path) {
   return NADMM_OK;
 }
 
-// path 4: whether the kernel for narrow rows makes the sweep (more than 16 free classes)
+// path 4: whether the single-pass kernel for wide rows makes a sweep with the transpose product, and whether the kernel for narrow
+// rows makes a sweep (more than 16 free classes)
+bool wide_sweep(const Layout& L, bool has_x, bool has_v) { return L.wide && wide_takes(L.s, has_x, has_v); }
 bool narrow_sweep(const Layout& L, bool has_x, bool has_v) { return L.narrow && L.s.NC > 16 && narrow_takes(L.s, has_x, has_v); }
 
 // partial row losses that a sweep leaves (with_cols: one that also forms A^T rows)
@@ -280,7 +282,7 @@ int sparse_plan(const nadmm_problem* prob, const Layout& L, void* ws, hipStream_
 // previous sweep's partial sums, which that kernel adds up itself, and partial_out where this sweep's go.
 int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArgs ra, bool with_cols,
           int* nparts, hipStream_t st, const CgPend* cg = nullptr, const ReduceArgs* prev = nullptr,
-          float* partial_out = nullptr) {
+          float* partial_out = nullptr, bool packed = false) {
   if (cg != nullptr && path != 2 && path != 3) return NADMM_EINVAL;
   if ((prev != nullptr || partial_out != nullptr) && path != 3) return NADMM_EINVAL;
   ra.A = prob->d_A;
@@ -351,8 +353,8 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
       *nparts = L.narrow_parts;
       return NADMM_OK;
     }
-    if (with_cols && L.wide && wide_takes(L.s, ra.B0 != nullptr, ra.B1 != nullptr)) {
-      NADMM_HIP(launch_wide(ra, at<char>(ws, L.operands), at<float>(ws, L.partial), L.wide_parts, st));
+    if (with_cols && wide_sweep(L, ra.B0 != nullptr, ra.B1 != nullptr)) {
+      NADMM_HIP(launch_wide(ra, at<char>(ws, L.operands), packed, at<float>(ws, L.partial), L.wide_parts, st));
       *nparts = L.wide_parts;
       return NADMM_OK;
     }
@@ -420,7 +422,7 @@ int reduce(const nadmm_problem* prob, const Layout& L, void* ws, int nparts, int
 int hv_apply(const nadmm_problem* prob, const Layout& L, int path, void* ws, const float* X, bool write_pcache,
              const float* v, float* out, double* dot_part, const int32_t* flag, int* nparts_out, hipStream_t st,
              const CgPend* cg = nullptr, const int32_t* red_flag = nullptr, const int32_t* cur = nullptr,
-             const float* v_alt = nullptr, float* w_rows = nullptr, const NewtonHeadArgs* head = nullptr) {
+             const float* v_alt = nullptr, float* w_rows = nullptr, const NewtonHeadArgs* head = nullptr, bool packed = false) {
   RowArgs ra = blank_rows();
   ra.kind = kRowsHv;
   ra.Z1out = w_rows;  // fused single-pass path only: the directional logits A v, n x (C-1)
@@ -431,7 +433,7 @@ int hv_apply(const nadmm_problem* prob, const Layout& L, int path, void* ws, con
   ra.rows_out = at<float>(ws, L.drows);
   ra.flag = flag;
   int nparts = 0;
-  int rc = sweep(prob, L, path, ws, ra, true, &nparts, st, cg);
+  int rc = sweep(prob, L, path, ws, ra, true, &nparts, st, cg, nullptr, nullptr, packed);
   if (rc != NADMM_OK) return rc;
   if (nparts_out) *nparts_out = nparts;
   if (out == nullptr) return NADMM_OK;
@@ -535,9 +537,17 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
     NADMM_HIP(launch_cg_reduce_update(reduce_args(prob, L, ws, nparts, 0, dvec, q, nullptr, &ds->cg_active), cu, st));
     return NADMM_OK;
   }
-  int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, q, at<double>(ws, L.dotpart), &ds->cg_active, nullptr, st);
+  // wide rows with long vectors: the update's second kernel also lays out the direction for the next iteration's sweep
+  const bool packs = path == 4 && wide_sweep(L, false, true) && cg_update_two_kernels(L.s.d);
+  int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, q, at<double>(ws, L.dotpart), &ds->cg_active, nullptr, st, nullptr, nullptr,
+                    nullptr, nullptr, nullptr, nullptr, packs && k > 0 && X == nullptr);
   if (rc != NADMM_OK) return rc;
-  NADMM_HIP(launch_cg_update(cu, st));
+  if (!packs) {
+    NADMM_HIP(launch_cg_update(cu, st));
+    return NADMM_OK;
+  }
+  NADMM_HIP(launch_cg_residual(cu, st));
+  NADMM_HIP(launch_wide_direction(cu, L.s, at<char>(ws, L.operands), st));
   return NADMM_OK;
 }
 

@@ -242,6 +242,9 @@ int cg_update_blocks(int64_t d);
 bool cg_fused_tail_supported(int64_t d, int nparts);
 hipError_t launch_cg_reduce_update(const ReduceArgs& r, const CgUpdateArgs& a, hipStream_t st);
 hipError_t launch_cg_update(const CgUpdateArgs& a, hipStream_t st);
+// long vectors take two kernels, of which this is the first (residual and its partial sums)
+bool cg_update_two_kernels(int64_t d);
+hipError_t launch_cg_residual(const CgUpdateArgs& a, hipStream_t st);
 
 struct CgFinishArgs {
   const DevState* st;
@@ -395,7 +398,10 @@ bool wide_takes(const Shape& s, bool has_x, bool has_v);  // whether it makes th
 int wide_num_partials(const Shape& s, int wg_cap);   // workgroups, at most wg_cap if that is > 0
 size_t wide_operand_bytes(const Shape& s);
 // packs the operands into `operands` and makes the sweep; partial sums and partial losses as launch_fused
-hipError_t launch_wide(const RowArgs& a, void* operands, float* partial, int nparts, hipStream_t st);
+// packed: the operands of this call are in place (launch_wide_direction)
+hipError_t launch_wide(const RowArgs& a, void* operands, bool packed, float* partial, int nparts, hipStream_t st);
+// the second half of a two-kernel CG update; leaves the new direction as the operands of the next product as well
+hipError_t launch_wide_direction(const CgUpdateArgs& a, const Shape& s, void* operands, hipStream_t st);
 
 // ---- sparse storage of A (nadmm_sparse.hip) ----
 // compressed rows of an nrows x ncols matrix; used for A (row view) and for A^T (column view of A)

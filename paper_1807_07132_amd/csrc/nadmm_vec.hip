@@ -1166,15 +1166,22 @@ int cg_update_blocks(int64_t d) {
   return (int)(b < 1024 ? b : 1024);
 }
 
+bool cg_update_two_kernels(int64_t d) { return d > 24 * kTail; }
+
+hipError_t launch_cg_residual(const CgUpdateArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(cg_residual_kernel, dim3(cg_update_blocks(a.d)), dim3(kCgThreads), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_cg_update(const CgUpdateArgs& a, hipStream_t st) {
   if (a.d <= 8 * kTail) {
     hipLaunchKernelGGL(cg_update_kernel<8>, dim3(1), dim3(kTail), 0, st, a);
-  } else if (a.d <= 24 * kTail) {
+  } else if (!cg_update_two_kernels(a.d)) {
     hipLaunchKernelGGL(cg_update_kernel<24>, dim3(1), dim3(kTail), 0, st, a);
   } else {
-    const int blocks = cg_update_blocks(a.d);
-    hipLaunchKernelGGL(cg_residual_kernel, dim3(blocks), dim3(kCgThreads), 0, st, a);
-    hipLaunchKernelGGL(cg_direction_kernel, dim3(blocks), dim3(kCgThreads), 0, st, a);
+    const hipError_t e = launch_cg_residual(a, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(cg_direction_kernel, dim3(cg_update_blocks(a.d)), dim3(kCgThreads), 0, st, a);
   }
   return hipGetLastError();
 }

@@ -7,9 +7,10 @@
 //   * the accumulators of A^T D of ALL columns stay in registers (8 per step of 32 columns, block of 16 classes and wave);
 //   * the tile stays on the chip, as bf16 high and low parts, between the product with [X|V] and the product with D: 2 KB
 //     of LDS per step, and in registers for the steps beyond LS per wave;
-//   * the operands [X|V] are not resident: they are split and laid out once per call (pack_operands_kernel) and stream from
-//     the L2 beside the rows of A.  Loads return in order, so A and operands form ONE stream that runs D steps ahead across
-//     the tiles: a wait for a step's operands never waits for rows that were requested later.
+//   * the operands [X|V] are split and laid out once per call (pack_operands_kernel).  Those of the first steps of a wave stay
+//     in registers, as many as there is room for; the others stream from the L2 beside the rows of A.  Loads return in order,
+//     so A and operands form ONE stream that runs D steps ahead across the tiles: a wait for a step's operands never waits
+//     for rows that were requested later.
 // Wave w owns a contiguous run of steps in both products.  Per tile: the K-split partials of the logits are exchanged
 // through LDS, every wave adds up all of them and forms the rows of D for itself (it needs all 16 rows as an operand), so
 // that D is never exchanged.  The transposed operand of the second product comes from LDS by transposing reads
@@ -18,10 +19,10 @@
 // take one half each, so two instructions give all four terms of (Dhi + Dlo)(Ahi + Alo).
 // The product of a tile with its D is taken together with the conversion of the next tile, step by step, so that the stream
 // only pauses for the K-split exchange and the rows.
-// Measured against two sweeps (with the other kernels of the call): CG iteration on 50000 x 3072, C = 10: 227 -> 162 us (sweep
-// 141 us, 4.4 TB/s), on 75000 x 2048, C = 10 with resident operands: 240 -> 152 us (sweep 112 us, 5.5 TB/s, the rate at which a
-// plain read streams here); 250000 x 2000, C = 20: 772 -> 545 us.  Streamed operands cost 64 bytes per step, class and part
-// from the L2 next to 2 KB of A.
+// Measured against two sweeps (with the other kernels of the call): CG iteration on 50000 x 3072, C = 10: 227 -> 156 us, on
+// 75000 x 2048, C = 10 with resident operands: 240 -> 152 us (sweep 112 us, 5.5 TB/s, the rate at which a plain read streams
+// here); 250000 x 2000, C = 20: 772 -> 567 us.  Streamed operands cost 64 bytes per step, class and part from the L2 next to
+// 2 KB of A; the operands of as many steps as the registers hold are therefore loaded once (resident_steps).
 #include "nadmm_internal.h"
 #include "nadmm_cgstep.h"
 #include "nadmm_mfma.h"
@@ -60,27 +61,9 @@ __device__ __forceinline__ int column_of(int kg, int e) { return 16 * (e >> 2) +
 // parts: X in three (full float32 accuracy of the logits), V in two; columns past p are zero.
 // ex: the classes from 16 on (at most kExtra) go into one block of 16 columns behind the step's 16 classes instead, all parts of
 // them side by side: column kExtra * part + class - 16.
-__global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restrict__ X, const float* __restrict__ V, int p, int NC,
-                                                            int steps, int ex, char* __restrict__ dst, const int32_t* flag) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int cols = ex ? 16 + kExtra : NC;       // ex: the missing extra classes are written as zeros
-  const int per_step = cols * 4;
-  if (t >= steps * per_step) return;
-  const int s = t / per_step, rest = t - s * per_step;
-  const int cls = rest % cols, kg = rest / cols;  // neighbouring threads read neighbouring classes
-  const int parts = (X != nullptr ? 3 : 0) + (V != nullptr ? 2 : 0);
-  const int clc = cls < NC ? cls : NC - 1;
-  float x[8], v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int j = kStepCols * s + column_of(kg, e);
-    const size_t at = (size_t)(j < p ? j : p - 1) * NC + clc;
-    const float xv = X != nullptr ? X[at] : 0.f, vv = V != nullptr ? V[at] : 0.f;
-    const bool ok = j < p && cls < NC;
-    x[e] = ok ? xv : 0.f;
-    v[e] = ok ? vv : 0.f;
-  }
-  if (flag != nullptr && *flag == 0) return;
+__device__ __forceinline__ void store_operands(char* dst, int s, int cls, int kg, int NC, int ex, bool has_x, bool has_v,
+                                               const float (&x)[8], const float (&v)[8]) {
+  const int parts = (has_x ? 3 : 0) + (has_v ? 2 : 0);
   char* base;
   size_t stride;  // from part to part
   if (ex) {
@@ -97,7 +80,7 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restr
     stride = (size_t)ncls * 64;
   }
   int k = 0;
-  if (X != nullptr) {
+  if (has_x) {
     u32x4 a, b, d;
     split8_3(x, a, b, d);
     *reinterpret_cast<u32x4*>(base) = a;
@@ -105,11 +88,88 @@ __global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restr
     *reinterpret_cast<u32x4*>(base + 2 * stride) = d;
     k = 3;
   }
-  if (V != nullptr) {
+  if (has_v) {
     u32x4 a, b;
     split8(v, a, b);
     *reinterpret_cast<u32x4*>(base + k * stride) = a;
     *reinterpret_cast<u32x4*>(base + (k + 1) * stride) = b;
+  }
+}
+
+__global__ __launch_bounds__(256) void pack_operands_kernel(const float* __restrict__ X, const float* __restrict__ V, int p, int NC,
+                                                            int steps, int ex, char* __restrict__ dst, const int32_t* flag) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int cols = ex ? 16 + kExtra : NC;       // ex: the missing extra classes are written as zeros
+  const int per_step = cols * 4;
+  if (t >= steps * per_step) return;
+  const int s = t / per_step, rest = t - s * per_step;
+  const int cls = rest % cols, kg = rest / cols;  // neighbouring threads read neighbouring classes
+  const int clc = cls < NC ? cls : NC - 1;
+  float x[8], v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int j = kStepCols * s + column_of(kg, e);
+    const size_t at = (size_t)(j < p ? j : p - 1) * NC + clc;
+    const float xv = X != nullptr ? X[at] : 0.f, vv = V != nullptr ? V[at] : 0.f;
+    const bool ok = j < p && cls < NC;
+    x[e] = ok ? xv : 0.f;
+    v[e] = ok ? vv : 0.f;
+  }
+  if (flag != nullptr && *flag == 0) return;
+  store_operands(dst, s, cls, kg, NC, ex, X != nullptr, V != nullptr, x, v);
+}
+
+// The second half of the CG update of long vectors (p' = p + a d, d' = r' + (rr'/rr) d, Section 2.4; rr' from the partial
+// sums that the residual's kernel left) by the threads that lay out the operands of the next product: every element of the
+// vectors belongs to one of them, and the new direction is packed while it is in registers.  One launch less per iteration:
+// 10 CG iterations at 50000 x 3072, C = 10: 1587 -> 1558 us.
+__global__ __launch_bounds__(256) void cg_direction_pack_kernel(const CgUpdateArgs a, int nrr, int p, int NC, int steps, int ex, char* dst) {
+  __shared__ double sm[256 / 64 + 1];
+  DevState* st = a.st;
+  if (st->cg_go == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && st->cg_ok == 0) st->cg_active = 0;  // no positive curvature
+    return;
+  }
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int cols = ex ? 16 + kExtra : NC;
+  const int per_step = cols * 4;
+  const bool mine = t < steps * per_step;
+  const int tc = mine ? t : 0;
+  const int s = tc / per_step, rest = tc - s * per_step;
+  const int cls = rest % cols, kg = rest / cols;
+  const int clc = cls < NC ? cls : NC - 1;
+  float d[8], pe[8], re[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int j = kStepCols * s + column_of(kg, e);
+    const size_t at = (size_t)(j < p ? j : p - 1) * NC + clc;
+    d[e] = a.dvec[at];
+    pe[e] = a.pdir[at];
+    re[e] = a.r[at];
+  }
+  const float al = st->cg_alpha;
+  const double rr = st->rr_prev;
+  double acc = 0.0;
+  for (int k = threadIdx.x; k < nrr; k += 256) acc += a.rr_part[k];
+  const double rr_new = cg_block_sum<256>(acc, sm);
+  const bool stop = sqrt(rr_new) <= (double)a.tol * sqrt(st->gg_cg);
+  const float be = (float)(rr_new / rr);
+  if (mine) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int j = kStepCols * s + column_of(kg, e);
+      const bool ok = j < p && cls < NC;
+      const size_t at = (size_t)j * NC + cls;
+      if (ok) a.pdir[at] = fmaf(al, d[e], pe[e]);
+      d[e] = ok ? fmaf(be, d[e], re[e]) : 0.f;
+      if (ok && !stop) a.dvec[at] = d[e];
+    }
+    if (!stop) store_operands(dst, s, cls, kg, NC, ex, false, true, d, d);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rr = rr_new;
+    st->cg_iters += 1;
+    if (stop) st->cg_active = 0;
   }
 }
 
@@ -609,6 +669,9 @@ __global__ __launch_bounds__(kThreads) void wide_kernel(const WideArgs wa) {
 
 int steps_of(int p) { return (p + kStepCols - 1) / kStepCols; }
 
+bool extra_classes(int NC) { return NC > 16 && NC <= 16 + kExtra; }
+int pack_blocks(int p, int NC) { return (steps_of(p) * (extra_classes(NC) ? 16 + kExtra : NC) * 4 + 255) / 256; }
+
 bool rows_16_byte_aligned(const RowArgs& a) { return (a.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(a.A) & 15) == 0; }
 
 template <int SPW, int D, int NB, bool EX, int KIND, bool HAS0, bool HAS1, bool STORES, bool ANY>
@@ -685,19 +748,26 @@ int wide_num_partials(const Shape& s, int wg_cap) {
 
 size_t wide_operand_bytes(const Shape& s) { return (size_t)steps_of(s.p) * (s.NC * 5 * 64 + 1024); }  // at most, see pack_operands_kernel
 
-hipError_t launch_wide(const RowArgs& a, void* operands, float* partial, int nparts, hipStream_t st) {
+hipError_t launch_wide_direction(const CgUpdateArgs& a, const Shape& s, void* operands, hipStream_t st) {
+  hipLaunchKernelGGL(cg_direction_pack_kernel, dim3(pack_blocks(s.p, s.NC)), dim3(256), 0, st, a, cg_update_blocks(a.d), s.p, s.NC, steps_of(s.p),
+                     extra_classes(s.NC) ? 1 : 0, static_cast<char*>(operands));
+  return hipGetLastError();
+}
+
+hipError_t launch_wide(const RowArgs& a, void* operands, bool packed, float* partial, int nparts, hipStream_t st) {
   WideArgs wa;
   wa.r = a;
   wa.op = static_cast<const char*>(operands);
   wa.partial = partial;
   wa.steps = steps_of(a.p);
   wa.rows_per_wg = (int)((a.n + nparts - 1) / nparts);
-  const bool extra = a.NC > 16 && a.NC <= 16 + kExtra;
-  const int threads = wa.steps * (extra ? 16 + kExtra : a.NC) * 4;
-  hipLaunchKernelGGL(pack_operands_kernel, dim3((threads + 255) / 256), dim3(256), 0, st, a.B0, a.B1, a.p, a.NC, wa.steps, extra ? 1 : 0,
-                     static_cast<char*>(operands), a.flag);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const bool extra = extra_classes(a.NC);
+  if (!packed) {
+    hipLaunchKernelGGL(pack_operands_kernel, dim3(pack_blocks(a.p, a.NC)), dim3(256), 0, st, a.B0, a.B1, a.p, a.NC, wa.steps, extra ? 1 : 0,
+                       static_cast<char*>(operands), a.flag);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const int spw = (wa.steps + kWaves - 1) / kWaves;
   if (a.NC <= 16) {
     if (spw <= 4) return launch_spw<4, 1, false, 4, 4, 4>(wa, nparts, st);

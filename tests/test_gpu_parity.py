@@ -576,6 +576,24 @@ def test_wide_single_pass(n, p, C, pad):
     assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
 
 
+# Long vectors of wide rows (d > 24576): the CG update's second kernel lays out the next direction's operands.  A solve of ten
+# iterations that is stopped on the way by its tolerance and one that is not, one block of classes, extra classes, two blocks.
+@pytest.mark.parametrize("tol", [0.0, 0.05])
+@pytest.mark.parametrize("n,p,C", [(300, 2740, 10), (200, 1310, 20), (210, 1030, 25)])
+def test_wide_cg_on_long_vectors(n, p, C, tol):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    gp = nadmm.Problem(dev(w.A), dev(w.b), C, w.s, 0.1, 0.1, dev(w.z), dev(w.y))
+    op = oracle_problem(w)
+    op.lam, op.rho = 0.1, 0.1
+    _, g = orc.loss_grad(op, w.X0)
+    g = g.astype(np.float32)
+    force_path(gp, 4)
+    p_out, it, rel = nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g), 10, tol)
+    p_ref, it_ref, rel_ref = orc.cg(op, w.X0, g.astype(np.float64), 10, tol)
+    assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
+    assert (it_ref < 10) == (tol > 0.0)
+
+
 # Rows of up to 128 columns: the kernel for narrow rows (1 to 4 column steps, one and two blocks of classes, tiles of 16, 32 and
 # 64 rows with remainders, more rows than one round of 512 workgroups) and the thin-data kernel on rows that are no whole number
 # of 16-byte pieces (lda = p odd, a few elements of padding, one row, the last piece of the matrix at every offset).
