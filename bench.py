@@ -25,12 +25,12 @@ LG_PER_STEP = 100
 # names the summary it comes from and the digest of the kernel sources it was measured with: if the sources of
 # that kernel path have changed since, the line reports traffic = null instead of a stale figure.
 MEASURED_HV_TRAFFIC = {
-    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "d910ee797784"),
-    ("tall_binary_1375000x28_C2", 3): (154.4e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "e5e4ee407ae4"),
-    ("wide_50000x3072_C10", 4): (1259.6e6, "profiles/hessvec_sliced_wide_50000x3072_C10.md", "fc83e16f100a"),
-    ("large_multiclass_250000x2000_C20", 4): (4220.8e6, "profiles/hessvec_sliced_large_multiclass_250000x2000_C20.md", "fc83e16f100a"),
+    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "ec0c66948978"),
+    ("tall_binary_1375000x28_C2", 3): (154.4e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "85d4e64e5aae"),
+    ("wide_50000x3072_C10", 4): (685.2e6, "profiles/hessvec_wide_50000x3072_C10.md", "d0d3a96807f2"),
+    ("large_multiclass_250000x2000_C20", 4): (2191.4e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "d0d3a96807f2"),
     # sparse storage: bytes between the L2 caches and the memory side, most of them operand rows served by the Infinity Cache
-    ("e18_like_40628x279998_C20_sparse", 5): (12480.0e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "8090591d36f9"),
+    ("e18_like_40628x279998_C20_sparse", 5): (12472.9e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "6d47ae5f463d"),
 }
 PATH_SOURCES = {1: ["nadmm_generic.hip", "nadmm_rows16.h"], 2: ["nadmm_fused.hip", "nadmm_narrow.hip", "nadmm_cgstep.h"], 3: ["nadmm_thin.hip", "nadmm_cgstep.h"],
                 4: ["nadmm_sliced.hip", "nadmm_wide.hip", "nadmm_rows16.h", "nadmm_cgstep.h"], 5: ["nadmm_sparse.hip", "nadmm_generic.hip", "nadmm_rows16.h"]}
@@ -319,7 +319,7 @@ def main():
     bytes_hv = bytes_A + 3 * 4.0 * d
     bytes_lg = bytes_A + 4.0 * n + 4 * 4.0 * d
     extra = {"kernel_path": {1: "two-pass fp32 vector kernels", 2: "fused single pass (matrix cores)",
-                             3: "thin-data single pass", 4: "column-sliced two sweeps (matrix cores)",
+                             3: "thin-data single pass", 4: "wide rows, one or two sweeps (matrix cores)",
                              5: "sparse storage: row view, then column view"}[path]}
     if w.sparse:
         extra["stored_entries"] = int(w.A.nnz)
