@@ -25,7 +25,7 @@ LG_PER_STEP = 100
 # names the summary it comes from and the digest of the kernel sources it was measured with: if the sources of
 # that kernel path have changed since, the line reports traffic = null instead of a stale figure.
 MEASURED_HV_TRAFFIC = {
-    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "ec0c66948978"),
+    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "a1f21c590b39"),
     ("tall_binary_1375000x28_C2", 3): (154.4e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "85d4e64e5aae"),
     ("wide_50000x3072_C10", 4): (685.2e6, "profiles/hessvec_wide_50000x3072_C10.md", "d0d3a96807f2"),
     ("large_multiclass_250000x2000_C20", 4): (2191.4e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "d0d3a96807f2"),

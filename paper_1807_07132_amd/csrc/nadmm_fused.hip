@@ -13,8 +13,8 @@
 //   phase 2  out^T (16 x cols) += D^T A_tile        -- A re-read from a
 //            wave-private LDS copy written in phase 1 in 16-byte pieces and
 //            transposed by the read (ds_read_b64_tr_b16).  (Interleaving
-//            row pairs in registers and writing 4-byte words took 64
-//            instructions and 48 LDS writes more per tile and wave and the
+//            row pairs in registers and writing 4-byte words took 8 %
+//            more vector instructions, as many LDS instructions, and the
 //            registers that the any-stride variant with X and V spilled:
 //            60000 x 785, C = 10, Hessian-vector product 67.8 -> 55.3 us.)
 // A is read from HBM exactly once; the p x (C-1) accumulators stay in registers
