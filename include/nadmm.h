@@ -30,7 +30,7 @@
  *     depends on shape, stride and alignment:
  *       p <= 32 and C-1 <= 3, with p > q - 4, q (C-1) <= 64 for q = 4 ceil(lda/4) (so at most 3 elements between rows), and
  *         n lda >= 8: the thin-data kernel, one lane per sample, except 16-byte aligned rows with elements between them, q (C-1) > 16
- *         and 2048 < n < 65536 (393216 where q (C-1) = 64); a CG solve of more than n q / 16384 iterations on up to 2048 rows
+ *         and 2048 < n < 65536 (393216 where q (C-1) = 64); a CG or Newton solve on up to 2048 rows
  *         is one launch;
  *       these, and other rows of up to 128 columns (96 with more than 16 free classes): a matrix-core kernel with one wave per
  *         tile, except other rows of C-1 <= 16 that are 16-byte aligned, or of 48 columns and more, and fewer than 32768

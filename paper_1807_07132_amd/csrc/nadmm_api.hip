@@ -552,21 +552,15 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
   return NADMM_OK;
 }
 
-// Small thin problems: all CG iterations in one launch, instead of one or two launches each (nadmm_small.hip).
-bool small_cg(const Layout& L, int path, int max_iter) { return path == 3 && max_iter >= 1 && small_cg_supported(L.s, max_iter); }
-SmallCg small_cg_args(const nadmm_problem* prob, const Layout& L, void* ws, DevState* ds, const float* X, int max_iter, float tol,
-                      float* zp, const int32_t* flag) {
-  SmallCg c;
+// Small thin problems: the whole solve in one launch (nadmm_small.hip).
+SmallSolve small_solve_args(const nadmm_problem* prob, const Layout& L, const float* X, int max_cg, float cg_tol) {
+  SmallSolve c;
   std::memset(&c, 0, sizeof(c));
   c.A = prob->d_A; c.n = prob->n; c.lda = prob->lda; c.p = prob->p; c.NC = L.s.NC;
   c.X = X;
-  c.Pin = X != nullptr ? nullptr : at<float>(ws, L.pcache);
   c.scale = prob->loss_scale; c.lambda = prob->lambda; c.rho = prob->rho; c.rho_scale = L.rho_scale;
-  c.st = ds;
-  c.pdir = at<float>(ws, L.pdir); c.r = at<float>(ws, L.r); c.dvec = at<float>(ws, L.dvec);
-  c.max_iter = max_iter; c.tol = tol;
-  c.zp = zp;
-  c.flag = flag;
+  c.max_cg = max_cg;
+  c.cg_tol = cg_tol;
   return c;
 }
 
@@ -609,9 +603,24 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
   float* r = at<float>(d_ws, L.r);
   float* dvec = at<float>(d_ws, L.dvec);
 
+  const int ncand = params->max_ls + 2;
+  if (path == 3 && params->max_newton >= 1 && small_solve_supported(L.s, params->max_cg)) {
+    SmallSolve c = small_solve_args(prob, L, d_X, params->max_cg, params->cg_tol);
+    c.newton = 1;
+    c.z = prob->d_z; c.y = prob->d_y; c.labels = prob->d_labels;
+    c.max_newton = params->max_newton;
+    c.grad_tol = params->grad_tol;
+    c.beta = params->armijo_beta;
+    c.ncand = ncand;
+    fill_alphas(c.alphas, ncand, params->backtrack_gamma);
+    c.X_out = d_X;
+    c.st = ds;
+    c.outer_flag = outer_flag;
+    NADMM_HIP(launch_small_solve(c, st));
+    return NADMM_OK;
+  }
   if (path == 5 && (rc = sparse_plan(prob, L, d_ws, st)) != NADMM_OK) return rc;
   NADMM_HIP(launch_state_init(ds, outer_flag, st));
-  const int ncand = params->max_ls + 2;
 
   for (int t = 0; t < params->max_newton; ++t) {
     // gradient and objective at X; caches the probabilities and the logits A X
@@ -660,19 +669,15 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     nh.gg_part = nh.pen_part + reduce_out_blocks(L.s.d);
     nh.npart = reduce_out_blocks(L.s.d);
     nh.rho_scale = L.rho_scale;
-    const bool small = small_cg(L, path, params->max_cg);  // CG and the logits A p of the step in one launch
     // on the fused path the head is one more workgroup of the first CG iteration's reduction instead of a launch of its own
     const bool head_in_reduce = cg_deferred(path) && params->max_cg >= 1 && L.s.d <= kReduceFinishMax;
     if (!head_in_reduce) NADMM_HIP(launch_newton_head(nh, st));
 
     // CG on H p = -g with the probabilities of this iterate
-    const bool thin_def = thin_deferred(path) && L.thin_ok && !small && params->max_cg >= 1;
+    const bool thin_def = thin_deferred(path) && L.thin_ok && params->max_cg >= 1;
     const bool hist = use_hist && cg_deferred(path) && params->max_cg >= 1 && params->max_cg <= L.hist_bufs;
     const size_t hist_stride = align256((size_t)L.s.n * L.s.NC * sizeof(float)) / sizeof(float);
-    if (small)
-      NADMM_HIP(launch_small_cg(small_cg_args(prob, L, d_ws, ds, nullptr, params->max_cg, params->cg_tol, at<float>(d_ws, L.zp),
-                                              &ds->newton_active), st));
-    for (int k = 0; k < params->max_cg && !small; ++k) {
+    for (int k = 0; k < params->max_cg; ++k) {
       float* w_rows = hist ? at<float>(d_ws, L.hist) + (size_t)k * hist_stride : nullptr;
       if ((rc = cg_iteration(prob, L, path, d_ws, ds, nullptr, false, params->cg_tol, k, st, w_rows,
                              (k == 0 && head_in_reduce) ? &nh : nullptr, thin_def)) != NADMM_OK)
@@ -689,9 +694,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     rz.Z1out = at<float>(d_ws, L.zp);
     rz.flag = &ds->newton_active;
     const bool eval_finishes = hist && ls_eval_takes_pending(prob->n);  // the row kernel of the line search applies the last update
-    if (small) {
-      // A p is in place
-    } else if (hist) {  // A p comes from the history; the last update alone, unless the line search's row kernel takes it along
+    if (hist) {  // A p comes from the history; the last update alone, unless the line search's row kernel takes it along
       if (!eval_finishes)
         NADMM_HIP(launch_cg_pending_finish(cg_pend(L, d_ws, ds, (params->max_cg - 1) & 1, true, params->cg_tol), st));
     } else if (pend) {
@@ -971,6 +974,15 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   if ((rc = choose_path(L, &path)) != NADMM_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   DevState* ds = at<DevState>(d_ws, L.state);
+  if (path == 3 && small_solve_supported(L.s, max_iter)) {
+    SmallSolve c = small_solve_args(prob, L, d_X, max_iter, tol);
+    c.g = d_g;
+    c.p_out = d_p;
+    c.iters_out = d_iters;
+    c.relres_out = d_relres;
+    NADMM_HIP(launch_small_solve(c, st));
+    return NADMM_OK;
+  }
   if (path == 5 && (rc = sparse_plan(prob, L, d_ws, st)) != NADMM_OK) return rc;
 
   NADMM_HIP(launch_state_init(ds, nullptr, st));
@@ -985,9 +997,7 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   nh.newton_mode = 0;
   NADMM_HIP(launch_newton_head(nh, st));
 
-  const bool small = small_cg(L, path, max_iter);
-  if (small) NADMM_HIP(launch_small_cg(small_cg_args(prob, L, d_ws, ds, d_X, max_iter, tol, nullptr, nullptr), st));
-  for (int k = 0; k < max_iter && !small; ++k) {
+  for (int k = 0; k < max_iter; ++k) {
     if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st)) != NADMM_OK) return rc;
   }
   const bool pend = cg_deferred(path) && max_iter > 0;

@@ -11,17 +11,17 @@
 
 namespace nadmm {
 
-// Raises a kernel's dynamic-LDS limit to the 160 KB of a gfx950 compute unit, once per device
+// Raises a kernel's dynamic-LDS limit to the 160 KB of a gfx950 compute unit (less for kernels with LDS arrays of their own), once per device
 // (the attribute belongs to the kernel's code object on the current device).
 // done_mask: devices on which this has been done; host threads may race to it, the attribute is then set twice.
 typedef std::atomic<uint64_t> LdsLimitMask;
-inline hipError_t ensure_lds_limit(const void* kernel, LdsLimitMask* done_mask) {
+inline hipError_t ensure_lds_limit(const void* kernel, LdsLimitMask* done_mask, int bytes = 160 * 1024) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   const uint64_t bit = (uint64_t)1 << (dev & 63);
   if ((done_mask->load(std::memory_order_acquire) & bit) == 0) {
-    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
     done_mask->fetch_or(bit, std::memory_order_release);
   }
@@ -360,26 +360,37 @@ int thin_num_partials(const Shape& s);
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
                        const ReduceArgs* prev = nullptr);
 
-// ---- all CG iterations of a small thin problem in one launch (nadmm_small.hip) ----
-struct SmallCg {
+// ---- a whole CG or Newton solve of a small thin problem in one launch (nadmm_small.hip) ----
+struct SmallSolve {
   const float* A;
   int64_t n, lda;
   int32_t p, NC;
-  const float* X;        // NULL: the cached probabilities Pin are used
-  const float* Pin;      // n x NC
+  int32_t quads;           // set by the launcher: rows are whole aligned quads
+  const float* X;
+  const float* z;          // as in nadmm_problem; not read by a CG solve
+  const float* y;
+  const int32_t* labels;   // Newton solve
   float scale, lambda, rho;
-  const float* rho_scale;
-  DevState* st;          // CG as newton_head_kernel started it; left as after the last iteration taken
-  float* pdir;
-  float* r;
-  float* dvec;
-  int32_t max_iter;
-  float tol;
-  float* zp;             // n x NC, optional: the logits A p of the iterate
-  const int32_t* flag;
+  const float* rho_scale;  // optional device scalar factor on rho
+  int32_t max_cg;
+  float cg_tol;
+  // CG solve: from g to p_out, iters_out and relres_out (optional)
+  const float* g;
+  float* p_out;
+  int32_t* iters_out;
+  float* relres_out;
+  // Newton solve (Algorithm 3): X_out may be X; scalars and statistics go to st
+  int32_t newton;
+  int32_t max_newton;
+  float grad_tol, beta;
+  int32_t ncand;           // candidates of the line search
+  float alphas[kCandSlots];
+  float* X_out;
+  DevState* st;
+  const int32_t* outer_flag;  // as for launch_state_init
 };
-bool small_cg_supported(const Shape& s, int32_t max_iter);
-hipError_t launch_small_cg(const SmallCg& c, hipStream_t st);
+bool small_solve_supported(const Shape& s, int32_t max_cg);
+hipError_t launch_small_solve(const SmallSolve& c, hipStream_t st);
 
 // ---- column-sliced two-sweep matrix-core path (nadmm_sliced.hip): any p, C-1 <= 32, lda % 4 == 0 ----
 bool sliced_supported(const Shape& s, int64_t lda, const void* A);

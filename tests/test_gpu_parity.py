@@ -682,7 +682,7 @@ def test_narrow_rows_keep_float32_accuracy(n, p, C, pad):
     assert max(errs) <= FLOAT32_ACCURACY
 
 
-# All CG iterations of a small thin problem in one launch: rows at the limits of one workgroup (4 rows for 256 or 512 threads; 2049
+# A CG or Newton solve of a small thin problem in one launch: rows at the limits of one workgroup (4 rows for 256 or 512 threads; 2049
 # rows take the general path), all numbers of classes, columns that are no whole number of 16-byte pieces, CG that stops early.
 @pytest.mark.parametrize("tol", [0.0, 3e-2])
 @pytest.mark.parametrize("n,p,C", [(1, 4, 2), (3, 1, 2), (255, 32, 3), (1000, 20, 3), (1023, 21, 4), (1024, 7, 2), (1025, 16, 4), (2047, 29, 2),
@@ -705,7 +705,7 @@ def test_small_cg(n, p, C, tol):
     assert forced or st["cg_iters"] == [i["cg_iters"] for i in st_ref["iters"]]
 
 
-# The same on either side of the number of iterations from which the one launch is taken (more than n 4 ceil(p/4) / 16384).
+# The same with few iterations.
 @pytest.mark.parametrize("n,p,C,k", [(2048, 32, 2, 4), (2048, 32, 2, 5), (1000, 20, 3, 1), (1000, 20, 3, 2), (2048, 29, 3, 3), (2048, 29, 3, 4), (512, 31, 2, 1)])
 def test_small_cg_with_few_iterations(n, p, C, k):
     w = workloads.generic(n, p, C, seed=n + k, x_std=0.5 / math.sqrt(p), mean=True)
@@ -720,6 +720,39 @@ def test_small_cg_with_few_iterations(n, p, C, k):
     w.max_newton, w.max_cg = 2, k
     assert rel_l2(host(X), oracle_newton_following(op, w.X0, w, st["alpha"])[0]) <= TOL_ITERATE
     assert st["cg_iters"] == [k, k]
+
+
+# The one launch of a small Newton solve: line searches that reduce their step (sum scaling, far from the minimiser), a row block of
+# which A starts on any 4-byte boundary, and the stopping test of Algorithm 3 before the first and between iterations.
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("n,p,C", [(257, 12, 3), (1024, 20, 3), (1500, 31, 2), (2048, 13, 4)])
+def test_small_newton(n, p, C, shift):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=6.0 / math.sqrt(p))
+    flat = torch.empty(shift + n * p, device="cuda")
+    A = flat[shift:].as_strided((n, p), (p, 1), shift)
+    A.copy_(dev(w.A))
+    gp = nadmm.Problem(A, dev(w.b), C, w.s, w.lam, w.rho, dev(w.z), dev(w.y))
+    op = oracle_problem(w)
+    k = 6
+    X = dev(w.X0)
+    st = nadmm.nadmm_local_newton(gp, X, nadmm.make_params(4, k, 10))
+    w.max_newton, w.max_cg = 4, k
+    X_ref, st_ref, forced = oracle_newton_following(op, w.X0, w, st["alpha"])
+    assert rel_l2(host(X), X_ref) <= TOL_ITERATE
+    assert st["newton_iters"] == 4 and st["cg_iters"] == [i["cg_iters"] for i in st_ref["iters"]]
+    assert min(st["alpha"]) < 1.0                  # a step was reduced
+    assert rel_abs(st["loss_initial"], orc.loss(op, w.X0)) <= 1e-6 and rel_abs(st["loss_final"], orc.loss(op, host(X))) <= 1e-5
+    X1 = dev(w.X0)                                 # without statistics: the same iterate, bit for bit
+    nadmm.nadmm_local_newton(gp, X1, nadmm.make_params(4, k, 10), want_stats=False)
+    assert torch.equal(X, X1)
+    gn = st["grad_norm"]
+    X2 = dev(w.X0)
+    st2 = nadmm.nadmm_local_newton(gp, X2, nadmm.make_params(4, k, 10, grad_tol=2.0 * max(gn)))
+    assert st2["newton_iters"] == 0 and st2["cg_iters_total"] == 0 and torch.equal(X2, dev(w.X0))
+    assert rel_abs(st2["grad_norm_final"], gn[0]) <= 1e-12
+    stop = min(range(4), key=lambda i: gn[i])      # the first iteration whose gradient is below the tolerance ends the solve
+    st3 = nadmm.nadmm_local_newton(gp, dev(w.X0), nadmm.make_params(4, k, 10, grad_tol=1.0000001 * gn[stop]))
+    assert st3["newton_iters"] == stop
 
 
 # Thin rows with a stride of whole quads and padding, 16-byte aligned or not (A four bytes further): the thin-data kernel by force, which
