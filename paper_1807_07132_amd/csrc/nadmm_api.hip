@@ -108,7 +108,8 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->fused_ok = !L->sparse && fused_supported(s, p->lda, p->d_A);
   L->fused_parts = L->fused_ok ? (L->narrow ? L->narrow_parts : fused_num_partials(s)) : 0;
   if (wg_cap > 0 && L->fused_parts > wg_cap) L->fused_parts = wg_cap;
-  L->thin_parts = L->thin_ok || L->thin_any ? thin_num_partials(s) : 0;
+  L->thin_parts = L->thin_ok ? thin_num_partials(s) : (L->thin_any ? thin_stream_partials(s) : 0);
+  const int thin_room = L->thin_ok || L->thin_any ? std::max(thin_num_partials(s), L->thin_parts) : 0;
   const size_t vec = hv_only ? 0 : align256((size_t)s.d * sizeof(float));
   const size_t rows = align256((size_t)s.n * s.NC * sizeof(float));
   const size_t rows_solver = hv_only ? 0 : rows;
@@ -142,12 +143,12 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   if (L->wide_parts > parts) parts = L->wide_parts;
   if (L->narrow_parts > parts) parts = L->narrow_parts;
   if (L->sliced_parts > parts) parts = L->sliced_parts;
-  if (L->thin_parts > parts) parts = L->thin_parts;
+  if (thin_room > parts) parts = thin_room;
   L->partial = off; off += align256((size_t)parts * s.d * sizeof(float));
   // thin-data path: the sweeps of a CG solve write their partial sums to two buffers in turn (each reads the previous one's)
   L->partial2 = off; off += (L->thin_ok && !hv_only) ? align256((size_t)L->thin_parts * s.d * sizeof(float)) : 0;
   int lblocks = L->gen_row_blocks > L->fused_parts ? L->gen_row_blocks : L->fused_parts;
-  if (L->thin_parts > lblocks) lblocks = L->thin_parts;
+  if (thin_room > lblocks) lblocks = thin_room;
   if (L->sliced_loss > lblocks) lblocks = L->sliced_loss;
   if (L->wide_parts > lblocks) lblocks = L->wide_parts;
   if (L->narrow_parts > lblocks) lblocks = L->narrow_parts;

@@ -13,6 +13,7 @@
 // Inside a Newton iteration the sweep of CG iteration k also does what lies between
 // two sweeps (Section 2.4): it adds up the partial sums of sweep k - 1, forms q = H d
 // and applies the CG update before it reads its operand (instantiations with CG).
+#include <algorithm>
 #include <cstring>
 
 #include "nadmm_internal.h"
@@ -42,24 +43,93 @@ struct ThinArgs {
 
 // NQ = p / 4: float4 per row, which is also the float4 per lane in a chunk of 256 rows
 // ROWS: how the rows lie.  kDense: lda = p, a multiple of 4, 16-byte aligned.  The others (p odd, a few columns of padding, A
-// 4-byte aligned; NQ = ceil(lda / 4)) went through the two-pass vector kernels before (1375000 x 29, C = 2, objective and
-// gradient: 192 us) or would go through the matrix-core kernel for narrow rows, where one lane in 16 has work in the rows stage
-// (103 us).  256 consecutive rows are still one contiguous block of memory, fetched in 16-byte pieces that need only be 4-byte
-// aligned.
-//   kBlock: lda is no multiple of 4.  The block is copied to LDS as it lies, and the lanes read their rows back in 4-byte
-//     pieces: no bank conflicts where lda is odd, two lanes to a bank where it is even.
-//   kQuads: lda = 4 NQ.  No piece crosses a row, so that rows lie in LDS as those of kDense do; as one block the rows of all
-//     lanes would start on one or a few banks (Hessian-vector product on 1200000 rows: lda = 32, C = 2: 102 -> 44 us, lda = 16,
-//     C = 2: 34 -> 23 us).
+// 4-byte aligned; NQ = ceil(lda / 4)) would go through the matrix-core kernel for narrow rows, where one lane in 16 has work in
+// the rows stage (1375000 x 29, C = 2, objective and gradient: 103 us).
+//   kBlock: lda is no multiple of 4.  A block of rows lies in LDS as it does in memory, and the lanes read their rows back in
+//     4-byte pieces: no bank conflicts where lda is odd, two lanes to a bank where it is even.
+//   kQuads: lda = 4 NQ.  The lanes read whole quads, which lie turned within their rows.
 enum Rows { kDense, kBlock, kQuads };
 
-// floats per row in LDS, off the bank period (kBlock: room for one row, which starts wherever the block has it)
-constexpr int tile_stride(int pp, Rows rows) { return rows != kBlock && pp % 8 == 0 ? pp + 4 : pp; }
+// floats per row in LDS, off the bank period
+constexpr int tile_stride(int pp) { return pp % 8 == 0 ? pp + 4 : pp; }
 
-template <int NQ, int NC, bool CG, Rows ROWS>
+// Everything a lane does with its row of A once it is in registers: logits, probabilities with the log-sum-exp shift, its row of D
+// or of P - Y, the optional outputs, and its share of A^T rows.  P: the cached probabilities on entry (has0 false).
+// x(j, c), v(j, c): the operands' entries, uniform in a wave.
+template <int PP, int NC, typename OpX, typename OpV>
+__device__ __forceinline__ void thin_row(const RowArgs& a, bool has0, bool has1, bool with_cols, bool valid, int64_t row,
+                                         const float (&av)[PP], OpX&& x, OpV&& v, float (&P)[NC], int label,
+                                         float (&acc)[PP][NC], double& loss_acc) {
+  float z[NC], w[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) { z[c] = 0.f; w[c] = 0.f; }
+  if (has0) {
+#pragma unroll
+    for (int j = 0; j < PP; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) z[c] = fmaf(av[j], x(j, c), z[c]);
+  }
+  if (has1) {
+#pragma unroll
+    for (int j = 0; j < PP; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) w[c] = fmaf(av[j], v(j, c), w[c]);
+  }
+  const size_t ro = (size_t)row * NC;
+  if (a.kind == kRowsLogits) {
+    if (valid) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (has0 && a.Z0out) a.Z0out[ro + c] = z[c];
+        if (has1 && a.Z1out) a.Z1out[ro + c] = w[c];
+      }
+    }
+    return;
+  }
+  float d[NC];
+  float M = 0.f, alpha = 1.f;
+  if (has0) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) M = fmaxf(M, z[c]);
+    alpha = expf(-M);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) { P[c] = expf(z[c] - M); alpha += P[c]; }
+    const float inv = 1.f / alpha;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) P[c] *= inv;
+  }
+  if (a.kind == kRowsHv) {
+    float tt = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) tt = fmaf(P[c], w[c], tt);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) d[c] = valid ? P[c] * (w[c] - tt) : 0.f;
+  } else {
+    float zb = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (c == label) zb = z[c];
+      d[c] = valid ? P[c] - (c == label ? 1.f : 0.f) : 0.f;
+    }
+    if (valid) loss_acc += (double)M + (double)logf(alpha) - (double)zb;
+  }
+  if (valid) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (a.Pout) a.Pout[ro + c] = P[c];
+      if (has0 && a.Z0out) a.Z0out[ro + c] = z[c];
+    }
+  }
+  if (with_cols) {
+#pragma unroll
+    for (int j = 0; j < PP; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[j][c] = fmaf(av[j], d[c], acc[j][c]);
+  }
+}
+
+template <int NQ, int NC, bool CG>
 __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
-  constexpr bool GEN = ROWS != kDense;
-  static_assert(!(CG && GEN), "the deferred CG update reads the partial sums in whole quads");
   constexpr int PP = 4 * NQ;
   constexpr int kMaxQuads = NQ;
   constexpr int nquads = NQ;
@@ -68,8 +138,7 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
   extern __shared__ __attribute__((aligned(16))) float tile[];  // 256 rows, see tile_stride
   __shared__ double red[4];
   const int t = threadIdx.x;
-  const int p = GEN ? a.p : PP;
-  constexpr int PS = tile_stride(PP, ROWS);
+  constexpr int p = PP, PS = tile_stride(PP);
   const bool has0 = !CG && a.B0 != nullptr;
   const bool has1 = CG || a.B1 != nullptr;
   const bool with_cols = ta.partial != nullptr;
@@ -146,9 +215,8 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
     for (int j = 0; j < PP; ++j)
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const int jc = GEN ? (j < p ? j : p - 1) : j;  // columns past p meet zeros of the row
-        xs[j][c] = has0 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B0[jc * NC + c]))) : 0.f;
-        vs[j][c] = has1 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B1[jc * NC + c]))) : 0.f;
+        xs[j][c] = has0 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B0[j * NC + c]))) : 0.f;
+        vs[j][c] = has1 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B1[j * NC + c]))) : 0.f;
       }
   }
 
@@ -161,7 +229,7 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
 
   // position of this lane's k-th float4 inside a chunk: element 4 (t + 256 k) = row * PP + col
   int prow[kMaxQuads], pcol[kMaxQuads];
-  if constexpr (ROWS != kBlock) {
+  {
     int row = (4 * t) / PP, col = (4 * t) % PP;
 #pragma unroll
     for (int k = 0; k < kMaxQuads; ++k) {
@@ -178,19 +246,7 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
   // wait for exactly the chunk it needs.
   f32x4 pf[2][kMaxQuads];
   const int64_t own_last4 = (r_end > r_begin ? r_end : r_begin + 1) * nquads - 1;
-  const int ld = (int)a.lda;                                          // GEN: <= 32
-  const int64_t last_el = GEN ? (a.n - 1) * a.lda + a.p - 4 : 0;      // GEN: where the matrix's last 16 bytes start
   auto load_chunk = [&](int b, int64_t row0) {
-    if constexpr (GEN) {
-      const int64_t rc = row0 < a.n ? row0 : a.n - 1;
-#pragma unroll
-      for (int k = 0; k < kMaxQuads; ++k) {
-        const int64_t e0 = rc * ld + 4 * (t + k * kThinThreads);
-        const Quad q = *reinterpret_cast<const Quad*>(a.A + (e0 < last_el ? e0 : last_el));
-        pf[b][k] = f32x4{q.x, q.y, q.z, q.w};
-      }
-      return;
-    }
     const int64_t base4 = row0 * nquads + t;
 #pragma unroll
     for (int k = 0; k < kMaxQuads; ++k) {
@@ -204,22 +260,7 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
     __syncthreads();  // rows of the previous chunk have been read
 #pragma unroll
     for (int k = 0; k < kMaxQuads; ++k) {
-      if constexpr (GEN) {
-        const int at = 4 * (t + k * kThinThreads);  // kBlock: the tile holds 4 NQ 256 floats
-        f32x4 v = pf[b][k];
-        if (row0 + kThinThreads >= a.n) {  // uniform: the last rows; a piece fetched from the matrix's end holds its elements further up
-          const int64_t over = row0 * ld + at - last_el;
-          const int sh = over <= 0 ? 0 : (over < 4 ? (int)over : 4);
-          const f32x4 u = v;
-          v[0] = sh == 0 ? u[0] : (sh == 1 ? u[1] : (sh == 2 ? u[2] : (sh == 3 ? u[3] : 0.f)));
-          v[1] = sh == 0 ? u[1] : (sh == 1 ? u[2] : (sh == 2 ? u[3] : 0.f));
-          v[2] = sh == 0 ? u[2] : (sh == 1 ? u[3] : 0.f);
-          v[3] = sh == 0 ? u[3] : 0.f;
-        }
-        *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[ROWS == kBlock ? at : prow[k] * PS + pcol[k]], 16)) = v;
-      } else {
-        *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[prow[k] * PS + pcol[k]], 16)) = pf[b][k];
-      }
+      *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[prow[k] * PS + pcol[k]], 16)) = pf[b][k];
     }
     load_chunk(b, row0 + 2 * kThinThreads);
     __syncthreads();
@@ -227,93 +268,17 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
     const int64_t row = row0 + t;
     const bool valid = row < r_end;
     float av[PP];
-    if constexpr (ROWS == kBlock) {
 #pragma unroll
-      for (int j = 0; j < PP; ++j) {
-        const float v = tile[t * ld + j];  // at most 255 ld + PP - 1 < 256 PP
-        av[j] = (j < PP - 4 || j < p) ? v : 0.f;  // p > PP - 4
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < PP / 4; ++q) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(__builtin_assume_aligned(&tile[t * PS + 4 * q], 16));
-        av[4 * q + 0] = v[0]; av[4 * q + 1] = v[1]; av[4 * q + 2] = v[2]; av[4 * q + 3] = v[3];
-      }
+    for (int q = 0; q < PP / 4; ++q) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(__builtin_assume_aligned(&tile[t * PS + 4 * q], 16));
+      av[4 * q + 0] = v[0]; av[4 * q + 1] = v[1]; av[4 * q + 2] = v[2]; av[4 * q + 3] = v[3];
     }
-    if constexpr (ROWS == kQuads) {  // what lies past column p
+    float P[NC];
 #pragma unroll
-      for (int j = PP - 4; j < PP; ++j) av[j] = j < p ? av[j] : 0.f;
-    }
-    float z[NC], w[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) { z[c] = 0.f; w[c] = 0.f; }
-    if (has0) {
-#pragma unroll
-      for (int j = 0; j < PP; ++j)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) z[c] = fmaf(av[j], xs[j][c], z[c]);
-    }
-    if (has1) {
-#pragma unroll
-      for (int j = 0; j < PP; ++j)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) w[c] = fmaf(av[j], vs[j][c], w[c]);
-    }
-    const size_t ro = (size_t)row * NC;
-    if (a.kind == kRowsLogits) {
-      if (valid) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          if (has0 && a.Z0out) a.Z0out[ro + c] = z[c];
-          if (has1 && a.Z1out) a.Z1out[ro + c] = w[c];
-        }
-      }
-      return;
-    }
-    float P[NC], d[NC];
-    float M = 0.f, alpha = 1.f;
-    if (has0) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) M = fmaxf(M, z[c]);
-      alpha = expf(-M);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) { P[c] = expf(z[c] - M); alpha += P[c]; }
-      const float inv = 1.f / alpha;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) P[c] *= inv;
-    } else {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) P[c] = valid ? a.Pin[ro + c] : 0.f;
-    }
-    if (a.kind == kRowsHv) {
-      float tt = 0.f;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) tt = fmaf(P[c], w[c], tt);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) d[c] = valid ? P[c] * (w[c] - tt) : 0.f;
-    } else {
-      const int b = valid ? a.labels[row] : -1;
-      float zb = 0.f;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (c == b) zb = z[c];
-        d[c] = valid ? P[c] - (c == b ? 1.f : 0.f) : 0.f;
-      }
-      if (valid) loss_acc += (double)M + (double)logf(alpha) - (double)zb;
-    }
-    if (valid) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (a.Pout) a.Pout[ro + c] = P[c];
-        if (has0 && a.Z0out) a.Z0out[ro + c] = z[c];
-      }
-    }
-    if (with_cols) {
-#pragma unroll
-      for (int j = 0; j < PP; ++j)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[j][c] = fmaf(av[j], d[c], acc[j][c]);
-    }
+    for (int c = 0; c < NC; ++c) P[c] = (!has0 && valid && a.Pin != nullptr) ? a.Pin[(size_t)row * NC + c] : 0.f;
+    const int label = (valid && a.kind != kRowsHv && a.kind != kRowsLogits) ? a.labels[row] : -1;
+    thin_row<PP, NC>(a, has0, has1, with_cols, valid, row, av, [&](int j, int c) { return xs[j][c]; },
+                     [&](int j, int c) { return vs[j][c]; }, P, label, acc, loss_acc);
   };
 
   if (r_begin < r_end) {
@@ -355,19 +320,201 @@ __global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
   if (a.loss_part != nullptr && t == 0) a.loss_part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-template <int NQ, int NC, bool CG, Rows ROWS>
+// The same for the other rows (kBlock, kQuads): no barrier and no prefetch registers.  A wave copies chunks of 64 rows -- one block
+// of memory -- straight into its own part of LDS (global_load_lds), takes its rows from there into registers and has the next chunk
+// on its way before it computes.  What is in flight is LDS, not registers: 16 waves per compute unit with up to 8 KB each.
+// What bounds it: HBM.  Against chunks of 256 rows through registers (204 of them, so that only 512 of the 768 workgroups fitted,
+// and surplus pieces past every chunk): objective and gradient at 1375000 x 29, C = 2: 53.5 -> 35.8 us (4.46 TB/s with the reduction's
+// launch; the floor of one read of A is 28 us); Hessian-vector product at 600000 x 30, C = 3: 45.9 -> 20.7 us.
+typedef __attribute__((address_space(1))) const void gvoid;
+typedef __attribute__((address_space(3))) void lvoid;
+template <int BYTES>  // lane l: BYTES from its own address g to l BYTES behind the wave's address to
+__device__ __forceinline__ void copy_to_lds(const float* g, float* to) {
+  static_assert(BYTES == 16 || BYTES == 4, "sizes that are used here");
+  if constexpr (BYTES == 16) __builtin_amdgcn_global_load_lds((gvoid*)g, (lvoid*)to, 16, 0, 0);
+  else __builtin_amdgcn_global_load_lds((gvoid*)g, (lvoid*)to, 4, 0, 0);
+}
+
+// What the sweep makes, fixed at compile time: chosen inside the loop it cost copies of all accumulators and spills.
+enum StreamOp { kHvX, kHvP, kGrad, kLoss, kLogits };  // kHvP: with cached probabilities
+
+template <int NQ, int NC, int THREADS, Rows ROWS, StreamOp OP>
+__global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta) {
+  constexpr int PP = 4 * NQ, D = PP * NC, W = THREADS / 64;
+  RowArgs a = ta.r;
+  a.kind = OP == kHvX || OP == kHvP ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : kRowsLogits));
+  if (a.flag != nullptr && *a.flag == 0) return;
+  extern __shared__ __attribute__((aligned(16))) float tile[];  // [wave][64 rows]
+  __shared__ double red[W];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int p = a.p, ld = ROWS == kQuads ? PP : (int)a.lda;
+  const bool has0 = OP == kLogits ? a.B0 != nullptr : OP != kHvP;
+  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvP);
+  constexpr bool with_cols = OP == kHvX || OP == kHvP || OP == kGrad;
+  constexpr bool wants_label = OP == kGrad || OP == kLoss, wants_p = OP == kHvP;
+  float* mine = tile + wave * (64 * PP);
+
+  const bool aligned = (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
+  const int64_t end_el = ROWS == kQuads && aligned ? a.n * ld : (a.n - 1) * ld + p;  // elements that may be read
+  const int64_t last_el = (a.n - 1) * ld + p - 1;
+  // kQuads: quad q of row r lies (q + turn(r)) % NQ quads behind the row's start, so that the lanes' reads of one quad spread over
+  // the banks
+  auto turn = [](int r) { return NQ % 8 == 0 ? (r & 7) : (NQ % 4 == 0 ? ((r >> 1) & 3) : (NQ % 2 == 0 ? ((r >> 2) & 1) : 0)); };
+  auto source = [&](int slot) {  // kQuads: element of the chunk whose quad lies in this slot
+    const int r = slot / NQ, q = slot % NQ - turn(r);
+    return (r * NQ + (q < 0 ? q + NQ : q)) * 4;
+  };
+  auto fetch = [&](int64_t chunk) {
+    const int64_t e0 = chunk * 64 * ld;
+    if (aligned && e0 + 64 * ld <= end_el) {  // uniform
+#pragma unroll
+      for (int k = 0; k < NQ; ++k) {
+        const int s = k * 64 + lane;
+        if (ROWS == kQuads) copy_to_lds<16>(a.A + e0 + source(s), mine + k * 256);
+        else if (k < NQ - 1 || s < 16 * ld) copy_to_lds<16>(a.A + e0 + 4 * s, mine + k * 256);  // 4 (NQ - 1) < ld
+      }
+    } else {  // the matrix's last rows, or rows that start between 16-byte boundaries
+#pragma unroll 1
+      for (int i = 0; i < ld; ++i) {
+        const int s = i * 64 + lane;
+        const int64_t e = e0 + (ROWS == kQuads ? source(s >> 2) + (s & 3) : s);
+        copy_to_lds<4>(a.A + (e < last_el ? e : last_el), mine + i * 64);
+      }
+    }
+  };
+
+  // one entry of X and of V per lane (p (C-1) <= 64); the products read them lane by lane as scalar registers
+  const int le = lane < p * NC ? lane : p * NC - 1;
+  float x_in = has0 ? a.B0[le] : 0.f, v_in = has1 ? a.B1[le] : 0.f;
+  x_in = lane < p * NC ? x_in : 0.f;
+  v_in = lane < p * NC ? v_in : 0.f;
+  auto entry = [](float all, int e) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(all), e)); };
+  float acc[PP][NC];
+#pragma unroll
+  for (int j = 0; j < PP; ++j)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[j][c] = 0.f;
+  double loss_acc = 0.0;
+
+  const int64_t nchunks = (a.n + 63) / 64, step = (int64_t)gridDim.x * W;
+  float Pn[NC];
+  int label_n = -1;
+  auto request = [&](int64_t chunk) {  // what a row needs beside A, ahead of its chunk: loads return in order
+    const int64_t row = chunk * 64 + lane;
+    const int64_t rc = row < a.n ? row : a.n - 1;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) Pn[c] = wants_p ? a.Pin[rc * NC + c] : 0.f;
+    if (wants_label) label_n = a.labels[rc];
+    fetch(chunk);
+  };
+  int64_t chunk = blockIdx.x + (int64_t)gridDim.x * wave;
+  if (chunk < nchunks) request(chunk);
+  while (chunk < nchunks) {  // uniform in a wave; no barrier inside
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the chunk is in LDS
+    float av[PP], P[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) P[c] = Pn[c];
+    const int label = label_n;
+    if constexpr (ROWS == kBlock) {
+#pragma unroll
+      for (int j = 0; j < PP; ++j) av[j] = mine[lane * ld + j];  // at most 63 ld + PP - 1 < 64 PP
+    } else {
+      const int tr = turn(lane);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int at = q + tr < NQ ? q + tr : q + tr - NQ;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&mine[lane * PP + 4 * at]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[4 * q + e] = v[e];
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // and in registers: its place is free
+#pragma unroll
+    for (int j = PP - 4; j < PP; ++j) av[j] = j < p ? av[j] : 0.f;  // p > PP - 4
+    const int64_t row = chunk * 64 + lane;
+    if (chunk == nchunks - 1) {  // uniform: rows past the end
+#pragma unroll
+      for (int j = 0; j < PP; ++j) av[j] = row < a.n ? av[j] : 0.f;
+    }
+    const int64_t next = chunk + step;
+    if (next < nchunks) request(next);
+    thin_row<PP, NC>(a, has0, has1, with_cols, row < a.n, row, av, [&](int j, int c) { return entry(x_in, j * NC + c); },
+                     [&](int j, int c) { return entry(v_in, j * NC + c); }, P, label, acc, loss_acc);
+    chunk = next;
+  }
+
+  // ---- workgroup sums as in thin_kernel ----
+  __syncthreads();
+  float* wsum = tile;  // [wave][row of 16 lanes][D]: 4 D floats of a wave's 64 PP
+  if (with_cols) {
+#pragma unroll
+    for (int j = 0; j < PP; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const float v = mfma_detail::row16_sum(acc[j][c]);
+        if ((lane & 15) == 0) wsum[(wave * 4 + (lane >> 4)) * D + j * NC + c] = v;
+      }
+  }
+  if (a.loss_part != nullptr) {
+    loss_acc = mfma_detail::wave64_sum(loss_acc);
+    if (lane == 0) red[wave] = loss_acc;
+  }
+  __syncthreads();
+  if (with_cols && t < p * NC) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      s += (wsum[(4 * w) * D + t] + wsum[(4 * w + 1) * D + t]) + (wsum[(4 * w + 2) * D + t] + wsum[(4 * w + 3) * D + t]);
+    ta.partial[(size_t)blockIdx.x * (p * NC) + t] = s;
+  }
+  if (a.loss_part != nullptr && t == 0) {
+    double s = red[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) s += red[w];
+    a.loss_part[blockIdx.x] = s;
+  }
+}
+
+template <int NQ, int NC, Rows ROWS, StreamOp OP>
+hipError_t launch_stream_op(const ThinArgs& ta, int grid, hipStream_t st) {
+  constexpr int THREADS = 4 * NQ * NC <= 32 ? 1024 : 512;  // accumulators in 128 or 256 registers
+  constexpr size_t lds = (size_t)THREADS * 4 * NQ * sizeof(float);
+  if constexpr (lds + 1024 > 64 * 1024) {
+    static LdsLimitMask done{0};
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&thin_stream_kernel<NQ, NC, THREADS, ROWS, OP>), &done, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((thin_stream_kernel<NQ, NC, THREADS, ROWS, OP>), dim3(grid), dim3(THREADS), lds, st, ta);
+  return hipGetLastError();
+}
+
+template <int NQ, int NC, Rows ROWS>
+hipError_t launch_stream(const ThinArgs& ta, int grid, hipStream_t st) {
+  const RowArgs& a = ta.r;
+  const bool cols = ta.partial != nullptr;
+  if constexpr (4 * NQ * NC <= 64) {
+    if (a.kind == kRowsHv && cols && a.B1 != nullptr && (a.B0 != nullptr || a.Pin != nullptr))
+      return a.B0 != nullptr ? launch_stream_op<NQ, NC, ROWS, kHvX>(ta, grid, st) : launch_stream_op<NQ, NC, ROWS, kHvP>(ta, grid, st);
+    if (a.kind == kRowsGrad && cols && a.B0 != nullptr) return launch_stream_op<NQ, NC, ROWS, kGrad>(ta, grid, st);
+    if (a.kind == kRowsLoss && !cols && a.B0 != nullptr) return launch_stream_op<NQ, NC, ROWS, kLoss>(ta, grid, st);
+    if (a.kind == kRowsLogits && !cols) return launch_stream_op<NQ, NC, ROWS, kLogits>(ta, grid, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int NQ, int NC, bool CG>
 hipError_t launch_rows(const ThinArgs& ta, int grid, hipStream_t st) {
-  const size_t lds = (size_t)kThinThreads * tile_stride(4 * NQ, ROWS) * sizeof(float);
-  hipLaunchKernelGGL((thin_kernel<NQ, NC, CG, ROWS>), dim3(grid), dim3(kThinThreads), lds, st, ta);
+  const size_t lds = (size_t)kThinThreads * tile_stride(4 * NQ) * sizeof(float);
+  hipLaunchKernelGGL((thin_kernel<NQ, NC, CG>), dim3(grid), dim3(kThinThreads), lds, st, ta);
   return hipGetLastError();
 }
 
 template <int NQ, int NC>
 hipError_t launch_thin_t(const ThinArgs& ta, int grid, bool cg, Rows rows, hipStream_t st) {
   if (rows != kDense && cg) return hipErrorInvalidValue;
-  if (rows == kQuads) return launch_rows<NQ, NC, false, kQuads>(ta, grid, st);
-  if (rows == kBlock) return launch_rows<NQ, NC, false, kBlock>(ta, grid, st);
-  return cg ? launch_rows<NQ, NC, true, kDense>(ta, grid, st) : launch_rows<NQ, NC, false, kDense>(ta, grid, st);
+  if (rows == kQuads) return launch_stream<NQ, NC, kQuads>(ta, grid, st);
+  if (rows == kBlock) return launch_stream<NQ, NC, kBlock>(ta, grid, st);
+  return cg ? launch_rows<NQ, NC, true>(ta, grid, st) : launch_rows<NQ, NC, false>(ta, grid, st);
 }
 
 template <int NQ>
@@ -418,6 +565,9 @@ int thin_num_partials(const Shape& s) {
   const int64_t per = (chunks + g - 1) / g;
   return (int)((chunks + per - 1) / per);
 }
+
+// other rows (thin_stream_kernel): one workgroup per compute unit, and every wave with a chunk of 64 rows before any has two
+int thin_stream_partials(const Shape& s) { return (int)std::min<int64_t>(256, (s.n + 63) / 64); }
 
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg, const ReduceArgs* prev) {
   ThinArgs ta;
