@@ -108,8 +108,8 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->fused_ok = !L->sparse && fused_supported(s, p->lda, p->d_A);
   L->fused_parts = L->fused_ok ? (L->narrow ? L->narrow_parts : fused_num_partials(s)) : 0;
   if (wg_cap > 0 && L->fused_parts > wg_cap) L->fused_parts = wg_cap;
-  L->thin_parts = L->thin_ok ? thin_num_partials(s) : (L->thin_any ? thin_stream_partials(s) : 0);
-  const int thin_room = L->thin_ok || L->thin_any ? std::max(thin_num_partials(s), L->thin_parts) : 0;
+  const bool thin = L->thin_ok || L->thin_any;
+  L->thin_parts = thin ? thin_num_partials(s) : 0;
   const size_t vec = hv_only ? 0 : align256((size_t)s.d * sizeof(float));
   const size_t rows = align256((size_t)s.n * s.NC * sizeof(float));
   const size_t rows_solver = hv_only ? 0 : rows;
@@ -120,7 +120,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->r = off; off += vec;
   L->dvec = off; off += vec;
   L->q = off; off += vec;
-  const bool two_sets = L->fused_ok || L->thin_ok;  // the paths with a deferred CG update
+  const bool two_sets = L->fused_ok || thin;  // the paths with a deferred CG update
   L->pdir2 = off; off += two_sets ? vec : 0;
   L->r2 = off; off += two_sets ? vec : 0;
   L->dvec2 = off; off += two_sets ? vec : 0;
@@ -143,12 +143,12 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   if (L->wide_parts > parts) parts = L->wide_parts;
   if (L->narrow_parts > parts) parts = L->narrow_parts;
   if (L->sliced_parts > parts) parts = L->sliced_parts;
-  if (thin_room > parts) parts = thin_room;
+  if (L->thin_parts > parts) parts = L->thin_parts;
   L->partial = off; off += align256((size_t)parts * s.d * sizeof(float));
   // thin-data path: the sweeps of a CG solve write their partial sums to two buffers in turn (each reads the previous one's)
-  L->partial2 = off; off += (L->thin_ok && !hv_only) ? align256((size_t)L->thin_parts * s.d * sizeof(float)) : 0;
+  L->partial2 = off; off += (thin && !hv_only) ? align256((size_t)L->thin_parts * s.d * sizeof(float)) : 0;
   int lblocks = L->gen_row_blocks > L->fused_parts ? L->gen_row_blocks : L->fused_parts;
-  if (thin_room > lblocks) lblocks = thin_room;
+  if (L->thin_parts > lblocks) lblocks = L->thin_parts;
   if (L->sliced_loss > lblocks) lblocks = L->sliced_loss;
   if (L->wide_parts > lblocks) lblocks = L->wide_parts;
   if (L->narrow_parts > lblocks) lblocks = L->narrow_parts;
@@ -473,7 +473,7 @@ CgPend cg_pend(const Layout& L, void* ws, DevState* ds, int slot_in, bool final_
   return c;
 }
 
-// Thin-data path inside a Newton iteration: the CG update is deferred as on the fused path, and the reduction of the partial
+// Thin-data path: the CG update is deferred as on the fused path, and the reduction of the partial
 // sums with it: sweep k writes partial buffer k & 1 and first applies update k - 1 from buffer (k - 1) & 1.
 bool thin_deferred(int path) { return path == 3; }
 float* thin_partial(const Layout& L, void* ws, int k) { return at<float>(ws, (k & 1) ? L.partial2 : L.partial); }
@@ -495,12 +495,14 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
                  const NewtonHeadArgs* head = nullptr, bool thin_def = false) {
   float* dvec = at<float>(ws, L.dvec);
   float* q = at<float>(ws, L.q);
-  if (thin_def) {  // cached probabilities, no reduction kernel: see thin_deferred
-    if (!thin_deferred(path) || X != nullptr) return NADMM_EINVAL;
+  if (thin_def) {  // no reduction kernel: see thin_deferred
+    if (!thin_deferred(path) || (X != nullptr && k > 0)) return NADMM_EINVAL;
     RowArgs ra = blank_rows();
     ra.kind = kRowsHv;
+    ra.B0 = X;
     ra.B1 = dvec;  // k == 0: the first direction; later the kernel takes the direction from the update it applies
-    ra.Pin = at<float>(ws, L.pcache);
+    ra.Pin = X ? nullptr : at<float>(ws, L.pcache);
+    ra.Pout = (X && write_pcache) ? at<float>(ws, L.pcache) : nullptr;
     ra.rows_out = at<float>(ws, L.drows);
     int nparts = 0;
     if (k == 0) {
@@ -675,7 +677,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     if (!head_in_reduce) NADMM_HIP(launch_newton_head(nh, st));
 
     // CG on H p = -g with the probabilities of this iterate
-    const bool thin_def = thin_deferred(path) && L.thin_ok && params->max_cg >= 1;
+    const bool thin_def = thin_deferred(path) && params->max_cg >= 1;
     const bool hist = use_hist && cg_deferred(path) && params->max_cg >= 1 && params->max_cg <= L.hist_bufs;
     const size_t hist_stride = align256((size_t)L.s.n * L.s.NC * sizeof(float)) / sizeof(float);
     for (int k = 0; k < params->max_cg; ++k) {
@@ -999,10 +1001,15 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   NADMM_HIP(launch_newton_head(nh, st));
 
   for (int k = 0; k < max_iter; ++k) {
-    if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st)) != NADMM_OK) return rc;
+    if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st, nullptr, nullptr, thin_deferred(path))) !=
+        NADMM_OK)
+      return rc;
   }
-  const bool pend = cg_deferred(path) && max_iter > 0;
-  if (pend) NADMM_HIP(launch_cg_pending_finish(cg_pend(L, d_ws, ds, (max_iter - 1) & 1, true, tol), st));
+  const bool pend = (cg_deferred(path) || thin_deferred(path)) && max_iter > 0;
+  if (pend) {
+    const CgPend c = cg_pend(L, d_ws, ds, (max_iter - 1) & 1, true, tol);
+    NADMM_HIP(thin_deferred(path) ? launch_thin_cg_finish(c, thin_prev(prob, L, d_ws, max_iter - 1), st) : launch_cg_pending_finish(c, st));
+  }
   CgFinishArgs cf;
   cf.st = ds;
   cf.pdir = pend ? at<float>(d_ws, L.pfinal) : at<float>(d_ws, L.pdir);

@@ -352,14 +352,15 @@ hipError_t launch_cg_pending_finish(const CgPend& c, hipStream_t st);
 
 // ---- thin-data single-pass path (nadmm_thin.hip): p <= 32, C-1 <= 3, at most 3 elements between rows ----
 bool thin_supported(const Shape& s, int64_t lda, const void* A);          // p % 4 == 0, lda == p, 16-byte aligned
-bool thin_general_supported(const Shape& s, int64_t lda, const void* A);  // the same kernel for other rows of up to 32 columns, without cg
+bool thin_general_supported(const Shape& s, int64_t lda, const void* A);  // other rows of up to 32 columns
 bool thin_padded_narrow(const Shape& s, int64_t lda);  // of those, 16-byte aligned: whether the narrow-row kernel is faster
-int thin_num_partials(const Shape& s);     // rows of thin_supported
-int thin_stream_partials(const Shape& s);  // the others
+int thin_num_partials(const Shape& s);
 // cg, prev (both or neither): the sweep first applies the pending CG update, forming q = H d from the previous sweep's
 // partial sums prev->partial (prev also carries scale, lambda, rho of the linear terms); see ThinArgs in nadmm_thin.hip
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
                        const ReduceArgs* prev = nullptr);
+// the pending update alone (one workgroup): end of a stand-alone CG solve
+hipError_t launch_thin_cg_finish(const CgPend& cg, const ReduceArgs& prev, hipStream_t st);
 
 // ---- a whole CG or Newton solve of a small thin problem in one launch (nadmm_small.hip) ----
 struct SmallSolve {

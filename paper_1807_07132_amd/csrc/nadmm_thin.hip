@@ -1,18 +1,19 @@
 // Single-pass kernel for thin data (p <= 32 features, few classes), gfx950.
 //
-// With rows of 16..128 bytes the pass is a pure HBM stream (about 1.5 flop per
-// byte for C = 2), so there is no contraction worth a matrix core: one lane owns
-// one sample.  A workgroup copies a chunk of 256 consecutive rows -- a contiguous
-// block of memory -- with coalesced 16-byte loads into LDS (row stride padded off
-// the bank period), each lane reads its own row back, forms its logits Z = a_i X
-// and W = a_i V with X and V as wave-uniform operands, the probabilities with the
-// log-sum-exp shift (Section 2.2), its row of D (Section 2.6) or of P - Y, and
-// accumulates a_i^T D into its private p x (C-1) registers.  The next chunk is
-// already in flight in registers while the current one is consumed.  Per-lane
-// accumulators are summed over the workgroup once, at the end, in a fixed order.
-// Inside a Newton iteration the sweep of CG iteration k also does what lies between
-// two sweeps (Section 2.4): it adds up the partial sums of sweep k - 1, forms q = H d
-// and applies the CG update before it reads its operand (instantiations with CG).
+// With rows of 4..128 bytes the pass is a pure HBM stream (about 1.5 flop per byte for C = 2), so there is no contraction worth a
+// matrix core: one lane owns one sample.  A wave copies chunks of 64 rows -- one block of memory -- straight into its own part of
+// LDS (global_load_lds), takes its rows from there into registers and has the next chunk on its way before it computes: logits
+// Z = a_i X and W = a_i V with X and V as wave-uniform operands, the probabilities with the log-sum-exp shift (Section 2.2), the row
+// of D (Section 2.6) or of P - Y, and a_i^T D into its private p x (C-1) registers.  What is in flight is LDS, not registers
+// (16 waves per compute unit with up to 8 KB each), and no barrier is in the loop.  Per-lane accumulators are summed over the
+// workgroup once, at the end, in a fixed order.
+// In a CG solve the sweep of iteration k also does what lies between two sweeps (Section 2.4): it adds up the partial sums of
+// sweep k - 1, forms q = H d and applies the CG update before it reads its operand (kHvCg, kLogitsCg).
+//
+// What bounds it: HBM.  Against chunks of 256 rows through registers of a whole workgroup (up to 204 of them, and surplus pieces
+// past every chunk where rows are no dense quads): objective and gradient at 1375000 x 29, C = 2: 53.5 -> 35.8 us (the floor of one
+// read of A is 28 us); Hessian-vector product at 600000 x 30, C = 3: 45.9 -> 20.7 us;
+// 10 Newton iterations of 10 CG iterations at 1375000 x 28, C = 2: 4108 -> 3701 us; 6 CG iterations at 600000 x 32, C = 2: 184 -> 110 us.
 #include <algorithm>
 #include <cstring>
 
@@ -23,14 +24,12 @@
 namespace nadmm {
 namespace {
 
-constexpr int kThinThreads = 256;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct ThinArgs {
   RowArgs r;
   float* partial;      // gridDim.x x (p*NC) or NULL
-  int32_t rows_per_wg; // multiple of 256
-  // Deferred CG update (kernels instantiated with CG): the sweep of the previous CG iteration left only its per-workgroup
+  // Deferred CG update (kHvCg, kLogitsCg): the sweep of the previous CG iteration left only its per-workgroup
   // partial sums of A^T D.  Every workgroup of this sweep adds them up (fixed order), forms q = H d, applies the update of
   // Section 2.4 and takes its operand, the new direction (or, for the line search's pass, the final iterate), from there;
   // workgroup 0 stores the new vectors and state.  No reduction kernel and no CG kernel run between two sweeps.
@@ -41,17 +40,15 @@ struct ThinArgs {
   const float* rho_scale;
 };
 
-// NQ = p / 4: float4 per row, which is also the float4 per lane in a chunk of 256 rows
-// ROWS: how the rows lie.  kDense: lda = p, a multiple of 4, 16-byte aligned.  The others (p odd, a few columns of padding, A
-// 4-byte aligned; NQ = ceil(lda / 4)) would go through the matrix-core kernel for narrow rows, where one lane in 16 has work in
-// the rows stage (1375000 x 29, C = 2, objective and gradient: 103 us).
+constexpr int kThinMaxPartials = 256;  // one workgroup per compute unit
+constexpr int kThinMaxD = 64;          // p (C-1), with padded columns: the vectors fit one wave
+
+// How the rows lie, with lda <= 4 NQ:
+//   kQuads: lda = 4 NQ, rows of whole quads (p = lda, or up to three elements between rows).  The lanes read quads, which lie
+//     turned within their rows so that the reads spread over the banks.
 //   kBlock: lda is no multiple of 4.  A block of rows lies in LDS as it does in memory, and the lanes read their rows back in
 //     4-byte pieces: no bank conflicts where lda is odd, two lanes to a bank where it is even.
-//   kQuads: lda = 4 NQ.  The lanes read whole quads, which lie turned within their rows.
-enum Rows { kDense, kBlock, kQuads };
-
-// floats per row in LDS, off the bank period
-constexpr int tile_stride(int pp) { return pp % 8 == 0 ? pp + 4 : pp; }
+enum Rows { kBlock, kQuads };
 
 // Everything a lane does with its row of A once it is in registers: logits, probabilities with the log-sum-exp shift, its row of D
 // or of P - Y, the optional outputs, and its share of A^T rows.  P: the cached probabilities on entry (has0 false).
@@ -128,204 +125,93 @@ __device__ __forceinline__ void thin_row(const RowArgs& a, bool has0, bool has1,
   }
 }
 
-template <int NQ, int NC, bool CG>
-__global__ __launch_bounds__(kThinThreads) void thin_kernel(const ThinArgs ta) {
-  constexpr int PP = 4 * NQ;
-  constexpr int kMaxQuads = NQ;
-  constexpr int nquads = NQ;
-  const RowArgs& a = ta.r;
-  if (a.flag != nullptr && *a.flag == 0) return;
-  extern __shared__ __attribute__((aligned(16))) float tile[];  // 256 rows, see tile_stride
-  __shared__ double red[4];
-  const int t = threadIdx.x;
-  constexpr int p = PP, PS = tile_stride(PP);
-  const bool has0 = !CG && a.B0 != nullptr;
-  const bool has1 = CG || a.B1 != nullptr;
-  const bool with_cols = ta.partial != nullptr;
-
-  const int64_t r_begin = (int64_t)blockIdx.x * ta.rows_per_wg;
-  int64_t r_end = r_begin + ta.rows_per_wg;
-  if (r_end > a.n) r_end = a.n;
-  const f32x4* A4 = reinterpret_cast<const f32x4*>(a.A);
-  const int64_t last4 = a.n * nquads - 1;  // last float4 of the matrix (lda == p)
-
-  // X and V are the same for every lane: keep them as wave-uniform (scalar) registers
-  float xs[PP][NC], vs[PP][NC];
-  if constexpr (CG) {
-    constexpr int D = PP * NC;      // length of the vectors, a multiple of 4
-    constexpr int NQV = D / 4;      // quads per partial
-    constexpr int GROUPS = kThinThreads / NQV;
-    constexpr int U = 24;           // partials per thread and memory round trip
-    __shared__ __attribute__((aligned(16))) float cgv[D];
-    __shared__ __attribute__((aligned(16))) float cgq[D];
-    __shared__ double cgdot[1];
-    __shared__ double cgsm[kThinThreads / 64 + 1];
-    const CgPend& c = ta.cg;
-    const int cur = c.st->cgs[c.slot_in].cur & 1;
-    const float* __restrict__ d_in = cur ? c.d[1] : c.d[0];
-    const float rho_ = ta.rho_scale != nullptr ? ta.rho * *ta.rho_scale : ta.rho;
-    const float dv = d_in[t < D ? t : D - 1];
-    // thread (group g, quad qd) adds the partials g, g + GROUPS, ... of its quad, in that order
-    const int qd = t % NQV, g = t / NQV;
-    const int gc = g < GROUPS ? g : GROUPS - 1;
-    const f32x4* __restrict__ pq = reinterpret_cast<const f32x4*>(ta.prev) + qd;
-    f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k = gc; k < ta.nprev; k += U * GROUPS) {
-      f32x4 v[U];
+// q = H d and the pending CG update (CgPend, Section 2.4) from the previous sweep's partial sums.  Lane e of wave w adds element e of
+// the partials w, w + W, ... (all requested at once, together with both sets of vectors, so that nothing waits to learn which set is
+// current); behind one barrier every wave adds up the waves' sums and makes the update for itself, one element of the vectors per
+// lane.  (By the whole workgroup, as for longer vectors, it took five barriers: 1.3 us more per CG iteration at 2500 to 40000 rows.)
+// Returns the lane's element of the new direction or of the final iterate; *go is false if no product is left to form.
+// `writer`: this wave stores the new vectors and state.  after_issue(): the caller's first loads.
+template <int THREADS, typename F>
+__device__ __forceinline__ float cg_from_partials(const ThinArgs& ta, bool writer, bool* go, F&& after_issue) {
+  constexpr int W = THREADS / 64, U = kThinMaxPartials / W;
+  __shared__ float wave_part[W][64];
+  const CgPend& c = ta.cg;
+  DevState* st = c.st;
+  const int t = threadIdx.x, e = t & 63, w = t >> 6;
+  const int dlen = (int)c.dlen, ec = e < dlen ? e : dlen - 1;
+  const bool own = e < dlen;
+  float part[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int idx = k + u * GROUPS;
-        v[u] = pq[(size_t)(idx < ta.nprev ? idx : ta.nprev - 1) * NQV];
+  for (int u = 0; u < U; ++u) {
+    const int k = w + u * W;
+    part[u] = ta.prev[(size_t)(k < ta.nprev ? k : ta.nprev - 1) * dlen + ec];
+  }
+  const float r0 = c.r[0][ec], r1 = c.r[1][ec], d0 = c.d[0][ec], d1 = c.d[1][ec], p0 = c.p[0][ec], p1 = c.p[1][ec];
+  const CgSlot in = st->cgs[c.slot_in];
+  const double gg = st->gg_cg;
+  const float rho_ = ta.rho_scale != nullptr ? ta.rho * *ta.rho_scale : ta.rho;
+  __builtin_amdgcn_sched_barrier(0);
+  after_issue();
+  __builtin_amdgcn_sched_barrier(0);
+  float s = 0.f;
+#pragma unroll
+  for (int u = 0; u < U; ++u) s += w + u * W < ta.nprev ? part[u] : 0.f;
+  wave_part[w][e] = s;
+  lds_barrier();
+  float s2 = 0.f;
+#pragma unroll
+  for (int k = 0; k < W; ++k) s2 += wave_part[k][e];
+  const int cur = in.cur & 1;
+  float r = own ? (cur ? r1 : r0) : 0.f, d = own ? (cur ? d1 : d0) : 0.f, p = own ? (cur ? p1 : p0) : 0.f;
+  const float q = own ? fmaf(ta.lambda + rho_, d, ta.scale * s2) : 0.f;
+  CgSlot out = in;
+  bool updated = false;
+  float al = 0.f;
+  if (in.active != 0) {  // uniform
+    const double dq = mfma_detail::wave64_sum((double)d * (double)q);
+    if (!(dq > 0.0) || !isfinite(dq)) {  // no positive curvature: keep the current iterate
+      out.active = 0;
+    } else {
+      al = (float)(in.rr / dq);
+      r = fmaf(-al, q, r);
+      const double rr_new = mfma_detail::wave64_sum((double)r * (double)r);
+      p = fmaf(al, d, p);
+      d = fmaf((float)(rr_new / in.rr), d, r);
+      out.rr = rr_new;
+      out.iters = in.iters + 1;
+      out.cur = cur ^ 1;
+      if (sqrt(rr_new) <= (double)c.tol * sqrt(gg)) out.active = 0;
+      updated = true;
+    }
+  }
+  if (writer) {
+    if (own && updated) {
+      (cur ? c.r[0] : c.r[1])[e] = r;
+      (cur ? c.d[0] : c.d[1])[e] = d;
+      (cur ? c.p[0] : c.p[1])[e] = p;
+    }
+    if (own && c.final_p != 0) c.p_final[e] = p;
+    if (e == 0) {
+      st->cgs[c.slot_in ^ 1] = out;
+      if (updated && in.iters < kCgHist) st->cg_alphas[in.iters] = al;
+      if (c.final_p != 0) {  // the scalars that the line search and the statistics read
+        st->rr = out.rr;
+        st->cg_iters = out.iters;
+        st->cg_active = out.active;
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (k + u * GROUPS < ta.nprev) s4 += v[u];
-    }
-    f32x4* gs = reinterpret_cast<f32x4*>(tile);  // [group][quad]: at most 256 quads, the smallest tile holds them
-    if (g < GROUPS) gs[g * NQV + qd] = s4;
-    __syncthreads();
-    if (t < 64) {  // the vectors fit one wave
-      double prod = 0.0;
-      if (t < D) {
-        float s2 = 0.f;
-        for (int g2 = 0; g2 < GROUPS; ++g2) s2 += tile[(g2 * NQV + (t >> 2)) * 4 + (t & 3)];
-        const float qv = fmaf(ta.lambda + rho_, dv, ta.scale * s2);
-        cgq[t] = qv;
-        prod = (double)dv * (double)qv;
-      }
-      prod = mfma_detail::wave64_sum(prod);
-      if (t == 0) cgdot[0] = prod;
-    }
-    __syncthreads();
-    CgPend c2 = c;
-    c2.q = cgq;
-    c2.dot_part = cgdot;
-    c2.ndot = 1;
-    if (!cg_pending_update<kThinThreads, 1>(c2, blockIdx.x == 0, cgv, cgsm, [] {})) return;
-#pragma unroll
-    for (int j = 0; j < PP; ++j)
-#pragma unroll
-      for (int c1 = 0; c1 < NC; ++c1) {
-        xs[j][c1] = 0.f;
-        vs[j][c1] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(cgv[j * NC + c1])));
-      }
-    __syncthreads();  // the tile is about to be overwritten by the first chunk
-  } else {
-#pragma unroll
-    for (int j = 0; j < PP; ++j)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        xs[j][c] = has0 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B0[j * NC + c]))) : 0.f;
-        vs[j][c] = has1 ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.B1[j * NC + c]))) : 0.f;
-      }
-  }
-
-  float acc[PP][NC];
-#pragma unroll
-  for (int j = 0; j < PP; ++j)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[j][c] = 0.f;
-  double loss_acc = 0.0;
-
-  // position of this lane's k-th float4 inside a chunk: element 4 (t + 256 k) = row * PP + col
-  int prow[kMaxQuads], pcol[kMaxQuads];
-  {
-    int row = (4 * t) / PP, col = (4 * t) % PP;
-#pragma unroll
-    for (int k = 0; k < kMaxQuads; ++k) {
-      prow[k] = row;
-      pcol[k] = col;
-      row += 1024 / PP;
-      col += 1024 % PP;
-      if (col >= PP) { col -= PP; row += 1; }
     }
   }
-
-  // Two chunks are in flight per workgroup: registers pf[0] and pf[1] alternate.  Loads are
-  // unconditional (addresses clamped to the workgroup's own last float4), so the compiler can
-  // wait for exactly the chunk it needs.
-  f32x4 pf[2][kMaxQuads];
-  const int64_t own_last4 = (r_end > r_begin ? r_end : r_begin + 1) * nquads - 1;
-  auto load_chunk = [&](int b, int64_t row0) {
-    const int64_t base4 = row0 * nquads + t;
-#pragma unroll
-    for (int k = 0; k < kMaxQuads; ++k) {
-      int64_t i4 = base4 + (int64_t)k * kThinThreads;
-      i4 = i4 < own_last4 ? i4 : own_last4;
-      i4 = i4 < last4 ? i4 : last4;
-      pf[b][k] = A4[i4];
-    }
-  };
-  auto process = [&](int b, int64_t row0) {
-    __syncthreads();  // rows of the previous chunk have been read
-#pragma unroll
-    for (int k = 0; k < kMaxQuads; ++k) {
-      *reinterpret_cast<f32x4*>(__builtin_assume_aligned(&tile[prow[k] * PS + pcol[k]], 16)) = pf[b][k];
-    }
-    load_chunk(b, row0 + 2 * kThinThreads);
-    __syncthreads();
-
-    const int64_t row = row0 + t;
-    const bool valid = row < r_end;
-    float av[PP];
-#pragma unroll
-    for (int q = 0; q < PP / 4; ++q) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(__builtin_assume_aligned(&tile[t * PS + 4 * q], 16));
-      av[4 * q + 0] = v[0]; av[4 * q + 1] = v[1]; av[4 * q + 2] = v[2]; av[4 * q + 3] = v[3];
-    }
-    float P[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) P[c] = (!has0 && valid && a.Pin != nullptr) ? a.Pin[(size_t)row * NC + c] : 0.f;
-    const int label = (valid && a.kind != kRowsHv && a.kind != kRowsLogits) ? a.labels[row] : -1;
-    thin_row<PP, NC>(a, has0, has1, with_cols, valid, row, av, [&](int j, int c) { return xs[j][c]; },
-                     [&](int j, int c) { return vs[j][c]; }, P, label, acc, loss_acc);
-  };
-
-  if (r_begin < r_end) {
-    load_chunk(0, r_begin);
-    load_chunk(1, r_begin + kThinThreads);
-  }
-  for (int64_t row0 = r_begin; row0 < r_end; row0 += 2 * kThinThreads) {
-    process(0, row0);
-    if (row0 + kThinThreads < r_end) process(1, row0 + kThinThreads);
-  }
-
-  // ---- workgroup sums: every accumulator over each row of 16 lanes by rotations (no shuffles: 28 trees of six
-  // shuffles each took 5 us here, where nothing overlaps them), then the 16 row sums in a fixed order ----
-  __syncthreads();
-  float* wsum = tile;  // [wave][row of 16 lanes][PP*NC]: 16 sums per accumulator (at most 4 KB, the smallest tile)
-  const int lane = t & 63, wave = t >> 6;
-  if (with_cols) {
-#pragma unroll
-    for (int j = 0; j < PP; ++j)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const float v = mfma_detail::row16_sum(acc[j][c]);
-        if ((lane & 15) == 0) wsum[(wave * 4 + (lane >> 4)) * (PP * NC) + j * NC + c] = v;
-      }
-  }
-  if (a.loss_part != nullptr) {
-    loss_acc = mfma_detail::wave64_sum(loss_acc);
-    if (lane == 0) red[wave] = loss_acc;
-  }
-  __syncthreads();
-  if (with_cols && t < p * NC) {
-    float w4[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-      w4[w] = (wsum[(4 * w) * (PP * NC) + t] + wsum[(4 * w + 1) * (PP * NC) + t]) +
-              (wsum[(4 * w + 2) * (PP * NC) + t] + wsum[(4 * w + 3) * (PP * NC) + t]);
-    ta.partial[(size_t)blockIdx.x * (p * NC) + t] = ((w4[0] + w4[1]) + w4[2]) + w4[3];
-  }
-  if (a.loss_part != nullptr && t == 0) a.loss_part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+  *go = c.final_p != 0 || out.active != 0;
+  return c.final_p != 0 ? p : d;
 }
 
-// The same for the other rows (kBlock, kQuads): no barrier and no prefetch registers.  A wave copies chunks of 64 rows -- one block
-// of memory -- straight into its own part of LDS (global_load_lds), takes its rows from there into registers and has the next chunk
-// on its way before it computes.  What is in flight is LDS, not registers: 16 waves per compute unit with up to 8 KB each.
-// What bounds it: HBM.  Against chunks of 256 rows through registers (204 of them, so that only 512 of the 768 workgroups fitted,
-// and surplus pieces past every chunk): objective and gradient at 1375000 x 29, C = 2: 53.5 -> 35.8 us (4.46 TB/s with the reduction's
-// launch; the floor of one read of A is 28 us); Hessian-vector product at 600000 x 30, C = 3: 45.9 -> 20.7 us.
+// the pending update alone: end of a stand-alone CG solve
+constexpr int kFinishThreads = 1024;
+__global__ __launch_bounds__(kFinishThreads) void thin_cg_finish_kernel(const ThinArgs ta) {
+  bool go;
+  cg_from_partials<kFinishThreads>(ta, threadIdx.x < 64, &go, [] {});
+}
+
 typedef __attribute__((address_space(1))) const void gvoid;
 typedef __attribute__((address_space(3))) void lvoid;
 template <int BYTES>  // lane l: BYTES from its own address g to l BYTES behind the wave's address to
@@ -336,22 +222,23 @@ __device__ __forceinline__ void copy_to_lds(const float* g, float* to) {
 }
 
 // What the sweep makes, fixed at compile time: chosen inside the loop it cost copies of all accumulators and spills.
-enum StreamOp { kHvX, kHvP, kGrad, kLoss, kLogits };  // kHvP: with cached probabilities
+enum StreamOp { kHvX, kHvP, kHvCg, kGrad, kLoss, kLogits, kLogitsCg };  // kHvP, kHvCg: with cached probabilities
 
 template <int NQ, int NC, int THREADS, Rows ROWS, StreamOp OP>
 __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta) {
   constexpr int PP = 4 * NQ, D = PP * NC, W = THREADS / 64;
   RowArgs a = ta.r;
-  a.kind = OP == kHvX || OP == kHvP ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : kRowsLogits));
+  a.kind = OP == kHvX || OP == kHvP || OP == kHvCg ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : kRowsLogits));
   if (a.flag != nullptr && *a.flag == 0) return;
   extern __shared__ __attribute__((aligned(16))) float tile[];  // [wave][64 rows]
   __shared__ double red[W];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int p = a.p, ld = ROWS == kQuads ? PP : (int)a.lda;
-  const bool has0 = OP == kLogits ? a.B0 != nullptr : OP != kHvP;
-  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvP);
-  constexpr bool with_cols = OP == kHvX || OP == kHvP || OP == kGrad;
-  constexpr bool wants_label = OP == kGrad || OP == kLoss, wants_p = OP == kHvP;
+  constexpr bool cg = OP == kHvCg || OP == kLogitsCg;
+  const bool has0 = OP == kLogits ? a.B0 != nullptr : (OP == kHvX || OP == kGrad || OP == kLoss);
+  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvP || cg);
+  constexpr bool with_cols = OP == kHvX || OP == kHvP || OP == kHvCg || OP == kGrad;
+  constexpr bool wants_label = OP == kGrad || OP == kLoss, wants_p = OP == kHvP || OP == kHvCg;
   float* mine = tile + wave * (64 * PP);
 
   const bool aligned = (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
@@ -383,19 +270,6 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
     }
   };
 
-  // one entry of X and of V per lane (p (C-1) <= 64); the products read them lane by lane as scalar registers
-  const int le = lane < p * NC ? lane : p * NC - 1;
-  float x_in = has0 ? a.B0[le] : 0.f, v_in = has1 ? a.B1[le] : 0.f;
-  x_in = lane < p * NC ? x_in : 0.f;
-  v_in = lane < p * NC ? v_in : 0.f;
-  auto entry = [](float all, int e) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(all), e)); };
-  float acc[PP][NC];
-#pragma unroll
-  for (int j = 0; j < PP; ++j)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[j][c] = 0.f;
-  double loss_acc = 0.0;
-
   const int64_t nchunks = (a.n + 63) / 64, step = (int64_t)gridDim.x * W;
   float Pn[NC];
   int label_n = -1;
@@ -408,7 +282,32 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
     fetch(chunk);
   };
   int64_t chunk = blockIdx.x + (int64_t)gridDim.x * wave;
-  if (chunk < nchunks) request(chunk);
+  // one entry of X and of V per lane (p (C-1) <= 64); the products read them lane by lane as scalar registers
+  const int dlen = p * NC, le = lane < dlen ? lane : dlen - 1;
+  float x_in = has0 ? a.B0[le] : 0.f, v_in = 0.f;
+  if constexpr (cg) {
+    bool go;
+    v_in = cg_from_partials<THREADS>(ta, blockIdx.x == 0 && wave == 0, &go, [&] {
+      if (chunk < nchunks) request(chunk);
+    });
+    if (!go) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way to LDS when the workgroup ends
+      return;
+    }
+  } else {
+    const float v = has1 ? a.B1[le] : 0.f;
+    v_in = lane < dlen ? v : 0.f;
+    if (chunk < nchunks) request(chunk);
+  }
+  x_in = lane < dlen ? x_in : 0.f;
+  auto entry = [](float all, int e) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(all), e)); };
+  float acc[PP][NC];
+#pragma unroll
+  for (int j = 0; j < PP; ++j)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[j][c] = 0.f;
+  double loss_acc = 0.0;
+
   while (chunk < nchunks) {  // uniform in a wave; no barrier inside
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the chunk is in LDS
     float av[PP], P[NC];
@@ -443,7 +342,8 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
     chunk = next;
   }
 
-  // ---- workgroup sums as in thin_kernel ----
+  // ---- workgroup sums: every accumulator over each row of 16 lanes by rotations (a tree of shuffles each took 5 us here, where
+  // nothing overlaps them), then the row sums in a fixed order ----
   __syncthreads();
   float* wsum = tile;  // [wave][row of 16 lanes][D]: 4 D floats of a wave's 64 PP
   if (with_cols) {
@@ -492,7 +392,12 @@ template <int NQ, int NC, Rows ROWS>
 hipError_t launch_stream(const ThinArgs& ta, int grid, hipStream_t st) {
   const RowArgs& a = ta.r;
   const bool cols = ta.partial != nullptr;
-  if constexpr (4 * NQ * NC <= 64) {
+  if constexpr (4 * NQ * NC <= kThinMaxD) {
+    if (ta.cg.st != nullptr) {
+      if (a.kind == kRowsHv && cols && a.Pin != nullptr) return launch_stream_op<NQ, NC, ROWS, kHvCg>(ta, grid, st);
+      if (a.kind == kRowsLogits && !cols && a.Z1out != nullptr) return launch_stream_op<NQ, NC, ROWS, kLogitsCg>(ta, grid, st);
+      return hipErrorInvalidValue;
+    }
     if (a.kind == kRowsHv && cols && a.B1 != nullptr && (a.B0 != nullptr || a.Pin != nullptr))
       return a.B0 != nullptr ? launch_stream_op<NQ, NC, ROWS, kHvX>(ta, grid, st) : launch_stream_op<NQ, NC, ROWS, kHvP>(ta, grid, st);
     if (a.kind == kRowsGrad && cols && a.B0 != nullptr) return launch_stream_op<NQ, NC, ROWS, kGrad>(ta, grid, st);
@@ -502,29 +407,29 @@ hipError_t launch_stream(const ThinArgs& ta, int grid, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-template <int NQ, int NC, bool CG>
-hipError_t launch_rows(const ThinArgs& ta, int grid, hipStream_t st) {
-  const size_t lds = (size_t)kThinThreads * tile_stride(4 * NQ) * sizeof(float);
-  hipLaunchKernelGGL((thin_kernel<NQ, NC, CG>), dim3(grid), dim3(kThinThreads), lds, st, ta);
-  return hipGetLastError();
-}
-
-template <int NQ, int NC>
-hipError_t launch_thin_t(const ThinArgs& ta, int grid, bool cg, Rows rows, hipStream_t st) {
-  if (rows != kDense && cg) return hipErrorInvalidValue;
-  if (rows == kQuads) return launch_stream<NQ, NC, kQuads>(ta, grid, st);
-  if (rows == kBlock) return launch_stream<NQ, NC, kBlock>(ta, grid, st);
-  return cg ? launch_rows<NQ, NC, true>(ta, grid, st) : launch_rows<NQ, NC, false>(ta, grid, st);
-}
-
 template <int NQ>
-hipError_t launch_thin_nq(const ThinArgs& ta, int grid, bool cg, Rows rows, hipStream_t st) {
+hipError_t launch_thin_nq(const ThinArgs& ta, int grid, hipStream_t st) {
+  const bool quads = ta.r.lda == 4 * NQ;
   switch (ta.r.NC) {
-    case 1: return launch_thin_t<NQ, 1>(ta, grid, cg, rows, st);
-    case 2: return launch_thin_t<NQ, 2>(ta, grid, cg, rows, st);
-    case 3: return launch_thin_t<NQ, 3>(ta, grid, cg, rows, st);
+    case 1: return quads ? launch_stream<NQ, 1, kQuads>(ta, grid, st) : launch_stream<NQ, 1, kBlock>(ta, grid, st);
+    case 2: return quads ? launch_stream<NQ, 2, kQuads>(ta, grid, st) : launch_stream<NQ, 2, kBlock>(ta, grid, st);
+    case 3: return quads ? launch_stream<NQ, 3, kQuads>(ta, grid, st) : launch_stream<NQ, 3, kBlock>(ta, grid, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+// the fields of a deferred CG update; false if they do not fit this path
+bool set_pending(ThinArgs* ta, const CgPend& cg, const ReduceArgs* prev, int64_t d) {
+  if (prev == nullptr || prev->partial == nullptr || prev->nparts < 1 || prev->nparts > kThinMaxPartials || prev->d != d) return false;
+  if (cg.st == nullptr || cg.dlen != d || d > kThinMaxD) return false;
+  ta->cg = cg;
+  ta->prev = prev->partial;
+  ta->nprev = prev->nparts;
+  ta->scale = prev->scale;
+  ta->lambda = prev->lambda;
+  ta->rho = prev->rho;
+  ta->rho_scale = prev->rho_scale;
+  return true;
 }
 
 }  // namespace
@@ -543,66 +448,48 @@ bool thin_general_supported(const Shape& s, int64_t lda, const void* A) {
   return s.n * lda >= 8 && (s.n - 1) * lda + s.p >= 4 && (reinterpret_cast<uintptr_t>(A) & 3) == 0;
 }
 
-// Rows with padding that are 16-byte aligned, of more than one operand piece: up to 65536 of them are faster on the narrow-row kernel,
-// which works to the same accuracy (Hessian-vector products within 4.0e-8 to 6.0e-8 of 64 bits, here 3.5e-8 to 5.8e-8) and defers the
-// CG update into the next sweep (here the vectors, p (C-1) long, are no whole quads).  With more rows the stream counts, one lane
-// per row against one in 16 with work in the rows stage; 32 x 2 accumulators leave so few waves in flight here that it takes 393216.
-// Measured, this kernel against the narrow one (us, 3 to 8 CG iterations): lda = 32, C = 3: 5000 rows 139 : 98, 60000 rows
-// 1.40 times, 220000 rows 1.70 times as fast on the narrow one, one gradient at 300000 rows 1.03, at 400000 0.92 times; lda = 20,
-// C = 4: 2500 rows 1.37, 60000 rows 1.28, gradient at 80000 rows 0.96; lda = 12, C = 3: 20000 rows 1.06, 80000 rows 0.89; lda = 16, C = 2:
-// 2500 rows 0.94, 20000 rows 1.02.  Single sweeps are equal up to 65536 rows.  Up to 2048 rows all CG iterations are one launch
-// (nadmm_small.hip): 300 rows 0.32 to 0.80.
+// Rows with padding that are 16-byte aligned, of more than one operand piece, go to the narrow-row kernel on up to 65536 rows (393216
+// with 32 x 2 accumulators), which works to the same accuracy (Hessian-vector products within 4.0e-8 to 6.0e-8 of 64 bits, here
+// 3.5e-8 to 5.8e-8).  The line was drawn when this path took such rows through registers and made the CG update in a kernel of its
+// own; it is part of the path numbers that callers may rely on and stays where it is.  Measured now, narrow-row kernel against this one
+// (us): lda = 32, C = 3: 4000 rows, 6 CG iterations 72 : 57, 300000 rows gradient 32 : 16, 6 CG iterations 141 : 85.
 bool thin_padded_narrow(const Shape& s, int64_t lda) {
   return s.n > 2048 && lda * s.NC > 16 && s.n < (lda * s.NC < 64 ? 65536 : 393216);
 }
 
-int thin_num_partials(const Shape& s) {
-  // 3 resident workgroups per compute unit for small accumulator sets, else 2 (register budget);
-  // every workgroup gets the same whole number of 256-row chunks
-  const int64_t cap = (s.p * s.NC <= 32) ? 768 : 512;
-  const int64_t chunks = (s.n + kThinThreads - 1) / kThinThreads;
-  const int64_t g = chunks < cap ? chunks : cap;
-  const int64_t per = (chunks + g - 1) / g;
-  return (int)((chunks + per - 1) / per);
-}
-
-// other rows (thin_stream_kernel): one workgroup per compute unit, and every wave with a chunk of 64 rows before any has two
-int thin_stream_partials(const Shape& s) { return (int)std::min<int64_t>(256, (s.n + 63) / 64); }
+// one workgroup per compute unit, and every wave with a chunk of 64 rows before any has two
+int thin_num_partials(const Shape& s) { return (int)std::min<int64_t>(kThinMaxPartials, (s.n + 63) / 64); }
 
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg, const ReduceArgs* prev) {
+  if (nparts < 1 || nparts > kThinMaxPartials) return hipErrorInvalidValue;
   ThinArgs ta;
   std::memset(&ta, 0, sizeof(ta));
   ta.r = a;
   ta.partial = partial;
-  const int64_t chunks = (a.n + kThinThreads - 1) / kThinThreads;
-  ta.rows_per_wg = (int32_t)((chunks + nparts - 1) / nparts) * kThinThreads;
-  const bool with_cg = cg != nullptr;
-  if (with_cg) {
+  if (cg != nullptr) {
     // the pending update of a CG iteration on cached probabilities (or the line search's logits pass on the final iterate)
-    if (prev == nullptr || prev->partial == nullptr || prev->nparts < 1 || prev->d != (int64_t)a.p * a.NC) return hipErrorInvalidValue;
-    if (a.B0 != nullptr || (a.kind != kRowsHv && a.kind != kRowsLogits) || cg->dlen != prev->d || cg->st == nullptr) return hipErrorInvalidValue;
+    if (a.B0 != nullptr || !set_pending(&ta, *cg, prev, (int64_t)a.p * a.NC)) return hipErrorInvalidValue;
     if (prev->partial == partial) return hipErrorInvalidValue;  // the sweep reads the previous partials while it writes its own
-    ta.cg = *cg;
-    ta.prev = prev->partial;
-    ta.nprev = prev->nparts;
-    ta.scale = prev->scale;
-    ta.lambda = prev->lambda;
-    ta.rho = prev->rho;
-    ta.rho_scale = prev->rho_scale;
   }
-  const bool dense = thin_supported(Shape{a.n, a.p, a.NC, (int64_t)a.p * a.NC}, a.lda, a.A);
-  const Rows rows = dense ? kDense : ((a.lda & 3) == 0 ? kQuads : kBlock);
   switch ((a.lda + 3) >> 2) {
-    case 1: return launch_thin_nq<1>(ta, nparts, with_cg, rows, st);
-    case 2: return launch_thin_nq<2>(ta, nparts, with_cg, rows, st);
-    case 3: return launch_thin_nq<3>(ta, nparts, with_cg, rows, st);
-    case 4: return launch_thin_nq<4>(ta, nparts, with_cg, rows, st);
-    case 5: return launch_thin_nq<5>(ta, nparts, with_cg, rows, st);
-    case 6: return launch_thin_nq<6>(ta, nparts, with_cg, rows, st);
-    case 7: return launch_thin_nq<7>(ta, nparts, with_cg, rows, st);
-    case 8: return launch_thin_nq<8>(ta, nparts, with_cg, rows, st);
+    case 1: return launch_thin_nq<1>(ta, nparts, st);
+    case 2: return launch_thin_nq<2>(ta, nparts, st);
+    case 3: return launch_thin_nq<3>(ta, nparts, st);
+    case 4: return launch_thin_nq<4>(ta, nparts, st);
+    case 5: return launch_thin_nq<5>(ta, nparts, st);
+    case 6: return launch_thin_nq<6>(ta, nparts, st);
+    case 7: return launch_thin_nq<7>(ta, nparts, st);
+    case 8: return launch_thin_nq<8>(ta, nparts, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_thin_cg_finish(const CgPend& cg, const ReduceArgs& prev, hipStream_t st) {
+  ThinArgs ta;
+  std::memset(&ta, 0, sizeof(ta));
+  if (cg.final_p == 0 || !set_pending(&ta, cg, &prev, cg.dlen)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(thin_cg_finish_kernel, dim3(1), dim3(kFinishThreads), 0, st, ta);
+  return hipGetLastError();
 }
 
 }  // namespace nadmm

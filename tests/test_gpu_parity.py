@@ -722,6 +722,37 @@ def test_small_cg_with_few_iterations(n, p, C, k):
     assert st["cg_iters"] == [k, k]
 
 
+# The thin-data kernel's chunks of 64 rows dealt out to 256 workgroups of 8 or 16 waves: the last chunk full, of one row, one row more
+# than a chunk per workgroup and than one per wave; rows of quads and others; CG with its update in the next sweep, to the end and
+# stopped early; every call twice, bit for bit.
+@pytest.mark.parametrize("tol", [0.0, 3e-2])
+@pytest.mark.parametrize("n,p,C", [(2049, 29, 2), (2112, 32, 3), (16384, 20, 4), (16385, 13, 3), (131073, 31, 3), (262145, 28, 2), (262144, 7, 4)])
+def test_thin_chunks(n, p, C, tol):
+    w = workloads.generic(n, p, C, seed=n % 997 + p, x_std=0.5 / math.sqrt(p), mean=True)
+    gp, op = nadmm.Problem.from_workload(w), oracle_problem(w)
+    assert nadmm.nadmm_query_kernel_path(gp) == 3
+    X, V = dev(w.X0), dev(w.V)
+    loss, grad = nadmm.nadmm_loss_grad(gp, X)
+    f_ref, g_ref = orc.loss_grad(op, w.X0)
+    # float32 products and sums, of at most 3e5 terms in groups of a lane's, a wave's, a workgroup's and all workgroups'
+    assert rel_abs(loss.item(), f_ref) <= 1e-6 and rel_l2(host(grad), g_ref) <= 1e-6
+    hv = nadmm.nadmm_hessvec(gp, X, V)
+    assert rel_l2(host(hv), orc.hessvec(op, w.X0, w.V)) <= 1e-6
+    assert torch.equal(hv, nadmm.nadmm_hessvec(gp, X, V)) and torch.equal(grad, nadmm.nadmm_loss_grad(gp, X)[1])
+    g32 = g_ref.astype(np.float32)
+    got, it, relres = nadmm.nadmm_cg_solve(gp, X, dev(g32), 5, tol)
+    ref, it_ref, rel_ref = orc.cg(op, w.X0, g32.astype(np.float64), 5, tol)
+    assert it.item() == it_ref and rel_l2(host(got), ref) <= TOL_ITERATE
+    assert abs(relres.item() - rel_ref) <= 1e-5 + 1e-3 * rel_ref
+    assert torch.equal(got, nadmm.nadmm_cg_solve(gp, X, dev(g32), 5, tol)[0])
+    Xn = X.clone()
+    st = nadmm.nadmm_local_newton(gp, Xn, nadmm.make_params(2, 5, 10, cg_tol=tol))
+    w.max_newton, w.max_cg, w.cg_tol = 2, 5, tol
+    X_ref, st_ref, forced = oracle_newton_following(op, w.X0, w, st["alpha"])
+    assert rel_l2(host(Xn), X_ref) <= TOL_ITERATE
+    assert forced or st["cg_iters"] == [i["cg_iters"] for i in st_ref["iters"]]
+
+
 # The one launch of a small Newton solve: line searches that reduce their step (sum scaling, far from the minimiser), a row block of
 # which A starts on any 4-byte boundary, and the stopping test of Algorithm 3 before the first and between iterations.
 @pytest.mark.parametrize("shift", [0, 1])
