@@ -256,6 +256,9 @@ int choose_path(const Layout& L, int* path) {
 bool wide_sweep(const Layout& L, bool has_x, bool has_v) { return L.wide && wide_takes(L.s, has_x, has_v); }
 bool narrow_sweep(const Layout& L, bool has_x, bool has_v) { return L.narrow && L.s.NC > 16 && narrow_takes(L.s, has_x, has_v); }
 
+// Line search: whether the sweep over A evaluates the step sizes itself (kRowsSearch) instead of leaving the logits for a row kernel.
+bool sweep_evaluates(const Layout& L, int path, int ncand) { return path == 2 && !L.narrow && ncand <= kSweepCand; }
+
 // partial row losses that a sweep leaves (with_cols: one that also forms A^T rows)
 int loss_blocks(const Layout& L, int path, bool with_cols) {
   if (path == 4) return narrow_sweep(L, true, false) ? L.narrow_parts : (with_cols && wide_sweep(L, true, false) ? L.wide_parts : L.sliced_loss);
@@ -1038,38 +1041,51 @@ int nadmm_line_search(const nadmm_problem* prob, const float* d_X, const float* 
   if (path == 5 && (rc = sparse_plan(prob, L, d_ws, st)) != NADMM_OK) return rc;
   NADMM_HIP(launch_state_init(ds, nullptr, st));
 
-  RowArgs ra = blank_rows();
-  ra.kind = kRowsLogits;
-  ra.B0 = d_X;
-  ra.B1 = d_p;
-  ra.Z0out = at<float>(d_ws, L.zx);
-  ra.Z1out = at<float>(d_ws, L.zp);
-  int nparts = 0;
-  if ((rc = sweep(prob, L, path, d_ws, ra, false, &nparts, st)) != NADMM_OK) return rc;
-
   const int ncand = max_ls + 2;
   const bool need_f0 = std::isnan(loss_at_X);
-  LsEvalArgs le;
-  std::memset(&le, 0, sizeof(le));
-  le.Zx = at<float>(d_ws, L.zx);
-  le.Zp = at<float>(d_ws, L.zp);
-  le.labels = prob->d_labels;
-  le.n = prob->n;
-  le.NC = L.s.NC;
-  fill_alphas(le.alphas, ncand, gamma);
-  le.alphas[ncand] = 0.f;
-  le.ncand = ncand + (need_f0 ? 1 : 0);
-  le.lpart = at<double>(d_ws, L.lpart);
-  NADMM_HIP(launch_ls_eval(le, st));
+  const int neval = ncand + (need_f0 ? 1 : 0);
+  float alphas[kCandSlots];
+  fill_alphas(alphas, ncand, gamma);
+  alphas[ncand] = 0.f;
+  RowArgs ra = blank_rows();
+  ra.B0 = d_X;
+  ra.B1 = d_p;
+  int nparts = 0, nblocks = 0;
+  if (sweep_evaluates(L, path, neval)) {  // the sweep itself evaluates the step sizes
+    ra.kind = kRowsSearch;
+    ra.labels = prob->d_labels;
+    ra.lpart = at<double>(d_ws, L.lpart);
+    ra.ncand = neval;
+    std::copy(alphas, alphas + neval, ra.alphas);
+    if ((rc = sweep(prob, L, path, d_ws, ra, false, &nparts, st)) != NADMM_OK) return rc;
+    nblocks = nparts;
+  } else {
+    ra.kind = kRowsLogits;
+    ra.Z0out = at<float>(d_ws, L.zx);
+    ra.Z1out = at<float>(d_ws, L.zp);
+    if ((rc = sweep(prob, L, path, d_ws, ra, false, &nparts, st)) != NADMM_OK) return rc;
+    LsEvalArgs le;
+    std::memset(&le, 0, sizeof(le));
+    le.Zx = at<float>(d_ws, L.zx);
+    le.Zp = at<float>(d_ws, L.zp);
+    le.labels = prob->d_labels;
+    le.n = prob->n;
+    le.NC = L.s.NC;
+    std::copy(alphas, alphas + neval, le.alphas);
+    le.ncand = neval;
+    le.lpart = at<double>(d_ws, L.lpart);
+    NADMM_HIP(launch_ls_eval(le, st));
+    nblocks = ls_eval_blocks(prob->n);
+  }
 
   LsTailArgs lt;
   std::memset(&lt, 0, sizeof(lt));
   lt.st = ds;
-  lt.lpart = le.lpart;
-  lt.nblocks = ls_eval_blocks(prob->n);
+  lt.lpart = at<double>(d_ws, L.lpart);
+  lt.nblocks = nblocks;
   lt.ncand = ncand;
   lt.zero_slot = need_f0 ? ncand : -1;
-  std::memcpy(lt.alphas, le.alphas, sizeof(lt.alphas));
+  std::copy(alphas, alphas + neval, lt.alphas);
   lt.loss_at_X = loss_at_X;
   lt.use_state_loss = 0;
   lt.scale = prob->loss_scale;

@@ -20,6 +20,9 @@
 // A is read from HBM exactly once; the p x (C-1) accumulators stay in registers
 // for the whole row range and are written once as a per-workgroup partial.
 //
+// A line search (kRowsSearch) makes one pass with X and the direction; its rows stage also forms the row losses of all step sizes, 16
+// lanes per row again.  Logits to memory (8.6 MB at 60000 x 785, C = 10) and a row kernel on them took longer: 65.3 -> 56.5 us.
+//
 // Arithmetic: every fp32 operand is split into bf16 high and low parts
 // (x = hi + lo + O(2^-18 |x|)), and each product uses the three MFMA terms
 // hi*hi + hi*lo + lo*hi with fp32 accumulation (v_mfma_f32_16x16x32_bf16).
@@ -198,6 +201,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
   }
   if (deferred) lds_barrier();  // every wave has picked its operands from LDS: the step slots may be overwritten
 
+  const float my_alpha = KIND == kRowsSearch ? a.alphas[m < a.ncand ? m : 0] : 0.f;
   u32x4 dhi, dlo;  // D of the current tile as MFMA operand
   for (int64_t row0 = r_begin; row0 < r_end; row0 += th_rows) {
     // the row this wave handles in the rows stage: e = wave, row = row0 + 4 kg + (e & 3) + 16 (e >> 2)
@@ -206,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
     const int64_t my_rowc = my_valid ? my_row : tile_end(row0) - 1;
     float aux = 0.f;  // cached probability (Hessian-vector rows without X) or label (gradient / loss rows)
     if (KIND == kRowsHv && !has0) aux = a.Pin[(size_t)my_rowc * NC + mc];
-    if (KIND == kRowsGrad || KIND == kRowsLoss) aux = __int_as_float(a.labels[my_rowc]);
+    if (KIND == kRowsGrad || KIND == kRowsLoss || KIND == kRowsSearch) aux = __int_as_float(a.labels[my_rowc]);
 
     // ---------------- phase 1 ----------------
     f32x4 accZ[2], accW[2];
@@ -316,6 +320,44 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
       }
     }
     const size_t my_off = (size_t)my_row * NC + m;
+    if constexpr (KIND == kRowsSearch) {
+      // Row losses at z + alpha w for the step size of lane m: the 16 class lanes of a row hand their logits to the 16 step-size
+      // lanes through LDS (wave-private, 512 bytes).  One thread per (row, step size), as in the line search's own row kernel, but
+      // without 2 n (C-1) floats to memory and back.
+      float* zb = dbuf + wave * 128;
+      zb[lane] = z;
+      zb[64 + lane] = w;
+      tile_barrier();  // the partials have been read: what follows runs beside other waves' next tile
+      const f32x4* zq = reinterpret_cast<const f32x4*>(zb + 16 * kg);
+      const f32x4* wq = reinterpret_cast<const f32x4*>(zb + 64 + 16 * kg);
+      f32x4 zz[4];
+      float mx = 0.f, zl = 0.f;  // the reference class has logit 0
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (4 * q < NC) {  // uniform
+          const f32x4 z4 = zq[q], w4 = wq[q];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = fmaf(my_alpha, w4[e], z4[e]);
+            const bool real = 4 * q + e < NC;
+            zz[q][e] = v;
+            mx = real ? fmaxf(mx, v) : mx;
+            zl = (real && 4 * q + e == __float_as_int(aux)) ? v : zl;
+          }
+        }
+      }
+      float es = expf(-mx);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (4 * q < NC) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (4 * q + e < NC) es += expf(zz[q][e] - mx);
+        }
+      }
+      if (my_valid) loss_acc += (double)mx + (double)logf(es) - (double)zl;
+      continue;
+    }
     if (KIND == kRowsLogits) {
       if (cv && my_valid) {
         if (has0 && a.Z0out) a.Z0out[my_off] = z;
@@ -470,6 +512,19 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
       }
     }
   }
+  if constexpr (KIND == kRowsSearch) {  // the step sizes' sums: a wave's four rows, then the waves in order
+    double* red = reinterpret_cast<double*>(part);
+    loss_acc += __shfl_xor(loss_acc, 16, 64);
+    loss_acc += __shfl_xor(loss_acc, 32, 64);
+    __syncthreads();
+    if (lane < 16) red[wave * 16 + lane] = loss_acc;
+    __syncthreads();
+    if ((int)threadIdx.x < a.ncand) {
+      double t = 0.0;
+      for (int wv = 0; wv < kWaves; ++wv) t += red[wv * 16 + threadIdx.x];
+      a.lpart[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+    }
+  }
   if (KIND == kRowsGrad || KIND == kRowsLoss) {
     loss_acc = mfma_detail::wave64_sum(loss_acc);
     double* red = reinterpret_cast<double*>(dbuf);
@@ -522,7 +577,8 @@ template <int SPW, int KIND, bool HAS0, bool HAS1>
 hipError_t launch_one(const FusedArgs& fa, int grid, size_t lds_bytes, hipStream_t st) {
   const RowArgs& a = fa.r;
   const bool stores = KIND == kRowsLogits || a.Pout != nullptr || a.Z0out != nullptr || a.Z1out != nullptr;
-  if constexpr (!HAS0 && HAS1 && (KIND == kRowsHv || KIND == kRowsLogits)) {
+  if constexpr (KIND == kRowsSearch) return launch_k<SPW, KIND, HAS0, HAS1, false>(fa, grid, lds_bytes, st);
+  else if constexpr (!HAS0 && HAS1 && (KIND == kRowsHv || KIND == kRowsLogits)) {
     // the instantiation with the larger update capacity needs more registers in its prologue: it is taken only for a
     // pending CG update on vectors that do not fit the smaller one
     if (fa.cg.st == nullptr || (fa.cg.dlen >> 2) <= (int64_t)kThreads * SPW) {
@@ -555,6 +611,9 @@ hipError_t launch_spw(const FusedArgs& fa, int grid, size_t lds_bytes, hipStream
       if (h1) return launch_one<SPW, kRowsLogits, false, true>(fa, grid, lds_bytes, st);
       if (h0) return launch_one<SPW, kRowsLogits, true, false>(fa, grid, lds_bytes, st);
       return hipErrorInvalidValue;
+    case kRowsSearch:
+      if (!h0 || !h1 || a.labels == nullptr || a.lpart == nullptr || a.ncand < 1 || a.ncand > kSweepCand) return hipErrorInvalidValue;
+      return launch_one<SPW, kRowsSearch, true, true>(fa, grid, lds_bytes, st);
     default:
       return hipErrorInvalidValue;
   }
@@ -597,7 +656,7 @@ hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_
   // to even out.
   const int ntiles = (fa.rows_per_wg + kTileRows - 1) / kTileRows;
   fa.tile_rows = ntiles >= 4 ? (fa.rows_per_wg + ntiles - 1) / ntiles : kTileRows;
-  const size_t lds_bytes = (size_t)fa.steps * kStepBytes + kPartBytes + kSumBytes;
+  const size_t lds_bytes = (size_t)fa.steps * kStepBytes + kPartBytes + (a.kind == kRowsSearch ? 2 : 1) * kSumBytes;
   const int spw = (fa.steps + kWaves - 1) / kWaves;
   switch (spw) {
     case 1: return launch_spw<1>(fa, grid, lds_bytes, st);

@@ -82,7 +82,9 @@ struct __attribute__((packed, aligned(4))) Quad {
 //   kind 1  gradient rows:        R = P - Y, row losses                  (Sections 2.1, 2.2)
 //   kind 2  row losses only
 //   kind 3  logits only:          Z0 = A B0 and / or Z1 = A B1
-enum RowKind { kRowsHv = 0, kRowsGrad = 1, kRowsLoss = 2, kRowsLogits = 3 };
+//   kind 4  line search:          row losses at Z0 + alpha Z1 for every step size of `alphas` (no logits are stored)
+enum RowKind { kRowsHv = 0, kRowsGrad = 1, kRowsLoss = 2, kRowsLogits = 3, kRowsSearch = 4 };
+constexpr int kSweepCand = 16;  // step sizes that a sweep of kind 4 evaluates at most: one per class lane of the rows stage
 
 struct RowArgs {
   const float* A;
@@ -101,6 +103,9 @@ struct RowArgs {
   double* loss_part;   // per-workgroup partial sums of row losses (kinds 1, 2)
   int32_t kind;
   const int32_t* flag; // if non-NULL and *flag == 0 the kernel does nothing
+  double* lpart;       // kind 4: [step size][workgroup] partial sums of row losses
+  int32_t ncand;       // kind 4: step sizes, at most kSweepCand
+  float alphas[kSweepCand];
 };
 
 // A CG update (Section 2.4) that has not been applied yet, handed to the kernel that needs its result: the

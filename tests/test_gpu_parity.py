@@ -204,6 +204,25 @@ def test_line_search(cache, name, path):
             assert rel_abs(f_new.item(), f_ref) <= TOL_PRIMITIVE
 
 
+# The line search evaluated by the sweep itself (kernel path 2, up to 16 step sizes with the one for F(X)) and, from 17 on, by a kernel
+# on stored logits: one and several tiles of 32 rows with remainders, one and several column steps, 1, 9 and 16 class lanes, any stride.
+@pytest.mark.parametrize("n,p,C", [(1, 20, 2), (33, 129, 10), (8193, 260, 10), (8450, 785, 17), (300, 960, 3), (9001, 100, 17)])
+def test_line_search_in_the_sweep(n, p, C):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    gp, op = nadmm.Problem.from_workload(w), oracle_problem(w)
+    force_path(gp, 2)
+    f0, g = orc.loss(op, w.X0), orc.grad(op, w.X0)
+    g32 = g.astype(np.float32)
+    for scale, max_ls in ((1.0, 10), (40.0, 13), (40.0, 14), (4000.0, 15), (-1.0, 13), (-1.0, 0)):
+        pdir = (-scale * g).astype(np.float32)
+        a_ref, f_ref, ok_ref, _ = orc.line_search(op, w.X0, pdir, g32, 1e-4, 0.5, max_ls)
+        for given in (math.nan, f0):
+            alpha, f_new, ok = nadmm.nadmm_line_search(gp, dev(w.X0), dev(pdir), dev(g32), given, 1e-4, 0.5, max_ls)
+            assert alpha.item() == a_ref and bool(ok.item()) == ok_ref
+            # the product A p takes three terms (relative error below 4 * 2^-17), and the losses here are mostly the step's own logits
+            assert rel_abs(f_new.item(), f_ref) <= 4 * 2.0 ** -17
+
+
 NEWTON_CASES = ["tiny", "image_like_3k", "wide_700", "tall_binary_50k", "large_multiclass_900", "ragged_1237x45_C5",
                 "fused_any_3000x785_C10", "sliced_any_700x1101_C4",
                 "single_row_1x7_C4", "fused_9001x260_C10", "fused_4100x36_C17", "thin_70001x32_C3", "thin_300x12_C4", "sliced_3000x100_C26",
