@@ -991,8 +991,7 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   }
   if (path == 5 && (rc = sparse_plan(prob, L, d_ws, st)) != NADMM_OK) return rc;
 
-  NADMM_HIP(launch_state_init(ds, nullptr, st));
-  NewtonHeadArgs nh;
+  NewtonHeadArgs nh;  // sets every field of the state that a CG solve reads
   std::memset(&nh, 0, sizeof(nh));
   nh.st = ds;
   nh.g = d_g;
@@ -1010,8 +1009,16 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   }
   const bool pend = (cg_deferred(path) || thin_deferred(path)) && max_iter > 0;
   if (pend) {
-    const CgPend c = cg_pend(L, d_ws, ds, (max_iter - 1) & 1, true, tol);
+    CgPend c = cg_pend(L, d_ws, ds, (max_iter - 1) & 1, true, tol);
+    // the last update leaves the iterate where the caller wants it (its 16-byte stores need an aligned vector)
+    const bool direct = thin_deferred(path) || (reinterpret_cast<uintptr_t>(d_p) & 15) == 0;
+    if (direct) {
+      c.p_final = d_p;
+      c.iters_out = d_iters;
+      c.relres_out = d_relres;
+    }
     NADMM_HIP(thin_deferred(path) ? launch_thin_cg_finish(c, thin_prev(prob, L, d_ws, max_iter - 1), st) : launch_cg_pending_finish(c, st));
+    if (direct) return NADMM_OK;
   }
   CgFinishArgs cf;
   cf.st = ds;
@@ -1037,9 +1044,8 @@ int nadmm_line_search(const nadmm_problem* prob, const float* d_X, const float* 
   int path = 0;
   if ((rc = choose_path(L, &path)) != NADMM_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
-  DevState* ds = at<DevState>(d_ws, L.state);
+  DevState* ds = at<DevState>(d_ws, L.state);  // written only: nothing here reads the state
   if (path == 5 && (rc = sparse_plan(prob, L, d_ws, st)) != NADMM_OK) return rc;
-  NADMM_HIP(launch_state_init(ds, nullptr, st));
 
   const int ncand = max_ls + 2;
   const bool need_f0 = std::isnan(loss_at_X);

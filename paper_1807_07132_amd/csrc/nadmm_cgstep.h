@@ -161,6 +161,12 @@ __device__ __forceinline__ bool cg_pending_update(const CgPend& c, bool writer, 
   return want_p || out.active != 0;
 }
 
+// The results of a CG solve whose last update a kernel has just applied, by the thread that wrote the state.
+__device__ __forceinline__ void cg_solve_results(const CgPend& c) {
+  if (c.iters_out != nullptr) *c.iters_out = c.st->cg_iters;
+  if (c.relres_out != nullptr) *c.relres_out = c.st->gg_cg > 0.0 ? (float)sqrt(c.st->rr / c.st->gg_cg) : 0.f;
+}
+
 // The scalars of a pending update alone, for a kernel whose workgroups all need the step length of the last CG
 // iteration (identical arithmetic in every workgroup): <d, q> from its partial sums in a fixed order, a = rr / <d, q>.
 struct CgPendScalars {

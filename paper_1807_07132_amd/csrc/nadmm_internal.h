@@ -126,6 +126,8 @@ struct CgPend {
   float tol;
   float* p_final;        // final_p: workgroup 0 leaves the iterate here and copies the state to the scalars of DevState
   int64_t dlen;
+  int32_t* iters_out;    // the kernels that end a stand-alone CG solve, optional: its results
+  float* relres_out;
 };
 
 // Column-pass (transpose product) description: partial[k] = (rows of chunk k of A)^T rows_in

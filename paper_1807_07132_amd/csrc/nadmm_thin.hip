@@ -210,6 +210,7 @@ constexpr int kFinishThreads = 1024;
 __global__ __launch_bounds__(kFinishThreads) void thin_cg_finish_kernel(const ThinArgs ta) {
   bool go;
   cg_from_partials<kFinishThreads>(ta, threadIdx.x < 64, &go, [] {});
+  if (threadIdx.x == 0) cg_solve_results(ta.cg);
 }
 
 typedef __attribute__((address_space(1))) const void gvoid;

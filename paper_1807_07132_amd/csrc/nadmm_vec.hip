@@ -359,15 +359,17 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a) {
   if (a.gg_part != nullptr) {
     gg = partial_sum_block(a.gg_part, a.npart, sm);  // the reduction has written p, r, d already
   } else {
-    for (int64_t e0 = threadIdx.x; e0 < a.d; e0 += (int64_t)kBlk * blockDim.x) {
-      float gv[kBlk];
+    constexpr int U = 16;  // loads of a thread in flight
+    for (int64_t e0 = threadIdx.x; e0 < a.d; e0 += (int64_t)U * blockDim.x) {
+      float gv[U];
 #pragma unroll
-      for (int u = 0; u < kBlk; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int64_t e = e0 + (int64_t)u * blockDim.x;
-        gv[u] = e < a.d ? a.g[e] : 0.f;
+        const float v = a.g[e < a.d ? e : a.d - 1];
+        gv[u] = e < a.d ? v : 0.f;
       }
 #pragma unroll
-      for (int u = 0; u < kBlk; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int64_t e = e0 + (int64_t)u * blockDim.x;
         gg += (double)gv[u] * (double)gv[u];
         if (e < a.d) {
@@ -648,6 +650,7 @@ constexpr int kPendPer = 8;   // quads per thread: the fused single-pass path ha
 __global__ __launch_bounds__(kPendThreads) void cg_pending_finish_kernel(const CgPend c) {
   __shared__ double sm[kPendThreads / 64 + 1];
   cg_pending_update<kPendThreads, kPendPer>(c, true, c.p_final, sm, [] {});
+  if (threadIdx.x == 0) cg_solve_results(c);
 }
 
 __global__ __launch_bounds__(256) void cg_finish_kernel(const CgFinishArgs a) {
