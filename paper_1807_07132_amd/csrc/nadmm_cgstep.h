@@ -16,11 +16,11 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// sm: THREADS / 64 doubles that no thread still reads from an earlier use
 template <int THREADS>
-__device__ __forceinline__ double cg_block_sum(double v, double* sm /* THREADS / 64 + 1 doubles */) {
+__device__ __forceinline__ double cg_block_sum(double v, double* sm) {
   v = mfma_detail::wave64_sum(v);  // rotations inside rows of 16 lanes, the four row totals in a fixed order
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  lds_barrier();  // previous users of sm are done
   if (lane == 0) sm[wave] = v;
   lds_barrier();
   double t = 0.0;
@@ -32,7 +32,7 @@ __device__ __forceinline__ double cg_block_sum(double v, double* sm /* THREADS /
 // Leaves the vector the caller wants (d', or p' if c.final_p) in vec[0 .. dlen) (LDS or global, 16-byte aligned;
 // complete and visible to the whole workgroup on return).  Returns false if the caller wants d and CG is, or has
 // just become, inactive: there is no product left to form.  dlen <= 4 THREADS * PERQ, ndot <= THREADS, the vectors
-// of CgPend 16-byte aligned.  `sm`: THREADS / 64 + 1 doubles of LDS.
+// of CgPend 16-byte aligned.  `sm`: 2 THREADS / 64 doubles of LDS that nothing else uses meanwhile.
 // `writer`: this workgroup stores the new vectors and the new state (workgroup 0 of the kernel).
 // Every load the update needs is issued up front into registers, as few 16-byte loads per thread, then
 // `after_issue()` runs (the caller starts its own first loads there, in flight right behind the vectors: loads
@@ -100,8 +100,9 @@ __device__ __forceinline__ bool cg_pending_update(const CgPend& c, bool writer, 
       }
       tr = fmaf(-al, tq, tr);
       if (tail) acc += (double)tr * (double)tr;
-      const double rr_new = cg_block_sum<THREADS>(acc, sm);
-      const bool stop = sqrt(rr_new) <= (double)c.tol * sqrt(gg);
+      const double rr_new = cg_block_sum<THREADS>(acc, sm + THREADS / 64);
+      // a tolerance of 0 is met by a zero residual only: no square roots in the chain
+      const bool stop = c.tol > 0.f ? sqrt(rr_new) <= (double)c.tol * sqrt(gg) : rr_new == 0.0;
       be = (float)(rr_new / in.rr);
       out.rr = rr_new;
       out.iters = in.iters + 1;
@@ -237,7 +238,7 @@ __device__ __forceinline__ void cg_pending_final_walk(const CgPend& c, double* s
     }
     c.p_final[e] = pn;
   }
-  const double rr_new = cg_block_sum<THREADS>(acc, sm);
+  const double rr_new = cg_block_sum<THREADS>(acc, sm + THREADS / 64);
   if (threadIdx.x == 0) {
     CgSlot out = s.in;
     if (s.updated) {

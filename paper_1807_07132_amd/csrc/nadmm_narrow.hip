@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads, 2) void narrow_kernel(const NarrowArgs na
   constexpr int kWaveLds = wave_lds_bytes(S, RT, NB);
   constexpr int kTile = 16 * RT;             // rows of a wave's round
   __shared__ __attribute__((aligned(16))) char lds[kWaves * kWaveLds];
-  __shared__ double red[kWaves + 1];
+  __shared__ double red[2 * kWaves];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = lane & 15, kg = lane >> 4;

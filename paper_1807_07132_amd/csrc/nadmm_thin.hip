@@ -180,7 +180,8 @@ __device__ __forceinline__ float cg_from_partials(const ThinArgs& ta, bool write
       out.rr = rr_new;
       out.iters = in.iters + 1;
       out.cur = cur ^ 1;
-      if (sqrt(rr_new) <= (double)c.tol * sqrt(gg)) out.active = 0;
+      // a tolerance of 0 is met by a zero residual only: no square roots in the chain
+      if (c.tol > 0.f ? sqrt(rr_new) <= (double)c.tol * sqrt(gg) : rr_new == 0.0) out.active = 0;
       updated = true;
     }
   }

@@ -648,7 +648,7 @@ __global__ __launch_bounds__(kTail) void cg_reduce_update_kernel(const ReduceArg
 constexpr int kPendThreads = 512;
 constexpr int kPendPer = 8;   // quads per thread: the fused single-pass path has p (C-1) <= 960 * 16 <= 4 * 512 * 8
 __global__ __launch_bounds__(kPendThreads) void cg_pending_finish_kernel(const CgPend c) {
-  __shared__ double sm[kPendThreads / 64 + 1];
+  __shared__ double sm[2 * (kPendThreads / 64)];
   cg_pending_update<kPendThreads, kPendPer>(c, true, c.p_final, sm, [] {});
   if (threadIdx.x == 0) cg_solve_results(c);
 }
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(256) void ls_eval_kernel(const LsEvalArgs a) {
   const int wg = blockIdx.x - role0, nwg = gridDim.x - role0;
   float hal[NK > 0 ? NK : 1];
   if (NK > 0) {
-    __shared__ double smd[256 / 64 + 1];
+    __shared__ double smd[2 * (256 / 64)];
     if (role0 != 0 && blockIdx.x == 0) {
       cg_pending_final_walk<256>(a.pend, smd);
       return;
