@@ -30,7 +30,7 @@ constexpr int kSlotBytes = 3072;  // one step of a tile of 16 rows: high, middle
 struct NarrowArgs {
   RowArgs r;
   float* partial;       // gridDim.x x (p*NC), or NULL (no transpose product)
-  int32_t rows_per_wg;  // multiple of the rows of one round of the workgroup's waves
+  int32_t rounds, more; // rounds of a workgroup (a tile for each of its waves); the first `more` workgroups make one more
   CgPend cg;            // cg.st != NULL: the operand B1 is the result of a pending CG update (kernels without B0 only)
 };
 
@@ -56,8 +56,9 @@ __global__ __launch_bounds__(kThreads, 2) void narrow_kernel(const NarrowArgs na
   char* slots = lds + wave * kWaveLds;
   const int col_max = ANY ? p - 4 : ((p + 3) & ~3) - 4;  // the last column a 16-byte piece is fetched from
 
-  const int64_t r_begin = (int64_t)blockIdx.x * na.rows_per_wg;
-  int64_t r_end = r_begin + na.rows_per_wg;
+  const int wg = blockIdx.x;
+  const int64_t r_begin = ((int64_t)wg * na.rounds + (wg < na.more ? wg : na.more)) * (kWaves * kTile);
+  int64_t r_end = r_begin + (int64_t)(na.rounds + (wg < na.more ? 1 : 0)) * (kWaves * kTile);
   if (r_end > a.n) r_end = a.n;
 
   // ---- rows of A, RT tiles of 16; a step's columns lie in the k-slots as two pieces of four, so that the four lanes of a
@@ -423,11 +424,17 @@ int64_t narrow_min_rows(int32_t p) { return steps_of(p) <= 2 ? 32768 : 49152; }
 // Two blocks of classes: X and V together fit the registers up to two steps only (else two sweeps).
 bool narrow_takes(const Shape& s, bool has_x, bool has_v) { return s.NC <= 16 || s.p <= 2 * kStepCols || !(has_x && has_v); }
 
+// Workgroups: two per compute unit, each with equally many rounds of its waves as far as that goes with fewer of them; with 3 to 8
+// rounds each, 512 of which some make a round less, since then the compute units that had a single one count: 100000 x 70, C = 7,
+// Hessian-vector product 18.9 -> 16.9 us, 10 CG iterations 184 -> 172 us (391 workgroups of 4 rounds before); 150000 x 64, C = 7:
+// 19.8 -> 17.2 us.  With 2 rounds the larger number of partial sums costs what it gains (50000 x 70: 14.7 : 14.9), beyond 8 equal.
+// More than 16 free classes stay: their scratch is close to what nadmm_hessvec_static holds.
 int narrow_num_partials(const Shape& s) {
   const int64_t round = (int64_t)kWaves * 16 * tiles_of(steps_of(s.p), s.NC > 16 ? 2 : 1);
   const int64_t rounds = (s.n + round - 1) / round;
   const int64_t g = rounds < 512 ? rounds : 512;
   const int64_t per = (rounds + g - 1) / g;
+  if (s.NC <= 16 && per >= 3 && per <= 8) return 512;
   return (int)((rounds + per - 1) / per);
 }
 
@@ -445,7 +452,8 @@ hipError_t launch_narrow(const RowArgs& a, float* partial, int nparts, hipStream
   const int steps = steps_of(a.p);
   const int64_t round = (int64_t)kWaves * 16 * tiles_of(steps, a.NC > 16 ? 2 : 1);
   const int64_t rounds = (a.n + round - 1) / round;
-  na.rows_per_wg = (int32_t)((rounds + nparts - 1) / nparts * round);
+  na.rounds = (int32_t)(rounds / nparts);
+  na.more = (int32_t)(rounds % nparts);
   if (a.NC <= 16) {
     switch (steps) {
       case 1: return launch_steps<1, 1>(na, nparts, st);

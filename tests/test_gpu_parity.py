@@ -741,6 +741,21 @@ def test_small_cg_with_few_iterations(n, p, C, k):
     assert st["cg_iters"] == [k, k]
 
 
+# Rounds of the kernel for narrow rows dealt out to its workgroups: the last counts before and the first with 512 uneven ones (3 to 8
+# rounds of 256, 128 and 64 rows), one row more than a whole number of rounds, one row less, the first count past 8.
+@pytest.mark.parametrize("n,p,C", [(65536, 100, 3), (65537, 100, 3), (98305, 70, 17), (131071, 65, 4), (131073, 40, 3), (262145, 9, 6), (262145, 70, 3)])
+def test_narrow_rounds(n, p, C):
+    w = workloads.generic(n, p, C, seed=n % 991 + p, x_std=0.5 / math.sqrt(p), mean=True)
+    gp, op = nadmm.Problem.from_workload(w), oracle_problem(w)
+    X, V = dev(w.X0), dev(w.V)
+    loss, grad = nadmm.nadmm_loss_grad(gp, X)
+    f_ref, g_ref = orc.loss_grad(op, w.X0)
+    assert rel_abs(loss.item(), f_ref) <= 1e-6 and rel_l2(host(grad), g_ref) <= FLOAT32_ACCURACY
+    hv = nadmm.nadmm_hessvec(gp, X, V)
+    assert rel_l2(host(hv), orc.hessvec(op, w.X0, w.V)) <= FLOAT32_ACCURACY
+    assert torch.equal(hv, nadmm.nadmm_hessvec(gp, X, V))
+
+
 # The thin-data kernel's chunks of 64 rows dealt out to 256 workgroups of 8 or 16 waves: the last chunk full, of one row, one row more
 # than a chunk per workgroup and than one per wave; rows of quads and others; CG with its update in the next sweep, to the end and
 # stopped early; every call twice, bit for bit.
