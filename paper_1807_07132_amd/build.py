@@ -14,7 +14,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnadmm.so")
 
-SOURCES = ["nadmm_api.hip", "nadmm_generic.hip", "nadmm_vec.hip", "nadmm_fused.hip", "nadmm_thin.hip", "nadmm_sliced.hip",
+SOURCES = ["nadmm_api.hip", "nadmm_generic.hip", "nadmm_vec.hip", "nadmm_fused.hip", "nadmm_thin.hip", "nadmm_thin_block.hip", "nadmm_sliced.hip",
            "nadmm_wide.hip", "nadmm_narrow.hip", "nadmm_small.hip", "nadmm_admm.hip", "nadmm_sparse.hip"]
 
 FLAGS = [

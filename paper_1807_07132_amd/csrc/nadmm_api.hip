@@ -257,7 +257,7 @@ bool wide_sweep(const Layout& L, bool has_x, bool has_v) { return L.wide && wide
 bool narrow_sweep(const Layout& L, bool has_x, bool has_v) { return L.narrow && L.s.NC > 16 && narrow_takes(L.s, has_x, has_v); }
 
 // Line search: whether the sweep over A evaluates the step sizes itself (kRowsSearch) instead of leaving the logits for a row kernel.
-bool sweep_evaluates(const Layout& L, int path, int ncand) { return path == 2 && !L.narrow && ncand <= kSweepCand; }
+bool sweep_evaluates(const Layout& L, int path, int ncand) { return ((path == 2 && !L.narrow) || path == 3) && ncand <= kSweepCand; }
 
 // partial row losses that a sweep leaves (with_cols: one that also forms A^T rows)
 int loss_blocks(const Layout& L, int path, bool with_cols) {
@@ -699,6 +699,15 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     rz.B1 = pstep;
     rz.Z1out = at<float>(d_ws, L.zp);
     rz.flag = &ds->newton_active;
+    const bool in_sweep = thin_def && sweep_evaluates(L, path, ncand);  // the pass that forms A p evaluates the step sizes
+    if (in_sweep) {
+      rz.kind = kRowsSearch;
+      rz.Pin = at<float>(d_ws, L.zx);
+      rz.labels = prob->d_labels;
+      rz.lpart = at<double>(d_ws, L.lpart);
+      rz.ncand = ncand;
+      fill_alphas(rz.alphas, ncand, params->backtrack_gamma);
+    }
     const bool eval_finishes = hist && ls_eval_takes_pending(prob->n);  // the row kernel of the line search applies the last update
     if (hist) {  // A p comes from the history; the last update alone, unless the line search's row kernel takes it along
       if (!eval_finishes)
@@ -734,13 +743,13 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     le.ncand = ncand;
     le.lpart = at<double>(d_ws, L.lpart);
     le.flag = &ds->newton_active;
-    NADMM_HIP(launch_ls_eval(le, st));
+    if (!in_sweep) NADMM_HIP(launch_ls_eval(le, st));
 
     LsTailArgs lt;
     std::memset(&lt, 0, sizeof(lt));
     lt.st = ds;
     lt.lpart = le.lpart;
-    lt.nblocks = ls_eval_blocks(prob->n);
+    lt.nblocks = in_sweep ? nparts : ls_eval_blocks(prob->n);
     lt.ncand = ncand;
     lt.zero_slot = -1;
     std::memcpy(lt.alphas, le.alphas, sizeof(lt.alphas));

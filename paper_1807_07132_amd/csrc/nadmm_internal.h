@@ -95,7 +95,7 @@ struct RowArgs {
   const float* B0;     // p x NC, operand of the logits Z = A B0 (X); NULL if P comes from Pin
   const float* B1;     // p x NC, operand of the directional logits W = A B1 (V or p); may be NULL
   const int32_t* labels;
-  const float* Pin;    // n x NC cached probabilities (kind 0 with B0 == NULL)
+  const float* Pin;    // n x NC, with B0 == NULL: cached probabilities (kind 0) or logits A X (kind 4)
   float* rows_out;     // n x NC: D (kind 0) or R (kind 1); may be NULL
   float* Pout;         // n x NC: probabilities, optional
   float* Z0out;        // n x NC: logits A B0, optional

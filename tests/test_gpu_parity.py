@@ -204,13 +204,15 @@ def test_line_search(cache, name, path):
             assert rel_abs(f_new.item(), f_ref) <= TOL_PRIMITIVE
 
 
-# The line search evaluated by the sweep itself (kernel path 2, up to 16 step sizes with the one for F(X)) and, from 17 on, by a kernel
-# on stored logits: one and several tiles of 32 rows with remainders, one and several column steps, 1, 9 and 16 class lanes, any stride.
-@pytest.mark.parametrize("n,p,C", [(1, 20, 2), (33, 129, 10), (8193, 260, 10), (8450, 785, 17), (300, 960, 3), (9001, 100, 17)])
-def test_line_search_in_the_sweep(n, p, C):
+# The line search evaluated by the sweep itself (up to 16 step sizes with the one for F(X)) and, from 17 on, by a kernel on stored
+# logits.  Path 2: one and several tiles of 32 rows with remainders, one and several column steps, 1, 9 and 16 class lanes, any stride.
+# Path 3: part of a chunk of 64 rows, one and several chunks per wave, rows of quads and others, 1 to 3 free classes.
+@pytest.mark.parametrize("n,p,C,path", [(1, 20, 2, 2), (33, 129, 10, 2), (8193, 260, 10, 2), (8450, 785, 17, 2), (300, 960, 3, 2), (9001, 100, 17, 2),
+                                        (50, 8, 2, 3), (2049, 29, 2, 3), (16385, 7, 4, 3), (70001, 32, 2, 3), (262209, 20, 4, 3)])
+def test_line_search_in_the_sweep(n, p, C, path):
     w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
     gp, op = nadmm.Problem.from_workload(w), oracle_problem(w)
-    force_path(gp, 2)
+    force_path(gp, path)
     f0, g = orc.loss(op, w.X0), orc.grad(op, w.X0)
     g32 = g.astype(np.float32)
     for scale, max_ls in ((1.0, 10), (40.0, 13), (40.0, 14), (4000.0, 15), (-1.0, 13), (-1.0, 0)):
@@ -221,6 +223,11 @@ def test_line_search_in_the_sweep(n, p, C):
             assert alpha.item() == a_ref and bool(ok.item()) == ok_ref
             # the product A p takes three terms (relative error below 4 * 2^-17), and the losses here are mostly the step's own logits
             assert rel_abs(f_new.item(), f_ref) <= 4 * 2.0 ** -17
+    for max_ls in (13, 15):  # a Newton iteration with as many step sizes as the pass that forms A p evaluates, and with two more
+        X = dev(w.X0)
+        st = nadmm.nadmm_local_newton(gp, X, nadmm.make_params(2, 3, max_ls))
+        w.max_newton, w.max_cg, w.max_ls = 2, 3, max_ls
+        assert rel_l2(host(X), oracle_newton_following(op, w.X0, w, st["alpha"])[0]) <= TOL_ITERATE
 
 
 NEWTON_CASES = ["tiny", "image_like_3k", "wide_700", "tall_binary_50k", "large_multiclass_900", "ragged_1237x45_C5",
