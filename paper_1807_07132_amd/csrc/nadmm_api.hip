@@ -287,9 +287,9 @@ int sparse_plan(const nadmm_problem* prob, const Layout& L, void* ws, hipStream_
 // previous sweep's partial sums, which that kernel adds up itself, and partial_out where this sweep's go.
 int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArgs ra, bool with_cols,
           int* nparts, hipStream_t st, const CgPend* cg = nullptr, const ReduceArgs* prev = nullptr,
-          float* partial_out = nullptr, bool packed = false) {
+          float* partial_out = nullptr, bool packed = false, const NewtonHeadArgs* head = nullptr) {
   if (cg != nullptr && path != 2 && path != 3) return NADMM_EINVAL;
-  if ((prev != nullptr || partial_out != nullptr) && path != 3) return NADMM_EINVAL;
+  if ((prev != nullptr || partial_out != nullptr || head != nullptr) && path != 3) return NADMM_EINVAL;
   ra.A = prob->d_A;
   ra.n = prob->n;
   ra.p = prob->p;
@@ -348,7 +348,7 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
   }
   if (path == 3) {
     float* pout = partial_out != nullptr ? partial_out : at<float>(ws, L.partial);
-    NADMM_HIP(launch_thin(ra, with_cols ? pout : nullptr, L.thin_parts, st, cg, prev));
+    NADMM_HIP(launch_thin(ra, with_cols ? pout : nullptr, L.thin_parts, st, cg, prev, head));
     *nparts = L.thin_parts;
     return NADMM_OK;
   }
@@ -508,6 +508,11 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
     ra.Pout = (X && write_pcache) ? at<float>(ws, L.pcache) : nullptr;
     ra.rows_out = at<float>(ws, L.drows);
     int nparts = 0;
+    if (k == 0 && head != nullptr) {  // the gradient's sweep wrote the other buffer (local_newton_enqueue)
+      ra.flag = &ds->newton_active;
+      const ReduceArgs prev = thin_prev(prob, L, ws, 1);
+      return sweep(prob, L, path, ws, ra, true, &nparts, st, nullptr, &prev, thin_partial(L, ws, 0), false, head);
+    }
     if (k == 0) {
       ra.flag = &ds->cgs[0].active;
       return sweep(prob, L, path, ws, ra, true, &nparts, st, nullptr, nullptr, thin_partial(L, ws, 0));
@@ -639,9 +644,12 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     ra.Z0out = at<float>(d_ws, L.zx);
     ra.loss_part = at<double>(d_ws, L.loss_part);
     ra.flag = &ds->newton_active;
+    // thin-data path: the gradient's reduction and the head of the iteration are made by the first sweep of the CG solve
+    const bool thin_def = thin_deferred(path) && params->max_cg >= 1;
     int nparts = 0;
-    if ((rc = sweep(prob, L, path, d_ws, ra, true, &nparts, st)) != NADMM_OK) return rc;
-    {
+    if ((rc = sweep(prob, L, path, d_ws, ra, true, &nparts, st, nullptr, nullptr, thin_def ? thin_partial(L, d_ws, 1) : nullptr)) != NADMM_OK)
+      return rc;
+    if (!thin_def) {
       // gradient; the same kernel leaves the partial sums of the penalty terms and of ||g||^2 and starts CG (p = 0, r = d = -g)
       ReduceArgs rg = reduce_args(prob, L, d_ws, nparts, 1, d_X, g, nullptr, &ds->newton_active);
       rg.pen_part = at<double>(d_ws, L.headpart);
@@ -664,6 +672,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     nh.z = prob->d_z;
     nh.y = prob->d_y;
     nh.g = g;
+    nh.g_out = g;
     nh.pdir = pdir;
     nh.r = r;
     nh.dvec = dvec;
@@ -677,16 +686,15 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     nh.rho_scale = L.rho_scale;
     // on the fused path the head is one more workgroup of the first CG iteration's reduction instead of a launch of its own
     const bool head_in_reduce = cg_deferred(path) && params->max_cg >= 1 && L.s.d <= kReduceFinishMax;
-    if (!head_in_reduce) NADMM_HIP(launch_newton_head(nh, st));
+    if (!head_in_reduce && !thin_def) NADMM_HIP(launch_newton_head(nh, st));
 
     // CG on H p = -g with the probabilities of this iterate
-    const bool thin_def = thin_deferred(path) && params->max_cg >= 1;
     const bool hist = use_hist && cg_deferred(path) && params->max_cg >= 1 && params->max_cg <= L.hist_bufs;
     const size_t hist_stride = align256((size_t)L.s.n * L.s.NC * sizeof(float)) / sizeof(float);
     for (int k = 0; k < params->max_cg; ++k) {
       float* w_rows = hist ? at<float>(d_ws, L.hist) + (size_t)k * hist_stride : nullptr;
       if ((rc = cg_iteration(prob, L, path, d_ws, ds, nullptr, false, params->cg_tol, k, st, w_rows,
-                             (k == 0 && head_in_reduce) ? &nh : nullptr, thin_def)) != NADMM_OK)
+                             (k == 0 && (head_in_reduce || thin_def)) ? &nh : nullptr, thin_def)) != NADMM_OK)
         return rc;
     }
 

@@ -169,6 +169,7 @@ struct NewtonHeadArgs {
   const float* z;
   const float* y;
   const float* g;
+  float* g_out;        // launch_thin with head: where the gradient is left (g is not read then)
   float* pdir;
   float* r;
   float* dvec;
@@ -365,7 +366,7 @@ int thin_num_partials(const Shape& s);
 // cg, prev (both or neither): the sweep first applies the pending CG update, forming q = H d from the previous sweep's
 // partial sums prev->partial (prev also carries scale, lambda, rho of the linear terms); see ThinArgs in nadmm_thin.hip
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
-                       const ReduceArgs* prev = nullptr);
+                       const ReduceArgs* prev = nullptr, const NewtonHeadArgs* head = nullptr);
 // the pending update alone (one workgroup): end of a stand-alone CG solve
 hipError_t launch_thin_cg_finish(const CgPend& cg, const ReduceArgs& prev, hipStream_t st);
 

@@ -10,6 +10,8 @@
 // workgroup once, at the end, in a fixed order.
 // In a CG solve the sweep of iteration k also does what lies between two sweeps (Section 2.4): it adds up the partial sums of
 // sweep k - 1, forms q = H d and applies the CG update before it reads its operand (kHvCg, kLogitsCg, kSearchCg).
+// The first sweep of a Newton iteration's CG solve makes the gradient's reduction and the head of the iteration the same way (kHvHead):
+// two Newton iterations of 6 CG iterations at 100000 x 28, C = 2: 149 -> 137 us.
 // A line search evaluates its step sizes in the pass that forms A p (kSearch, kSearchCg): a lane has its row's logits in registers, and
 // the exponentials run beside the stream.  Against logits to memory and a row kernel on them: line search at 1400000 x 28, C = 2:
 // 56.4 -> 42.8 us, 10 x 10 iterations at 1375000 x 28: 3703 -> 3516 us; 2500 rows equal.
@@ -34,6 +36,9 @@ struct ThinArgs {
   // Section 2.4 and takes its operand, the new direction (or, for the line search's pass, the final iterate), from there;
   // workgroup 0 stores the new vectors and state.  No reduction kernel and no CG kernel run between two sweeps.
   CgPend cg;           // cg.q and cg.dot_part are not used: this kernel forms both itself
+  // kHvHead: the first sweep of a CG solve inside a Newton iteration.  The gradient's sweep left its partial sums only; every workgroup
+  // forms g from them, workgroup 0 stores g and what newton_head_kernel leaves, and the operand is the first direction -g.
+  NewtonHeadArgs head;
   const float* prev;   // the previous sweep's partial sums, nprev x (p*NC)
   int32_t nprev;
   float scale, lambda, rho;
@@ -129,27 +134,49 @@ __device__ __forceinline__ void thin_row(const RowArgs& a, bool has0, bool has1,
   }
 }
 
-// q = H d and the pending CG update (CgPend, Section 2.4) from the previous sweep's partial sums.  Lane e of wave w adds element e of
-// the partials w, w + W, ... (all requested at once, together with both sets of vectors, so that nothing waits to learn which set is
-// current); behind one barrier every wave adds up the waves' sums and makes the update for itself, one element of the vectors per
-// lane.  (By the whole workgroup, as for longer vectors, it took five barriers: 1.3 us more per CG iteration at 2500 to 40000 rows.)
+// Sum over the partials of element e = lane: lane e of wave w adds those of w, w + W, ... (requested by request(), all at once), and
+// behind one barrier every wave adds up the waves' sums.
+template <int THREADS>
+struct PartialSum {
+  static constexpr int W = THREADS / 64, U = kThinMaxPartials / W;
+  float part[U];
+  __device__ __forceinline__ void request(const ThinArgs& ta, int dlen, int ec) {
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = w + u * W;
+      part[u] = ta.prev[(size_t)(k < ta.nprev ? k : ta.nprev - 1) * dlen + ec];
+    }
+  }
+  __device__ __forceinline__ float sum(const ThinArgs& ta) {
+    __shared__ float wave_part[W][64];
+    const int e = threadIdx.x & 63, w = threadIdx.x >> 6;
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += w + u * W < ta.nprev ? part[u] : 0.f;
+    wave_part[w][e] = s;
+    lds_barrier();
+    float s2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < W; ++k) s2 += wave_part[k][e];
+    return s2;
+  }
+};
+
+// q = H d and the pending CG update (CgPend, Section 2.4) from the previous sweep's partial sums, which are requested together with
+// both sets of vectors, so that nothing waits to learn which set is current; every wave makes the update for itself, one element of
+// the vectors per lane.  (By the whole workgroup, as for longer vectors, it took five barriers: 1.3 us more per CG iteration at 2500 to 40000 rows.)
 // Returns the lane's element of the new direction or of the final iterate; *go is false if no product is left to form.
 // `writer`: this wave stores the new vectors and state.  after_issue(): the caller's first loads.
 template <int THREADS, typename F>
 __device__ __forceinline__ float cg_from_partials(const ThinArgs& ta, bool writer, bool* go, F&& after_issue) {
-  constexpr int W = THREADS / 64, U = kThinMaxPartials / W;
-  __shared__ float wave_part[W][64];
   const CgPend& c = ta.cg;
   DevState* st = c.st;
-  const int t = threadIdx.x, e = t & 63, w = t >> 6;
+  const int e = threadIdx.x & 63;
   const int dlen = (int)c.dlen, ec = e < dlen ? e : dlen - 1;
   const bool own = e < dlen;
-  float part[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int k = w + u * W;
-    part[u] = ta.prev[(size_t)(k < ta.nprev ? k : ta.nprev - 1) * dlen + ec];
-  }
+  PartialSum<THREADS> partials;
+  partials.request(ta, dlen, ec);
   const float r0 = c.r[0][ec], r1 = c.r[1][ec], d0 = c.d[0][ec], d1 = c.d[1][ec], p0 = c.p[0][ec], p1 = c.p[1][ec];
   const CgSlot in = st->cgs[c.slot_in];
   const double gg = st->gg_cg;
@@ -157,14 +184,7 @@ __device__ __forceinline__ float cg_from_partials(const ThinArgs& ta, bool write
   __builtin_amdgcn_sched_barrier(0);
   after_issue();
   __builtin_amdgcn_sched_barrier(0);
-  float s = 0.f;
-#pragma unroll
-  for (int u = 0; u < U; ++u) s += w + u * W < ta.nprev ? part[u] : 0.f;
-  wave_part[w][e] = s;
-  lds_barrier();
-  float s2 = 0.f;
-#pragma unroll
-  for (int k = 0; k < W; ++k) s2 += wave_part[k][e];
+  const float s2 = partials.sum(ta);
   const int cur = in.cur & 1;
   float r = own ? (cur ? r1 : r0) : 0.f, d = own ? (cur ? d1 : d0) : 0.f, p = own ? (cur ? p1 : p0) : 0.f;
   const float q = own ? fmaf(ta.lambda + rho_, d, ta.scale * s2) : 0.f;
@@ -210,6 +230,52 @@ __device__ __forceinline__ float cg_from_partials(const ThinArgs& ta, bool write
   return c.final_p != 0 ? p : d;
 }
 
+// The gradient, the head of a Newton iteration and the start of CG (newton_head_kernel) from the partial sums of the gradient's sweep,
+// likewise: returns the lane's element of the first direction -g; *go is false if the iteration has ended.
+template <int THREADS, typename F>
+__device__ __forceinline__ float head_from_partials(const ThinArgs& ta, bool writer, bool* go, F&& after_issue) {
+  const NewtonHeadArgs& h = ta.head;
+  const int e = threadIdx.x & 63;
+  const int dlen = (int)h.d, ec = e < dlen ? e : dlen - 1;
+  const bool own = e < dlen;
+  PartialSum<THREADS> partials;
+  partials.request(ta, dlen, ec);
+  const float x_in = h.X[ec], z_in = h.z != nullptr ? h.z[ec] : 0.f, y_in = h.y != nullptr ? h.y[ec] : 0.f;
+  double lp[kThinMaxPartials / 64];  // row losses, one partial sum per workgroup of the gradient's sweep
+#pragma unroll
+  for (int u = 0; u < kThinMaxPartials / 64; ++u) {
+    const int k = e + 64 * u;
+    lp[u] = writer ? h.loss_part[k < h.nblocks ? k : h.nblocks - 1] : 0.0;
+  }
+  const float rho_ = h.rho_scale != nullptr ? h.rho * *h.rho_scale : h.rho;
+  __builtin_amdgcn_sched_barrier(0);
+  after_issue();
+  __builtin_amdgcn_sched_barrier(0);
+  const float s = partials.sum(ta);
+  const float x = own ? x_in : 0.f, z = own ? z_in : 0.f, y = own ? y_in : 0.f;
+  const float g = own ? h.scale * s + (h.lambda * x + rho_ * (x - z) + y) : 0.f;
+  const double gg = mfma_detail::wave64_sum((double)g * (double)g);
+  *go = gg > 0.0 && !(h.grad_tol > 0.f && sqrt(gg) < (double)h.grad_tol);
+  if (writer) {
+    const double u = (double)x - (double)z + (double)y / (double)rho_;
+    const double pen = mfma_detail::wave64_sum(own ? 0.5 * (double)h.lambda * (double)x * (double)x + 0.5 * (double)rho_ * u * u : 0.0);
+    double data = 0.0;
+#pragma unroll
+    for (int k = 0; k < kThinMaxPartials / 64; ++k) data += e + 64 * k < h.nblocks ? lp[k] : 0.0;
+    data = mfma_detail::wave64_sum(data);
+    if (own) {
+      h.g_out[e] = g;
+      h.pdir[e] = 0.f;
+      h.r[e] = -g;
+      h.dvec[e] = -g;
+    }
+    // (the flag that newton_head_scalars lowers at the end of the iteration is read by the other workgroups of this kernel; whether
+    // they see it before or after, they have nothing to do then: go is false for all)
+    if (e == 0) newton_head_scalars(h, gg, (double)h.scale * data + pen);
+  }
+  return -g;
+}
+
 typedef __attribute__((address_space(1))) const void gvoid;
 typedef __attribute__((address_space(3))) void lvoid;
 template <int BYTES>  // lane l: BYTES from its own address g to l BYTES behind the wave's address to
@@ -220,24 +286,27 @@ __device__ __forceinline__ void copy_to_lds(const float* g, float* to) {
 }
 
 // What the sweep makes, fixed at compile time: chosen inside the loop it cost copies of all accumulators and spills.
-// kHvP, kHvCg: with cached probabilities; kSearchCg: with cached logits A X.
-enum StreamOp { kHvX, kHvP, kHvCg, kGrad, kLoss, kLogits, kLogitsCg, kSearch, kSearchCg };
+// kHvP, kHvCg, kHvHead: with cached probabilities; kSearchCg: with cached logits A X.
+enum StreamOp { kHvX, kHvP, kHvCg, kHvHead, kGrad, kLoss, kLogits, kLogitsCg, kSearch, kSearchCg };
 
 template <int NQ, int NC, int THREADS, Rows ROWS, StreamOp OP>
 __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta) {
   constexpr int PP = 4 * NQ, D = PP * NC, W = THREADS / 64;
   RowArgs a = ta.r;
-  a.kind = OP == kHvX || OP == kHvP || OP == kHvCg ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : (OP == kLogits || OP == kLogitsCg ? kRowsLogits : kRowsSearch)));
-  if (a.flag != nullptr && *a.flag == 0) return;
+  a.kind = OP == kHvX || OP == kHvP || OP == kHvCg || OP == kHvHead ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : (OP == kLogits || OP == kLogitsCg ? kRowsLogits : kRowsSearch)));
+  if (a.flag != nullptr && *a.flag == 0) {
+    if (OP == kHvHead && blockIdx.x == 0 && threadIdx.x == 0) ta.head.st->cgs[0] = CgSlot{0.0, 0, 0, 0, 0};  // a stopped Newton iteration leaves CG inactive
+    return;
+  }
   extern __shared__ __attribute__((aligned(16))) float tile[];  // [wave][64 rows]
   __shared__ double red[W];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int p = a.p, ld = ROWS == kQuads ? PP : (int)a.lda;
   constexpr bool cg = OP == kHvCg || OP == kLogitsCg || OP == kSearchCg, search = OP == kSearch || OP == kSearchCg;
   const bool has0 = OP == kLogits ? a.B0 != nullptr : (OP == kHvX || OP == kGrad || OP == kLoss || OP == kSearch);
-  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvP || OP == kSearch || cg);
-  constexpr bool with_cols = OP == kHvX || OP == kHvP || OP == kHvCg || OP == kGrad;
-  constexpr bool wants_label = OP == kGrad || OP == kLoss || search, wants_p = OP == kHvP || OP == kHvCg || OP == kSearchCg;
+  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvP || OP == kHvHead || OP == kSearch || cg);
+  constexpr bool with_cols = OP == kHvX || OP == kHvP || OP == kHvCg || OP == kHvHead || OP == kGrad;
+  constexpr bool wants_label = OP == kGrad || OP == kLoss || search, wants_p = OP == kHvP || OP == kHvCg || OP == kHvHead || OP == kSearchCg;
   float* mine = tile + wave * (64 * PP);
 
   const bool aligned = (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
@@ -284,11 +353,14 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
   // one entry of X and of V per lane (p (C-1) <= 64); the products read them lane by lane as scalar registers
   const int dlen = p * NC, le = lane < dlen ? lane : dlen - 1;
   float x_in = has0 ? a.B0[le] : 0.f, v_in = 0.f;
-  if constexpr (cg) {
+  if constexpr (cg || OP == kHvHead) {
     bool go;
-    v_in = cg_from_partials<THREADS>(ta, blockIdx.x == 0 && wave == 0, &go, [&] {
+    const bool writer = blockIdx.x == 0 && wave == 0;
+    auto first = [&] {
       if (chunk < nchunks) request(chunk);
-    });
+    };
+    if constexpr (OP == kHvHead) v_in = head_from_partials<THREADS>(ta, writer, &go, first);
+    else v_in = cg_from_partials<THREADS>(ta, writer, &go, first);
     if (!go) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way to LDS when the workgroup ends
       return;
@@ -465,6 +537,10 @@ hipError_t launch_stream(const ThinArgs& ta, int grid, hipStream_t st) {
       if (a.kind == kRowsHv && cols && a.Pin != nullptr) return launch_stream_op<NQ, NC, ROWS, kHvCg>(ta, grid, st);
       if (a.kind == kRowsLogits && !cols && a.Z1out != nullptr) return launch_stream_op<NQ, NC, ROWS, kLogitsCg>(ta, grid, st);
       if (a.kind == kRowsSearch && !cols && a.Pin != nullptr) return launch_stream_op<NQ, NC, ROWS, kSearchCg>(ta, grid, st);
+      return hipErrorInvalidValue;
+    }
+    if (ta.head.st != nullptr) {
+      if (a.kind == kRowsHv && cols && a.Pin != nullptr) return launch_stream_op<NQ, NC, ROWS, kHvHead>(ta, grid, st);
       return hipErrorInvalidValue;
     }
     if (a.kind == kRowsHv && cols && a.B1 != nullptr && (a.B0 != nullptr || a.Pin != nullptr))

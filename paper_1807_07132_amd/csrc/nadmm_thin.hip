@@ -59,7 +59,8 @@ bool thin_padded_narrow(const Shape& s, int64_t lda) {
 // one workgroup per compute unit, and every wave with a chunk of 64 rows before any has two
 int thin_num_partials(const Shape& s) { return (int)std::min<int64_t>(kThinMaxPartials, (s.n + 63) / 64); }
 
-hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg, const ReduceArgs* prev) {
+hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg, const ReduceArgs* prev,
+                       const NewtonHeadArgs* head) {
   if (nparts < 1 || nparts > kThinMaxPartials) return hipErrorInvalidValue;
   if (a.kind == kRowsSearch && (a.labels == nullptr || a.lpart == nullptr || a.ncand < 1 || a.ncand > kSweepCand)) return hipErrorInvalidValue;
   ThinArgs ta;
@@ -70,6 +71,14 @@ hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t
     // the pending update of a CG iteration on cached probabilities (or the line search's logits pass on the final iterate)
     if (a.B0 != nullptr || !set_pending(&ta, *cg, prev, (int64_t)a.p * a.NC)) return hipErrorInvalidValue;
     if (prev->partial == partial) return hipErrorInvalidValue;  // the sweep reads the previous partials while it writes its own
+  } else if (head != nullptr) {
+    if (a.B0 != nullptr || prev == nullptr || prev->partial == nullptr || prev->partial == partial || prev->nparts < 1 ||
+        prev->nparts > kThinMaxPartials || head->st == nullptr || head->newton_mode == 0 || head->d != (int64_t)a.p * a.NC ||
+        head->d > kThinMaxD || head->loss_part == nullptr || head->g_out == nullptr || head->nblocks < 1 || head->nblocks > kThinMaxPartials)
+      return hipErrorInvalidValue;
+    ta.head = *head;
+    ta.prev = prev->partial;
+    ta.nprev = prev->nparts;
   }
   return (a.lda & 3) == 0 ? launch_thin_quads(ta, nparts, st) : launch_thin_block(ta, nparts, st);
 }

@@ -389,30 +389,7 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a) {
                                   : penalty_block(a.X, a.z, a.y, a.d, a.lambda, rho_, sm);
     loss = (double)a.scale * data + pen;
   }
-  if (threadIdx.x == 0) {
-    st->gg = gg;
-    st->rr = gg;
-    st->gg_cg = gg;
-    st->cg_iters = 0;
-    st->cg_active = gg > 0.0 ? 1 : 0;
-    int32_t cg_on = st->cg_active;
-    if (a.newton_mode && (sqrt(gg) < (double)a.grad_tol || !(gg > 0.0))) cg_on = 0;
-    st->cgs[0] = CgSlot{gg, cg_on, 0, 0, 0};
-    if (a.newton_mode) {
-      const double gn = sqrt(gg);
-      st->loss = loss;
-      nadmm_stats* s = &st->stats;
-      if (a.iter == 0) { st->loss_initial = loss; s->loss_initial = loss; s->loss_final = loss; }
-      s->grad_norm_final = gn;
-      if (gn < (double)a.grad_tol || !(gg > 0.0)) {
-        st->newton_active = 0;
-        st->cg_active = 0;
-      } else if (a.iter < NADMM_TRACE_LEN) {
-        s->loss[a.iter] = loss;
-        s->grad_norm[a.iter] = gn;
-      }
-    }
-  }
+  if (threadIdx.x == 0) newton_head_scalars(a, gg, loss);
 }
 
 __global__ __launch_bounds__(kTail) void newton_head_kernel(const NewtonHeadArgs a) { newton_head_body(a); }

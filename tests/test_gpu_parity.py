@@ -792,6 +792,14 @@ def test_thin_chunks(n, p, C, tol):
     X_ref, st_ref, forced = oracle_newton_following(op, w.X0, w, st["alpha"])
     assert rel_l2(host(Xn), X_ref) <= TOL_ITERATE
     assert forced or st["cg_iters"] == [i["cg_iters"] for i in st_ref["iters"]]
+    # objective and stopping test of the head, which the first CG sweep makes: before the first iteration and before the second
+    assert rel_abs(st["loss_initial"], f_ref) <= 1e-6 and rel_abs(st["grad_norm"][0], np.linalg.norm(g_ref)) <= 1e-6
+    assert st["grad_norm"][1] < st["grad_norm"][0]
+    for stop, tol_g in ((0, 1.01 * st["grad_norm"][0]), (1, 1.01 * st["grad_norm"][1])):
+        Xs = X.clone()
+        st1 = nadmm.nadmm_local_newton(gp, Xs, nadmm.make_params(3, 5, 10, cg_tol=tol, grad_tol=tol_g))
+        assert st1["newton_iters"] == stop and (stop > 0 or torch.equal(Xs, X))
+        assert st1["grad_norm_final"] == st["grad_norm"][stop]
 
 
 # The one launch of a small Newton solve: line searches that reduce their step (sum scaling, far from the minimiser), a row block of
