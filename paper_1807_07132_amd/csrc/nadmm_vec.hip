@@ -359,7 +359,7 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a) {
   if (a.gg_part != nullptr) {
     gg = partial_sum_block(a.gg_part, a.npart, sm);  // the reduction has written p, r, d already
   } else {
-    constexpr int U = 16;  // loads of a thread in flight
+    constexpr int U = kBlk;  // (16, most of which repeat the last element on 1024 threads, took 2 to 4 us more per CG solve)
     for (int64_t e0 = threadIdx.x; e0 < a.d; e0 += (int64_t)U * blockDim.x) {
       float gv[U];
 #pragma unroll
