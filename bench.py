@@ -25,14 +25,14 @@ LG_PER_STEP = 100
 # names the summary it comes from and the digest of the kernel sources it was measured with: if the sources of
 # that kernel path have changed since, the line reports traffic = null instead of a stale figure.
 MEASURED_HV_TRAFFIC = {
-    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "423edfe860d6"),
-    ("tall_binary_1375000x28_C2", 3): (154.4e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "f9c060aed35f"),
-    ("wide_50000x3072_C10", 4): (685.6e6, "profiles/hessvec_wide_50000x3072_C10.md", "857977ae8f7e"),
-    ("large_multiclass_250000x2000_C20", 4): (2191.6e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "857977ae8f7e"),
+    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "3f27fe8658a8"),
+    ("tall_binary_1375000x28_C2", 3): (154.2e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "aca739adb193"),
+    ("wide_50000x3072_C10", 4): (685.2e6, "profiles/hessvec_wide_50000x3072_C10.md", "e2b5c987b0fb"),
+    ("large_multiclass_250000x2000_C20", 4): (2191.1e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "e2b5c987b0fb"),
     # sparse storage: bytes between the L2 caches and the memory side, most of them operand rows served by the Infinity Cache
-    ("e18_like_40628x279998_C20_sparse", 5): (12472.7e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "ae528284a032"),
+    ("e18_like_40628x279998_C20_sparse", 5): (12473.6e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "da09fc4f28fe"),
 }
-PATH_SOURCES = {1: ["nadmm_generic.hip", "nadmm_rows16.h"], 2: ["nadmm_fused.hip", "nadmm_narrow.hip", "nadmm_cgstep.h"], 3: ["nadmm_thin.hip", "nadmm_cgstep.h"],
+PATH_SOURCES = {1: ["nadmm_generic.hip", "nadmm_rows16.h"], 2: ["nadmm_fused.hip", "nadmm_narrow.hip", "nadmm_cgstep.h"], 3: ["nadmm_thin.h", "nadmm_thin.hip", "nadmm_cgstep.h"],
                 4: ["nadmm_sliced.hip", "nadmm_wide.hip", "nadmm_rows16.h", "nadmm_cgstep.h"], 5: ["nadmm_sparse.hip", "nadmm_generic.hip", "nadmm_rows16.h"]}
 DTYPE = ("f32 data and results; products on bf16 MFMA with split operands and f32 accumulate (6 terms for A X, 3 for A V, 3 for A^T D, 4 in the "
          "wide-row kernel, 6 for all in the narrow-row one) or f32 FMA (thin and sparse data); f64 scalar sums")

@@ -495,11 +495,11 @@ ReduceArgs thin_prev(const nadmm_problem* prob, const Layout& L, void* ws, int k
 // the gradient's reduction wrote; if this head finds the iteration finished, one sweep was made for nothing).
 int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws, DevState* ds, const float* X,
                  bool write_pcache, float tol, int k, hipStream_t st, float* w_rows = nullptr,
-                 const NewtonHeadArgs* head = nullptr, bool thin_def = false) {
+                 const NewtonHeadArgs* head = nullptr) {
   float* dvec = at<float>(ws, L.dvec);
   float* q = at<float>(ws, L.q);
-  if (thin_def) {  // no reduction kernel: see thin_deferred
-    if (!thin_deferred(path) || (X != nullptr && k > 0)) return NADMM_EINVAL;
+  if (thin_deferred(path)) {  // no reduction kernel; the first product comes with X or with the head of a Newton iteration
+    if ((X != nullptr && k > 0) || (k == 0 && (X != nullptr) == (head != nullptr))) return NADMM_EINVAL;
     RowArgs ra = blank_rows();
     ra.kind = kRowsHv;
     ra.B0 = X;
@@ -541,7 +541,7 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
   cu.rr_part = at<double>(ws, L.rrpart);
   cu.d = L.s.d;
   cu.tol = tol;
-  const int parts = path == 3 ? L.thin_parts : (path == 2 ? L.fused_parts : (path == 4 ? std::max(std::max(L.wide_parts, L.sliced_parts), L.narrow_parts) : L.gen_chunks));
+  const int parts = path == 4 ? std::max(std::max(L.wide_parts, L.sliced_parts), L.narrow_parts) : L.gen_chunks;
   if (cg_fused_tail_supported(L.s.d, parts)) {
     int nparts = 0;
     int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, nullptr, nullptr, &ds->cg_active, &nparts, st);
@@ -694,7 +694,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     for (int k = 0; k < params->max_cg; ++k) {
       float* w_rows = hist ? at<float>(d_ws, L.hist) + (size_t)k * hist_stride : nullptr;
       if ((rc = cg_iteration(prob, L, path, d_ws, ds, nullptr, false, params->cg_tol, k, st, w_rows,
-                             (k == 0 && (head_in_reduce || thin_def)) ? &nh : nullptr, thin_def)) != NADMM_OK)
+                             (k == 0 && (head_in_reduce || thin_def)) ? &nh : nullptr)) != NADMM_OK)
         return rc;
     }
 
@@ -1020,9 +1020,7 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   NADMM_HIP(launch_newton_head(nh, st));
 
   for (int k = 0; k < max_iter; ++k) {
-    if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st, nullptr, nullptr, thin_deferred(path))) !=
-        NADMM_OK)
-      return rc;
+    if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st)) != NADMM_OK) return rc;
   }
   const bool pend = (cg_deferred(path) || thin_deferred(path)) && max_iter > 0;
   if (pend) {

@@ -286,14 +286,14 @@ __device__ __forceinline__ void copy_to_lds(const float* g, float* to) {
 }
 
 // What the sweep makes, fixed at compile time: chosen inside the loop it cost copies of all accumulators and spills.
-// kHvP, kHvCg, kHvHead: with cached probabilities; kSearchCg: with cached logits A X.
-enum StreamOp { kHvX, kHvP, kHvCg, kHvHead, kGrad, kLoss, kLogits, kLogitsCg, kSearch, kSearchCg };
+// kHvCg, kHvHead: with cached probabilities; kSearchCg: with cached logits A X.
+enum StreamOp { kHvX, kHvCg, kHvHead, kGrad, kLoss, kLogits, kLogitsCg, kSearch, kSearchCg };
 
 template <int NQ, int NC, int THREADS, Rows ROWS, StreamOp OP>
 __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta) {
   constexpr int PP = 4 * NQ, D = PP * NC, W = THREADS / 64;
   RowArgs a = ta.r;
-  a.kind = OP == kHvX || OP == kHvP || OP == kHvCg || OP == kHvHead ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : (OP == kLogits || OP == kLogitsCg ? kRowsLogits : kRowsSearch)));
+  a.kind = OP == kHvX || OP == kHvCg || OP == kHvHead ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : (OP == kLogits || OP == kLogitsCg ? kRowsLogits : kRowsSearch)));
   if (a.flag != nullptr && *a.flag == 0) {
     if (OP == kHvHead && blockIdx.x == 0 && threadIdx.x == 0) ta.head.st->cgs[0] = CgSlot{0.0, 0, 0, 0, 0};  // a stopped Newton iteration leaves CG inactive
     return;
@@ -304,9 +304,9 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
   const int p = a.p, ld = ROWS == kQuads ? PP : (int)a.lda;
   constexpr bool cg = OP == kHvCg || OP == kLogitsCg || OP == kSearchCg, search = OP == kSearch || OP == kSearchCg;
   const bool has0 = OP == kLogits ? a.B0 != nullptr : (OP == kHvX || OP == kGrad || OP == kLoss || OP == kSearch);
-  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvP || OP == kHvHead || OP == kSearch || cg);
-  constexpr bool with_cols = OP == kHvX || OP == kHvP || OP == kHvCg || OP == kHvHead || OP == kGrad;
-  constexpr bool wants_label = OP == kGrad || OP == kLoss || search, wants_p = OP == kHvP || OP == kHvCg || OP == kHvHead || OP == kSearchCg;
+  const bool has1 = OP == kLogits ? a.B1 != nullptr : (OP == kHvX || OP == kHvHead || OP == kSearch || cg);
+  constexpr bool with_cols = OP == kHvX || OP == kHvCg || OP == kHvHead || OP == kGrad;
+  constexpr bool wants_label = OP == kGrad || OP == kLoss || search, wants_p = OP == kHvCg || OP == kHvHead || OP == kSearchCg;
   float* mine = tile + wave * (64 * PP);
 
   const bool aligned = (reinterpret_cast<uintptr_t>(a.A) & 15) == 0;
@@ -543,8 +543,7 @@ hipError_t launch_stream(const ThinArgs& ta, int grid, hipStream_t st) {
       if (a.kind == kRowsHv && cols && a.Pin != nullptr) return launch_stream_op<NQ, NC, ROWS, kHvHead>(ta, grid, st);
       return hipErrorInvalidValue;
     }
-    if (a.kind == kRowsHv && cols && a.B1 != nullptr && (a.B0 != nullptr || a.Pin != nullptr))
-      return a.B0 != nullptr ? launch_stream_op<NQ, NC, ROWS, kHvX>(ta, grid, st) : launch_stream_op<NQ, NC, ROWS, kHvP>(ta, grid, st);
+    if (a.kind == kRowsHv && cols && a.B0 != nullptr && a.B1 != nullptr) return launch_stream_op<NQ, NC, ROWS, kHvX>(ta, grid, st);
     if (a.kind == kRowsGrad && cols && a.B0 != nullptr) return launch_stream_op<NQ, NC, ROWS, kGrad>(ta, grid, st);
     if (a.kind == kRowsLoss && !cols && a.B0 != nullptr) return launch_stream_op<NQ, NC, ROWS, kLoss>(ta, grid, st);
     if (a.kind == kRowsLogits && !cols) return launch_stream_op<NQ, NC, ROWS, kLogits>(ta, grid, st);
