@@ -25,8 +25,8 @@ LG_PER_STEP = 100
 # names the summary it comes from and the digest of the kernel sources it was measured with: if the sources of
 # that kernel path have changed since, the line reports traffic = null instead of a stale figure.
 MEASURED_HV_TRAFFIC = {
-    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "3f27fe8658a8"),
-    ("tall_binary_1375000x28_C2", 3): (154.2e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "aca739adb193"),
+    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "03389cbbafdd"),
+    ("tall_binary_1375000x28_C2", 3): (154.2e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "b06fa75b1b47"),
     ("wide_50000x3072_C10", 4): (685.2e6, "profiles/hessvec_wide_50000x3072_C10.md", "e2b5c987b0fb"),
     ("large_multiclass_250000x2000_C20", 4): (2191.1e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "e2b5c987b0fb"),
     # sparse storage: bytes between the L2 caches and the memory side, most of them operand rows served by the Infinity Cache

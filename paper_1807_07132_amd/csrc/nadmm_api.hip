@@ -287,7 +287,8 @@ int sparse_plan(const nadmm_problem* prob, const Layout& L, void* ws, hipStream_
 // previous sweep's partial sums, which that kernel adds up itself, and partial_out where this sweep's go.
 int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArgs ra, bool with_cols,
           int* nparts, hipStream_t st, const CgPend* cg = nullptr, const ReduceArgs* prev = nullptr,
-          float* partial_out = nullptr, bool packed = false, const NewtonHeadArgs* head = nullptr) {
+          float* partial_out = nullptr, bool packed = false, const NewtonHeadArgs* head = nullptr,
+          const SearchArgs* search = nullptr) {
   if (cg != nullptr && path != 2 && path != 3) return NADMM_EINVAL;
   if ((prev != nullptr || partial_out != nullptr || head != nullptr) && path != 3) return NADMM_EINVAL;
   ra.A = prob->d_A;
@@ -342,13 +343,13 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
   }
   if (path == 2) {
     if (L.narrow) NADMM_HIP(launch_narrow(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.fused_parts, st, cg));
-    else NADMM_HIP(launch_fused(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.fused_parts, st, cg));
+    else NADMM_HIP(launch_fused(ra, with_cols ? at<float>(ws, L.partial) : nullptr, L.fused_parts, st, cg, search));
     *nparts = L.fused_parts;
     return NADMM_OK;
   }
   if (path == 3) {
     float* pout = partial_out != nullptr ? partial_out : at<float>(ws, L.partial);
-    NADMM_HIP(launch_thin(ra, with_cols ? pout : nullptr, L.thin_parts, st, cg, prev, head));
+    NADMM_HIP(launch_thin(ra, with_cols ? pout : nullptr, L.thin_parts, st, cg, prev, head, search));
     *nparts = L.thin_parts;
     return NADMM_OK;
   }
@@ -708,13 +709,14 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     rz.Z1out = at<float>(d_ws, L.zp);
     rz.flag = &ds->newton_active;
     const bool in_sweep = thin_def && sweep_evaluates(L, path, ncand);  // the pass that forms A p evaluates the step sizes
+    SearchArgs sr{};
     if (in_sweep) {
       rz.kind = kRowsSearch;
       rz.Pin = at<float>(d_ws, L.zx);
       rz.labels = prob->d_labels;
-      rz.lpart = at<double>(d_ws, L.lpart);
-      rz.ncand = ncand;
-      fill_alphas(rz.alphas, ncand, params->backtrack_gamma);
+      sr.lpart = at<double>(d_ws, L.lpart);
+      sr.ncand = ncand;
+      fill_alphas(sr.alphas, ncand, params->backtrack_gamma);
     }
     const bool eval_finishes = hist && ls_eval_takes_pending(prob->n);  // the row kernel of the line search applies the last update
     if (hist) {  // A p comes from the history; the last update alone, unless the line search's row kernel takes it along
@@ -724,7 +726,8 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
       const CgPend c = cg_pend(L, d_ws, ds, (params->max_cg - 1) & 1, true, params->cg_tol);
       if (thin_def) {  // the last sweep's partial sums are added up by this pass as well
         const ReduceArgs prev = thin_prev(prob, L, d_ws, params->max_cg - 1);
-        if ((rc = sweep(prob, L, path, d_ws, rz, false, &nparts, st, &c, &prev)) != NADMM_OK) return rc;
+        if ((rc = sweep(prob, L, path, d_ws, rz, false, &nparts, st, &c, &prev, nullptr, false, nullptr, in_sweep ? &sr : nullptr)) != NADMM_OK)
+          return rc;
       } else if ((rc = sweep(prob, L, path, d_ws, rz, false, &nparts, st, &c)) != NADMM_OK) {
         return rc;
       }
@@ -1075,10 +1078,11 @@ int nadmm_line_search(const nadmm_problem* prob, const float* d_X, const float* 
   if (sweep_evaluates(L, path, neval)) {  // the sweep itself evaluates the step sizes
     ra.kind = kRowsSearch;
     ra.labels = prob->d_labels;
-    ra.lpart = at<double>(d_ws, L.lpart);
-    ra.ncand = neval;
-    std::copy(alphas, alphas + neval, ra.alphas);
-    if ((rc = sweep(prob, L, path, d_ws, ra, false, &nparts, st)) != NADMM_OK) return rc;
+    SearchArgs sr{};
+    sr.lpart = at<double>(d_ws, L.lpart);
+    sr.ncand = neval;
+    std::copy(alphas, alphas + neval, sr.alphas);
+    if ((rc = sweep(prob, L, path, d_ws, ra, false, &nparts, st, nullptr, nullptr, nullptr, false, nullptr, &sr)) != NADMM_OK) return rc;
     nblocks = nparts;
   } else {
     ra.kind = kRowsLogits;

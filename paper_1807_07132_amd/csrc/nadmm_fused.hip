@@ -52,6 +52,7 @@ struct FusedArgs {
   int32_t steps;      // ceil(p / 32)
   int32_t rows_per_wg;
   int32_t tile_rows;  // rows per tile, <= 32
+  SearchArgs search;  // kRowsSearch
   CgPend cg;          // cg.st != NULL: the operand B1 is the result of a pending CG update (kernels without B0 only)
 };
 
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
   }
   if (deferred) lds_barrier();  // every wave has picked its operands from LDS: the step slots may be overwritten
 
-  const float my_alpha = KIND == kRowsSearch ? a.alphas[m < a.ncand ? m : 0] : 0.f;
+  const float my_alpha = KIND == kRowsSearch ? fa.search.alphas[m < fa.search.ncand ? m : 0] : 0.f;
   u32x4 dhi, dlo;  // D of the current tile as MFMA operand
   for (int64_t row0 = r_begin; row0 < r_end; row0 += th_rows) {
     // the row this wave handles in the rows stage: e = wave, row = row0 + 4 kg + (e & 3) + 16 (e >> 2)
@@ -519,10 +520,10 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs fa) {
     __syncthreads();
     if (lane < 16) red[wave * 16 + lane] = loss_acc;
     __syncthreads();
-    if ((int)threadIdx.x < a.ncand) {
+    if ((int)threadIdx.x < fa.search.ncand) {
       double t = 0.0;
       for (int wv = 0; wv < kWaves; ++wv) t += red[wv * 16 + threadIdx.x];
-      a.lpart[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+      fa.search.lpart[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
     }
   }
   if (KIND == kRowsGrad || KIND == kRowsLoss) {
@@ -612,7 +613,7 @@ hipError_t launch_spw(const FusedArgs& fa, int grid, size_t lds_bytes, hipStream
       if (h0) return launch_one<SPW, kRowsLogits, true, false>(fa, grid, lds_bytes, st);
       return hipErrorInvalidValue;
     case kRowsSearch:
-      if (!h0 || !h1 || a.labels == nullptr || a.lpart == nullptr || a.ncand < 1 || a.ncand > kSweepCand) return hipErrorInvalidValue;
+      if (!h0 || !h1 || a.labels == nullptr || fa.search.lpart == nullptr || fa.search.ncand < 1 || fa.search.ncand > kSweepCand) return hipErrorInvalidValue;
       return launch_one<SPW, kRowsSearch, true, true>(fa, grid, lds_bytes, st);
     default:
       return hipErrorInvalidValue;
@@ -636,9 +637,10 @@ int fused_num_partials(const Shape& s) {
   return (int)(g < 1 ? 1 : g);
 }
 
-hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg) {
+hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg, const SearchArgs* search) {
   FusedArgs fa;
   fa.r = a;
+  fa.search = search != nullptr ? *search : SearchArgs{};
   if (cg != nullptr) {
     if (a.B0 != nullptr || a.B1 == nullptr || (a.kind != kRowsHv && a.kind != kRowsLogits)) return hipErrorInvalidValue;
     if (cg->ndot < 1 || cg->ndot > kThreads || cg->dlen != (int64_t)a.p * a.NC) return hipErrorInvalidValue;

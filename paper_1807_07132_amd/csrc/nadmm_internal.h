@@ -103,8 +103,12 @@ struct RowArgs {
   double* loss_part;   // per-workgroup partial sums of row losses (kinds 1, 2)
   int32_t kind;
   const int32_t* flag; // if non-NULL and *flag == 0 the kernel does nothing
-  double* lpart;       // kind 4: [step size][workgroup] partial sums of row losses
-  int32_t ncand;       // kind 4: step sizes, at most kSweepCand
+};
+
+// Kind 4 (not part of RowArgs: its size costs kernels without it registers, the wide-row ones two more spilled in their stream)
+struct SearchArgs {
+  double* lpart;       // [step size][workgroup] partial sums of row losses
+  int32_t ncand;       // step sizes, at most kSweepCand
   float alphas[kSweepCand];
 };
 
@@ -354,7 +358,8 @@ int fused_num_partials(const Shape& s);
 // over A; leaves per-workgroup partial sums of A^T rows in `partial`
 // (nparts = fused_num_partials() blocks of d floats) and per-workgroup partial
 // losses in a.loss_part[0 .. nparts).
-hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr);
+hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
+                        const SearchArgs* search = nullptr);
 // the pending update alone (one workgroup): end of a stand-alone CG solve
 hipError_t launch_cg_pending_finish(const CgPend& c, hipStream_t st);
 
@@ -366,7 +371,7 @@ int thin_num_partials(const Shape& s);
 // cg, prev (both or neither): the sweep first applies the pending CG update, forming q = H d from the previous sweep's
 // partial sums prev->partial (prev also carries scale, lambda, rho of the linear terms); see ThinArgs in nadmm_thin.hip
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
-                       const ReduceArgs* prev = nullptr, const NewtonHeadArgs* head = nullptr);
+                       const ReduceArgs* prev = nullptr, const NewtonHeadArgs* head = nullptr, const SearchArgs* search = nullptr);
 // the pending update alone (one workgroup): end of a stand-alone CG solve
 hipError_t launch_thin_cg_finish(const CgPend& cg, const ReduceArgs& prev, hipStream_t st);
 

@@ -31,6 +31,7 @@ namespace nadmm {
 struct ThinArgs {
   RowArgs r;
   float* partial;      // gridDim.x x (p*NC) or NULL
+  SearchArgs search;   // kSearch, kSearchCg
   // Deferred CG update (kHvCg, kLogitsCg): the sweep of the previous CG iteration left only its per-workgroup
   // partial sums of A^T D.  Every workgroup of this sweep adds them up (fixed order), forms q = H d, applies the update of
   // Section 2.4 and takes its operand, the new direction (or, for the line search's pass, the final iterate), from there;
@@ -427,13 +428,13 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
         }
 #pragma unroll
       for (int k0 = 0; k0 < kSweepCand; k0 += 4) {
-        if (k0 >= a.ncand) continue;  // uniform; four step sizes at a time, those past the last one repeat the first
+        if (k0 >= ta.search.ncand) continue;  // uniform; four step sizes at a time, those past the last one repeat the first
 #pragma unroll
         for (int k = k0; k < k0 + 4; ++k) {
           float zz[NC], M = 0.f, zb = 0.f, es;
 #pragma unroll
           for (int c = 0; c < NC; ++c) {
-            zz[c] = fmaf(a.alphas[k], w[c], z[c]);
+            zz[c] = fmaf(ta.search.alphas[k], w[c], z[c]);
             M = fmaxf(M, zz[c]);
             zb = c == label ? zz[c] : zb;  // the reference class has logit 0
           }
@@ -458,7 +459,7 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
     double* sums = reinterpret_cast<double*>(tile);  // [step size][row of 16 lanes]: 512 W bytes, the smallest tile has 1024 W
 #pragma unroll
     for (int k0 = 0; k0 < kSweepCand; k0 += 4) {
-      if (k0 >= a.ncand) continue;
+      if (k0 >= ta.search.ncand) continue;
       double s[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) s[k] = mfma_detail::row16_sum(cand[k0 + k]);
@@ -471,13 +472,13 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
     if (t < 64) {  // four lanes per step size
       const int k = t >> 2;
       double s = 0.0;
-      if (k < a.ncand) {
+      if (k < ta.search.ncand) {
 #pragma unroll
         for (int w = 0; w < W; ++w) s += sums[k * (4 * W) + 4 * w + (t & 3)];
       }
       s += __shfl_xor(s, 1, 64);
       s += __shfl_xor(s, 2, 64);
-      if ((t & 3) == 0 && k < a.ncand) a.lpart[(size_t)k * gridDim.x + blockIdx.x] = s;
+      if ((t & 3) == 0 && k < ta.search.ncand) ta.search.lpart[(size_t)k * gridDim.x + blockIdx.x] = s;
     }
     return;
   }

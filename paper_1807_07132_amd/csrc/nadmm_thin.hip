@@ -60,13 +60,16 @@ bool thin_padded_narrow(const Shape& s, int64_t lda) {
 int thin_num_partials(const Shape& s) { return (int)std::min<int64_t>(kThinMaxPartials, (s.n + 63) / 64); }
 
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg, const ReduceArgs* prev,
-                       const NewtonHeadArgs* head) {
+                       const NewtonHeadArgs* head, const SearchArgs* search) {
   if (nparts < 1 || nparts > kThinMaxPartials) return hipErrorInvalidValue;
-  if (a.kind == kRowsSearch && (a.labels == nullptr || a.lpart == nullptr || a.ncand < 1 || a.ncand > kSweepCand)) return hipErrorInvalidValue;
+  if (a.kind == kRowsSearch &&
+      (a.labels == nullptr || search == nullptr || search->lpart == nullptr || search->ncand < 1 || search->ncand > kSweepCand))
+    return hipErrorInvalidValue;
   ThinArgs ta;
   std::memset(&ta, 0, sizeof(ta));
   ta.r = a;
   ta.partial = partial;
+  if (search != nullptr) ta.search = *search;
   if (cg != nullptr) {
     // the pending update of a CG iteration on cached probabilities (or the line search's logits pass on the final iterate)
     if (a.B0 != nullptr || !set_pending(&ta, *cg, prev, (int64_t)a.p * a.NC)) return hipErrorInvalidValue;
