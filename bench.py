@@ -32,20 +32,29 @@ MEASURED_HV_TRAFFIC = {
     # sparse storage: bytes between the L2 caches and the memory side, most of them operand rows served by the Infinity Cache
     ("e18_like_40628x279998_C20_sparse", 5): (12473.6e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "da09fc4f28fe"),
 }
-PATH_SOURCES = {1: ["nadmm_generic.hip", "nadmm_rows16.h"], 2: ["nadmm_fused.hip", "nadmm_narrow.hip", "nadmm_cgstep.h"], 3: ["nadmm_thin.h", "nadmm_thin.hip", "nadmm_cgstep.h"],
-                4: ["nadmm_sliced.hip", "nadmm_wide.hip", "nadmm_rows16.h", "nadmm_cgstep.h"], 5: ["nadmm_sparse.hip", "nadmm_generic.hip", "nadmm_rows16.h"]}
+CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1807_07132_amd", "csrc")
+PATH_SOURCES = {1: ["nadmm_generic.hip"], 2: ["nadmm_fused.hip", "nadmm_narrow.hip"], 3: ["nadmm_thin.hip", "nadmm_thin_block.hip"],
+                4: ["nadmm_sliced.hip", "nadmm_wide.hip", "nadmm_narrow.hip"], 5: ["nadmm_sparse.hip", "nadmm_generic.hip"]}
 DTYPE = ("f32 data and results; products on bf16 MFMA with split operands and f32 accumulate (6 terms for A X, 3 for A V, 3 for A^T D, 4 in the "
          "wide-row kernel, 6 for all in the narrow-row one) or f32 FMA (thin and sparse data); f64 scalar sums")
 
 
-def source_digest(path):
-    """Digest of the kernel sources of one kernel path (plus the shared helpers and the reduction)."""
+def source_digest(path, csrc=CSRC):
+    """Digest of the kernel sources of one kernel path, of the reduction's, and of every file of theirs that these include (the size of
+    an argument struct alone has changed what the compiler makes of a kernel)."""
     import hashlib
-    here = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1807_07132_amd", "csrc")
+    import re
     h = hashlib.sha256()
-    for name in PATH_SOURCES[path] + ["nadmm_mfma.h", "nadmm_vec.hip"]:
-        with open(os.path.join(here, name), "rb") as f:
-            h.update(f.read())
+    names, k = PATH_SOURCES[path] + ["nadmm_vec.hip"], 0
+    while k < len(names):
+        with open(os.path.join(csrc, names[k]), "rb") as f:
+            text = f.read()
+        h.update(text)
+        for inc in re.findall(rb'^#include "([^"]+)"', text, re.M):
+            inc = inc.decode()
+            if inc not in names and os.path.exists(os.path.join(csrc, inc)):
+                names.append(inc)
+        k += 1
     return h.hexdigest()[:12]
 
 

@@ -349,6 +349,29 @@ def test_lds_limit_is_noted_without_a_race(tmp_path):
     assert run.returncode == 0, run.stderr
 
 
+def test_traffic_figures_go_by_every_file_their_kernels_include(tmp_path):
+    """The benchmark reports traffic measured with the sources as they are: a change of any file that a path's kernels include counts."""
+    import importlib.util
+    import shutil
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    csrc = tmp_path / "csrc"
+    shutil.copytree(os.path.join(ROOT, "paper_1807_07132_amd", "csrc"), csrc)
+    flags = [f if "csrc" not in f else f"-I{csrc}" for f in GXX]
+    for path, sources in bench.PATH_SOURCES.items():
+        deps = subprocess.check_output([*flags, "-MM", "-x", "c++", *[str(csrc / s) for s in sources], str(csrc / "nadmm_vec.hip")], text=True)
+        files = {os.path.basename(f) for f in deps.replace("\\\n", " ").split() if os.path.dirname(f) == str(csrc)}
+        assert "nadmm_internal.h" in files and set(sources) <= files
+        before = bench.source_digest(path, str(csrc))
+        assert before == bench.source_digest(path)
+        for f in files:
+            kept = (csrc / f).read_bytes()
+            (csrc / f).write_bytes(kept + b"\n// changed\n")
+            assert bench.source_digest(path, str(csrc)) != before, (path, f)
+            (csrc / f).write_bytes(kept)
+
+
 def test_product_path_does_not_import_the_oracle():
     code = ("import sys; sys.path.insert(0, %r); import paper_1807_07132_amd.nadmm, paper_1807_07132_amd.workloads;"
             "assert not any(m == 'oracle' or m.startswith('oracle.') for m in sys.modules)" % ROOT)
