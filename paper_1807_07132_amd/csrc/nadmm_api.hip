@@ -492,7 +492,7 @@ ReduceArgs thin_prev(const nadmm_problem* prob, const Layout& L, void* ws, int k
 // itself), and the update of the last iteration is applied by whatever consumes the iterate (cg_pend(final_p)).
 // w_rows (deferred form only): where the sweep leaves A d_k, or NULL.
 // head (deferred form, k == 0): the work of newton_head_kernel is done by a workgroup of this iteration's reduction; the sweep
-// and the reduction then go by the Newton iteration's flag as the previous head left it (the first direction is the -g that
+// and the reduction then go by newton_entered, as the previous head left it (the first direction is the -g that
 // the gradient's reduction wrote; if this head finds the iteration finished, one sweep was made for nothing).
 int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws, DevState* ds, const float* X,
                  bool write_pcache, float tol, int k, hipStream_t st, float* w_rows = nullptr,
@@ -510,7 +510,7 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
     ra.rows_out = at<float>(ws, L.drows);
     int nparts = 0;
     if (k == 0 && head != nullptr) {  // the gradient's sweep wrote the other buffer (local_newton_enqueue)
-      ra.flag = &ds->newton_active;
+      ra.flag = newton_entered(ds, head->iter);
       const ReduceArgs prev = thin_prev(prob, L, ws, 1);
       return sweep(prob, L, path, ws, ra, true, &nparts, st, nullptr, &prev, thin_partial(L, ws, 0), false, head);
     }
@@ -525,7 +525,7 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
   if (cg_deferred(path)) {
     double* dot = at<double>(ws, L.dotpart);
     if (k == 0)  // nothing pending: d is the first direction, state slot 0 as the initialisation left it
-      return hv_apply(prob, L, path, ws, X, write_pcache, dvec, q, dot, head != nullptr ? &ds->newton_active : &ds->cgs[0].active,
+      return hv_apply(prob, L, path, ws, X, write_pcache, dvec, q, dot, head != nullptr ? newton_entered(ds, head->iter) : &ds->cgs[0].active,
                       nullptr, st, nullptr, nullptr, nullptr, nullptr, w_rows, head);
     const CgPend c = cg_pend(L, ws, ds, (k - 1) & 1, false, tol);
     return hv_apply(prob, L, path, ws, nullptr, false, dvec, q, dot, nullptr, nullptr, st, &c, &ds->cgs[k & 1].active,
@@ -644,7 +644,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     ra.Pout = at<float>(d_ws, L.pcache);
     ra.Z0out = at<float>(d_ws, L.zx);
     ra.loss_part = at<double>(d_ws, L.loss_part);
-    ra.flag = &ds->newton_active;
+    ra.flag = newton_entered(ds, t);
     // thin-data path: the gradient's reduction and the head of the iteration are made by the first sweep of the CG solve
     const bool thin_def = thin_deferred(path) && params->max_cg >= 1;
     int nparts = 0;
@@ -652,7 +652,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
       return rc;
     if (!thin_def) {
       // gradient; the same kernel leaves the partial sums of the penalty terms and of ||g||^2 and starts CG (p = 0, r = d = -g)
-      ReduceArgs rg = reduce_args(prob, L, d_ws, nparts, 1, d_X, g, nullptr, &ds->newton_active);
+      ReduceArgs rg = reduce_args(prob, L, d_ws, nparts, 1, d_X, g, nullptr, newton_entered(ds, t));
       rg.pen_part = at<double>(d_ws, L.headpart);
       rg.gg_part = rg.pen_part + reduce_out_blocks(L.s.d);
       rg.cg_p = pdir;
@@ -707,7 +707,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     rz.kind = kRowsLogits;
     rz.B1 = pstep;
     rz.Z1out = at<float>(d_ws, L.zp);
-    rz.flag = &ds->newton_active;
+    rz.flag = newton_goes_on(ds, t);
     const bool in_sweep = thin_def && sweep_evaluates(L, path, ncand);  // the pass that forms A p evaluates the step sizes
     SearchArgs sr{};
     if (in_sweep) {
@@ -753,7 +753,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     fill_alphas(le.alphas, ncand, params->backtrack_gamma);
     le.ncand = ncand;
     le.lpart = at<double>(d_ws, L.lpart);
-    le.flag = &ds->newton_active;
+    le.flag = newton_goes_on(ds, t);
     if (!in_sweep) NADMM_HIP(launch_ls_eval(le, st));
 
     LsTailArgs lt;
@@ -777,7 +777,7 @@ static int local_newton_enqueue(const nadmm_problem* prob, float* d_X, const nad
     lt.d = L.s.d;
     lt.X_apply = d_X;
     lt.iter = t;
-    lt.flag = &ds->newton_active;
+    lt.flag = newton_goes_on(ds, t);
     lt.rho_scale = L.rho_scale;
     lt.qpart = at<double>(d_ws, L.dotpart);
     NADMM_HIP(launch_ls_tail(lt, st));

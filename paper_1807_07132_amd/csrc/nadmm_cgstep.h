@@ -162,33 +162,6 @@ __device__ __forceinline__ bool cg_pending_update(const CgPend& c, bool writer, 
   return want_p || out.active != 0;
 }
 
-// The scalars of newton_head_kernel, by one thread: objective, ||g||, the stopping test of Algorithm 3 and the state that CG starts from.
-__device__ __forceinline__ void newton_head_scalars(const NewtonHeadArgs& a, double gg, double loss) {
-  DevState* st = a.st;
-  st->gg = gg;
-  st->rr = gg;
-  st->gg_cg = gg;
-  st->cg_iters = 0;
-  st->cg_active = gg > 0.0 ? 1 : 0;
-  int32_t cg_on = st->cg_active;
-  if (a.newton_mode && (sqrt(gg) < (double)a.grad_tol || !(gg > 0.0))) cg_on = 0;
-  st->cgs[0] = CgSlot{gg, cg_on, 0, 0, 0};
-  if (a.newton_mode) {
-    const double gn = sqrt(gg);
-    st->loss = loss;
-    nadmm_stats* s = &st->stats;
-    if (a.iter == 0) { st->loss_initial = loss; s->loss_initial = loss; s->loss_final = loss; }
-    s->grad_norm_final = gn;
-    if (gn < (double)a.grad_tol || !(gg > 0.0)) {
-      st->newton_active = 0;
-      st->cg_active = 0;
-    } else if (a.iter < NADMM_TRACE_LEN) {
-      s->loss[a.iter] = loss;
-      s->grad_norm[a.iter] = gn;
-    }
-  }
-}
-
 // The results of a CG solve whose last update a kernel has just applied, by the thread that wrote the state.
 __device__ __forceinline__ void cg_solve_results(const CgPend& c) {
   if (c.iters_out != nullptr) *c.iters_out = c.st->cg_iters;

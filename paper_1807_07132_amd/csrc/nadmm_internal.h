@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <cmath>
 
 #include "nadmm.h"
 
@@ -56,7 +57,7 @@ struct DevState {
   double loss_new;  // line search: Fhat(X + alpha p)
   double loss_initial;
   float alpha;      // line search result
-  int32_t newton_active;
+  int32_t newton_even;  // see newton_entered
   int32_t cg_active;
   int32_t cg_iters;
   int32_t armijo_ok;
@@ -64,12 +65,19 @@ struct DevState {
   int32_t cg_go;    // two-kernel CG update: the first kernel's verdict (active and positive curvature)
   int32_t cg_ok;    //   0 if the first kernel met non-positive curvature
   float cg_alpha;   //   step length of this CG iteration
-  int32_t pad_[3];
+  int32_t newton_odd;
+  int32_t pad_[2];
   double rr_prev;   //   ||r||^2 before this CG iteration
   CgSlot cgs[2];    // deferred CG update (fused single-pass path): see CgPend
   float cg_alphas[kCgHist];  // deferred CG update: step length of every iteration taken (p = sum_k alpha_k d_k)
   nadmm_stats stats;  // copied to the host at the end of nadmm_local_newton
 };
+
+// Iteration `iter` of Algorithm 3 is entered if its word is not 0.  Its head leaves in the other word whether the iteration goes on,
+// and the next iteration is entered by that.  A kernel that makes the head beside other work goes by the first word in all its
+// workgroups: none reads what another one of the same kernel writes.
+inline __host__ __device__ int32_t* newton_entered(DevState* st, int32_t iter) { return (iter & 1) != 0 ? &st->newton_odd : &st->newton_even; }
+inline __host__ __device__ int32_t* newton_goes_on(DevState* st, int32_t iter) { return newton_entered(st, iter + 1); }
 
 // 16 bytes of a row of A that need only start on a 4-byte boundary: the load type of the matrix-core kernels' variants
 // for rows that are not 16-byte aligned (any row stride, A 4-byte aligned).
@@ -186,6 +194,38 @@ struct NewtonHeadArgs {
   int32_t npart;
   const float* rho_scale;  // optional device scalar factor on rho
 };
+
+// The scalars of an iteration's head, by one thread: objective, ||g||, the stopping test of Algorithm 3 and the state that CG starts from.
+inline __host__ __device__ void newton_head_scalars(const NewtonHeadArgs& a, double gg, double loss) {
+  DevState* st = a.st;
+  st->gg = gg;
+  st->rr = gg;
+  st->gg_cg = gg;
+  st->cg_iters = 0;
+  st->cg_active = gg > 0.0 ? 1 : 0;
+  int32_t cg_on = st->cg_active;
+  if (a.newton_mode && (sqrt(gg) < (double)a.grad_tol || !(gg > 0.0))) cg_on = 0;
+  st->cgs[0] = CgSlot{gg, cg_on, 0, 0, 0};
+  if (a.newton_mode) {
+    const double gn = sqrt(gg);
+    st->loss = loss;
+    nadmm_stats* s = &st->stats;
+    if (a.iter == 0) { st->loss_initial = loss; s->loss_initial = loss; s->loss_final = loss; }
+    s->grad_norm_final = gn;
+    *newton_goes_on(st, a.iter) = cg_on;
+    if (cg_on == 0) {
+      st->cg_active = 0;
+    } else if (a.iter < NADMM_TRACE_LEN) {
+      s->loss[a.iter] = loss;
+      s->grad_norm[a.iter] = gn;
+    }
+  }
+}
+// The head of an iteration that is not entered: CG stays inactive, the next iteration is not entered either.
+inline __host__ __device__ void newton_head_skipped(const NewtonHeadArgs& a) {
+  a.st->cgs[0] = CgSlot{0.0, 0, 0, 0, 0};
+  *newton_goes_on(a.st, a.iter) = 0;
+}
 
 struct ReduceArgs {
   const float* partial;
@@ -322,7 +362,7 @@ struct LsTailArgs {
 };
 hipError_t launch_ls_tail(const LsTailArgs& a, hipStream_t st);
 
-// outer_flag, if non-NULL, is copied into newton_active: a stopped outer iteration turns the local solve into no-ops
+// outer_flag, if non-NULL, is copied into the words of newton_entered: a stopped outer iteration turns the local solve into no-ops
 hipError_t launch_state_init(DevState* st, const int32_t* outer_flag, hipStream_t stream);
 
 // ---- ADMM outer solver (nadmm_admm.hip) ----

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(THREADS) void small_solve_kernel(const SmallSolve c
   constexpr int DEPTH = THREADS <= 256 ? R : 2;    // chunks of rows in flight while they are staged
   if (c.outer_flag != nullptr && *c.outer_flag == 0) {  // the outer iteration has stopped: the solve is not made
     if (c.newton && threadIdx.x == 0) {
-      c.st->newton_active = 0;
+      c.st->newton_even = 0;
       c.st->cg_active = 0;
     }
     return;
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(THREADS) void small_solve_kernel(const SmallSolve c
   if (t == 0) {
     st->loss = loss; st->gg = gg; st->rr = rr; st->gg_cg = gg; st->loss_new = loss_new; st->loss_initial = loss_initial;
     st->alpha = alpha;
-    st->newton_active = newton_active; st->cg_active = active; st->cg_iters = iters; st->armijo_ok = ok; st->ls_evals = evals;
+    st->newton_even = newton_active; st->cg_active = active; st->cg_iters = iters; st->armijo_ok = ok; st->ls_evals = evals;
     nadmm_stats* s = &st->stats;
     s->newton_iters = s_newton; s->cg_iters_total = s_cg; s->ls_evals_total = s_ls; s->armijo_failed = s_failed;
     s->loss_initial = loss_initial; s->loss_final = s_loss_final; s->grad_norm_final = s_gn;

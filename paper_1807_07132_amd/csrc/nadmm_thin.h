@@ -270,8 +270,6 @@ __device__ __forceinline__ float head_from_partials(const ThinArgs& ta, bool wri
       h.r[e] = -g;
       h.dvec[e] = -g;
     }
-    // (the flag that newton_head_scalars lowers at the end of the iteration is read by the other workgroups of this kernel; whether
-    // they see it before or after, they have nothing to do then: go is false for all)
     if (e == 0) newton_head_scalars(h, gg, (double)h.scale * data + pen);
   }
   return -g;
@@ -296,7 +294,7 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
   RowArgs a = ta.r;
   a.kind = OP == kHvX || OP == kHvCg || OP == kHvHead ? kRowsHv : (OP == kGrad ? kRowsGrad : (OP == kLoss ? kRowsLoss : (OP == kLogits || OP == kLogitsCg ? kRowsLogits : kRowsSearch)));
   if (a.flag != nullptr && *a.flag == 0) {
-    if (OP == kHvHead && blockIdx.x == 0 && threadIdx.x == 0) ta.head.st->cgs[0] = CgSlot{0.0, 0, 0, 0, 0};  // a stopped Newton iteration leaves CG inactive
+    if (OP == kHvHead && blockIdx.x == 0 && threadIdx.x == 0) newton_head_skipped(ta.head);
     return;
   }
   extern __shared__ __attribute__((aligned(16))) float tile[];  // [wave][64 rows]

@@ -102,7 +102,7 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a);  // d
 template <bool FINISH>
 __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (FINISH && blockIdx.x == gridDim.x - 1) {  // the workgroup beyond the last 32 elements
-    if (a.has_head != 0) newton_head_body(a.head);  // looks at the state's own activity flag
+    if (a.has_head != 0) newton_head_body(a.head);  // goes by the same flag, newton_entered
     else if (a.flag == nullptr || *a.flag != 0) reduce_loss_finish_role(a);
     return;
   }
@@ -332,7 +332,7 @@ __global__ void state_init_kernel(DevState* st, const int32_t* outer_flag) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   st->loss = 0.0; st->gg = 0.0; st->rr = 0.0; st->gg_cg = 0.0; st->loss_new = 0.0; st->loss_initial = 0.0;
   st->alpha = 0.f;
-  st->newton_active = outer_flag ? *outer_flag : 1; st->cg_active = st->newton_active; st->cg_iters = 0; st->armijo_ok = 1; st->ls_evals = 0;
+  st->newton_even = st->newton_odd = outer_flag ? *outer_flag : 1; st->cg_active = st->newton_even; st->cg_iters = 0; st->armijo_ok = 1; st->ls_evals = 0;
   st->cg_go = 0; st->cg_ok = 1; st->cg_alpha = 0.f; st->rr_prev = 0.0;
   nadmm_stats* s = &st->stats;
   s->newton_iters = 0; s->cg_iters_total = 0; s->ls_evals_total = 0; s->armijo_failed = 0;
@@ -349,9 +349,8 @@ __global__ void state_init_kernel(DevState* st, const int32_t* outer_flag) {
 __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a) {
   const float rho_ = a.rho_scale != nullptr ? a.rho * *a.rho_scale : a.rho;  // outer solver: common factor on the penalty
   __shared__ double sm[17];
-  DevState* st = a.st;
-  if (a.newton_mode && st->newton_active == 0) {
-    if (threadIdx.x == 0) st->cgs[0] = CgSlot{0.0, 0, 0, 0, 0};  // a stopped Newton iteration leaves CG inactive
+  if (a.newton_mode && *newton_entered(a.st, a.iter) == 0) {
+    if (threadIdx.x == 0) newton_head_skipped(a);
     return;
   }
 

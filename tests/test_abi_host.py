@@ -311,6 +311,100 @@ int main() {  // every one of these is refused before anything is launched: no d
 }
 """
 
+# The driver of Algorithm 3 with stand-ins for the kernel launches, on host memory: every sweep, reduction and line search goes by the
+# word that is set at its launch, and the head of iteration `stop` finds the gradient finished.
+NEWTON_DRIVER = r"""
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <initializer_list>
+#include "nadmm_internal.h"
+namespace nadmm {
+static int stop_at, grads, directions, steps, heads, shared;  // shared: heads that wrote a word their own kernel goes by
+static double last_gg;
+static bool on(const int32_t* flag) { return flag == nullptr || *flag != 0; }
+static void head(const NewtonHeadArgs& h, const int32_t* flag) {
+  const int32_t before = flag != nullptr ? *flag : 0;
+  if (*newton_entered(h.st, h.iter) == 0) newton_head_skipped(h);
+  else newton_head_scalars(h, h.iter == stop_at ? last_gg : 1.0, 2.0);
+  if (flag != nullptr) {
+    shared += *flag != before || flag != newton_entered(h.st, h.iter);
+    ++heads;
+  }
+}
+static hipError_t rows(const RowArgs& a) {
+  if (on(a.flag) && a.kind == kRowsGrad) ++grads;
+  return hipSuccess;
+}
+hipError_t launch_state_init(DevState* st, const int32_t* outer, hipStream_t) {
+  st->newton_even = st->newton_odd = outer != nullptr ? *outer : 1;
+  return hipSuccess;
+}
+hipError_t launch_generic_rows(const RowArgs& a, hipStream_t) { return rows(a); }
+hipError_t launch_generic_cols(const ColArgs&, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_fused(const RowArgs& a, float*, int, hipStream_t, const CgPend*, const SearchArgs*) { return rows(a); }
+hipError_t launch_narrow(const RowArgs& a, float*, int, hipStream_t, const CgPend*) { return rows(a); }
+hipError_t launch_wide(const RowArgs& a, void*, bool, float*, int, hipStream_t) { return rows(a); }
+hipError_t launch_wide_direction(const CgUpdateArgs&, const Shape&, void*, hipStream_t) { return hipSuccess; }
+hipError_t launch_sliced_logits(const RowArgs& a, hipStream_t) { return rows(a); }
+hipError_t launch_sliced_cols(const RowArgs&, const float*, float*, hipStream_t) { return hipSuccess; }
+hipError_t launch_thin(const RowArgs& a, float*, int, hipStream_t, const CgPend* cg, const ReduceArgs*, const NewtonHeadArgs* h, const SearchArgs*) {
+  rows(a);
+  if (h != nullptr) head(*h, a.flag);
+  if (cg != nullptr) {
+    if (cg->st->cgs[cg->slot_in].active != 0 && cg->final_p == 0) ++directions;
+    cg->st->cgs[cg->slot_in ^ 1] = cg->st->cgs[cg->slot_in];
+  }
+  return hipSuccess;
+}
+hipError_t launch_reduce_out(const ReduceArgs& r, hipStream_t) {
+  if (r.has_head != 0) head(r.head, r.flag);
+  return hipSuccess;
+}
+hipError_t launch_newton_head(const NewtonHeadArgs& h, hipStream_t) { head(h, nullptr); return hipSuccess; }
+hipError_t launch_cg_reduce_update(const ReduceArgs&, const CgUpdateArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_cg_update(const CgUpdateArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_cg_residual(const CgUpdateArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_cg_pending_finish(const CgPend&, hipStream_t) { return hipSuccess; }
+hipError_t launch_ls_eval(const LsEvalArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_ls_tail(const LsTailArgs& a, hipStream_t) { steps += on(a.flag); return hipSuccess; }
+}  // namespace nadmm
+using namespace nadmm;
+int main() {
+  struct Case { int64_t n; int32_t p, C, path; } cases[] = {{5000, 28, 2, 0}, {5000, 29, 3, 0}, {60000, 784, 10, 0}, {100000, 70, 7, 0},
+                                                            {5000, 90, 20, 0}, {5000, 1100, 4, 0}, {5000, 28, 2, 1}};
+  alignas(16) static float v[4];
+  static int32_t labels[4];
+  for (const Case& c : cases)
+    for (int max_cg : {0, 1, 3})
+      for (double gg : {0.0, 1e-12, std::nan("")})
+        for (stop_at = 0; stop_at <= 4; ++stop_at) {  // 4: never
+          nadmm_problem prob{};
+          prob.d_A = v; prob.n = c.n; prob.p = c.p; prob.lda = c.p; prob.d_labels = labels; prob.C = c.C;
+          prob.loss_scale = 1.f; prob.rho = 1.f;
+          nadmm_params params{};
+          params.max_newton = 4; params.max_cg = max_cg; params.max_ls = 10; params.grad_tol = 1e-3f;
+          params.armijo_beta = 1e-4f; params.backtrack_gamma = 0.5f;
+          nadmm_set_kernel_path(c.path);
+          const size_t bytes = nadmm_workspace_bytes(&prob, &params);
+          void* ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+          grads = directions = steps = shared = 0;
+          last_gg = gg;
+          const int rc = nadmm_local_newton(&prob, v, &params, nullptr, ws, bytes, nullptr);
+          std::free(ws);
+          const bool thin = c.path == 0 && c.p <= 32;
+          if (rc != 0 || shared != 0 || steps != stop_at || grads != (stop_at < 4 ? stop_at + 1 : 4) ||
+              (thin && max_cg == 3 && directions != 2 * stop_at)) {
+            std::printf("n %ld p %d C %d path %d cg %d stop %d: rc %d shared %d steps %d grads %d directions %d\n", (long)c.n, c.p, c.C, c.path, max_cg,
+                        stop_at, rc, shared, steps, grads, directions);
+            return 1;
+          }
+        }
+  std::printf("heads %d\n", heads);  // made by a workgroup of another kernel
+  return heads > 0 ? 0 : 1;
+}
+"""
+
 LDS_MASK = r"""
 #include <thread>
 #include <vector>
@@ -337,6 +431,15 @@ def test_a_pending_cg_update_that_a_kernel_would_not_apply_is_refused(lib, tmp_p
     subprocess.check_call([*GXX, str(src), nadmm.LIB_PATH, f"-Wl,-rpath,{os.path.dirname(nadmm.LIB_PATH)}", "-Wl,--allow-shlib-undefined",
                            "-o", str(exe)])
     assert subprocess.check_output([str(exe)], timeout=60).split() == [b"1"] * 13      # hipErrorInvalidValue
+
+
+def test_no_kernel_writes_the_word_its_workgroups_go_by(lib, tmp_path):
+    src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
+    src.write_text(NEWTON_DRIVER)
+    subprocess.check_call([*GXX, "-O1", str(src), nadmm.LIB_PATH, f"-Wl,-rpath,{os.path.dirname(nadmm.LIB_PATH)}", "-Wl,--allow-shlib-undefined",
+                           "-o", str(exe)])
+    run = subprocess.run([str(exe)], timeout=60, capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
 
 
 def test_lds_limit_is_noted_without_a_race(tmp_path):

@@ -748,6 +748,27 @@ def test_small_cg_with_few_iterations(n, p, C, k):
     assert st["cg_iters"] == [k, k]
 
 
+# The stopping test of Algorithm 3 at every iteration of a solve: the iterate is that of a solve of so many iterations, bit for bit, and
+# nothing after it takes a step.  The heads of kernels of their own, beside the first reduction and in the first CG sweep.
+@pytest.mark.parametrize("n,p,C,path", [(2100, 28, 2, 3), (70001, 21, 3, 3), (3000, 100, 7, 2), (9001, 260, 10, 2), (40000, 64, 3, 2), (700, 90, 20, 4),
+                                        (300, 1100, 4, 4), (300, 40, 3, 1)])
+def test_newton_ends_at_every_iteration(n, p, C, path):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    gp = nadmm.Problem.from_workload(w)
+    force_path(gp, path)
+    X = dev(w.X0)
+    st = nadmm.nadmm_local_newton(gp, X, nadmm.make_params(5, 2, 10))
+    gn = st["grad_norm"]
+    assert all(b < 0.99 * a for a, b in zip(gn, gn[1:]))
+    for stop in range(5):
+        Xs, Xr = dev(w.X0), dev(w.X0)
+        got = nadmm.nadmm_local_newton(gp, Xs, nadmm.make_params(8, 2, 10, grad_tol=1.001 * gn[stop]))
+        ref = nadmm.nadmm_local_newton(gp, Xr, nadmm.make_params(stop, 2, 10))
+        assert torch.equal(Xs, Xr)
+        assert got["newton_iters"] == stop and got["cg_iters_total"] == ref["cg_iters_total"] and got["ls_evals_total"] == ref["ls_evals_total"]
+        assert got["grad_norm_final"] == gn[stop] and (stop == 0 or got["loss_final"] == ref["loss_final"])
+
+
 # Rounds of the kernel for narrow rows dealt out to its workgroups: the last counts before and the first with 512 uneven ones (3 to 8
 # rounds of 256, 128 and 64 rows), one row more than a whole number of rounds, one row less, the first count past 8.
 @pytest.mark.parametrize("n,p,C", [(65536, 100, 3), (65537, 100, 3), (98305, 70, 17), (131071, 65, 4), (131073, 40, 3), (262145, 9, 6), (262145, 70, 3)])
