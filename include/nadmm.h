@@ -29,11 +29,9 @@
  *     multiple of 4 (an n x lda allocation always is; what those elements hold does not matter).  Which kernels run
  *     depends on shape, stride and alignment:
  *       p <= 32 and C-1 <= 3, with p > q - 4, q (C-1) <= 64 for q = 4 ceil(lda/4) (so at most 3 elements between rows), and
- *         n lda >= 8: the thin-data kernel, one lane per sample, except 16-byte aligned rows with elements between them, q (C-1) > 16
- *         and 2048 < n < 65536 (393216 where q (C-1) = 64); a CG or Newton solve on up to 2048 rows
- *         is one launch;
- *       these, and other rows of up to 128 columns (96 with more than 16 free classes): a matrix-core kernel with one wave per
- *         tile, except other rows of C-1 <= 16 that are 16-byte aligned, or of 48 columns and more, and fewer than 32768
+ *         n lda >= 8: the thin-data kernel, one lane per sample; a CG or Newton solve on up to 2048 rows is one launch;
+ *       other rows of up to 128 columns (96 with more than 16 free classes): a matrix-core kernel with one wave per
+ *         tile, except rows of C-1 <= 16 that are 16-byte aligned, or of 48 columns and more, and fewer than 32768
  *         (p <= 64) or 49152;
  *       p <= 960 and C-1 <= 16: the single-pass matrix-core kernel, 55-60 % of the HBM roofline with aligned rows;
  *       p <= 3072 and C-1 <= 16, or p <= 2048 and up to 32 free classes: a single-pass kernel for wide rows, 33-50 % (CG at
@@ -333,7 +331,10 @@ int nadmm_admm_solve(const nadmm_problem* h_workers, int32_t N, float lambda, fl
  * thread makes afterwards, workspace sizes included), so the library has no state shared between threads:
  *   0 = automatic (default), 1 = two-pass fp32 vector kernels (any shape),
  *   2 = single-pass matrix-core kernels (C-1 <= 16, p <= 960; any row stride, A 4-byte aligned;
- *       p >= 4 unless the rows are 16-byte aligned; the kernel for narrow rows or the fused one), 3 = thin-data single-pass kernel (p <= 32, C-1 <= 3,
+ *       p >= 4 unless the rows are 16-byte aligned; the kernel for narrow rows or the fused one).  It is also the number of
+ *       16-byte aligned rows of the thin-data kernel with elements between them where, with q as above, q (C-1) > 16 and
+ *       2048 < n < 65536, or 393216 where q (C-1) = 64, which the kernel for narrow rows made once,
+ *   3 = thin-data single-pass kernel (p <= 32, C-1 <= 3,
  *       at most 3 elements between rows, A 4-byte aligned; exactly: above), 4 = matrix-core kernels for wide rows and many classes, in one pass or two sweeps (the automatic
  *       choice where 2 and 3 do not apply: C-1 <= 32; any row stride, A 4-byte aligned; p >= 4 unless
  *       the rows are 16-byte aligned), 5 = sparse-storage kernels (the only path for a problem with `sparse` set,

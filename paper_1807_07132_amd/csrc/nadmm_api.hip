@@ -39,7 +39,7 @@ struct Layout {
   int fused_parts, thin_parts, sliced_parts, sliced_loss, wide_parts;
   bool fused_ok, thin_ok, sliced_ok;
   bool thin_any;  // thin rows other than those of thin_ok: any alignment, a few elements of padding
-  bool thin_auto; // and the thin-data kernel is the automatic choice for them
+  bool thin_as_2; // of those, the ones whose path number is 2 (thin_numbered_2)
   bool narrow;   // paths 2 and 4 take the kernel for narrow rows (nadmm_narrow.hip) where it supports the sweep
   int narrow_parts;
   bool wide;     // path 4 makes its sweeps with a transpose product in a single pass (nadmm_wide.hip)
@@ -99,9 +99,9 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   if (L->sparse) L->gen_chunks = 1;  // the column view gives every element of A^T D whole
   L->thin_ok = !L->sparse && thin_supported(s, p->lda, p->d_A);
   L->thin_any = !L->sparse && !L->thin_ok && thin_general_supported(s, p->lda, p->d_A);
-  L->thin_auto = L->thin_any && !(aligned_rows(p) && thin_padded_narrow(s, p->lda));
+  L->thin_as_2 = L->thin_any && aligned_rows(p) && thin_numbered_2(s, p->lda);
   L->narrow = !L->sparse && narrow_supported(s, p->lda, p->d_A) &&
-              (s.NC > 16 || !aligned_or_long_rows(p) || s.n >= narrow_min_rows(s.p) || (L->thin_any && !L->thin_auto));
+              (s.NC > 16 || !aligned_or_long_rows(p) || s.n >= narrow_min_rows(s.p));
   L->narrow_parts = L->narrow ? narrow_num_partials(s) : 0;
   if (wg_cap > 0 && L->narrow_parts > wg_cap) L->narrow_parts = wg_cap;
   L->mc_auto = L->sparse || aligned_or_long_rows(p) || L->narrow;
@@ -177,7 +177,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   }
   L->total_base = off;
   // 2 max_cg n (C-1) floats written and read instead of n p floats read: taken with a margin
-  const bool fused_default = L->fused_ok && (g_path == 2 || (g_path == 0 && !L->thin_ok && !L->thin_auto && L->mc_auto));
+  const bool fused_default = L->fused_ok && !L->thin_as_2 && (g_path == 2 || (g_path == 0 && !L->thin_ok && !L->thin_any && L->mc_auto));
   L->hist_bufs = (!hv_only && fused_default && max_cg >= 1 && max_cg <= kCgHist && (int64_t)3 * max_cg * s.NC <= s.p) ? max_cg : 0;
   L->hist = off; off += (size_t)L->hist_bufs * rows;
   L->total = off;
@@ -222,7 +222,7 @@ int scratch_on_current_device(void** out) {
   return NADMM_OK;
 }
 
-// 1 = two-pass vector kernels, 2 = single-pass matrix-core kernels (fused, narrow rows), 3 = thin-data single pass,
+// The kernels that run.  1 = two-pass vector kernels, 2 = single-pass matrix-core kernels (fused, narrow rows), 3 = thin-data single pass,
 // 4 = wide rows and many classes on matrix cores (wide rows in one pass, narrow rows, column-sliced two sweeps), 5 = sparse storage
 int choose_path(const Layout& L, int* path) {
   if (L.sparse) {
@@ -234,7 +234,7 @@ int choose_path(const Layout& L, int* path) {
   if (g_path == 1) { *path = 1; return NADMM_OK; }
   if (g_path == 2) {
     if (!L.fused_ok) return NADMM_EUNSUPPORTED;
-    *path = 2;
+    *path = L.thin_as_2 ? 3 : 2;
     return NADMM_OK;
   }
   if (g_path == 3) {
@@ -247,7 +247,7 @@ int choose_path(const Layout& L, int* path) {
     *path = 4;
     return NADMM_OK;
   }
-  *path = L.thin_ok || L.thin_auto ? 3 : (L.fused_ok && L.mc_auto ? 2 : (L.sliced_ok && L.mc_auto ? 4 : 1));
+  *path = L.thin_ok || L.thin_any ? 3 : (L.fused_ok && L.mc_auto ? 2 : (L.sliced_ok && L.mc_auto ? 4 : 1));
   return NADMM_OK;
 }
 
@@ -881,7 +881,8 @@ int nadmm_query_kernel_path(const nadmm_problem* prob) {
   make_layout(prob, &L);
   int path = 0;
   rc = choose_path(L, &path);
-  return rc != NADMM_OK ? rc : path;
+  if (rc != NADMM_OK) return rc;
+  return path == 3 && L.thin_as_2 && g_path != 3 ? 2 : path;
 }
 
 size_t nadmm_workspace_bytes(const nadmm_problem* prob, const nadmm_params* params) {

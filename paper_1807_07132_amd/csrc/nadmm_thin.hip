@@ -47,12 +47,14 @@ bool thin_general_supported(const Shape& s, int64_t lda, const void* A) {
   return s.n * lda >= 8 && (s.n - 1) * lda + s.p >= 4 && (reinterpret_cast<uintptr_t>(A) & 3) == 0;
 }
 
-// Rows with padding that are 16-byte aligned, of more than one operand piece, go to the narrow-row kernel on up to 65536 rows (393216
-// with 32 x 2 accumulators), which works to the same accuracy (Hessian-vector products within 4.0e-8 to 6.0e-8 of 64 bits, here
-// 3.5e-8 to 5.8e-8).  The line was drawn when this path took such rows through registers and made the CG update in a kernel of its
-// own; it is part of the path numbers that callers may rely on and stays where it is.  Measured now, narrow-row kernel against this one
-// (us): lda = 32, C = 3: 4000 rows, 6 CG iterations 72 : 57, 300000 rows gradient 32 : 16, 6 CG iterations 141 : 85.
-bool thin_padded_narrow(const Shape& s, int64_t lda) {
+// Rows with padding that are 16-byte aligned, of more than one operand piece, on up to 65535 rows (393215 with 32 x 2 accumulators):
+// the narrow-row kernel made them under path number 2 until this kernel came to stream chunks straight to LDS and to defer the CG update
+// for all rows.  The number is part of what callers may rely on, the kernel is this one: nothing is faster on the other (505 shapes, 2049
+// to 393215 rows; single sweeps of up to 65535 rows equal, since launches bound them).  Narrow-row kernel against this one (us): lda = 32,
+// C = 3: 5000 rows, 6 CG iterations 64.9 : 54.6; 200000 rows, gradient 24.6 : 15.3, 6 CG iterations 112 : 62.5; lda = 8, C = 4: 40000 rows, 2 Newton
+// iterations of 5 CG iterations 161 : 117, a line search 20.3 : 17.7.  Both work to the same accuracy (Hessian-vector products within
+// 4.0e-8 to 6.0e-8 of 64 bits there, 3.5e-8 to 5.8e-8 here).
+bool thin_numbered_2(const Shape& s, int64_t lda) {
   return s.n > 2048 && lda * s.NC > 16 && s.n < (lda * s.NC < 64 ? 65536 : 393216);
 }
 

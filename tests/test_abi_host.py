@@ -234,7 +234,7 @@ def test_kernel_path_switch(lib):
 # the same path with the same workspace.
 @pytest.mark.parametrize("kw,path", [
     (dict(n=1375000, p=29, Cc=2), 3), (dict(n=1000, p=30, Cc=2), 3),
-    # 16-byte aligned rows with padding: the kernel for narrow rows on 2049 to 65535 (393215) of them with more than 16 padded unknowns
+    # 16-byte aligned rows with padding: number 2 on 2049 to 65535 (393215) of them with more than 16 padded unknowns
     (dict(n=2048, p=30, lda=32, Cc=2), 3), (dict(n=2049, p=30, lda=32, Cc=2), 2), (dict(n=65535, p=15, lda=16, Cc=4), 2),
     (dict(n=65536, p=15, lda=16, Cc=4), 3), (dict(n=393215, p=30, lda=32, Cc=3), 2), (dict(n=393216, p=30, lda=32, Cc=3), 3),
     (dict(n=5000, p=15, lda=16, Cc=2), 3), (dict(n=5000, p=5, lda=8, Cc=4), 2), (dict(n=5000, p=5, lda=8, Cc=3), 3),
@@ -405,6 +405,40 @@ int main() {
 }
 """
 
+# Which kernels a gradient launches, with stand-ins for the launches.  Arguments: n p lda C, path to force.
+ROUTES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "nadmm_internal.h"
+namespace nadmm {
+static const char* taken = "other";
+hipError_t launch_thin(const RowArgs&, float*, int, hipStream_t, const CgPend*, const ReduceArgs*, const NewtonHeadArgs*, const SearchArgs*) {
+  taken = "thin";
+  return hipSuccess;
+}
+hipError_t launch_narrow(const RowArgs&, float*, int, hipStream_t, const CgPend*) { taken = "narrow"; return hipSuccess; }
+hipError_t launch_fused(const RowArgs&, float*, int, hipStream_t, const CgPend*, const SearchArgs*) { taken = "fused"; return hipSuccess; }
+hipError_t launch_reduce_out(const ReduceArgs&, hipStream_t) { return hipSuccess; }
+}  // namespace nadmm
+int main(int argc, char** argv) {
+  alignas(16) static float v[4];
+  static double loss;
+  static int32_t labels[4];
+  for (int i = 1; i + 4 < argc; i += 5) {
+    nadmm_problem prob{};
+    prob.d_A = v; prob.n = std::atoll(argv[i]); prob.p = std::atoi(argv[i + 1]); prob.lda = std::atoi(argv[i + 2]); prob.C = std::atoi(argv[i + 3]);
+    prob.d_labels = labels; prob.loss_scale = 1.f; prob.rho = 1.f;
+    nadmm_set_kernel_path(std::atoi(argv[i + 4]));
+    const size_t bytes = nadmm_workspace_bytes(&prob, nullptr);
+    void* ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+    const int rc = nadmm_loss_grad(&prob, v, &loss, v, ws, bytes, nullptr);
+    std::printf("%s%d ", nadmm::taken, rc != 0 ? rc : nadmm_query_kernel_path(&prob));
+    std::free(ws);
+  }
+  return 0;
+}
+"""
+
 LDS_MASK = r"""
 #include <thread>
 #include <vector>
@@ -440,6 +474,22 @@ def test_no_kernel_writes_the_word_its_workgroups_go_by(lib, tmp_path):
                            "-o", str(exe)])
     run = subprocess.run([str(exe)], timeout=60, capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
+
+
+def test_aligned_thin_rows_with_padding_take_the_thin_kernel_under_either_number(lib, tmp_path):
+    src, exe = tmp_path / "routes.cpp", tmp_path / "routes"
+    src.write_text(ROUTES)
+    subprocess.check_call([*GXX, "-O1", str(src), nadmm.LIB_PATH, f"-Wl,-rpath,{os.path.dirname(nadmm.LIB_PATH)}", "-Wl,--allow-shlib-undefined",
+                           "-o", str(exe)])
+    cases, want = [], []
+    for n, p, lda, cls, number in ((2048, 30, 32, 2, 3), (2049, 30, 32, 2, 2), (65535, 15, 16, 4, 2), (65536, 15, 16, 4, 3), (393215, 30, 32, 3, 2),
+                                   (393216, 30, 32, 3, 3), (5000, 5, 8, 4, 2), (5000, 5, 8, 3, 3), (40000, 30, 32, 3, 2)):
+        cases += [(n, p, lda, cls, path) for path in ((0, 2, 3) if number == 2 else (0, 3))]
+        want += ["thin2", "thin2", "thin3"] if number == 2 else ["thin3", "thin3"]
+    cases += [(2048, 30, 32, 2, 2), (65536, 15, 16, 4, 2), (5000, 32, 32, 2, 2)]      # the matrix-core kernels by force, as for dense rows
+    want += ["fused2", "narrow2", "fused2"]
+    got = subprocess.check_output([str(exe), *[str(v) for c in cases for v in c]], timeout=60, text=True).split()
+    assert got == want, list(zip(cases, got, want))
 
 
 def test_lds_limit_is_noted_without_a_race(tmp_path):

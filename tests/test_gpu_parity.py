@@ -857,8 +857,8 @@ def test_small_newton(n, p, C, shift):
 
 
 # Thin rows with a stride of whole quads and padding, 16-byte aligned or not (A four bytes further): the thin-data kernel by force, which
-# lays them out row by row in LDS, and the automatic choice (the kernel for narrow rows on 2049 to 65535 aligned ones).
-# Rows at the edges of a chunk of 256, the last piece of the matrix, every number of quads.
+# lays them out row by row in LDS, and the automatic choice (the same kernel, under path number 2 on 2049 to 65535 aligned ones).
+# Rows at the edges of four chunks of 64, the last piece of the matrix, every number of quads.
 @pytest.mark.parametrize("path", [0, 3])
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("n,p,lda,C", [(3, 3, 4, 4), (255, 5, 8, 3), (256, 8, 8, 2), (257, 11, 12, 4), (2048, 13, 16, 3), (2049, 16, 16, 2), (511, 17, 20, 4),
