@@ -437,7 +437,7 @@ __global__ __launch_bounds__(THREADS) void thin_stream_kernel(const ThinArgs ta)
             zb = c == label ? zz[c] : zb;  // the reference class has logit 0
           }
           if constexpr (NC == 1) {
-            es = 1.f + expf(-fabsf(zz[0]));  // of exp(-M) and exp(z - M) one is exp(0), the other exp(-|z|)
+            es = 1.f + expf(fmaf(-2.f, M, zz[0]));  // of exp(-M) and exp(z - M) one is exp(0), the other exp(-|z|); NaN at z = +inf, as everywhere else
           } else {
             es = expf(-M);
 #pragma unroll

@@ -230,6 +230,29 @@ def test_line_search_in_the_sweep(n, p, C, path):
         assert rel_l2(host(X), oracle_newton_following(op, w.X0, w, st["alpha"])[0]) <= TOL_ITERATE
 
 
+# A direction along which one row's logit overflows: its loss is NaN where that logit is +inf, on every path, and a step size with it is taken
+# (Algorithm 2's test does not fail against NaN).  Path 1 evaluates stored logits.
+@pytest.mark.parametrize("label", ["first", "reference"])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("n,p,C", [(3000, 28, 2), (2500, 29, 2), (50, 8, 2), (3000, 12, 4)])
+def test_line_search_where_a_logit_overflows(n, p, C, sign, label):
+    w = workloads.generic(n, p, C, seed=n + p)
+    w.A[n // 2, :2] = 4.0
+    w.b[n // 2] = 0 if label == "first" else C - 1
+    X, pdir = np.zeros_like(w.X0), np.zeros_like(w.X0)
+    pdir[:2, 0] = sign * 6e37                  # 2 * 4 * 6e37 is beyond float32
+    w.A[np.arange(n) != n // 2, :2] = 0.0
+    gp = nadmm.Problem.from_workload(w)
+    got = {}
+    for path in (3, 1):
+        force_path(gp, path)
+        for f0 in (0.0, 1e80):                 # below and above what the penalty adds
+            got[path, f0] = [v.item() for v in nadmm.nadmm_line_search(gp, dev(X), dev(pdir), dev(X), f0, 1e-4, 0.5, 3)]
+    for f0 in (0.0, 1e80):
+        assert got[3, f0] == pytest.approx(got[1, f0], rel=1e-6, nan_ok=True), f0
+        assert math.isnan(got[1, f0][1]) == (sign > 0)
+
+
 NEWTON_CASES = ["tiny", "image_like_3k", "wide_700", "tall_binary_50k", "large_multiclass_900", "ragged_1237x45_C5",
                 "fused_any_3000x785_C10", "sliced_any_700x1101_C4",
                 "single_row_1x7_C4", "fused_9001x260_C10", "fused_4100x36_C17", "thin_70001x32_C3", "thin_300x12_C4", "sliced_3000x100_C26",
