@@ -428,13 +428,15 @@ bool narrow_takes(const Shape& s, bool has_x, bool has_v) { return s.NC <= 16 ||
 // rounds each, 512 of which some make a round less, since then the compute units that had a single one count: 100000 x 70, C = 7,
 // Hessian-vector product 18.9 -> 16.9 us, 10 CG iterations 184 -> 172 us (391 workgroups of 4 rounds before); 150000 x 64, C = 7:
 // 19.8 -> 17.2 us.  With 2 rounds the larger number of partial sums costs what it gains (50000 x 70: 14.7 : 14.9), beyond 8 equal.
-// More than 16 free classes stay: their scratch is close to what nadmm_hessvec_static holds.
+// With two blocks of classes the same (72 shapes of 3 to 8 rounds: gradient, product and 4 CG iterations 0.86 to 1.01 of the time with
+// equal rounds): 137625 x 16, C = 20, product 19.8 -> 17.4 us, gradient 21.8 -> 18.8; 101580 x 84, C = 29, gradient 24.8 -> 22.8, 4 CG
+// iterations 137 -> 132; 232652 x 64, C = 22, product 31.3 -> 29.3.
 int narrow_num_partials(const Shape& s) {
   const int64_t round = (int64_t)kWaves * 16 * tiles_of(steps_of(s.p), s.NC > 16 ? 2 : 1);
   const int64_t rounds = (s.n + round - 1) / round;
   const int64_t g = rounds < 512 ? rounds : 512;
   const int64_t per = (rounds + g - 1) / g;
-  if (s.NC <= 16 && per >= 3 && per <= 8) return 512;
+  if (per >= 3 && per <= 8) return 512;
   return (int)((rounds + per - 1) / per);
 }
 

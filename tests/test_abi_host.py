@@ -439,6 +439,28 @@ int main(int argc, char** argv) {
 }
 """
 
+PARTIALS = r"""
+#include <cstdio>
+#include "nadmm_internal.h"
+int main() {  // workgroups of the kernel for narrow rows, one and two blocks of classes, at the edges of 2 to 9 rounds each
+  for (int p : {9, 32, 33, 64, 65, 96})
+    for (int NC : {3, 16, 17, 32})
+      for (int rounds = 1; rounds <= 9; ++rounds)
+        for (int past : {0, 1}) {
+          const int64_t round = p <= 32 ? (NC > 16 ? 128 : 256) : (p <= 64 && NC <= 16 ? 128 : 64);
+          nadmm::Shape s{};
+          s.n = 512 * round * rounds + past; s.p = p; s.NC = NC; s.d = (int64_t)p * NC;
+          const int per = rounds + past, total = 512 * rounds + past;
+          const int want = per >= 3 && per <= 8 ? 512 : (total + per - 1) / per;  // else equally many rounds each
+          if (nadmm::narrow_num_partials(s) != want) {
+            std::printf("p %d NC %d n %lld: %d, not %d\n", p, NC, (long long)s.n, nadmm::narrow_num_partials(s), want);
+            return 1;
+          }
+        }
+  return 0;
+}
+"""
+
 LDS_MASK = r"""
 #include <thread>
 #include <vector>
@@ -490,6 +512,15 @@ def test_aligned_thin_rows_with_padding_take_the_thin_kernel_under_either_number
     want += ["fused2", "narrow2", "fused2"]
     got = subprocess.check_output([str(exe), *[str(v) for c in cases for v in c]], timeout=60, text=True).split()
     assert got == want, list(zip(cases, got, want))
+
+
+def test_narrow_rows_workgroups_of_one_and_two_blocks_of_classes(lib, tmp_path):
+    src, exe = tmp_path / "partials.cpp", tmp_path / "partials"
+    src.write_text(PARTIALS)
+    subprocess.check_call([*GXX, str(src), nadmm.LIB_PATH, f"-Wl,-rpath,{os.path.dirname(nadmm.LIB_PATH)}", "-Wl,--allow-shlib-undefined",
+                           "-o", str(exe)])
+    run = subprocess.run([str(exe)], timeout=60, capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
 
 
 def test_lds_limit_is_noted_without_a_race(tmp_path):

@@ -793,8 +793,10 @@ def test_newton_ends_at_every_iteration(n, p, C, path):
 
 
 # Rounds of the kernel for narrow rows dealt out to its workgroups: the last counts before and the first with 512 uneven ones (3 to 8
-# rounds of 256, 128 and 64 rows), one row more than a whole number of rounds, one row less, the first count past 8.
-@pytest.mark.parametrize("n,p,C", [(65536, 100, 3), (65537, 100, 3), (98305, 70, 17), (131071, 65, 4), (131073, 40, 3), (262145, 9, 6), (262145, 70, 3)])
+# rounds of 256, 128 and 64 rows), one row more than a whole number of rounds, one row less, the first count past 8.  The same with two
+# blocks of classes (rounds of 128 and 64 rows).
+@pytest.mark.parametrize("n,p,C", [(65536, 100, 3), (65537, 100, 3), (98305, 70, 17), (131071, 65, 4), (131073, 40, 3), (262145, 9, 6), (262145, 70, 3),
+                                   (65536, 84, 29), (65537, 84, 29), (98303, 36, 18), (131073, 9, 20), (262145, 64, 22)])
 def test_narrow_rounds(n, p, C):
     w = workloads.generic(n, p, C, seed=n % 991 + p, x_std=0.5 / math.sqrt(p), mean=True)
     gp, op = nadmm.Problem.from_workload(w), oracle_problem(w)
