@@ -403,13 +403,13 @@ hipError_t launch_fused(const RowArgs& a, float* partial, int nparts, hipStream_
 // the pending update alone (one workgroup): end of a stand-alone CG solve
 hipError_t launch_cg_pending_finish(const CgPend& c, hipStream_t st);
 
-// ---- thin-data single-pass path (nadmm_thin.hip): p <= 32, C-1 <= 3, at most 3 elements between rows ----
+// ---- thin-data single-pass path (nadmm_thin.h, nadmm_thin.hip): p <= 32, C-1 <= 3, at most 3 elements between rows ----
 bool thin_supported(const Shape& s, int64_t lda, const void* A);          // p % 4 == 0, lda == p, 16-byte aligned
 bool thin_general_supported(const Shape& s, int64_t lda, const void* A);  // other rows of up to 32 columns
 bool thin_numbered_2(const Shape& s, int64_t lda);  // of those, 16-byte aligned: whether callers know them by path number 2
 int thin_num_partials(const Shape& s);
 // cg, prev (both or neither): the sweep first applies the pending CG update, forming q = H d from the previous sweep's
-// partial sums prev->partial (prev also carries scale, lambda, rho of the linear terms); see ThinArgs in nadmm_thin.hip
+// partial sums prev->partial (prev also carries scale, lambda, rho of the linear terms); see ThinArgs in nadmm_thin.h
 hipError_t launch_thin(const RowArgs& a, float* partial, int nparts, hipStream_t st, const CgPend* cg = nullptr,
                        const ReduceArgs* prev = nullptr, const NewtonHeadArgs* head = nullptr, const SearchArgs* search = nullptr);
 // the pending update alone (one workgroup): end of a stand-alone CG solve

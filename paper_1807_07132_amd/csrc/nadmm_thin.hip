@@ -39,8 +39,9 @@ bool thin_supported(const Shape& s, int64_t lda, const void* A) {
   return true;
 }
 
-// Any other rows of up to 32 columns: at most 3 elements of padding, so that 256 rows are one
-// block of about 256 p floats; the accumulators of the padded row fit the registers.
+// Any other rows of up to 32 columns: at most 3 elements of padding, so that a chunk of 64 rows is one block of little more than
+// 64 p floats; the accumulators of the padded row fit the registers.  The limits on the smallest matrices are those of an earlier form,
+// which fetched 16 bytes at a time; the kernel does without them, but callers may go by the path numbers that follow from them.
 bool thin_general_supported(const Shape& s, int64_t lda, const void* A) {
   const int64_t pp = (lda + 3) / 4 * 4;
   if (lda < s.p || lda > 32 || s.NC > 3 || pp * s.NC > 64 || s.p <= pp - 4) return false;
@@ -50,7 +51,7 @@ bool thin_general_supported(const Shape& s, int64_t lda, const void* A) {
 // Rows with padding that are 16-byte aligned, of more than one operand piece, on up to 65535 rows (393215 with 32 x 2 accumulators):
 // the narrow-row kernel made them under path number 2 until this kernel came to stream chunks straight to LDS and to defer the CG update
 // for all rows.  The number is part of what callers may rely on, the kernel is this one: nothing is faster on the other (505 shapes, 2049
-// to 393215 rows; single sweeps of up to 65535 rows equal, since launches bound them).  Narrow-row kernel against this one (us): lda = 32,
+// to 393215 rows; single sweeps of up to 65535 rows, which launches bound, equal to 0.3 of 11 us).  Narrow-row kernel against this one (us): lda = 32,
 // C = 3: 5000 rows, 6 CG iterations 64.9 : 54.6; 200000 rows, gradient 24.6 : 15.3, 6 CG iterations 112 : 62.5; lda = 8, C = 4: 40000 rows, 2 Newton
 // iterations of 5 CG iterations 161 : 117, a line search 20.3 : 17.7.  Both work to the same accuracy (Hessian-vector products within
 // 4.0e-8 to 6.0e-8 of 64 bits there, 3.5e-8 to 5.8e-8 here).

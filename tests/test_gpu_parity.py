@@ -221,9 +221,12 @@ def test_line_search_in_the_sweep(n, p, C, path):
         for given in (math.nan, f0):
             alpha, f_new, ok = nadmm.nadmm_line_search(gp, dev(w.X0), dev(pdir), dev(g32), given, 1e-4, 0.5, max_ls)
             assert alpha.item() == a_ref and bool(ok.item()) == ok_ref
-            # the product A p takes three terms (relative error below 4 * 2^-17), and the losses here are mostly the step's own logits
-            assert rel_abs(f_new.item(), f_ref) <= 4 * 2.0 ** -17
-    for max_ls in (13, 15):  # a Newton iteration with as many step sizes as the pass that forms A p evaluates, and with two more
+            # the losses here are mostly the step's own logits: the product A p in three terms (relative error below 4 * 2^-17) on path 2,
+            # float32 sums of at most 32 products on path 3, some of whose 33 roundings of 2^-24 add up
+            assert rel_abs(f_new.item(), f_ref) <= (4 * 2.0 ** -17 if path == 2 else 33 * 2.0 ** -24)
+    # a Newton iteration with as many step sizes as the pass that forms A p evaluates, and with two more (on path 3 that pass takes more than
+    # 2048 rows: fewer are solved in one launch, which tries the step sizes in turn)
+    for max_ls in (13, 15):
         X = dev(w.X0)
         st = nadmm.nadmm_local_newton(gp, X, nadmm.make_params(2, 3, max_ls))
         w.max_newton, w.max_cg, w.max_ls = 2, 3, max_ls
