@@ -196,7 +196,8 @@ int nadmm_hessvec(const nadmm_problem* prob, const float* d_X, const float* d_V,
  *     250000 x 2000, C = 20 needs 31.9 MB.
  *   - The single-pass kernel for wide rows leaves min(256, ceil(n/16)) partial sums of p (C-1) floats.  Where these do not fit the
  *     buffer and the two-sweep kernels' scratch does (250000 x 2000, C = 20), the call makes two sweeps: it sums in another order
- *     than nadmm_hessvec does and agrees with it to rounding (below 4 * 2^-16 relative), not bit for bit.
+ *     than nadmm_hessvec does and agrees with it to rounding (below 4 * 2^-16 relative), not bit for bit.  Likewise for sparse storage
+ *     with rows or columns of 512 entries and more, whose sums are shared by workgroups where the room for the shares is there.
  *   - Every call on one GPU shares that GPU's buffer, whatever the stream or thread: calls that overlap
  *     in time on one GPU race.  Order them on one stream (or with events).  Nothing in the buffer has to
  *     survive between calls and nothing has to start at zero.

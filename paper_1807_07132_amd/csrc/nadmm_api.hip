@@ -45,7 +45,9 @@ struct Layout {
   bool wide;     // path 4 makes its sweeps with a transpose product in a single pass (nadmm_wide.hip)
   bool mc_auto;  // the matrix-core paths are also the automatic choice (see kAnyStrideMinP)
   bool sparse;
-  int nwin_rows, nwin_cols;
+  int nwin_rows, nwin_cols, wshift_rows, wshift_cols;
+  size_t share, arrived;  // sparse storage: shares of rows longer than a window (SpmmArgs)
+  bool cut_rows;
   const float* rho_scale;  // device scalar factor on rho (outer solver with an adaptive penalty), or NULL
 };
 
@@ -84,8 +86,8 @@ int validate_problem(const nadmm_problem* p, bool need_labels) {
 // side share the compute units; each then keeps the long row ranges per workgroup that amortise a launch).
 // max_cg > 0: room for the directional logits A d_k of that many CG iterations, if the fused single-pass path is the
 // one a solve would take and keeping them is cheaper than the pass over A they replace (see local_newton_enqueue).
-// no_wide: the two-sweep kernels only (their partial sums take less room).
-void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg_cap = 0, int max_cg = 0, bool no_wide = false) {
+// tight: the kernels that need less room only (wide rows: two sweeps; sparse storage: rows longer than a window are not shared).
+void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg_cap = 0, int max_cg = 0, bool tight = false) {
   Shape s;
   s.n = p->n;
   s.p = p->p;
@@ -137,7 +139,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
     sliced_grid(s, &S2, &sps, &L->sliced_parts);  // partial sums per row group
     L->sliced_loss = sliced_loss_blocks(s);       // partial row losses per workgroup of sweep 1
   }
-  L->wide = L->sliced_ok && !no_wide && wide_supported(s, p->lda, p->d_A);
+  L->wide = L->sliced_ok && !tight && wide_supported(s, p->lda, p->d_A);
   L->wide_parts = L->wide ? wide_num_partials(s, wg_cap) : 0;
   int parts = L->gen_chunks > L->fused_parts ? L->gen_chunks : L->fused_parts;
   if (L->wide_parts > parts) parts = L->wide_parts;
@@ -170,10 +172,16 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
     const size_t npad = (size_t)4 * sparse_group(s.NC);
     const size_t a = (size_t)s.p * 2 * npad, b = (size_t)s.n * npad;  // [X | V] or D, rows padded
     off += align256((a > b ? a : b) * sizeof(float));
+    L->wshift_rows = sparse_window_shift(s.n, p->sparse->nnz);
+    L->wshift_cols = sparse_window_shift(s.p, p->sparse->nnz);
     L->nwin_rows = sparse_windows(s.n, p->sparse->nnz);
     L->nwin_cols = sparse_windows(s.p, p->sparse->nnz);
     L->win_rows = off; off += align256((size_t)(L->nwin_rows + 1) * sizeof(int32_t));
     L->win_cols = off; off += align256((size_t)(L->nwin_cols + 1) * sizeof(int32_t));
+    const size_t nwin = (size_t)std::max(L->nwin_rows, L->nwin_cols);
+    L->cut_rows = !tight;
+    L->share = off; off += tight ? 0 : align256(2 * nwin * 2 * s.NC * sizeof(float));
+    L->arrived = off; off += tight ? 0 : align256(nwin * sizeof(int32_t));
   }
   L->total_base = off;
   // 2 max_cg n (C-1) floats written and read instead of n p floats read: taken with a margin
@@ -277,8 +285,9 @@ SparseView col_view(const nadmm_problem* prob) {
 // Sparse storage: the windows of equal cost of both views, once per entry-point call (they depend on the
 // pointer arrays only, but the workspace is the caller's between calls).
 int sparse_plan(const nadmm_problem* prob, const Layout& L, void* ws, hipStream_t st) {
-  NADMM_HIP(launch_sparse_plan(row_view(prob), at<int32_t>(ws, L.win_rows), L.nwin_rows, st));
-  NADMM_HIP(launch_sparse_plan(col_view(prob), at<int32_t>(ws, L.win_cols), L.nwin_cols, st));
+  int32_t* arrived = L.cut_rows ? at<int32_t>(ws, L.arrived) : nullptr;
+  NADMM_HIP(launch_sparse_plan(row_view(prob), at<int32_t>(ws, L.win_rows), L.nwin_rows, L.wshift_rows, arrived, st));
+  NADMM_HIP(launch_sparse_plan(col_view(prob), at<int32_t>(ws, L.win_cols), L.nwin_cols, L.wshift_cols, arrived, st));
   return NADMM_OK;
 }
 
@@ -302,12 +311,15 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
     sa.nq = (L.s.NC + 3) / 4;
     sa.flag = ra.flag;
     sa.B = at<float>(ws, L.pack);
+    sa.share = at<float>(ws, L.share);
+    sa.arrived = L.cut_rows ? at<int32_t>(ws, L.arrived) : nullptr;
     if (ra.B0 != nullptr || ra.B1 != nullptr) {  // [Z | W] = A [X | V]
       const bool both = ra.B0 != nullptr && ra.B1 != nullptr;
       sa.S = row_view(prob);
       sa.out = at<float>(ws, L.zw);
       sa.win = at<int32_t>(ws, L.win_rows);
       sa.nwin = L.nwin_rows;
+      sa.wshift = L.wshift_rows;
       sa.ldo = (both ? 2 : 1) * L.s.NC;
       if (both && sparse_group(L.s.NC) > 4) {
         // a row of X and a row of V do not share a 128-byte cache line: two products of one operand each
@@ -336,6 +348,7 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
       sa.ooff = 0;
       sa.win = at<int32_t>(ws, L.win_cols);
       sa.nwin = L.nwin_cols;
+      sa.wshift = L.wshift_cols;
       NADMM_HIP(launch_spmm(sa, st));
       *nparts = 1;
     }
@@ -960,11 +973,11 @@ int nadmm_hessvec(const nadmm_problem* prob, const float* d_X, const float* d_V,
 
 size_t nadmm_static_scratch_bytes(void) { return NADMM_STATIC_SCRATCH_BYTES; }
 
-// Scratch of a Hessian-vector product in the built-in buffer: the single-pass kernels for wide rows are left out where
-// only the two-sweep kernels' partial sums fit it.
+// Scratch of a Hessian-vector product in the built-in buffer: the single-pass kernels for wide rows, and the shares of long sparse rows, are
+// left out where only what the others need fits it.
 static void static_layout(const nadmm_problem* prob, Layout* L) {
   make_layout(prob, L, true);
-  if (L->wide && L->total > (size_t)NADMM_STATIC_SCRATCH_BYTES) make_layout(prob, L, true, 0, 0, true);
+  if ((L->wide || L->sparse) && L->total > (size_t)NADMM_STATIC_SCRATCH_BYTES) make_layout(prob, L, true, 0, 0, true);
 }
 
 size_t nadmm_hessvec_static_bytes(const nadmm_problem* prob) {

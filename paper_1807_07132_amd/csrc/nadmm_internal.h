@@ -493,12 +493,17 @@ struct SpmmArgs {
   int32_t NC, nq, nops;  // nq = ceil(NC / 4) quads of a block hold data
   int32_t ldo, ooff;
   const int32_t* win;  // first row of each window of equal cost, nwin + 1 entries (launch_sparse_plan)
-  int32_t nwin;
+  int32_t nwin, wshift;  // their number, and log2 of their cost (sparse_window_shift)
   const int32_t* flag;
+  // rows longer than a window are shared by the windows they reach over: sums of the shares, 2 x nwin x nops NC floats, and how many of a row
+  // are there, nwin words that are 0 between launches (launch_sparse_plan); NULL: the window in which such a row starts takes all of it
+  float* share;
+  int32_t* arrived;
 };
 int sparse_group(int NC);
+int sparse_window_shift(int64_t nrows, int64_t nnz);
 int sparse_windows(int64_t nrows, int64_t nnz);
-hipError_t launch_sparse_plan(const SparseView& S, int32_t* win, int nwin, hipStream_t st);
+hipError_t launch_sparse_plan(const SparseView& S, int32_t* win, int nwin, int wshift, int32_t* arrived, hipStream_t st);
 // dst[r] = [src0[r] | src1[r]] with every block padded to 4 sparse_group(NC) floats; one of src0, src1 may be NULL
 hipError_t launch_sparse_pack(const float* src0, const float* src1, int64_t rows, int NC, float* dst,
                               const int32_t* flag, hipStream_t st);

@@ -157,6 +157,40 @@ def test_mostly_empty_rows_and_columns():
     assert rel_l2(host(nadmm.nadmm_hessvec(gp, dev(X), dev(V))), orc.hessvec(op, X, V)) <= TOL_PRIMITIVE
 
 
+# columns whose lengths lie around the lines at which the products change their way: 16 lanes or a wave, a wave or a workgroup, and the windows of
+# 512 to 4096 cost units at whose ends a column is cut (their size goes by nnz; 8 units a column come on top)
+EDGES = [0, 1, 15, 16, 17, 33, 47, 48, 49, 63, 64, 65, 504, 511, 512, 513, 1016, 1024, 1025, 2040, 2048, 2049, 4087, 4088, 4095, 4096, 4097, 6100]
+
+
+@pytest.mark.parametrize("C", [2, 10, 17, 21, 33])
+@pytest.mark.parametrize("copies, wide", [(1, False), (1, True), (40, False), (240, False)])
+def test_rows_and_columns_of_every_length(C, copies, wide):
+    if copies == 240 and C not in (2, 21):
+        pytest.skip("the largest windows: one shape each with few and with many classes")
+    rng = np.random.default_rng(50 + copies)
+    m = 6113
+    lens = rng.permutation(np.array(EDGES * copies if copies < 240 else [6100, 4097, 4096, 4088, 513, 48, 0] * 420))
+    rows = np.concatenate([np.sort(rng.choice(m, k, replace=False)) for k in lens] or [np.zeros(0)])
+    ptr = np.concatenate([[0], np.cumsum(lens)])
+    At = sp.csr_matrix((rng.standard_normal(len(rows)).astype(np.float32), rows.astype(np.int32), ptr), shape=(len(lens), m))
+    A = At if wide else At.T.tocsr()       # samples or features of these lengths
+    n, p = A.shape
+    b = rng.integers(0, C, size=n).astype(np.int32)
+    X = (rng.standard_normal((p, C - 1)) * 0.02).astype(np.float32)
+    V = rng.standard_normal((p, C - 1)).astype(np.float32)
+    gp = nadmm.Problem(nadmm.SparseA.from_scipy(A, A.tocsc()), dev(b), C, 1.0, 1e-3, 1.0, None, None)
+    op = orc.Problem(A, b, C, s=1.0, lam=1e-3, rho=1.0)
+    hv = nadmm.nadmm_hessvec(gp, dev(X), dev(V))
+    ref = orc.hessvec(op, X, V)
+    assert rel_l2(host(hv), ref) <= 4e-6   # float32 sums, as in test_sparse_and_dense_storage_of_one_matrix_agree; a wrong share of a column is 1e-3
+    assert np.abs(host(hv) - ref).max() <= 2e-4 * np.abs(ref).max()
+    for _ in range(3):                     # whichever share arrives last: the same additions
+        assert torch.equal(nadmm.nadmm_hessvec(gp, dev(X), dev(V)), hv)
+    loss, grad = nadmm.nadmm_loss_grad(gp, dev(X))
+    assert rel_abs(loss.item(), orc.loss(op, X)) <= TOL_PRIMITIVE
+    assert rel_l2(host(grad), orc.grad(op, X)) <= 4e-6
+
+
 def test_empty_matrix():
     n, p, C = 70, 30, 5
     A = sp.csr_matrix((n, p), dtype=np.float32)
