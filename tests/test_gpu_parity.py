@@ -628,6 +628,15 @@ def test_wide_single_pass(n, p, C, pad):
     assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
 
 
+# 17 to 32 free classes from 97 columns on: 4 to 9 column steps for eight waves, so that some hold none; fewer than 7 steps take two sweeps from
+# 12289 rows on.  Four waves form the probabilities of a tile (with X): tiles of 1 to 16 rows, one and two blocks of classes, extra classes.
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("n,p,C", [(1, 97, 18), (33, 100, 20), (257, 128, 33), (4099, 129, 21), (12288, 190, 19), (12289, 190, 19), (300, 192, 26), (70, 193, 18),
+                                   (12300, 200, 33), (530, 224, 20), (47, 256, 25), (1030, 257, 19), (31, 288, 33)])
+def test_wide_single_pass_with_few_steps(n, p, C, pad):
+    test_wide_single_pass(n, p, C, pad)
+
+
 # Sweeps with X of 17 to 32 free classes on either side of the numbers of rows from which two sweeps are taken instead (fewer than 16
 # column steps; two blocks of classes over 48 steps): gradient, objective, Newton (whose head adds up the row losses that the sweep left).
 @pytest.mark.parametrize("n,p,C", [(12288, 330, 20), (12289, 330, 20), (12289, 481, 18), (22528, 290, 21), (22529, 290, 21), (4096, 1550, 26), (4097, 1550, 26),
