@@ -181,7 +181,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
     const size_t nwin = (size_t)std::max(L->nwin_rows, L->nwin_cols);
     L->cut_rows = !tight;
     L->share = off; off += tight ? 0 : align256(2 * nwin * 2 * s.NC * sizeof(float));
-    L->arrived = off; off += tight ? 0 : align256(nwin * sizeof(int32_t));
+    L->arrived = off; off += tight ? 0 : align256(2 * nwin * sizeof(int32_t));
   }
   L->total_base = off;
   // 2 max_cg n (C-1) floats written and read instead of n p floats read: taken with a margin
@@ -282,12 +282,15 @@ SparseView col_view(const nadmm_problem* prob) {
   return SparseView{sp->d_col_ptr, sp->d_row_idx, sp->d_val_t, (int64_t)prob->p, (int32_t)prob->n, sp->nnz};
 }
 
+SparseWindows sparse_windows_of(const Layout& L, void* ws, bool by_rows) {
+  return by_rows ? SparseWindows{at<int32_t>(ws, L.win_rows), L.nwin_rows, L.wshift_rows} : SparseWindows{at<int32_t>(ws, L.win_cols), L.nwin_cols, L.wshift_cols};
+}
+
 // Sparse storage: the windows of equal cost of both views, once per entry-point call (they depend on the
 // pointer arrays only, but the workspace is the caller's between calls).
 int sparse_plan(const nadmm_problem* prob, const Layout& L, void* ws, hipStream_t st) {
-  int32_t* arrived = L.cut_rows ? at<int32_t>(ws, L.arrived) : nullptr;
-  NADMM_HIP(launch_sparse_plan(row_view(prob), at<int32_t>(ws, L.win_rows), L.nwin_rows, L.wshift_rows, arrived, st));
-  NADMM_HIP(launch_sparse_plan(col_view(prob), at<int32_t>(ws, L.win_cols), L.nwin_cols, L.wshift_cols, arrived, st));
+  NADMM_HIP(launch_sparse_plan(row_view(prob), sparse_windows_of(L, ws, true), col_view(prob), sparse_windows_of(L, ws, false),
+                               L.cut_rows ? at<int32_t>(ws, L.arrived) : nullptr, st));
   return NADMM_OK;
 }
 
@@ -306,49 +309,32 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
   ra.lda = prob->lda;
   ra.NC = L.s.NC;
   if (path == 5) {
+    const int NC = L.s.NC;
+    float* pack = at<float>(ws, L.pack);
     SpmmArgs sa;
-    sa.NC = L.s.NC;
-    sa.nq = (L.s.NC + 3) / 4;
+    std::memset(&sa, 0, sizeof(sa));
+    sa.B = pack;
+    sa.NC = NC;
+    sa.nq = (NC + 3) / 4;
     sa.flag = ra.flag;
-    sa.B = at<float>(ws, L.pack);
     sa.share = at<float>(ws, L.share);
     sa.arrived = L.cut_rows ? at<int32_t>(ws, L.arrived) : nullptr;
     if (ra.B0 != nullptr || ra.B1 != nullptr) {  // [Z | W] = A [X | V]
       const bool both = ra.B0 != nullptr && ra.B1 != nullptr;
       sa.S = row_view(prob);
       sa.out = at<float>(ws, L.zw);
-      sa.win = at<int32_t>(ws, L.win_rows);
-      sa.nwin = L.nwin_rows;
-      sa.wshift = L.wshift_rows;
-      sa.ldo = (both ? 2 : 1) * L.s.NC;
-      if (both && sparse_group(L.s.NC) > 4) {
-        // a row of X and a row of V do not share a 128-byte cache line: two products of one operand each
-        // fetch a line per stored entry and are faster than one product that fetches two
-        sa.nops = 1;
-        NADMM_HIP(launch_sparse_pack(ra.B0, nullptr, prob->p, L.s.NC, at<float>(ws, L.pack), ra.flag, st));
-        sa.ooff = 0;
-        NADMM_HIP(launch_spmm(sa, st));
-        NADMM_HIP(launch_sparse_pack(ra.B1, nullptr, prob->p, L.s.NC, at<float>(ws, L.pack), ra.flag, st));
-        sa.ooff = L.s.NC;
-        NADMM_HIP(launch_spmm(sa, st));
-      } else {
-        NADMM_HIP(launch_sparse_pack(ra.B0, ra.B1, prob->p, L.s.NC, at<float>(ws, L.pack), ra.flag, st));
-        sa.nops = both ? 2 : 1;
-        sa.ooff = 0;
-        NADMM_HIP(launch_spmm(sa, st));
-      }
+      sa.w = sparse_windows_of(L, ws, true);
+      sa.nops = both ? 2 : 1;
+      NADMM_HIP(launch_sparse_pack(ra.B0 != nullptr ? ra.B0 : ra.B1, both ? ra.B1 : nullptr, prob->p, NC, pack, ra.flag, st));
+      NADMM_HIP(launch_spmm(sa, st));
     }
-    NADMM_HIP(launch_logit_rows(ra, at<float>(ws, L.zw), 1, st));
+    if (with_cols) ra.rows_out = pack;  // the rows of D lie as the product with A^T reads them
+    NADMM_HIP(launch_logit_rows(ra, at<float>(ws, L.zw), 1, with_cols ? 4 * sparse_group(NC) : NC, st));
     if (with_cols) {  // A^T D from the column view
-      NADMM_HIP(launch_sparse_pack(ra.rows_out, nullptr, prob->n, L.s.NC, at<float>(ws, L.pack), ra.flag, st));
       sa.S = col_view(prob);
       sa.out = at<float>(ws, L.partial);
+      sa.w = sparse_windows_of(L, ws, false);
       sa.nops = 1;
-      sa.ldo = L.s.NC;
-      sa.ooff = 0;
-      sa.win = at<int32_t>(ws, L.win_cols);
-      sa.nwin = L.nwin_cols;
-      sa.wshift = L.wshift_cols;
       NADMM_HIP(launch_spmm(sa, st));
       *nparts = 1;
     }

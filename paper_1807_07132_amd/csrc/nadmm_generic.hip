@@ -179,7 +179,7 @@ constexpr int kLogitThreads = 1024;  // 16 waves x 16 rows = the kRowsPerBlock r
 // cover whole rows of the n x (C-1) arrays back to back; the rows are finished by rows16::finish.
 template <int NB>
 __global__ __launch_bounds__(kLogitThreads) void logit_rows_kernel(const RowArgs a, const float* __restrict__ zw,
-                                                                   int nslices) {
+                                                                   int nslices, int rows_ld) {
   if (a.flag != nullptr && *a.flag == 0) return;
   __shared__ double red[kLogitThreads / 64];
   constexpr int kIters = 4;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kLogitThreads) void logit_rows_kernel(const RowArgs
   double ell = 0.0;
 #pragma unroll
   for (int it = 0; it < kIters; ++it)
-    ell += rows16::finish<NB>(a, wrow0 + 4 * it + g, m, lc, has0, has1, z[it], w[it], aux[it], label[it]);
+    ell += rows16::finish<NB>(a, wrow0 + 4 * it + g, m, lc, has0, has1, z[it], w[it], aux[it], label[it], rows_ld);
   if (!with_loss) return;
   ell = mfma_detail::wave64_sum(ell);
   if (lane == 0) red[wave] = ell;
@@ -315,10 +315,10 @@ hipError_t launch_generic_rows(const RowArgs& a, hipStream_t st) {
   });
 }
 
-hipError_t launch_logit_rows(const RowArgs& a, const float* zw, int nslices, hipStream_t st) {
+hipError_t launch_logit_rows(const RowArgs& a, const float* zw, int nslices, int rows_ld, hipStream_t st) {
   const int blocks = generic_row_blocks(a.n);
-  if (a.NC <= 16) hipLaunchKernelGGL(logit_rows_kernel<1>, dim3(blocks), dim3(kLogitThreads), 0, st, a, zw, nslices);
-  else if (a.NC <= 32) hipLaunchKernelGGL(logit_rows_kernel<2>, dim3(blocks), dim3(kLogitThreads), 0, st, a, zw, nslices);
+  if (a.NC <= 16) hipLaunchKernelGGL(logit_rows_kernel<1>, dim3(blocks), dim3(kLogitThreads), 0, st, a, zw, nslices, rows_ld);
+  else if (a.NC <= 32) hipLaunchKernelGGL(logit_rows_kernel<2>, dim3(blocks), dim3(kLogitThreads), 0, st, a, zw, nslices, rows_ld);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -169,7 +169,8 @@ hipError_t launch_generic_rows(const RowArgs& a, hipStream_t st);
 hipError_t launch_generic_cols(const ColArgs& a, int nslabs, int nchunks, hipStream_t st);
 // rows stage on per-slice partial logits zw[slice][row][Z|W][C-1] (Z only if B0, W only if B1 is given);
 // partial losses per block of generic_row_blocks()
-hipError_t launch_logit_rows(const RowArgs& a, const float* zw, int nslices, hipStream_t st);
+// rows_ld: floats between the rows of a.rows_out
+hipError_t launch_logit_rows(const RowArgs& a, const float* zw, int nslices, int rows_ld, hipStream_t st);
 
 // ---- vector / tail kernels (nadmm_vec.hip) ----
 struct NewtonHeadArgs {
@@ -484,16 +485,19 @@ struct SparseView {
   int32_t ncols;
   int64_t nnz;
 };
-// out = S B for a packed dense operand B: ncols rows of nops blocks of 4 sparse_group(NC) floats (zero
-// padded); row r of the product goes to out[r * ldo + ooff + op * NC + c], op < nops, c < NC
+// Rows of a view in windows of equal cost: the first row of each, n + 1 entries, 1 << shift cost units
+struct SparseWindows {
+  int32_t* first;
+  int32_t n, shift;
+};
+// out = S B for a packed dense operand B: ncols rows of nops blocks of 4 sparse_group(NC) floats (what lies beyond the first NC of a block does not
+// matter); row r of the product goes to out[(r * nops + op) * NC + c], op < nops, c < NC
 struct SpmmArgs {
   SparseView S;
   const float* B;
   float* out;
   int32_t NC, nq, nops;  // nq = ceil(NC / 4) quads of a block hold data
-  int32_t ldo, ooff;
-  const int32_t* win;  // first row of each window of equal cost, nwin + 1 entries (launch_sparse_plan)
-  int32_t nwin, wshift;  // their number, and log2 of their cost (sparse_window_shift)
+  SparseWindows w;
   const int32_t* flag;
   // rows longer than a window are shared by the windows they reach over: sums of the shares, 2 x nwin x nops NC floats, and how many of a row
   // are there, nwin words that are 0 between launches (launch_sparse_plan); NULL: the window in which such a row starts takes all of it
@@ -503,8 +507,9 @@ struct SpmmArgs {
 int sparse_group(int NC);
 int sparse_window_shift(int64_t nrows, int64_t nnz);
 int sparse_windows(int64_t nrows, int64_t nnz);
-hipError_t launch_sparse_plan(const SparseView& S, int32_t* win, int nwin, int wshift, int32_t* arrived, hipStream_t st);
-// dst[r] = [src0[r] | src1[r]] with every block padded to 4 sparse_group(NC) floats; one of src0, src1 may be NULL
+// the windows of both views, and `arrived` zero for the larger number of them
+hipError_t launch_sparse_plan(const SparseView& S0, const SparseWindows& w0, const SparseView& S1, const SparseWindows& w1, int32_t* arrived, hipStream_t st);
+// dst[r] = [src0[r] | src1[r]] with every block padded to 4 sparse_group(NC) floats; src1 may be NULL
 hipError_t launch_sparse_pack(const float* src0, const float* src1, int64_t rows, int NC, float* dst,
                               const int32_t* flag, hipStream_t st);
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t st);

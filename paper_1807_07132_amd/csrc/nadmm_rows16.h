@@ -26,17 +26,17 @@ struct LaneClasses {
 };
 
 // One row.  z, w: the row's logits A X and A V (whichever operands the call has); pin: the cached probabilities
-// (used when the call has no X); label: the row's class (kinds with a loss).  Returns the row loss in the lane
+// (used when the call has no X); label: the row's class (kinds with a loss); rows_ld: floats between rows of a.rows_out.  Returns the row loss in the lane
 // with m == 0 of a valid row, 0 elsewhere and for kinds without a loss.
 template <int NB>
 __device__ __forceinline__ double finish(const RowArgs& a, int64_t row, int m, const LaneClasses<NB>& lc, bool has0,
                                          bool has1, const float (&z)[NB], const float (&w)[NB], const float (&pin)[NB],
-                                         int label) {
+                                         int label, int rows_ld) {
   using mfma_detail::row16_max;
   using mfma_detail::row16_sum;
   const int NC = a.NC;
   const bool valid = row < a.n;
-  const size_t ro = (size_t)(valid ? row : a.n - 1) * NC;
+  const size_t ro = (size_t)(valid ? row : a.n - 1) * NC, rd = (size_t)(valid ? row : a.n - 1) * rows_ld;
   if (a.kind == kRowsLogits) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -74,7 +74,7 @@ __device__ __forceinline__ double finish(const RowArgs& a, int64_t row, int m, c
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
       if (valid && lc.cv[nb]) {
-        a.rows_out[ro + lc.cl[nb]] = P[nb] * (w[nb] - t);
+        a.rows_out[rd + lc.cl[nb]] = P[nb] * (w[nb] - t);
         if (a.Pout) a.Pout[ro + lc.cl[nb]] = P[nb];
       }
     return 0.0;
@@ -85,7 +85,7 @@ __device__ __forceinline__ double finish(const RowArgs& a, int64_t row, int m, c
     const bool mine = lc.cv[nb] && 16 * nb + m == label;
     zb += mine ? z[nb] : 0.f;
     if (valid && lc.cv[nb]) {
-      if (a.kind == kRowsGrad && a.rows_out) a.rows_out[ro + lc.cl[nb]] = P[nb] - (mine ? 1.f : 0.f);
+      if (a.kind == kRowsGrad && a.rows_out) a.rows_out[rd + lc.cl[nb]] = P[nb] - (mine ? 1.f : 0.f);
       if (a.Pout) a.Pout[ro + lc.cl[nb]] = P[nb];
       if (a.Z0out) a.Z0out[ro + lc.cl[nb]] = z[nb];
     }

@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kThreads) void slice_logits_kernel(const SlicedArgs
           w[nb] = HAS1 ? zr[kMatW * NC + lc.cl[nb]] : 0.f;
         }
         // rows past the range belong to another workgroup (or do not exist): a row index of n marks them invalid
-        ell += rows16::finish<NB>(a, row < r_end ? row : a.n, m, lc, HAS0, HAS1, z, w, pin[u], label[u]);
+        ell += rows16::finish<NB>(a, row < r_end ? row : a.n, m, lc, HAS0, HAS1, z, w, pin[u], label[u], a.NC);
       }
     }
   }

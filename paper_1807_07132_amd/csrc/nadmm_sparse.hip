@@ -31,24 +31,27 @@ constexpr int kLong = 512;     // rows with at least this many entries are share
 constexpr int kShort = 48;     // rows with fewer entries are summed by 16 lanes (16 and 24: up to 16 % slower at 30 entries a row; 80: equal)
 constexpr int kMaxLong = (1 << kMaxShift) / (kLong + kRowCost) + 3;  // long rows that start in a window, and one that reaches into it
 
-// first row r in [0, nrows] whose cost prefix ptr[r] + kRowCost r reaches `target`
-__global__ __launch_bounds__(256) void plan_kernel(const SparseView S, int32_t* __restrict__ win, int nwin, int wshift,
+// Per window of either view (the first n0 blocks are of view 0): the first row r in [0, nrows] whose cost prefix ptr[r] + kRowCost r reaches it
+__global__ __launch_bounds__(256) void plan_kernel(const SparseView S0, const SparseWindows w0, const SparseView S1, const SparseWindows w1, int blocks0,
                                                    int32_t* __restrict__ arrived) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > nwin) return;
-  if (k < nwin && arrived != nullptr) arrived[k] = 0;
-  if (k == nwin) {
-    win[k] = (int32_t)S.nrows;
+  const bool second = (int)blockIdx.x >= blocks0;
+  const SparseView& S = second ? S1 : S0;
+  const SparseWindows& w = second ? w1 : w0;
+  const int k = ((int)blockIdx.x - (second ? blocks0 : 0)) * 256 + threadIdx.x;
+  if (k > w.n) return;
+  if (k < w.n && arrived != nullptr) arrived[k] = arrived[w.n + k] = 0;  // both operands' passes
+  if (k == w.n) {
+    w.first[k] = (int32_t)S.nrows;
     return;
   }
-  const int64_t target = (int64_t)k << wshift;
+  const int64_t target = (int64_t)k << w.shift;
   int64_t lo = 0, hi = S.nrows;  // answer in [lo, hi]
   while (lo < hi) {
     const int64_t mid = (lo + hi) >> 1;
     if (S.ptr[mid] + (int64_t)kRowCost * mid >= target) hi = mid;
     else lo = mid + 1;
   }
-  win[k] = (int32_t)lo;
+  w.first[k] = (int32_t)lo;
 }
 
 // dst[r][op][slot] = src_op[r][NC], zero in the padding (slot = 4 G floats); one thread per group of 4 floats
@@ -126,23 +129,23 @@ struct Shape64 {
 // NQ neighbouring lanes share an entry, one quad of its B row each, so that one load instruction touches
 // every row once (several loads of one lane to one cache line would wait on each other in the vector
 // L1).  Returns, in lanes 0 .. NQ-1, the sums of quad q = lane over the whole wave.
-template <int NQ, int NOPS>
-__device__ __forceinline__ void row_sum(const SpmmArgs& a, int64_t kb0, int64_t k1, int stride, int lane,
-                                        mfma_detail::f32x4 (&acc)[NOPS]) {
+template <int NQ, int NPER, int NOPS>
+__device__ __forceinline__ void row_sum(const SpmmArgs& a, const mfma_detail::f32x4* __restrict__ B, int64_t kb0, int64_t k1, int stride, int lane,
+                                        mfma_detail::f32x4 (&acc)[NPER]) {
   using mfma_detail::f32x4;
   constexpr int S = Shape64<NQ>::S, T = Shape64<NQ>::T, CE = Shape64<NQ>::CE;
   constexpr int G = NQ <= 1 ? 1 : (NQ <= 2 ? 2 : (NQ <= 4 ? 4 : 8));  // quads per row slot of B
   const int s = lane / NQ, q = lane - s * NQ;
   const bool active = lane < S * NQ;
-  const f32x4* __restrict__ Bq = reinterpret_cast<const f32x4*>(a.B) + q;
+  const f32x4* __restrict__ Bq = B + q;
 #pragma unroll
-  for (int op = 0; op < NOPS; ++op) acc[op] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int op = 0; op < NPER; ++op) acc[op] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (kb0 >= k1) return;
   Chunk cur = fetch_chunk(a.S, kb0, k1, CE, lane);
   for (int64_t kb = kb0; kb < k1; kb += stride) {
     const int64_t left = k1 - kb;
     const int nsub = left >= CE ? T : (int)((left + S - 1) / S);
-    f32x4 b[T][NOPS];
+    f32x4 b[T][NPER];
     float vv[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -150,13 +153,13 @@ __device__ __forceinline__ void row_sum(const SpmmArgs& a, int64_t kb0, int64_t 
       vv[t] = __shfl(cur.v, t * S + s, 64);
       const f32x4* __restrict__ row = Bq + (size_t)c * (NOPS * G);
 #pragma unroll
-      for (int op = 0; op < NOPS; ++op) b[t][op] = (t < nsub && active) ? row[op * G] : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int op = 0; op < NPER; ++op) b[t][op] = (t < nsub && active) ? row[op * G] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     if (kb + stride < k1) cur = fetch_chunk(a.S, kb + stride, k1, CE, lane);  // in flight during the products
 #pragma unroll
     for (int t = 0; t < T; ++t) {
 #pragma unroll
-      for (int op = 0; op < NOPS; ++op) {
+      for (int op = 0; op < NPER; ++op) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[op][e] = fmaf(vv[t], b[t][op][e], acc[op][e]);
       }
@@ -169,7 +172,7 @@ __device__ __forceinline__ void row_sum(const SpmmArgs& a, int64_t kb0, int64_t 
     if (h < cnt) {
       const bool take = s + h < cnt;
 #pragma unroll
-      for (int op = 0; op < NOPS; ++op) {
+      for (int op = 0; op < NPER; ++op) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float o = __shfl_down(acc[op][e], h * NQ, 64);
@@ -183,26 +186,27 @@ __device__ __forceinline__ void row_sum(const SpmmArgs& a, int64_t kb0, int64_t 
 
 // The same for four short rows at once, 16 lanes each (row k0 .. k0 + len is the same in all of them): a tree over 16 lanes instead of 64 and a quarter
 // of the waits.  Returns the sums of quad q in lane q of the 16.
-template <int NQ, int NOPS>
-__device__ __forceinline__ void short_rows_sum(const SpmmArgs& a, int64_t k0, int len, int lane, mfma_detail::f32x4 (&acc)[NOPS]) {
+template <int NQ, int NPER, int NOPS>
+__device__ __forceinline__ void short_rows_sum(const SpmmArgs& a, const mfma_detail::f32x4* __restrict__ B, int64_t k0, int len, int lane,
+                                               mfma_detail::f32x4 (&acc)[NPER]) {
   using mfma_detail::f32x4;
   constexpr int S = 16 / NQ, T = (16 + S - 1) / S;  // entries of a row per load instruction, such loads per 16 entries
   constexpr int G = NQ <= 1 ? 1 : (NQ <= 2 ? 2 : (NQ <= 4 ? 4 : 8));
   const int l = lane & 15, s = l / NQ, q = l - s * NQ;
-  const f32x4* __restrict__ Bq = reinterpret_cast<const f32x4*>(a.B) + q;
+  const f32x4* __restrict__ Bq = B + q;
 #pragma unroll
-  for (int op = 0; op < NOPS; ++op) acc[op] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int op = 0; op < NPER; ++op) acc[op] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int kb = 0; __any(kb < len); kb += 16) {
     int64_t k = k0 + kb + l;
     k = k < a.S.nnz ? k : a.S.nnz - 1;
     const int c0 = a.S.idx[k];
     const float v0 = kb + l < len ? a.S.val[k] : 0.f;
     const int c = c0 < 0 ? 0 : (c0 >= a.S.ncols ? a.S.ncols - 1 : c0);
-    constexpr int U = (T + 1) / 2 < 4 / NOPS ? (T + 1) / 2 : 4 / NOPS;  // loads in flight: more would cost the kernel waves
+    constexpr int U = (T + 1) / 2 < 4 / NPER ? (T + 1) / 2 : 4 / NPER;  // loads in flight: more would cost the kernel waves
 #pragma unroll
     for (int t0 = 0; t0 < T; t0 += U) {
       if (!__any(kb + t0 * S < len)) break;
-      f32x4 b[U][NOPS];
+      f32x4 b[U][NPER];
       float vv[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -213,12 +217,12 @@ __device__ __forceinline__ void short_rows_sum(const SpmmArgs& a, int64_t k0, in
         vv[u] = ok ? w : 0.f;
         const f32x4* __restrict__ row = Bq + (size_t)cc * (NOPS * G);
 #pragma unroll
-        for (int op = 0; op < NOPS; ++op) b[u][op] = ok ? row[op * G] : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int op = 0; op < NPER; ++op) b[u][op] = ok ? row[op * G] : f32x4{0.f, 0.f, 0.f, 0.f};
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
 #pragma unroll
-        for (int op = 0; op < NOPS; ++op) {
+        for (int op = 0; op < NPER; ++op) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[op][e] = fmaf(vv[u], b[u][op][e], acc[op][e]);
         }
@@ -231,7 +235,7 @@ __device__ __forceinline__ void short_rows_sum(const SpmmArgs& a, int64_t k0, in
     if (h < cnt) {
       const bool take = s + h < cnt;
 #pragma unroll
-      for (int op = 0; op < NOPS; ++op) {
+      for (int op = 0; op < NPER; ++op) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float o = __shfl_down(acc[op][e], h * NQ, 64);
@@ -243,11 +247,11 @@ __device__ __forceinline__ void short_rows_sum(const SpmmArgs& a, int64_t k0, in
   }
 }
 
-template <int NQ, int NOPS>
-__device__ __forceinline__ void store_row(const SpmmArgs& a, int row, int q, const mfma_detail::f32x4 (&acc)[NOPS]) {
-  float* __restrict__ orow = a.out + (size_t)row * a.ldo + a.ooff;
+template <int NPER>
+__device__ __forceinline__ void store_row(const SpmmArgs& a, float* __restrict__ out, int row, int q, const mfma_detail::f32x4 (&acc)[NPER]) {
+  float* __restrict__ orow = out + (size_t)row * (a.nops * a.NC);
 #pragma unroll
-  for (int op = 0; op < NOPS; ++op) {
+  for (int op = 0; op < NPER; ++op) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int c = 4 * q + e;
@@ -260,21 +264,22 @@ __device__ __forceinline__ int64_t lane_of(int64_t x, int i) {
   return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), i) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)x, i));
 }
 
-template <int NQ, int NOPS>
+// NPER of the NOPS operands are multiplied together, the others by further workgroups (blockIdx.y).
 // 5 to 7 quads: a wave more per SIMD than the compiler would leave room for (60000 x 9000, 200 a row, C = 28: 304 -> 294 us a Hessian-vector product;
 // fewer or more quads, or two operands, are slower with that, 2 to 25 %)
-__global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1) void spmm_kernel(const SpmmArgs a) {
+template <int NQ, int NPER, int NOPS>
+__global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1) void spmm_kernel(const SpmmArgs a) {
   constexpr int G = 8;  // bound of NQ, for the LDS staging of long rows
   constexpr int CE = Shape64<NQ>::CE;
   using mfma_detail::f32x4;
   if (a.flag != nullptr && *a.flag == 0) return;
   __shared__ int long_rows[kMaxLong];
   __shared__ int nlong_sh;
-  __shared__ float part[kMaxLong][kSpWaves][NOPS][G][4];
+  __shared__ float part[kMaxLong][kSpWaves][NPER][G][4];
   __shared__ int last_sh[2];
   const int win = blockIdx.x;
-  const int r0 = a.win[win], r1 = a.win[win + 1];
-  const int wshift = a.wshift;
+  const int r0 = a.w.first[win], r1 = a.w.first[win + 1];
+  const int wshift = a.w.shift;
   const int64_t kCut = a.arrived != nullptr ? (int64_t)1 << wshift : INT64_MAX;
   // the cut row that reaches into this window from before it, and the one that starts here and reaches beyond it (the last that starts here)
   bool into = false, beyond = false;
@@ -289,7 +294,12 @@ __global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
   if (r1 <= r0 && !into) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ldo = a.ldo;
+  constexpr int kSlot = NQ <= 1 ? 1 : (NQ <= 2 ? 2 : (NQ <= 4 ? 4 : 8));  // quads per row slot of an operand
+  const f32x4* __restrict__ B = reinterpret_cast<const f32x4*>(a.B) + blockIdx.y * kSlot;
+  float* __restrict__ out = a.out + blockIdx.y * a.NC;
+  const int ldo = NOPS * a.NC, width = NPER * a.NC;
+  float* share = a.share + (size_t)blockIdx.y * 2 * a.w.n * width;
+  int32_t* arrived = a.arrived + (size_t)blockIdx.y * a.w.n;
 
   if (threadIdx.x == 0) {
     nlong_sh = into ? 1 : 0;
@@ -310,11 +320,11 @@ __global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
   for (int sl = 0; sl < nlong; ++sl) {
     RowSpan sp = row_span(a.S, long_rows[sl]);
     if (sp.k1 - sp.k0 >= kCut) sp = cut_span(sp, long_rows[sl], win, wshift).here;
-    f32x4 acc[NOPS];
-    row_sum<NQ, NOPS>(a, sp.k0 + CE * wave, sp.k1, CE * kSpWaves, lane, acc);
+    f32x4 acc[NPER];
+    row_sum<NQ, NPER, NOPS>(a, B, sp.k0 + CE * wave, sp.k1, CE * kSpWaves, lane, acc);
     if (lane < NQ) {
 #pragma unroll
-      for (int op = 0; op < NOPS; ++op) {
+      for (int op = 0; op < NPER; ++op) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) part[sl][wave][op][lane][e] = acc[op][e];
       }
@@ -331,14 +341,14 @@ __global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
       if (sp.k1 - sp.k0 < kLong) len = (int)(sp.k1 - sp.k0);
     }
     if (len == 0)
-      for (int c = 0; c < NOPS * a.NC; ++c) a.out[(size_t)rl * ldo + a.ooff + c] = 0.f;
+      for (int c = 0; c < width; ++c) out[(size_t)rl * ldo + c] = 0.f;
     uint64_t todo = __ballot(len >= kShort);
     for (; todo != 0; todo &= todo - 1) {
       const int i = __builtin_ctzll(todo);
       const int64_t k0 = lane_of(from, i);
-      f32x4 acc[NOPS];
-      row_sum<NQ, NOPS>(a, k0, k0 + __builtin_amdgcn_readlane(len, i), CE, lane, acc);
-      if (lane < NQ) store_row<NQ, NOPS>(a, rb + kSpWaves * i, lane, acc);
+      f32x4 acc[NPER];
+      row_sum<NQ, NPER, NOPS>(a, B, k0, k0 + __builtin_amdgcn_readlane(len, i), CE, lane, acc);
+      if (lane < NQ) store_row<NPER>(a, out, rb + kSpWaves * i, lane, acc);
     }
     todo = __ballot(len > 0 && len < kShort);
     while (todo != 0) {
@@ -351,14 +361,14 @@ __global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
       const int src = mine < 0 ? 0 : mine;
       const int64_t s0 = __shfl(from, src, 64);
       const int slen = __shfl(len, src, 64);
-      f32x4 acc[NOPS];
-      short_rows_sum<NQ, NOPS>(a, s0, mine < 0 ? 0 : slen, lane, acc);
-      if (mine >= 0 && (lane & 15) < NQ) store_row<NQ, NOPS>(a, rb + kSpWaves * mine, lane & 15, acc);
+      f32x4 acc[NPER];
+      short_rows_sum<NQ, NPER, NOPS>(a, B, s0, mine < 0 ? 0 : slen, lane, acc);
+      if (mine >= 0 && (lane & 15) < NQ) store_row<NPER>(a, out, rb + kSpWaves * mine, lane & 15, acc);
     }
   }
   if (nlong == 0) return;
   __syncthreads();
-  constexpr int kPer = NOPS * G * 4;
+  constexpr int kPer = NPER * G * 4;
   for (int t = threadIdx.x; t < nlong * kPer; t += kSpThreads) {
     const int sl = t / kPer, j = t - sl * kPer;
     const int op = j / (4 * G), c = j - op * (4 * G);
@@ -370,9 +380,9 @@ __global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
     const int row = long_rows[sl];
     // share of a cut row: past the L2, which other XCDs do not see
     if ((into && sl == 0) || (beyond && row == r1 - 1))
-      __hip_atomic_store(a.share + (size_t)(2 * win + (row < r0 ? 0 : 1)) * (NOPS * a.NC) + op * a.NC + c, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(share + (size_t)(2 * win + (row < r0 ? 0 : 1)) * width + op * a.NC + c, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
-      a.out[(size_t)row * ldo + a.ooff + op * a.NC + c] = sum;
+      out[(size_t)row * ldo + op * a.NC + c] = sum;
   }
   if (!into && !beyond) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the shares are where every XCD reads them
@@ -382,34 +392,34 @@ __global__ __launch_bounds__(kSpThreads, NOPS == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
     int last = 0;
     if (threadIdx.x == 0 ? into : beyond) {
       const Cut c = cut_span(row_span(a.S, row), row, win, wshift);
-      last = __hip_atomic_fetch_add(a.arrived + c.first, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c.last - c.first;
-      if (last) __hip_atomic_store(a.arrived + c.first, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = __hip_atomic_fetch_add(arrived + c.first, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == c.last - c.first;
+      if (last) __hip_atomic_store(arrived + c.first, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     last_sh[threadIdx.x] = last;
   }
   __syncthreads();
-  const int width = NOPS * a.NC, side = threadIdx.x >> 7, j = threadIdx.x & 127;  // width <= 64
+  const int side = threadIdx.x >> 7, j = threadIdx.x & 127;  // width <= 64
   if (last_sh[side] != 0 && j < width) {
     const int row = side == 0 ? r0 - 1 : r1 - 1;
     const Cut c = cut_span(row_span(a.S, row), row, win, wshift);
-    auto share = [&](int w) {
-      return __hip_atomic_load(a.share + (size_t)(2 * w + (w == c.first ? 1 : 0)) * width + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    auto share_of = [&](int w) {
+      return __hip_atomic_load(share + (size_t)(2 * w + (w == c.first ? 1 : 0)) * width + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     float sum = 0.f;
     for (int w = c.first; w <= c.last; w += 8) {
       float x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = share(w + u <= c.last ? w + u : c.last);
+      for (int u = 0; u < 8; ++u) x[u] = share_of(w + u <= c.last ? w + u : c.last);
 #pragma unroll
       for (int u = 0; u < 8; ++u) sum += w + u <= c.last ? x[u] : 0.f;
     }
-    a.out[(size_t)row * ldo + a.ooff + j] = sum;
+    out[(size_t)row * ldo + j] = sum;
   }
 }
 
-template <int NQ, int NOPS>
+template <int NQ, int NPER, int NOPS>
 hipError_t launch_q(const SpmmArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((spmm_kernel<NQ, NOPS>), dim3(a.nwin), dim3(kSpThreads), 0, st, a);
+  hipLaunchKernelGGL((spmm_kernel<NQ, NPER, NOPS>), dim3(a.w.n, NOPS / NPER), dim3(kSpThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -437,38 +447,43 @@ int sparse_windows(int64_t nrows, int64_t nnz) {
   return (int)(w < 1 ? 1 : w);
 }
 
-hipError_t launch_sparse_plan(const SparseView& S, int32_t* win, int nwin, int wshift, int32_t* arrived, hipStream_t st) {
-  hipLaunchKernelGGL(plan_kernel, dim3((nwin + 1 + 255) / 256), dim3(256), 0, st, S, win, nwin, wshift, arrived);
+hipError_t launch_sparse_plan(const SparseView& S0, const SparseWindows& w0, const SparseView& S1, const SparseWindows& w1, int32_t* arrived, hipStream_t st) {
+  const int b0 = (w0.n + 1 + 255) / 256, b1 = (w1.n + 1 + 255) / 256;
+  hipLaunchKernelGGL(plan_kernel, dim3(b0 + b1), dim3(256), 0, st, S0, w0, S1, w1, b0, arrived);
   return hipGetLastError();
 }
 
 hipError_t launch_sparse_pack(const float* src0, const float* src1, int64_t rows, int NC, float* dst,
                               const int32_t* flag, hipStream_t st) {
-  const float* s0 = src0 ? src0 : src1;
-  const int nops = (src0 && src1) ? 2 : 1;
+  const int nops = src1 != nullptr ? 2 : 1;
   const int G = sparse_group(NC);
   const int64_t total = rows * nops * G;
-  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, s0, src1, rows, NC, G,
+  hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, src0, src1, rows, NC, G,
                      nops, dst, flag);
   return hipGetLastError();
 }
 
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t st) {
-  // two operands only where both rows share a 128-byte line (C-1 <= 16); wider ones are multiplied one by one
-  if (a.nq != (a.NC + 3) / 4 || a.nq < 1 || a.nq > 8 || a.nops < 1 || a.nops > (a.nq <= 4 ? 2 : 1)) return hipErrorInvalidValue;
+  // two operands in one pass only where both rows share a 128-byte line (C-1 <= 16): for wider ones two passes over the entries, which fetch a line
+  // per entry, take 2 x 620 us where one pass that fetches two takes 1523 (40628 x 279998, C = 20)
+  if (a.nq != (a.NC + 3) / 4 || a.nq < 1 || a.nq > 8 || a.nops < 1 || a.nops > 2) return hipErrorInvalidValue;
   switch (a.nq * 2 + (a.nops - 1)) {
-    case 2: return launch_q<1, 1>(a, st);
-    case 3: return launch_q<1, 2>(a, st);
-    case 4: return launch_q<2, 1>(a, st);
-    case 5: return launch_q<2, 2>(a, st);
-    case 6: return launch_q<3, 1>(a, st);
-    case 7: return launch_q<3, 2>(a, st);
-    case 8: return launch_q<4, 1>(a, st);
-    case 9: return launch_q<4, 2>(a, st);
-    case 10: return launch_q<5, 1>(a, st);
-    case 12: return launch_q<6, 1>(a, st);
-    case 14: return launch_q<7, 1>(a, st);
-    case 16: return launch_q<8, 1>(a, st);
+    case 2: return launch_q<1, 1, 1>(a, st);
+    case 3: return launch_q<1, 2, 2>(a, st);
+    case 4: return launch_q<2, 1, 1>(a, st);
+    case 5: return launch_q<2, 2, 2>(a, st);
+    case 6: return launch_q<3, 1, 1>(a, st);
+    case 7: return launch_q<3, 2, 2>(a, st);
+    case 8: return launch_q<4, 1, 1>(a, st);
+    case 9: return launch_q<4, 2, 2>(a, st);
+    case 10: return launch_q<5, 1, 1>(a, st);
+    case 11: return launch_q<5, 1, 2>(a, st);
+    case 12: return launch_q<6, 1, 1>(a, st);
+    case 13: return launch_q<6, 1, 2>(a, st);
+    case 14: return launch_q<7, 1, 1>(a, st);
+    case 15: return launch_q<7, 1, 2>(a, st);
+    case 16: return launch_q<8, 1, 1>(a, st);
+    case 17: return launch_q<8, 1, 2>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
