@@ -1020,7 +1020,7 @@ int nadmm_cg_solve(const nadmm_problem* prob, const float* d_X, const float* d_g
   nh.dvec = at<float>(d_ws, L.dvec);
   nh.d = L.s.d;
   nh.newton_mode = 0;
-  NADMM_HIP(launch_newton_head(nh, st));
+  NADMM_HIP(launch_cg_start(nh, at<double>(d_ws, L.rrpart), st));
 
   for (int k = 0; k < max_iter; ++k) {
     if ((rc = cg_iteration(prob, L, path, d_ws, ds, k == 0 ? d_X : nullptr, true, tol, k, st)) != NADMM_OK) return rc;

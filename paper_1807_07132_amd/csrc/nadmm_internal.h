@@ -280,6 +280,8 @@ struct LossFinishArgs {
 hipError_t launch_loss_finish(const LossFinishArgs& a, hipStream_t st);
 
 hipError_t launch_newton_head(const NewtonHeadArgs& a, hipStream_t st);
+// the same as the start of a stand-alone CG solve (newton_mode 0, no partial sums); part: cg_update_blocks(d) doubles
+hipError_t launch_cg_start(const NewtonHeadArgs& a, double* part, hipStream_t st);
 
 struct CgUpdateArgs {
   DevState* st;
