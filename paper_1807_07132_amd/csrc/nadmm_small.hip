@@ -32,12 +32,11 @@ __device__ __forceinline__ float lane_f(float v, int lane) {  // lane: a constan
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-template <int NQ, int NC, int THREADS>
+template <int NQ, int NC, int THREADS, int R>
 __global__ __launch_bounds__(THREADS) void small_solve_kernel(const SmallSolve c) {
   constexpr int PP = 4 * NQ, D = PP * NC;          // padded columns, vector length with them (<= 64)
-  constexpr int R = kRowsPerThread;
   constexpr int W = THREADS / 64;
-  constexpr int DEPTH = THREADS <= 256 ? R : 2;    // chunks of rows in flight while they are staged
+  constexpr int DEPTH = THREADS <= 256 || R < 4 ? R : 2;  // chunks of rows in flight while they are staged
   if (c.outer_flag != nullptr && *c.outer_flag == 0) {  // the outer iteration has stopped: the solve is not made
     if (c.newton && threadIdx.x == 0) {
       c.st->newton_even = 0;
@@ -288,6 +287,7 @@ __global__ __launch_bounds__(THREADS) void small_solve_kernel(const SmallSolve c
     float dv = r;
     const double bound = (double)c.cg_tol * sqrt(gg);
     for (int it = 0; it < c.max_cg && active != 0; ++it) {  // uniform
+      const double inv_rr = 1.0 / rr;  // here and not at its use, where the next direction waits for it
       // rows of D = P o W - P o rowsum(P o W), W = A d
       products(dv, dk);
 #pragma unroll
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(THREADS) void small_solve_kernel(const SmallSolve c
         // a bound of 0 is met by a zero residual only: no square root in the chain
         const bool stop = bound > 0.0 ? sqrt(rr_new) <= bound : rr_new == 0.0;
         if (stop) active = 0;
-        else dv = fmaf((float)(rr_new / rr), dv, r);
+        else dv = fmaf((float)(rr_new * inv_rr), dv, r);
         rr = rr_new;
         iters += 1;
       }
@@ -388,23 +388,30 @@ __global__ __launch_bounds__(THREADS) void small_solve_kernel(const SmallSolve c
   }
 }
 
-template <int NQ, int NC, int THREADS>
+template <int NQ, int NC, int THREADS, int R>
 hipError_t launch_n(const SmallSolve& c, hipStream_t st) {
   constexpr size_t lds = (size_t)THREADS * small_stride(4 * NQ) * sizeof(float);
   static_assert(lds >= (size_t)(THREADS / 64) * 16 * (4 * NQ * NC + 4) * sizeof(float), "the waves' partial sums fit the tile");
   if constexpr (lds + 8192 > 64 * 1024) {
     static LdsLimitMask done{0};
-    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&small_solve_kernel<NQ, NC, THREADS>), &done, (int)lds);
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void*>(&small_solve_kernel<NQ, NC, THREADS, R>), &done, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((small_solve_kernel<NQ, NC, THREADS>), dim3(1), dim3(THREADS), lds, st, c);
+  hipLaunchKernelGGL((small_solve_kernel<NQ, NC, THREADS, R>), dim3(1), dim3(THREADS), lds, st, c);
   return hipGetLastError();
 }
 
 template <int NQ, int NC>
 hipError_t launch_t(const SmallSolve& c, hipStream_t st) {
   if constexpr (4 * NQ * NC <= 64) {
-    return c.n <= 256 * kRowsPerThread ? launch_n<NQ, NC, 256>(c, st) : launch_n<NQ, NC, 512>(c, st);
+    // As many rows per thread as there are, on one wave per SIMD while that holds them (rounds with half the rows per thread on twice the waves take
+    // longer: 1000 x 20, C = 3, a Newton iteration of 10 CG iterations 32.7 us for 29.5, on 1024 threads 55).  Padding four rows for two: 500 x 8, C = 4,
+    // two Newton iterations of 5: 26.8 us, 23.3 without.
+    if (c.n <= 512) return launch_n<NQ, NC, 256, 2>(c, st);
+    if (c.n <= 768) return launch_n<NQ, NC, 256, 3>(c, st);
+    if (c.n <= 1024) return launch_n<NQ, NC, 256, 4>(c, st);
+    if (c.n <= 1536) return launch_n<NQ, NC, 512, 3>(c, st);
+    return launch_n<NQ, NC, 512, 4>(c, st);
   }
   return hipErrorInvalidValue;
 }
