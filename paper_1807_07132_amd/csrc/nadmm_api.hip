@@ -124,7 +124,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->q = off; off += vec;
   const bool two_sets = L->fused_ok || thin;  // the paths with a deferred CG update
   L->pdir2 = off; off += two_sets ? vec : 0;
-  L->r2 = off; off += two_sets ? vec : 0;
+  L->r2 = off; off += vec;  // all paths: the step over several workgroups reads one residual and writes the other
   L->dvec2 = off; off += two_sets ? vec : 0;
   L->pfinal = off; off += two_sets ? vec : 0;
   L->drows = off; off += rows;
@@ -156,8 +156,8 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   if (L->narrow_parts > lblocks) lblocks = L->narrow_parts;
   L->loss_part = off; off += hv_only ? 0 : align256((size_t)lblocks * sizeof(double));
   L->lpart = off; off += hv_only ? 0 : align256((size_t)ls_eval_blocks(s.n) * kCandSlots * sizeof(double));
-  L->dotpart = off; off += hv_only ? 0 : align256((size_t)2 * reduce_out_blocks(s.d) * sizeof(double));  // two sums per workgroup
-  L->rrpart = off; off += hv_only ? 0 : align256((size_t)cg_update_blocks(s.d) * sizeof(double));
+  L->dotpart = off; off += hv_only ? 0 : align256((size_t)4 * reduce_out_blocks(s.d) * sizeof(double));  // up to four sums per workgroup
+  L->rrpart = off; off += hv_only ? 0 : align256((size_t)cg_start_blocks(s.d) * sizeof(double));
   // partial sums of the penalty terms and of ||g||^2 that a Newton iteration's gradient leaves for its head (apart from dotpart:
   // the head may run beside the first reduction of the CG solve, which writes that)
   L->headpart = off; off += hv_only ? 0 : align256((size_t)2 * reduce_out_blocks(s.d) * sizeof(double));
@@ -325,7 +325,7 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
       sa.out = at<float>(ws, L.zw);
       sa.w = sparse_windows_of(L, ws, true);
       sa.nops = both ? 2 : 1;
-      NADMM_HIP(launch_sparse_pack(ra.B0 != nullptr ? ra.B0 : ra.B1, both ? ra.B1 : nullptr, prob->p, NC, pack, ra.flag, st));
+      if (!packed) NADMM_HIP(launch_sparse_pack(ra.B0 != nullptr ? ra.B0 : ra.B1, both ? ra.B1 : nullptr, prob->p, NC, pack, ra.flag, st));
       NADMM_HIP(launch_spmm(sa, st));
     }
     if (with_cols) ra.rows_out = pack;  // the rows of D lie as the product with A^T reads them
@@ -427,7 +427,8 @@ int reduce(const nadmm_problem* prob, const Layout& L, void* ws, int nparts, int
 int hv_apply(const nadmm_problem* prob, const Layout& L, int path, void* ws, const float* X, bool write_pcache,
              const float* v, float* out, double* dot_part, const int32_t* flag, int* nparts_out, hipStream_t st,
              const CgPend* cg = nullptr, const int32_t* red_flag = nullptr, const int32_t* cur = nullptr,
-             const float* v_alt = nullptr, float* w_rows = nullptr, const NewtonHeadArgs* head = nullptr, bool packed = false) {
+             const float* v_alt = nullptr, float* w_rows = nullptr, const NewtonHeadArgs* head = nullptr, bool packed = false,
+             const float* r_dot = nullptr) {
   RowArgs ra = blank_rows();
   ra.kind = kRowsHv;
   ra.Z1out = w_rows;  // fused single-pass path only: the directional logits A v, n x (C-1)
@@ -447,6 +448,7 @@ int hv_apply(const nadmm_problem* prob, const Layout& L, int path, void* ws, con
   ReduceArgs r = reduce_args(prob, L, ws, nparts, 0, v, out, dot_part, red_flag != nullptr ? red_flag : flag);
   r.cur = cur;
   r.V_alt = v_alt;
+  r.r_dot = r_dot;
   if (head != nullptr) {
     r.has_head = 1;
     r.head = *head;
@@ -531,6 +533,7 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
                     &ds->cgs[k & 1].cur, at<float>(ws, L.dvec2), w_rows);
   }
   CgUpdateArgs cu;
+  std::memset(&cu, 0, sizeof(cu));
   cu.st = ds;
   cu.pdir = at<float>(ws, L.pdir);
   cu.r = at<float>(ws, L.r);
@@ -549,17 +552,32 @@ int cg_iteration(const nadmm_problem* prob, const Layout& L, int path, void* ws,
     NADMM_HIP(launch_cg_reduce_update(reduce_args(prob, L, ws, nparts, 0, dvec, q, nullptr, &ds->cg_active), cu, st));
     return NADMM_OK;
   }
-  // wide rows with long vectors: the update's second kernel also lays out the direction for the next iteration's sweep
-  const bool packs = path == 4 && wide_sweep(L, false, true) && cg_update_two_kernels(L.s.d);
-  int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, q, at<double>(ws, L.dotpart), &ds->cg_active, nullptr, st, nullptr, nullptr,
-                    nullptr, nullptr, nullptr, nullptr, packs && k > 0 && X == nullptr);
+  // the update over several workgroups; on sparse data and for wide rows it also lays out the direction for the next iteration's sweep
+  const bool one = cg_one_step(L.s.d), wide_pack = path == 4 && one && wide_sweep(L, false, true) && !narrow_sweep(L, false, true);
+  const bool packs = path == 5 || wide_pack;
+  const int32_t* flag = &ds->cg_active;
+  if (one) {
+    cu.slot_in = k & 1;
+    if ((k & 1) != 0) cu.r = at<float>(ws, L.r2);
+    cu.r_out = at<float>(ws, (k & 1) != 0 ? L.r : L.r2);
+    cu.lambda = prob->lambda;
+    cu.rho = prob->rho;
+    cu.rho_scale = L.rho_scale;
+    flag = &ds->cgs[k & 1].active;
+  }
+  int rc = hv_apply(prob, L, path, ws, X, write_pcache, dvec, q, at<double>(ws, L.dotpart), flag, nullptr, st, nullptr, nullptr,
+                    nullptr, nullptr, nullptr, nullptr, packs && k > 0 && X == nullptr, one ? cu.r : nullptr);
   if (rc != NADMM_OK) return rc;
-  if (!packs) {
-    NADMM_HIP(launch_cg_update(cu, st));
+  if (path == 5) {
+    cu.pack = at<float>(ws, L.pack);
+    cu.pack_ld = 4 * sparse_group(L.s.NC);
+    cu.NC = L.s.NC;
+  }
+  if (wide_pack) {
+    NADMM_HIP(launch_wide_direction(cu, L.s, at<char>(ws, L.operands), st));
     return NADMM_OK;
   }
-  NADMM_HIP(launch_cg_residual(cu, st));
-  NADMM_HIP(launch_wide_direction(cu, L.s, at<char>(ws, L.operands), st));
+  NADMM_HIP(launch_cg_update(cu, st));
   return NADMM_OK;
 }
 

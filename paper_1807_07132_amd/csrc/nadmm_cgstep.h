@@ -29,6 +29,93 @@ __device__ __forceinline__ double cg_block_sum(double v, double* sm) {
   return t;
 }
 
+// The scalars of a CG update that several workgroups make, each with all of them (identical arithmetic: they agree bit for bit), so that no
+// kernel has to run between the residual and the direction that needs its norm.  With q = mu r + t, mu = lambda + rho,
+//   r' = r - a q = c r - a t,  c = 1 - a mu,   ||r'||^2 = c^2 <r, r> - 2 a c <r, t> + a^2 <t, t>,
+// all sums float64 of the vectors as they are.  mu r is what the data leave of H where its linear term outweighs them and CG
+// converges in a few iterations; the sums of r and q themselves would cancel there.  Where more than all but 10^-7 of the terms cancels
+// all the same (their error, 2^-53 of them, would be above 10^-9 of the result; float32 vectors round at 6 10^-8) each workgroup sums the norm from
+// the vectors.  (The norm is not carried over from one iteration to the next: where each step takes 10^6 off it, the rounding of r would be
+// all that is left of such a sum after two.)  sm: 5 THREADS / 64 doubles.
+struct CgStep {
+  bool go, stop;
+  float al, be;
+};
+template <int THREADS>
+__device__ __forceinline__ CgStep cg_step_scalars(const CgUpdateArgs& a, double* sm) {
+  constexpr int W = THREADS / 64, U = 4;
+  const CgSlot in = a.st->cgs[a.slot_in];
+  const double gg = a.st->gg_cg;
+  const double mu = linear_factor(a.lambda, a.rho, a.rho_scale);
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int k0 = threadIdx.x; k0 < a.ndot; k0 += THREADS * U) {
+    double x[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + u * THREADS < a.ndot ? k0 + u * THREADS : a.ndot - 1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[u][i] = a.dot_part[(size_t)i * a.ndot + k];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] += k0 + u * THREADS < a.ndot ? x[u][i] : 0.0;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = mfma_detail::wave64_sum(v[i]);
+    if (lane == 0) sm[i * W + wave] = v[i];
+  }
+  lds_barrier();
+  double dq = 0.0, rt = 0.0, tt = 0.0, rr = 0.0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    dq += sm[w];
+    rt += sm[W + w];
+    tt += sm[2 * W + w];
+    rr += sm[3 * W + w];
+  }
+  CgStep s;
+  s.go = in.active != 0 && dq > 0.0 && isfinite(dq);  // no positive curvature: keep the current iterate
+  s.al = s.go ? (float)(rr / dq) : 0.f;
+  const double al = s.al, c = 1.0 - al * mu;
+  const double size = c * c * rr + al * al * tt;
+  double rr_new = size - 2.0 * al * c * rt;
+  if (s.go && !(rr_new > 1e-7 * size)) {  // uniform over the grid
+    constexpr int B = 8;
+    double acc = 0.0;
+    for (int64_t e0 = threadIdx.x; e0 < a.d; e0 += THREADS * B) {
+      float q[B], r[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int64_t e = e0 + u * THREADS < a.d ? e0 + u * THREADS : a.d - 1;
+        q[u] = a.q[e];
+        r[u] = a.r[e];
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const double x = e0 + u * THREADS < a.d ? (double)fmaf(-s.al, q[u], r[u]) : 0.0;
+        acc += x * x;
+      }
+    }
+    rr_new = cg_block_sum<THREADS>(acc, sm + 4 * W);
+  }
+  s.stop = sqrt(rr_new) <= (double)a.tol * sqrt(gg);
+  s.be = (float)(rr_new / rr);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    CgSlot out = in;
+    out.rr = s.go ? rr_new : in.rr;
+    out.active = s.go && !s.stop ? 1 : 0;
+    out.iters = in.iters + (s.go ? 1 : 0);
+    a.st->cgs[a.slot_in ^ 1] = out;
+    a.st->rr = out.rr;  // for whatever comes behind the solve
+    a.st->cg_iters = out.iters;
+    a.st->cg_active = out.active;
+  }
+  return s;
+}
+
 // Leaves the vector the caller wants (d', or p' if c.final_p) in vec[0 .. dlen) (LDS or global, 16-byte aligned;
 // complete and visible to the whole workgroup on return).  Returns false if the caller wants d and CG is, or has
 // just become, inactive: there is no product left to form.  dlen <= 4 THREADS * PERQ, ndot <= THREADS, the vectors

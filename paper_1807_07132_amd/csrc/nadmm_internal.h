@@ -66,9 +66,8 @@ struct DevState {
   int32_t cg_ok;    //   0 if the first kernel met non-positive curvature
   float cg_alpha;   //   step length of this CG iteration
   int32_t newton_odd;
-  int32_t pad_[2];
   double rr_prev;   //   ||r||^2 before this CG iteration
-  CgSlot cgs[2];    // deferred CG update (fused single-pass path): see CgPend
+  CgSlot cgs[2];    // CG updates that several workgroups make (CgPend, cg_step_scalars)
   float cg_alphas[kCgHist];  // deferred CG update: step length of every iteration taken (p = sum_k alpha_k d_k)
   nadmm_stats stats;  // copied to the host at the end of nadmm_local_newton
 };
@@ -244,6 +243,7 @@ struct ReduceArgs {
   const float* V_alt;     // kind 0, optional with cur: V is V_alt if *cur != 0 (the two vector sets of a deferred CG update)
   const int32_t* cur;
   double* dot_part;       // kind 0, optional: per-workgroup sums of out[e] * V[e], reduce_out_blocks(d) entries
+  const float* r_dot;     // with dot_part (d <= 2^18), optional: the residual r; behind them as many sums of r t, of t^2 and of r^2, t = out - (lambda + rho) r
   double* pen_part;       // kind 1, optional: per-workgroup sums of the penalty terms lambda/2 x^2 + rho/2 (x - z + y/rho)^2
   double* gg_part;        // kind 1, optional: per-workgroup sums of out[e]^2
   float* cg_p;            // kind 1, optional: CG start from the gradient just formed, p = 0, r = d = -out
@@ -280,7 +280,7 @@ struct LossFinishArgs {
 hipError_t launch_loss_finish(const LossFinishArgs& a, hipStream_t st);
 
 hipError_t launch_newton_head(const NewtonHeadArgs& a, hipStream_t st);
-// the same as the start of a stand-alone CG solve (newton_mode 0, no partial sums); part: cg_update_blocks(d) doubles
+// the same as the start of a stand-alone CG solve (newton_mode 0, no partial sums); part: cg_start_blocks(d) doubles
 hipError_t launch_cg_start(const NewtonHeadArgs& a, double* part, hipStream_t st);
 
 struct CgUpdateArgs {
@@ -289,21 +289,31 @@ struct CgUpdateArgs {
   float* r;
   float* dvec;
   const float* q;
-  const double* dot_part;  // partial sums of <d, q> left by the reduction that formed q
-  int32_t ndot;
-  double* rr_part;         // cg_update_blocks(d) partial sums of the new ||r||^2 (two-kernel form, long vectors)
+  const double* dot_part;  // partial sums left by the reduction that formed q: of <d, q>, and behind them for the step those of ReduceArgs.r_dot
+  int32_t ndot;            // of each
+  double* rr_part;         // two-kernel form: cg_start_blocks(d) partial sums of the new ||r||^2
   int64_t d;
   float tol;
+  // the step over several workgroups (cg_one_step): st->cgs[slot_in] is read and the other one written, likewise r and r_out
+  int32_t slot_in;
+  float* r_out;
+  float lambda, rho;       // of H's linear term
+  const float* rho_scale;
+  float* pack;             // optional: the new direction also as rows of pack_ld floats for each NC elements, as the product with a sparse A reads it
+  int32_t pack_ld, NC;
 };
-int cg_update_blocks(int64_t d);
+bool cg_one_step(int64_t d);
+// lambda + rho_scale rho: the same bits wherever the step's sums are formed and used
+__host__ __device__ inline float linear_factor(float lambda, float rho, const float* rho_scale) {
+  return rho_scale != nullptr ? fmaf(rho, *rho_scale, lambda) : lambda + rho;
+}
+// the update with as many workgroups as the vectors take, in one launch (cg_one_step) or in two
+hipError_t launch_cg_update(const CgUpdateArgs& a, hipStream_t st);
+int cg_start_blocks(int64_t d);
 // Small problems (d <= 1024 and at most 64 partial sums per thread): the reduction of the partial sums
 // of A^T D, the linear term and the whole CG update in one single-workgroup kernel.
 bool cg_fused_tail_supported(int64_t d, int nparts);
 hipError_t launch_cg_reduce_update(const ReduceArgs& r, const CgUpdateArgs& a, hipStream_t st);
-hipError_t launch_cg_update(const CgUpdateArgs& a, hipStream_t st);
-// long vectors take two kernels, of which this is the first (residual and its partial sums)
-bool cg_update_two_kernels(int64_t d);
-hipError_t launch_cg_residual(const CgUpdateArgs& a, hipStream_t st);
 
 struct CgFinishArgs {
   const DevState* st;
@@ -474,7 +484,7 @@ size_t wide_operand_bytes(const Shape& s);
 // packs the operands into `operands` and makes the sweep; partial sums and partial losses as launch_fused
 // packed: the operands of this call are in place (launch_wide_direction)
 hipError_t launch_wide(const RowArgs& a, void* operands, bool packed, float* partial, int nparts, hipStream_t st);
-// the second half of a two-kernel CG update; leaves the new direction as the operands of the next product as well
+// launch_cg_update that leaves the new direction as the operands of the next product as well (cg_one_step only)
 hipError_t launch_wide_direction(const CgUpdateArgs& a, const Shape& s, void* operands, hipStream_t st);
 
 // ---- sparse storage of A (nadmm_sparse.hip) ----

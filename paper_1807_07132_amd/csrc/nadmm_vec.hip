@@ -117,6 +117,7 @@ __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (a.kind == 0) {
     lin0 = a.V[ec];
     lin1 = a.V_alt != nullptr ? a.V_alt[ec] : 0.f;
+    lin2 = a.r_dot != nullptr ? a.r_dot[ec] : 0.f;
   } else {
     lin0 = a.X[ec];
     lin1 = a.z != nullptr ? a.z[ec] : 0.f;
@@ -197,6 +198,16 @@ __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (first != nullptr) {
     prod = mfma_detail::half32_sum(prod);
     if (el == 0) first[blockIdx.x] = prod;
+    if (a.kind == 0 && a.r_dot != nullptr) {
+      const int n = FINISH ? gridDim.x - 1 : gridDim.x;
+      const double rv = ok ? (double)lin2 : 0.0, t = ok ? (double)out - (double)linear_factor(a.lambda, a.rho, a.rho_scale) * rv : 0.0;
+      const double rt = mfma_detail::half32_sum(rv * t), tt = mfma_detail::half32_sum(t * t), rr = mfma_detail::half32_sum(rv * rv);
+      if (el == 0) {
+        first[n + blockIdx.x] = rt;
+        first[2 * n + blockIdx.x] = tt;
+        first[3 * n + blockIdx.x] = rr;
+      }
+    }
   }
   if (a.kind != 0 && a.pen_part != nullptr) {
     pen = mfma_detail::half32_sum(pen);
@@ -332,8 +343,8 @@ __global__ void state_init_kernel(DevState* st, const int32_t* outer_flag) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   st->loss = 0.0; st->gg = 0.0; st->rr = 0.0; st->gg_cg = 0.0; st->loss_new = 0.0; st->loss_initial = 0.0;
   st->alpha = 0.f;
-  st->newton_even = st->newton_odd = outer_flag ? *outer_flag : 1; st->cg_active = st->newton_even; st->cg_iters = 0; st->armijo_ok = 1; st->ls_evals = 0;
   st->cg_go = 0; st->cg_ok = 1; st->cg_alpha = 0.f; st->rr_prev = 0.0;
+  st->newton_even = st->newton_odd = outer_flag ? *outer_flag : 1; st->cg_active = st->newton_even; st->cg_iters = 0; st->armijo_ok = 1; st->ls_evals = 0;
   nadmm_stats* s = &st->stats;
   s->newton_iters = 0; s->cg_iters_total = 0; s->ls_evals_total = 0; s->armijo_failed = 0;
   s->loss_initial = 0.0; s->loss_final = 0.0; s->grad_norm_final = 0.0;
@@ -393,90 +404,13 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a) {
 
 __global__ __launch_bounds__(kTail) void newton_head_kernel(const NewtonHeadArgs a) { newton_head_body(a); }
 
-// One CG iteration's vector work, given q = H d:  a = rr / <d,q>; p += a d; r -= a q;
-// stop on ||r|| <= tol ||g|| (eq. inexact); else d = r + (rr'/rr) d.
-// <d, q> arrives as partial sums from the reduction that formed q.  Every vector is then read once:
-// pass 1 forms the new residual (kept in registers, d <= PER * 1024) and its norm, pass 2 updates the
-// iterate and the direction.  Loads go out in blocks of 8 per vector and thread.  One workgroup: for
-// short vectors a second launch would cost more than the serial work.
-template <int PER>
-__global__ __launch_bounds__(kTail) void cg_update_kernel(const CgUpdateArgs a) {
-  __shared__ double sm[17];
-  DevState* st = a.st;
-  if (st->cg_active == 0) return;
-  constexpr int U = 8;
-  constexpr int N = PER > 0 ? PER : U;
-  static_assert(N % U == 0, "blocks of 8");
-  constexpr int kUnroll = PER > 0 ? PER / U : 1;
-  const int nblk = PER > 0 ? PER / U : (int)((a.d + (int64_t)U * kTail - 1) / ((int64_t)U * kTail));
-  const double dq = partial_sum_block(a.dot_part, a.ndot, sm);
-  const double rr = st->rr;
-  const double gg = st->gg_cg;
-  if (!(dq > 0.0) || !isfinite(dq)) {  // no positive curvature: keep the current iterate
-    __syncthreads();
-    if (threadIdx.x == 0) st->cg_active = 0;
-    return;
-  }
-  const float al = (float)(rr / dq);
-  float rn[N];
-  double rr_new = 0.0;
-#pragma unroll kUnroll
-  for (int b = 0; b < nblk; ++b) {
-    float y[U], re[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t e = threadIdx.x + (int64_t)(b * U + u) * kTail;
-      const bool ok = e < a.d;
-      y[u] = ok ? a.q[e] : 0.f;
-      re[u] = ok ? a.r[e] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t e = threadIdx.x + (int64_t)(b * U + u) * kTail;
-      const float v = fmaf(-al, y[u], re[u]);
-      rn[PER > 0 ? b * U + u : u] = v;
-      if (e < a.d) a.r[e] = v;
-      rr_new += (double)v * (double)v;
-    }
-  }
-  rr_new = block_sum(rr_new, sm);
-  const bool stop = sqrt(rr_new) <= (double)a.tol * sqrt(gg);
-  const float be = (float)(rr_new / rr);
-  // every thread re-reads only elements of r that it wrote itself
-#pragma unroll kUnroll
-  for (int b = 0; b < nblk; ++b) {
-    float x[U], pe[U], re[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t e = threadIdx.x + (int64_t)(b * U + u) * kTail;
-      const bool ok = e < a.d;
-      x[u] = ok ? a.dvec[e] : 0.f;
-      pe[u] = ok ? a.pdir[e] : 0.f;
-      re[u] = PER > 0 ? rn[b * U + u] : (ok ? a.r[e] : 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t e = threadIdx.x + (int64_t)(b * U + u) * kTail;
-      if (e < a.d) {
-        a.pdir[e] = fmaf(al, x[u], pe[u]);
-        if (!stop) a.dvec[e] = fmaf(be, x[u], re[u]);
-      }
-    }
-  }
-  if (threadIdx.x == 0) {
-    st->rr = rr_new;
-    st->cg_iters += 1;
-    if (stop) st->cg_active = 0;
-  }
-}
-
-// The same update for long vectors (d > 24576), spread over several workgroups in two kernels; the sum
-// of the new ||r||^2 passes between them as per-workgroup partials, added in a fixed order.  Flags that
-// one kernel reads are never written by the same kernel: the first one reads cg_active and leaves its
-// verdict in cg_go, the second one reads cg_go and writes cg_active.
 constexpr int kCgThreads = 256;
 constexpr int kCgPerThread = 8;
 constexpr int kCgChunk = kCgThreads * kCgPerThread;
+// Up to here the update is one launch.  What it costs against two is what each workgroup does for itself, 4 sums over d / 32 values and in the
+// worst case (cg_step_scalars) one over the vectors.  10 iterations with two launches and with one: wide rows, d = 27648: 349 and 320 us, 64512:
+// 586 and 549, 76000: 656 and 620, 114000: 832 and 796; sparse rows, 52500: 426 and 387, 126000: 470 and 437, 240000: 528 and 515.
+constexpr int64_t kCgStepMax = 131072;
 
 // Start of a CG solve on a long vector: p = 0, r = d = -g and partial sums of ||g||^2, one per workgroup.  newton_head_kernel alone is one workgroup
 // at 3 vectors written for one read: 12.9 us at 27648 elements (two launches 9.5), 21 at 76000, 450 at 1.9 million (about 14).
@@ -505,6 +439,57 @@ __global__ __launch_bounds__(kCgThreads) void cg_start_kernel(const NewtonHeadAr
   if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
+__device__ __forceinline__ void pack_element(float* __restrict__ pack, int pack_ld, int NC, int64_t e, float v) {
+  const uint32_t row = (uint32_t)e / (uint32_t)NC;  // d <= 2^28
+  pack[(size_t)row * pack_ld + ((uint32_t)e - row * (uint32_t)NC)] = v;
+}
+
+// One CG iteration's vector work (Section 2.4), given q = H d: a = rr / <d, q>; p += a d; r -= a q; stop on ||r|| <= tol ||g|| (eq. inexact);
+// else d = r + (rr'/rr) d.  Every workgroup takes the scalars from the reduction's partial sums for itself (cg_step_scalars).  One workgroup that
+// makes two passes over the vectors, up to 24576 elements, and two launches beyond cost 2 to 5 us more per iteration: CG of 4 iterations at 30000 x 500,
+// C = 20: 159 -> 139 us; 3000 x 4000, C = 10: 231 -> 215; on 3000 sparse rows of 200 entries, p = 2500, C = 6: 157 -> 137.
+__global__ __launch_bounds__(kCgThreads) void cg_step_kernel(const CgUpdateArgs a) {
+  __shared__ double sm[5 * (kCgThreads / 64)];
+  int64_t base = (int64_t)blockIdx.x * kCgChunk;
+  float x[kCgPerThread], pe[kCgPerThread], re[kCgPerThread], y[kCgPerThread];
+  auto request = [&]() {
+#pragma unroll
+    for (int u = 0; u < kCgPerThread; ++u) {
+      const int64_t e = base + threadIdx.x + u * kCgThreads, ec = e < a.d ? e : a.d - 1;
+      x[u] = a.dvec[ec];
+      pe[u] = a.pdir[ec];
+      re[u] = a.r[ec];
+      y[u] = a.q[ec];
+    }
+  };
+  request();
+  const CgStep s = cg_step_scalars<kCgThreads>(a, sm);
+  if (!s.go) return;
+  while (true) {
+#pragma unroll
+    for (int u = 0; u < kCgPerThread; ++u) {
+      const int64_t e = base + threadIdx.x + u * kCgThreads;
+      if (e < a.d) {
+        const float r = fmaf(-s.al, y[u], re[u]);
+        a.r_out[e] = r;
+        a.pdir[e] = fmaf(s.al, x[u], pe[u]);
+        if (!s.stop) {
+          const float d = fmaf(s.be, x[u], r);
+          a.dvec[e] = d;
+          if (a.pack != nullptr) pack_element(a.pack, a.pack_ld, a.NC, e, d);
+        }
+      }
+    }
+    base += (int64_t)gridDim.x * kCgChunk;
+    if (base >= a.d) break;
+    request();
+  }
+}
+
+// The same update for vectors too long for that (d > kCgStepMax), in two kernels; the sum
+// of the new ||r||^2 passes between them as per-workgroup partials, added in a fixed order.  Flags that
+// one kernel reads are never written by the same kernel: the first one reads cg_active and leaves its
+// verdict in cg_go, the second one reads cg_go and writes cg_active.
 __global__ __launch_bounds__(kCgThreads) void cg_residual_kernel(const CgUpdateArgs a) {
   __shared__ double sm[17];
   DevState* st = a.st;
@@ -567,7 +552,11 @@ __global__ __launch_bounds__(kCgThreads) void cg_direction_kernel(const CgUpdate
       const int64_t e = base + threadIdx.x + u * kCgThreads;
       if (e < a.d) {
         a.pdir[e] = fmaf(al, x[u], pe[u]);
-        if (!stop) a.dvec[e] = fmaf(be, x[u], re[u]);
+        if (!stop) {
+          const float d = fmaf(be, x[u], re[u]);
+          a.dvec[e] = d;
+          if (a.pack != nullptr) pack_element(a.pack, a.pack_ld, a.NC, e, d);
+        }
       }
     }
   }
@@ -1188,40 +1177,36 @@ hipError_t launch_newton_head(const NewtonHeadArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+int cg_start_blocks(int64_t d) {
+  const int64_t b = (d + kCgChunk - 1) / kCgChunk;
+  return (int)(b < 1024 ? b : 1024);
+}
+
 hipError_t launch_cg_start(const NewtonHeadArgs& a, double* part, hipStream_t st) {
   if (a.newton_mode != 0 || a.gg_part != nullptr || part == nullptr) return hipErrorInvalidValue;
-  if (!cg_update_two_kernels(a.d)) return launch_newton_head(a, st);
-  hipLaunchKernelGGL(cg_start_kernel, dim3(cg_update_blocks(a.d)), dim3(kCgThreads), 0, st, a, part);
+  if (a.d <= 24 * kTail) return launch_newton_head(a, st);
+  hipLaunchKernelGGL(cg_start_kernel, dim3(cg_start_blocks(a.d)), dim3(kCgThreads), 0, st, a, part);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   NewtonHeadArgs h = a;
   h.gg_part = part;
-  h.npart = cg_update_blocks(a.d);
+  h.npart = cg_start_blocks(a.d);
   return launch_newton_head(h, st);
 }
 
-int cg_update_blocks(int64_t d) {
-  int64_t b = (d + kCgChunk - 1) / kCgChunk;
-  return (int)(b < 1024 ? b : 1024);
-}
-
-bool cg_update_two_kernels(int64_t d) { return d > 24 * kTail; }
-
-hipError_t launch_cg_residual(const CgUpdateArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(cg_residual_kernel, dim3(cg_update_blocks(a.d)), dim3(kCgThreads), 0, st, a);
-  return hipGetLastError();
-}
+bool cg_one_step(int64_t d) { return d <= kCgStepMax; }
 
 hipError_t launch_cg_update(const CgUpdateArgs& a, hipStream_t st) {
-  if (a.d <= 8 * kTail) {
-    hipLaunchKernelGGL(cg_update_kernel<8>, dim3(1), dim3(kTail), 0, st, a);
-  } else if (!cg_update_two_kernels(a.d)) {
-    hipLaunchKernelGGL(cg_update_kernel<24>, dim3(1), dim3(kTail), 0, st, a);
-  } else {
-    const hipError_t e = launch_cg_residual(a, st);
+  if (a.ndot < 1 || a.d < 1) return hipErrorInvalidValue;
+  if (!cg_one_step(a.d)) {
+    hipLaunchKernelGGL(cg_residual_kernel, dim3(cg_start_blocks(a.d)), dim3(kCgThreads), 0, st, a);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cg_direction_kernel, dim3(cg_update_blocks(a.d)), dim3(kCgThreads), 0, st, a);
+    hipLaunchKernelGGL(cg_direction_kernel, dim3(cg_start_blocks(a.d)), dim3(kCgThreads), 0, st, a);
+    return hipGetLastError();
   }
+  if (a.r_out == nullptr || a.r_out == a.r) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(cg_step_kernel, dim3(cg_start_blocks(a.d)), dim3(kCgThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -656,7 +656,7 @@ def test_wide_or_two_sweeps_with_many_classes(n, p, C):
     assert rel_l2(host(X), oracle_newton_following(op, w.X0, w, st["alpha"])[0]) <= TOL_ITERATE
 
 
-# Long vectors of wide rows (d > 24576): the CG update's second kernel lays out the next direction's operands.  A solve of ten
+# Long vectors of wide rows: the CG update's kernel lays out the next direction's operands.  A solve of ten
 # iterations that is stopped on the way by its tolerance and one that is not, one block of classes, extra classes, two blocks.
 @pytest.mark.parametrize("tol", [0.0, 0.05])
 @pytest.mark.parametrize("n,p,C", [(300, 2740, 10), (200, 1310, 20), (210, 1030, 25)])
@@ -672,6 +672,26 @@ def test_wide_cg_on_long_vectors(n, p, C, tol):
     p_ref, it_ref, rel_ref = orc.cg(op, w.X0, g.astype(np.float64), 10, tol)
     assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
     assert (it_ref < 10) == (tol > 0.0)
+
+
+# CG updates made by several workgroups, each of which takes the norm of the new residual from sums of the old one and of what the
+# data leave of H (path 1: the general kernels).  Vectors of 1 and several workgroups and up to one, at and beyond the length where two kernels take over; a linear term that
+# is nothing, as large as the data and far above them, where the sums cancel and the norm is summed from the vectors.
+# Bounds: those of the other solves of fixed length; a residual at rounding level has only that level.
+@pytest.mark.parametrize("reg", [0.05, 0.5, 1e4])
+@pytest.mark.parametrize("n,p,C,path", [(30, 2048, 2, 1), (60, 1000, 6, 1), (24, 131072, 2, 1), (50, 8193, 9, 1), (300, 1400, 10, 4), (24, 131073, 2, 1)])
+def test_cg_update_of_several_workgroups(n, p, C, path, reg):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    gp = nadmm.Problem(dev(w.A), dev(w.b), C, w.s, reg, reg, dev(w.z), dev(w.y))
+    op = oracle_problem(w)
+    op.lam, op.rho = reg, reg
+    g = orc.loss_grad(op, w.X0)[1].astype(np.float32)
+    force_path(gp, path)
+    for K in (1, 2, 6):
+        p_out, it, rel = nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g), K, 0.0)
+        p_ref, it_ref, rel_ref = orc.cg(op, w.X0, g.astype(np.float64), K, 0.0)
+        assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
+        assert abs(rel.item() - rel_ref) <= 5e-3 * rel_ref + 1e-6
 
 
 # Rows of up to 128 columns: the kernel for narrow rows (1 to 4 column steps, one and two blocks of classes, tiles of 16, 32 and
