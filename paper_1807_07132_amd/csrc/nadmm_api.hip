@@ -124,7 +124,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->q = off; off += vec;
   const bool two_sets = L->fused_ok || thin;  // the paths with a deferred CG update
   L->pdir2 = off; off += two_sets ? vec : 0;
-  L->r2 = off; off += vec;  // all paths: the step over several workgroups reads one residual and writes the other
+  L->r2 = off; off += two_sets || cg_one_step(s.d) ? vec : 0;  // the one-launch CG update reads one residual and writes the other
   L->dvec2 = off; off += two_sets ? vec : 0;
   L->pfinal = off; off += two_sets ? vec : 0;
   L->drows = off; off += rows;
