@@ -243,7 +243,6 @@ struct ReduceArgs {
   const float* V_alt;     // kind 0, optional with cur: V is V_alt if *cur != 0 (the two vector sets of a deferred CG update)
   const int32_t* cur;
   double* dot_part;       // kind 0, optional: per-workgroup sums of out[e] * V[e], reduce_out_blocks(d) entries
-  const float* r_dot;     // with dot_part (d <= 2^18), optional: the residual r; behind them as many sums of r t, of t^2 and of r^2, t = out - (lambda + rho) r
   double* pen_part;       // kind 1, optional: per-workgroup sums of the penalty terms lambda/2 x^2 + rho/2 (x - z + y/rho)^2
   double* gg_part;        // kind 1, optional: per-workgroup sums of out[e]^2
   float* cg_p;            // kind 1, optional: CG start from the gradient just formed, p = 0, r = d = -out
@@ -259,6 +258,7 @@ struct ReduceArgs {
   // Hessian-vector product of a CG solve needs nothing of it: its direction is the -g that the gradient's reduction left)
   int32_t has_head;
   NewtonHeadArgs head;
+  const float* r_dot;     // with dot_part (d <= 2^18), optional: the residual r; behind them as many sums of r t, of t^2 and of r^2, t = out - (lambda + rho) r
 };
 constexpr int64_t kReduceFinishMax = 16384;
 int reduce_out_blocks(int64_t d);

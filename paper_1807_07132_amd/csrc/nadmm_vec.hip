@@ -98,8 +98,9 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a);  // d
 
 // FINISH: launched with one workgroup more, which finishes the objective after a gradient pass or does the work of
 // newton_head_kernel beside the first reduction of a CG solve (an instantiation of its own: that workgroup's registers
-// would cost the plain kernel its occupancy on long vectors).
-template <bool FINISH>
+// would cost the plain kernel its occupancy on long vectors).  STEP: with the sums of r_dot (an instantiation of
+// its own, and r_dot the last of the arguments: as a condition inside and in the middle of them every gradient took 0.2 us more).
+template <bool FINISH, bool STEP = false>
 __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (FINISH && blockIdx.x == gridDim.x - 1) {  // the workgroup beyond the last 32 elements
     if (a.has_head != 0) newton_head_body(a.head);  // goes by the same flag, newton_entered
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (a.kind == 0) {
     lin0 = a.V[ec];
     lin1 = a.V_alt != nullptr ? a.V_alt[ec] : 0.f;
-    lin2 = a.r_dot != nullptr ? a.r_dot[ec] : 0.f;
+    if constexpr (STEP) lin2 = a.r_dot[ec];
   } else {
     lin0 = a.X[ec];
     lin1 = a.z != nullptr ? a.z[ec] : 0.f;
@@ -198,8 +199,8 @@ __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (first != nullptr) {
     prod = mfma_detail::half32_sum(prod);
     if (el == 0) first[blockIdx.x] = prod;
-    if (a.kind == 0 && a.r_dot != nullptr) {
-      const int n = FINISH ? gridDim.x - 1 : gridDim.x;
+    if constexpr (STEP) {
+      const int n = gridDim.x;
       const double rv = ok ? (double)lin2 : 0.0, t = ok ? (double)out - (double)linear_factor(a.lambda, a.rho, a.rho_scale) * rv : 0.0;
       const double rt = mfma_detail::half32_sum(rv * t), tt = mfma_detail::half32_sum(t * t), rr = mfma_detail::half32_sum(rv * rv);
       if (el == 0) {
@@ -1156,8 +1157,10 @@ hipError_t launch_reduce_out(const ReduceArgs& a, hipStream_t st) {
   if (a.has_head != 0 && (a.kind != 0 || a.d > kReduceFinishMax || a.lf_loss_out != nullptr || a.head.st == nullptr ||
                           a.head.gg_part == nullptr || a.head.pen_part == nullptr))
     return hipErrorInvalidValue;
+  if (a.r_dot != nullptr && (a.kind != 0 || a.has_head != 0 || a.d > kWideFrom || a.dot_part == nullptr)) return hipErrorInvalidValue;
   if (a.d > kWideFrom) hipLaunchKernelGGL(reduce_out_wide_kernel, dim3(blocks), dim3(256), 0, st, a);
   else if (a.lf_loss_out != nullptr || a.has_head != 0) hipLaunchKernelGGL(reduce_out_kernel<true>, dim3(blocks + 1), dim3(256), 0, st, a);
+  else if (a.r_dot != nullptr) hipLaunchKernelGGL((reduce_out_kernel<false, true>), dim3(blocks), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(reduce_out_kernel<false>, dim3(blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }
