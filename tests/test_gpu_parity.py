@@ -637,7 +637,7 @@ def test_wide_single_pass_with_few_steps(n, p, C, pad):
     test_wide_single_pass(n, p, C, pad)
 
 
-# Sweeps with X of 17 to 32 free classes on either side of the numbers of rows from which two sweeps are taken instead (fewer than 16
+# Sweeps with X of 17 to 32 free classes at numbers of rows and columns where one sweep or two may be the faster (up to 16
 # column steps; two blocks of classes over 48 steps): gradient, objective, Newton (whose head adds up the row losses that the sweep left).
 @pytest.mark.parametrize("n,p,C", [(12288, 330, 20), (12289, 330, 20), (12289, 481, 18), (22528, 290, 21), (22529, 290, 21), (4096, 1550, 26), (4097, 1550, 26),
                                    (4097, 1550, 25)])
