@@ -165,6 +165,26 @@ def test_cg_fixed_iterations(cache, name, path):
             assert relres.item() < 1e-5
 
 
+# The sums over d of a line search on vectors of more than 8192 elements: one element beyond, whole and part chunks of 2048, more than 256
+# of them, and no z or y.
+@pytest.mark.parametrize("missing", ["", "z", "y", "zy"])
+@pytest.mark.parametrize("p,C", [(8193, 2), (3072, 5), (2341, 6), (65537, 9)])
+def test_line_search_on_long_vectors(p, C, missing):
+    w = workloads.generic(24, p, C, seed=p + C, x_std=0.5 / math.sqrt(p), mean=True)
+    z = None if "z" in missing else w.z
+    y = None if "y" in missing else w.y
+    op = orc.Problem(w.A, w.b, w.C, s=w.s, lam=0.3, rho=0.2, z=z, y=y)
+    gp = nadmm.Problem(dev(w.A), dev(w.b), w.C, w.s, 0.3, 0.2, None if z is None else dev(z), None if y is None else dev(y))
+    g = orc.grad(op, w.X0)
+    for scale in (1.0, 3000.0):
+        d = (-scale * g).astype(np.float32)
+        g32 = g.astype(np.float32)
+        a_ref, f_ref, ok_ref, _ = orc.line_search(op, w.X0, d, g32, w.beta, w.gamma, 20)
+        alpha, f_new, ok = nadmm.nadmm_line_search(gp, dev(w.X0), dev(d), dev(g32), math.nan, w.beta, w.gamma, 20)
+        assert alpha.item() == pytest.approx(a_ref, rel=1e-6) and bool(ok.item()) == ok_ref
+        assert rel_abs(f_new.item(), f_ref) <= TOL_PRIMITIVE
+
+
 @pytest.mark.parametrize("name", ["tiny", "ragged_1237x45_C5"])
 def test_cg_tolerance_mode(cache, name):
     w, gp, op = setup_case(cache, name)
