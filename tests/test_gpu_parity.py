@@ -12,6 +12,7 @@ import math
 
 import numpy as np
 import pytest
+import scipy.sparse as sp
 import torch
 
 from oracle import nadmm_oracle as orc
@@ -692,6 +693,30 @@ def test_wide_cg_on_long_vectors(n, p, C, tol):
     p_ref, it_ref, rel_ref = orc.cg(op, w.X0, g.astype(np.float64), 10, tol)
     assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
     assert (it_ref < 10) == (tol > 0.0)
+
+
+# Iterations behind the one that met the tolerance leave everything as it is, however many there are (the update's state alternates between
+# two slots): one launch (general kernels, wide rows, sparse storage) and two, and a gradient of zero, where no iteration is made.
+@pytest.mark.parametrize("n,p,C,path", [(60, 1000, 6, 1), (300, 1100, 4, 4), (300, 2740, 10, 4), (24, 131073, 2, 1), (60, 2000, 3, 5)])
+def test_cg_iterations_behind_the_last(n, p, C, path):
+    w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
+    op = oracle_problem(w)
+    A = dev(w.A)
+    if path == 5:
+        csr = sp.csr_matrix(w.A)
+        A = nadmm.SparseA.from_scipy(csr, csr.tocsc())
+    gp = nadmm.Problem(A, dev(w.b), C, w.s, op.lam, op.rho, dev(w.z), dev(w.y))
+    g = orc.loss_grad(op, w.X0)[1].astype(np.float32)
+    force_path(gp, path)
+    tol = 0.3
+    it_ref = orc.cg(op, w.X0, g.astype(np.float64), 20, tol)[1]
+    assert it_ref < 20
+    want = [t.clone() for t in nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g), it_ref, tol)]
+    for more in (1, 2, 3, 30):
+        got = nadmm.nadmm_cg_solve(gp, dev(w.X0), dev(g), it_ref + more, tol)
+        assert all(torch.equal(a, b) for a, b in zip(got, want)) and got[1].item() == it_ref
+        p_out, it, _ = nadmm.nadmm_cg_solve(gp, dev(w.X0), torch.zeros_like(dev(g)), more, tol)
+        assert it.item() == 0 and not p_out.any()
 
 
 # CG updates made by several workgroups, each of which takes the norm of the new residual from sums of the old one and of what the
