@@ -81,7 +81,7 @@ int validate_problem(const nadmm_problem* p, bool need_labels) {
 }
 
 // hv_only: only the regions that a stand-alone Hessian-vector product touches (rows of D, partial sums, partial
-// logits, the sparse path's packed operand and windows); the other offsets are then not to be used.
+// logits, the sparse path's packed operand, windows and shares); the other offsets are then not to be used.
 // wg_cap > 0: at most that many workgroups for the fused single-pass kernels (several workers' solves running side by
 // side share the compute units; each then keeps the long row ranges per workgroup that amortise a launch).
 // max_cg > 0: room for the directional logits A d_k of that many CG iterations, if the fused single-pass path is the
@@ -127,7 +127,7 @@ void make_layout(const nadmm_problem* p, Layout* L, bool hv_only = false, int wg
   L->r2 = off; off += two_sets || cg_one_step(s.d) ? vec : 0;  // the one-launch CG update reads one residual and writes the other
   L->dvec2 = off; off += two_sets ? vec : 0;
   L->pfinal = off; off += two_sets ? vec : 0;
-  L->drows = off; off += rows;
+  L->drows = off; off += L->sparse ? 0 : rows;  // sparse storage: D goes into the packed operand
   L->pcache = off; off += rows_solver;
   L->zx = off; off += rows_solver;
   L->zp = off; off += rows_solver;
@@ -328,7 +328,7 @@ int sweep(const nadmm_problem* prob, const Layout& L, int path, void* ws, RowArg
       if (!packed) NADMM_HIP(launch_sparse_pack(ra.B0 != nullptr ? ra.B0 : ra.B1, both ? ra.B1 : nullptr, prob->p, NC, pack, ra.flag, st));
       NADMM_HIP(launch_spmm(sa, st));
     }
-    if (with_cols) ra.rows_out = pack;  // the rows of D lie as the product with A^T reads them
+    ra.rows_out = with_cols ? pack : nullptr;  // the rows of D lie as the product with A^T reads them
     NADMM_HIP(launch_logit_rows(ra, at<float>(ws, L.zw), 1, with_cols ? 4 * sparse_group(NC) : NC, st));
     if (with_cols) {  // A^T D from the column view
       sa.S = col_view(prob);

@@ -115,6 +115,20 @@ def test_sparse_problems_on_the_host(lib):
     assert lib.nadmm_hessvec(C.byref(prob), fake, fake, fake, fake, need - 1, None) == nadmm.NADMM_EWORKSPACE
 
 
+def test_sparse_scratch_holds_what_the_kernels_use(lib):
+    """Sparse storage: logits [Z | W], the packed operand (into which the rows of D go as well), one partial sum and the windows' tables; no
+    further n (C-1) floats.  112000 x 30, C = 21 fits the built-in buffer with these and not with those."""
+    for n, p, cls, group in ((112000, 30, 21, 8), (100000, 2000, 17, 4), (50000, 9000, 5, 1)):
+        nc = cls - 1
+        sp = fake_sparse(nnz=3 * n)
+        prob = sparse_problem(sp, n=n, p=p, Cc=cls)
+        used = 4 * (2 * n * nc + 4 * group * max(2 * p, n) + p * nc)
+        tables = 1 << 19 if nc <= 4 else 2 << 20     # at most 4096 windows: 2 first rows, 2 tickets and 4 (C-1) floats each, rounded up
+        assert used < lib.nadmm_hessvec_static_bytes(C.byref(prob)) <= used + tables, (n, p, cls)
+    fits = sparse_problem(fake_sparse(nnz=336000), n=112000, p=30, Cc=21)
+    assert lib.nadmm_hessvec_static_bytes(C.byref(fits)) <= lib.nadmm_static_scratch_bytes()
+
+
 def test_workspace_bytes(lib):
     small = lib.nadmm_workspace_bytes(C.byref(fake_problem()), None)
     big = lib.nadmm_workspace_bytes(C.byref(fake_problem(n=60000, p=784, Cc=10)), None)
