@@ -45,12 +45,6 @@ template <int THREADS>
 __device__ __forceinline__ CgStep cg_step_scalars(const CgUpdateArgs& a, double* sm) {
   constexpr int W = THREADS / 64, U = 4;
   const CgSlot in = a.st->cgs[a.slot_in];
-  // CG has stopped: nothing is summed, and the other slot learns of it once.  With the sums, and the state written each time, an iteration behind the one
-  // that stopped took this kernel 4.9 us for 1.6 at 131072 unknowns, 4.2 for 3.0 at 27648 with operands to lay out: more than the two launches before (3.6).
-  if (in.active == 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0 && a.st->cgs[a.slot_in ^ 1].active != 0) a.st->cgs[a.slot_in ^ 1] = in;
-    return CgStep{false, false, 0.f, 0.f};
-  }
   const double gg = a.st->gg_cg;
   const double mu = linear_factor(a.lambda, a.rho, a.rho_scale);
   double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -66,6 +60,13 @@ __device__ __forceinline__ CgStep cg_step_scalars(const CgUpdateArgs& a, double*
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] += k0 + u * THREADS < a.ndot ? x[u][i] : 0.0;
+  }
+  // CG has stopped: the other slot learns of it once, nothing else is written.  An iteration behind the one that stopped took this kernel 4.9 us with all
+  // of what follows, 4.1 without, at 131072 unknowns, and 4.2 and 3.5 at 27648 with operands to lay out; the two launches of the other form take 3.6 and the gap
+  // between them.  Not ahead of the loads above (1.6 and 3.0 us): the loads would then wait for the slot, 0.15 to 0.3 us of every iteration that is made.
+  if (in.active == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && a.st->cgs[a.slot_in ^ 1].active != 0) a.st->cgs[a.slot_in ^ 1] = in;
+    return CgStep{false, false, 0.f, 0.f};
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
