@@ -185,7 +185,7 @@ int nadmm_hessvec(const nadmm_problem* prob, const float* d_X, const float* d_V,
  * nadmm_hessvec for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation as nadmm_hessvec and, where its
  * scratch fits (see below), the same kernels and bit for bit the same results; but the scratch memory (rows of D, per-workgroup partial sums, the
- * sparse path's logits, packed operand and windows) is a buffer built into
+ * sparse path's logits, packed operand, windows and shares) is a buffer built into
  * the library: NADMM_STATIC_SCRATCH_BYTES = 32 MiB of device memory that every GPU the library runs on
  * holds until the process ends.  The call allocates and frees nothing and does not synchronise.
  *   - A problem that needs more (nadmm_hessvec_static_bytes(prob) > nadmm_static_scratch_bytes(); e.g. dense
@@ -195,8 +195,7 @@ int nadmm_hessvec(const nadmm_problem* prob, const float* d_X, const float* d_V,
  *     250000 x 2000, C = 20 needs 31.9 MB.
  *   - The single-pass kernel for wide rows leaves min(256, ceil(n/16)) partial sums of p (C-1) floats.  Where these do not fit the
  *     buffer and the two-sweep kernels' scratch does (250000 x 2000, C = 20), the call makes two sweeps: it sums in another order
- *     than nadmm_hessvec does and agrees with it to rounding (below 4 * 2^-16 relative), not bit for bit.  Likewise for sparse storage
- *     with rows or columns of 512 entries and more, whose sums are shared by workgroups where the room for the shares is there.
+ *     than nadmm_hessvec does and agrees with it to rounding (below 4 * 2^-16 relative), not bit for bit.
  *   - Every call on one GPU shares that GPU's buffer, whatever the stream or thread: calls that overlap
  *     in time on one GPU race.  Order them on one stream (or with events).  Nothing in the buffer has to
  *     survive between calls and nothing has to start at zero.

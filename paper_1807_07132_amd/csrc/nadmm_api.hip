@@ -977,8 +977,8 @@ int nadmm_hessvec(const nadmm_problem* prob, const float* d_X, const float* d_V,
 
 size_t nadmm_static_scratch_bytes(void) { return NADMM_STATIC_SCRATCH_BYTES; }
 
-// Scratch of a Hessian-vector product in the built-in buffer: the single-pass kernels for wide rows, and the shares of long sparse rows, are
-// left out where only what the others need fits it.
+// Scratch of a Hessian-vector product in the built-in buffer: the single-pass kernels for wide rows, and the shares of long sparse rows (whose
+// sums are then made by one workgroup in the same order), are left out where only what the others need fits it.
 static void static_layout(const nadmm_problem* prob, Layout* L) {
   make_layout(prob, L, true);
   if ((L->wide || L->sparse) && L->total > (size_t)NADMM_STATIC_SCRATCH_BYTES) make_layout(prob, L, true, 0, 0, true);

@@ -512,7 +512,7 @@ struct SpmmArgs {
   SparseWindows w;
   const int32_t* flag;
   // rows longer than a window are shared by the windows they reach over: sums of the shares, 2 x nwin x nops NC floats, and how many of a row
-  // are there, nwin words that are 0 between launches (launch_sparse_plan); NULL: the window in which such a row starts takes all of it
+  // are there, nwin words that are 0 between launches (launch_sparse_plan); NULL: the workgroup in whose window such a row starts takes all of it
   float* share;
   int32_t* arrived;
 };

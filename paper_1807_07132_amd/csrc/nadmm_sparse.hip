@@ -11,10 +11,10 @@
 // so that a load instruction touches each of its rows once, and each lane keeps the partial sums of its quad; at the
 // end of a row of S the lanes holding the same quad are added across the wave.  Work is cut into
 // windows of equal cost (stored entries plus a fixed cost per row) by a binary search over the row
-// pointers; a workgroup owns the rows that start in its window: short rows go to single waves, long
+// pointers; a workgroup owns the rows that start in its window: rows of fewer than 48 entries go to 16 lanes each, others to single waves, long
 // ones are shared by its four waves and combined in LDS in wave order.  A row longer than a window is cut where the windows are: every one
 // it reaches over sums its share (the windows inside such a row have no rows of their own), and whichever arrives last adds the shares in their
-// order.  Before, one workgroup took such a row whole, 0.9 us for 240 entries, while the others had long ended: columns of the 60000 x 9000 counts
+// order; where the caller's memory has no room for the shares, one workgroup does both.  Before, one workgroup took such a row whole, 0.9 us for 240 entries, while the others had long ended: columns of the 60000 x 9000 counts
 // of the tests' kind (200 a row, C = 28) 241 us for the product with A^T, 62 for the one with A.  The order of additions depends on the
 // matrix only: results are reproducible bit for bit.
 #include "nadmm_internal.h"
@@ -267,7 +267,9 @@ __device__ __forceinline__ int64_t lane_of(int64_t x, int i) {
 // NPER of the NOPS operands are multiplied together, the others by further workgroups (blockIdx.y).
 // 5 to 7 quads: a wave more per SIMD than the compiler would leave room for (60000 x 9000, 200 a row, C = 28: 304 -> 294 us a Hessian-vector product;
 // fewer or more quads, or two operands, are slower with that, 2 to 25 %)
-template <int NQ, int NPER, int NOPS>
+// SHARED: rows as long as a window are shared by the workgroups of the windows they reach over.  Without room for the shares the one in whose
+// window such a row starts takes all of it, window by window and in the same order of additions: the results are the same bit for bit.
+template <int NQ, int NPER, int NOPS, bool SHARED>
 __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1) void spmm_kernel(const SpmmArgs a) {
   constexpr int G = 8;  // bound of NQ, for the LDS staging of long rows
   constexpr int CE = Shape64<NQ>::CE;
@@ -280,14 +282,14 @@ __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
   const int win = blockIdx.x;
   const int r0 = a.w.first[win], r1 = a.w.first[win + 1];
   const int wshift = a.w.shift;
-  const int64_t kCut = a.arrived != nullptr ? (int64_t)1 << wshift : INT64_MAX;
+  const int64_t kCut = (int64_t)1 << wshift;
   // the cut row that reaches into this window from before it, and the one that starts here and reaches beyond it (the last that starts here)
   bool into = false, beyond = false;
-  if (r0 > 0) {
+  if (SHARED && r0 > 0) {
     const RowSpan sp = row_span(a.S, r0 - 1);
     into = sp.k1 - sp.k0 >= kCut && cut_span(sp, r0 - 1, win, wshift).last >= win;
   }
-  if (r1 > r0) {
+  if (SHARED && r1 > r0) {
     const RowSpan sp = row_span(a.S, r1 - 1);
     beyond = sp.k1 - sp.k0 >= kCut && cut_span(sp, r1 - 1, win, wshift).last > win;
   }
@@ -298,8 +300,7 @@ __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
   const f32x4* __restrict__ B = reinterpret_cast<const f32x4*>(a.B) + blockIdx.y * kSlot;
   float* __restrict__ out = a.out + blockIdx.y * a.NC;
   const int ldo = NOPS * a.NC, width = NPER * a.NC;
-  float* share = a.share + (size_t)blockIdx.y * 2 * a.w.n * width;
-  int32_t* arrived = a.arrived + (size_t)blockIdx.y * a.w.n;
+  float* share = SHARED ? a.share + (size_t)blockIdx.y * 2 * a.w.n * width : nullptr;
 
   if (threadIdx.x == 0) {
     nlong_sh = into ? 1 : 0;
@@ -317,9 +318,8 @@ __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
   const int nlong = nlong_sh < kMaxLong ? nlong_sh : kMaxLong;
 
   // long rows: wave w takes chunks w, w + 4, ...; partial sums to LDS
-  for (int sl = 0; sl < nlong; ++sl) {
-    RowSpan sp = row_span(a.S, long_rows[sl]);
-    if (sp.k1 - sp.k0 >= kCut) sp = cut_span(sp, long_rows[sl], win, wshift).here;
+  constexpr int kPer = NPER * G * 4;
+  auto wave_sums = [&](const RowSpan& sp, int sl) {
     f32x4 acc[NPER];
     row_sum<NQ, NPER, NOPS>(a, B, sp.k0 + CE * wave, sp.k1, CE * kSpWaves, lane, acc);
     if (lane < NQ) {
@@ -329,6 +329,34 @@ __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
         for (int e = 0; e < 4; ++e) part[sl][wave][op][lane][e] = acc[op][e];
       }
     }
+  };
+  auto add_waves = [&](int sl, int j) {
+    const float* pj = &part[sl][0][0][0][0] + j;
+    float sum = pj[0];
+#pragma unroll
+    for (int w = 1; w < kSpWaves; ++w) sum += pj[w * kPer];
+    return sum;
+  };
+  for (int sl = 0; sl < nlong; ++sl) {
+    const int row = long_rows[sl];
+    RowSpan sp = row_span(a.S, row);
+    if (sp.k1 - sp.k0 >= kCut) {  // uniform
+      if constexpr (!SHARED) {
+        const Cut c = cut_span(sp, row, win, wshift);
+        const int j = threadIdx.x, op = j / (4 * G), cl = j - op * (4 * G);
+        float sum = c.first == c.last ? -0.f : 0.f;  // x + -0 is x
+        for (int w = c.first; w <= c.last; ++w) {
+          wave_sums(cut_span(sp, row, w, wshift).here, sl);
+          __syncthreads();
+          if (j < kPer) sum += add_waves(sl, j);
+          __syncthreads();
+        }
+        if (j < kPer && cl < a.NC) out[(size_t)row * ldo + op * a.NC + cl] = sum;
+        continue;
+      }
+      sp = cut_span(sp, row, win, wshift).here;
+    }
+    wave_sums(sp, sl);
   }
   // the other rows, those of a wave one per lane: 16 lanes sum a short one, the wave a longer one
   for (int rb = r0 + wave; rb < r1; rb += 64 * kSpWaves) {
@@ -368,23 +396,24 @@ __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
   }
   if (nlong == 0) return;
   __syncthreads();
-  constexpr int kPer = NPER * G * 4;
   for (int t = threadIdx.x; t < nlong * kPer; t += kSpThreads) {
     const int sl = t / kPer, j = t - sl * kPer;
     const int op = j / (4 * G), c = j - op * (4 * G);
-    const float* pj = &part[sl][0][0][0][0] + j;
-    float sum = pj[0];
-#pragma unroll
-    for (int w = 1; w < kSpWaves; ++w) sum += pj[w * kPer];
+    const float sum = add_waves(sl, j);
     if (c >= a.NC) continue;
     const int row = long_rows[sl];
+    if constexpr (!SHARED) {
+      const RowSpan sp = row_span(a.S, row);
+      if (sp.k1 - sp.k0 >= kCut) continue;  // summed above
+    }
     // share of a cut row: past the L2, which other XCDs do not see
     if ((into && sl == 0) || (beyond && row == r1 - 1))
       __hip_atomic_store(share + (size_t)(2 * win + (row < r0 ? 0 : 1)) * width + op * a.NC + c, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
       out[(size_t)row * ldo + op * a.NC + c] = sum;
   }
-  if (!into && !beyond) return;
+  if (!SHARED || (!into && !beyond)) return;
+  int32_t* arrived = a.arrived + (size_t)blockIdx.y * a.w.n;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the shares are where every XCD reads them
   __syncthreads();
   if (threadIdx.x < 2) {
@@ -419,7 +448,9 @@ __global__ __launch_bounds__(kSpThreads, NPER == 1 && NQ >= 5 && NQ <= 7 ? 7 : 1
 
 template <int NQ, int NPER, int NOPS>
 hipError_t launch_q(const SpmmArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((spmm_kernel<NQ, NPER, NOPS>), dim3(a.w.n, NOPS / NPER), dim3(kSpThreads), 0, st, a);
+  const dim3 grid(a.w.n, NOPS / NPER);
+  if (a.arrived != nullptr) hipLaunchKernelGGL((spmm_kernel<NQ, NPER, NOPS, true>), grid, dim3(kSpThreads), 0, st, a);
+  else hipLaunchKernelGGL((spmm_kernel<NQ, NPER, NOPS, false>), grid, dim3(kSpThreads), 0, st, a);
   return hipGetLastError();
 }
 

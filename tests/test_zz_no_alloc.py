@@ -4,6 +4,7 @@ the second on a smaller problem, on every kernel path; this file is collected la
 already run in the same process when it does, and it passes in a fresh process too."""
 import numpy as np
 import pytest
+import scipy.sparse as sp
 import torch
 
 from oracle import nadmm_oracle as orc
@@ -98,3 +99,36 @@ def test_static_scratch_where_only_two_sweeps_fit():
     ref = orc.hessvec(oracle_problem(w), w.X0, w.V)
     assert rel_l2(got.cpu().numpy(), ref) <= TOL_PRIMITIVE and rel_l2(want.cpu().numpy(), ref) <= TOL_PRIMITIVE
     assert rel_l2(got.cpu().numpy(), want.cpu().numpy().astype("float64")) <= 4 * 2.0 ** -16
+
+
+@pytest.mark.parametrize("n,C", [(86000, 33), (172000, 17), (244000, 10)])
+def test_static_scratch_without_room_for_the_shares_of_long_rows(n, C):
+    """Sparse storage where the sums that workgroups share do not fit the buffer and everything else does: rows and columns of several windows are
+    then summed by one workgroup, in the same order.  Two operands in two passes (C-1 > 16) and in one; lengths around and far beyond a window."""
+    p, NC = 3000, C - 1
+    rng = np.random.default_rng(C)
+    group = 4 * (8 if NC > 16 else 4)
+    nnz = 12 * n
+    cols = np.minimum((p * rng.random(nnz) ** 3).astype(np.int64), p - 1)     # columns of some hundred to tens of thousands of entries
+    rows = rng.integers(0, n, size=nnz)
+    full = np.concatenate([np.full(k, i) for i, k in zip((5, 6, 7, n - 2), (3000, 2048, 1024, 2999))])   # rows of several windows
+    A = sp.csr_matrix((np.ones(nnz + len(full), np.float32), (np.concatenate([rows, full]), np.concatenate([cols, *[np.arange(k) for k in (3000, 2048, 1024, 2999)]]))),
+                      shape=(n, p))
+    A.data[:] = rng.standard_normal(A.nnz) * 0.2
+    b = rng.integers(0, C, size=n).astype(np.int32)
+    X = (rng.standard_normal((p, NC)) * 0.1).astype(np.float32)
+    V = rng.standard_normal((p, NC)).astype(np.float32)
+    gp = nadmm.Problem(nadmm.SparseA.from_scipy(A, A.tocsc()), dev(b), C, 1.0, 1e-3, 1.0, None, None)
+    used = 4 * (2 * n * NC + group * max(n, 2 * p) + p * NC)
+    need = nadmm.nadmm_hessvec_static_bytes(gp)
+    windows = [(A.nnz + 8 * m) >> 11 for m in (n, p)]                         # there are no fewer
+    assert need <= nadmm.nadmm_static_scratch_bytes() < need + 16 * NC * max(windows)
+    assert need < used + 64 * max(windows)                                    # tables and no shares
+    want = nadmm.nadmm_hessvec(gp, dev(X), dev(V))
+    got = torch.full_like(want, float("nan"))
+    for _ in range(2):
+        nadmm.nadmm_hessvec_static(gp, dev(X), dev(V), got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)       # the same additions in the same order
+    op = orc.Problem(A, b, C, s=1.0, lam=1e-3, rho=1.0)
+    assert rel_l2(got.cpu().numpy(), orc.hessvec(op, X, V)) <= TOL_PRIMITIVE
