@@ -883,6 +883,8 @@ __global__ __launch_bounds__(256) void ls_vec_part_kernel(const LsTailArgs a, in
   }
 }
 
+// (Two loads per element need no clamped indices to be in flight together: with them 15.5 us for 13.3 at 5.3 million elements, 2.9 to 4.9 either way
+// from 12288 to 262144.)
 __global__ __launch_bounds__(256) void ls_apply_kernel(const DevState* st, const float* __restrict__ pdir,
                                                        float* __restrict__ X, int64_t d, const int32_t* flag) {
   if (flag != nullptr && *flag == 0) return;
@@ -891,9 +893,9 @@ __global__ __launch_bounds__(256) void ls_apply_kernel(const DevState* st, const
     float pv[kWidePer], xv[kWidePer];
 #pragma unroll
     for (int u = 0; u < kWidePer; ++u) {
-      const int64_t e = base + u * 256, ec = e < d ? e : d - 1;
-      pv[u] = pdir[ec];
-      xv[u] = X[ec];
+      const int64_t e = base + u * 256;
+      pv[u] = e < d ? pdir[e] : 0.f;
+      xv[u] = e < d ? X[e] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < kWidePer; ++u) {
