@@ -35,7 +35,7 @@ __device__ __forceinline__ double cg_block_sum(double v, double* sm) {
 // all sums float64 of the vectors as they are.  mu r is what the data leave of H where its linear term outweighs them and CG
 // converges in a few iterations; the sums of r and q themselves would cancel there.  Where more than all but 10^-7 of the terms cancels
 // all the same (their error, 2^-53 of them, would be above 10^-9 of the result; float32 vectors round at 6 10^-8) each workgroup sums the norm from
-// the vectors.  (The norm is not carried over from one iteration to the next: where each step takes 10^6 off it, the rounding of r would be
+// the vectors (what that costs: kCgStepMax).  (The norm is not carried over from one iteration to the next: where each step takes 10^6 off it, the rounding of r would be
 // all that is left of such a sum after two.)  sm: 5 THREADS / 64 doubles.
 struct CgStep {
   bool go, stop;

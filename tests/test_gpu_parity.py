@@ -721,7 +721,7 @@ def test_cg_iterations_behind_the_last(n, p, C, path):
 
 # CG updates made by several workgroups, each of which takes the norm of the new residual from sums of the old one and of what the
 # data leave of H (path 1: the general kernels).  Vectors of 1 and several workgroups and up to one, at and beyond the length where two kernels take over; a linear term that
-# is nothing, as large as the data and far above them, where the sums cancel and the norm is summed from the vectors.
+# is small, as large as the data and far above them.  None of these sums cancels (a thousandth of the terms and more is left).
 # Bounds: those of the other solves of fixed length; a residual at rounding level has only that level.
 @pytest.mark.parametrize("reg", [0.05, 0.5, 1e4])
 @pytest.mark.parametrize("n,p,C,path", [(30, 2048, 2, 1), (60, 1000, 6, 1), (24, 131072, 2, 1), (50, 8193, 9, 1), (300, 1400, 10, 4), (24, 131073, 2, 1)])
