@@ -166,11 +166,18 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 # A call of two launches takes the library 5.5 to 6 us of host time, and a small problem's kernels take no longer: what the binding adds is
-# what such a call costs (gradient at 1000 x 20: 13.8 -> 10.1 us, Hessian-vector product 12.1 -> 9.2).  torch.cuda.current_stream() alone took 2.9 us.
+# what such a call costs (gradient at 1000 x 20: 13.8 -> 10.1 us, Hessian-vector product 12.1 -> 9.2).  torch.cuda.current_stream() alone took 2.9 us;
+# it is taken where torch has not the two functions that it asks itself.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 class Problem:

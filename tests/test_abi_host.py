@@ -129,6 +129,20 @@ def test_sparse_scratch_holds_what_the_kernels_use(lib):
     assert lib.nadmm_hessvec_static_bytes(C.byref(fits)) <= lib.nadmm_static_scratch_bytes()
 
 
+@pytest.mark.parametrize("missing", [("_cuda_getCurrentRawStream",), ("_cuda_getDevice",), ("_cuda_getCurrentRawStream", "_cuda_getDevice")])
+def test_current_stream_without_torch_s_private_functions(monkeypatch, missing):
+    import importlib.util
+    import torch
+    for name in missing:
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 0x1234567890})())
+    spec = importlib.util.spec_from_file_location("paper_1807_07132_amd.nadmm_again", nadmm.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream(None) == 0x1234567890
+    assert again._stream(type("Stream", (), {"cuda_stream": 7})()) == 7
+
+
 def test_workspace_bytes(lib):
     small = lib.nadmm_workspace_bytes(C.byref(fake_problem()), None)
     big = lib.nadmm_workspace_bytes(C.byref(fake_problem(n=60000, p=784, Cc=10)), None)
