@@ -360,8 +360,10 @@ static void head(const NewtonHeadArgs& h, const int32_t* flag) {
     ++heads;
   }
 }
+static const int32_t* swept_by;  // what the last product went by
 static hipError_t rows(const RowArgs& a) {
   if (on(a.flag) && a.kind == kRowsGrad) ++grads;
+  if (a.kind == kRowsHv) swept_by = a.flag;
   return hipSuccess;
 }
 hipError_t launch_state_init(DevState* st, const int32_t* outer, hipStream_t) {
@@ -373,7 +375,25 @@ hipError_t launch_generic_cols(const ColArgs&, int, int, hipStream_t) { return h
 hipError_t launch_fused(const RowArgs& a, float*, int, hipStream_t, const CgPend*, const SearchArgs*) { return rows(a); }
 hipError_t launch_narrow(const RowArgs& a, float*, int, hipStream_t, const CgPend*) { return rows(a); }
 hipError_t launch_wide(const RowArgs& a, void*, bool, float*, int, hipStream_t) { return rows(a); }
-hipError_t launch_wide_direction(const CgUpdateArgs&, const Shape&, void*, hipStream_t) { return hipSuccess; }
+// A CG update by several workgroups: up to 131072 unknowns the state's slots and the two residuals take turns, beginning with slot 0, and the
+// product and its reduction before it went by the slot that it reads; beyond, everything stays in place.
+static int updates, off_turn, turn;
+static const float *residual, *next_residual, *summed;
+static hipError_t update(const CgUpdateArgs& a) {
+  ++updates;
+  if (cg_one_step(a.d)) {
+    if (turn == 0) residual = a.r;
+    else off_turn += a.r != next_residual;
+    off_turn += a.slot_in != (turn & 1) || a.r_out == nullptr || a.r_out == a.r || ((turn & 1) == 0) != (a.r == residual);
+    off_turn += swept_by != &a.st->cgs[a.slot_in].active || summed != a.r || a.ndot != reduce_out_blocks(a.d);
+    next_residual = a.r_out;
+  } else {
+    off_turn += a.r_out != nullptr || summed != nullptr || swept_by != &a.st->cg_active;
+  }
+  ++turn;
+  return hipSuccess;
+}
+hipError_t launch_wide_direction(const CgUpdateArgs& a, const Shape&, void*, hipStream_t) { return update(a); }
 hipError_t launch_sliced_logits(const RowArgs& a, hipStream_t) { return rows(a); }
 hipError_t launch_sliced_cols(const RowArgs&, const float*, float*, hipStream_t) { return hipSuccess; }
 hipError_t launch_thin(const RowArgs& a, float*, int, hipStream_t, const CgPend* cg, const ReduceArgs*, const NewtonHeadArgs* h, const SearchArgs*) {
@@ -386,13 +406,24 @@ hipError_t launch_thin(const RowArgs& a, float*, int, hipStream_t, const CgPend*
   return hipSuccess;
 }
 hipError_t launch_reduce_out(const ReduceArgs& r, hipStream_t) {
+  if (r.kind == 0) {
+    summed = r.r_dot;
+    off_turn += r.dot_part != nullptr && r.has_head == 0 && r.cur == nullptr && r.flag != swept_by;
+  }
   if (r.has_head != 0) head(r.head, r.flag);
   return hipSuccess;
 }
-hipError_t launch_newton_head(const NewtonHeadArgs& h, hipStream_t) { head(h, nullptr); return hipSuccess; }
+hipError_t launch_newton_head(const NewtonHeadArgs& h, hipStream_t) {
+  turn = 0;  // a CG solve begins
+  head(h, nullptr);
+  return hipSuccess;
+}
 hipError_t launch_cg_reduce_update(const ReduceArgs&, const CgUpdateArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_cg_update(const CgUpdateArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_cg_residual(const CgUpdateArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_cg_update(const CgUpdateArgs& a, hipStream_t) { return update(a); }
+hipError_t launch_sparse_plan(const SparseView&, const SparseWindows&, const SparseView&, const SparseWindows&, int32_t*, hipStream_t) { return hipSuccess; }
+hipError_t launch_sparse_pack(const float*, const float*, int64_t, int, float*, const int32_t*, hipStream_t) { return hipSuccess; }
+hipError_t launch_spmm(const SpmmArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_logit_rows(const RowArgs& a, const float*, int, int, hipStream_t) { return rows(a); }
 hipError_t launch_cg_pending_finish(const CgPend&, hipStream_t) { return hipSuccess; }
 hipError_t launch_ls_eval(const LsEvalArgs&, hipStream_t) { return hipSuccess; }
 hipError_t launch_ls_tail(const LsTailArgs& a, hipStream_t) { steps += on(a.flag); return hipSuccess; }
@@ -400,7 +431,9 @@ hipError_t launch_ls_tail(const LsTailArgs& a, hipStream_t) { steps += on(a.flag
 using namespace nadmm;
 int main() {
   struct Case { int64_t n; int32_t p, C, path; } cases[] = {{5000, 28, 2, 0}, {5000, 29, 3, 0}, {60000, 784, 10, 0}, {100000, 70, 7, 0},
-                                                            {5000, 90, 20, 0}, {5000, 1100, 4, 0}, {5000, 28, 2, 1}};
+                                                            {5000, 90, 20, 0}, {5000, 1100, 4, 0}, {5000, 28, 2, 1}, {5000, 3072, 10, 0}, {500, 4096, 33, 0},
+                                                            {100, 4097, 33, 0}, {100, 5000, 3, 1}, {100, 2000, 21, 5}, {100, 131073, 2, 5}};
+  nadmm_sparse sparse{};
   alignas(16) static float v[4];
   static int32_t labels[4];
   for (const Case& c : cases)
@@ -413,18 +446,24 @@ int main() {
           nadmm_params params{};
           params.max_newton = 4; params.max_cg = max_cg; params.max_ls = 10; params.grad_tol = 1e-3f;
           params.armijo_beta = 1e-4f; params.backtrack_gamma = 0.5f;
+          if (c.path == 5) {
+            static int64_t ptr[2];
+            sparse.nnz = 1000; sparse.d_row_ptr = sparse.d_col_ptr = ptr; sparse.d_col_idx = sparse.d_row_idx = labels; sparse.d_val = sparse.d_val_t = v;
+            prob.sparse = &sparse;
+          }
           nadmm_set_kernel_path(c.path);
           const size_t bytes = nadmm_workspace_bytes(&prob, &params);
           void* ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
-          grads = directions = steps = shared = 0;
+          grads = directions = steps = shared = updates = off_turn = 0;
           last_gg = gg;
           const int rc = nadmm_local_newton(&prob, v, &params, nullptr, ws, bytes, nullptr);
           std::free(ws);
           const bool thin = c.path == 0 && c.p <= 32;
-          if (rc != 0 || shared != 0 || steps != stop_at || grads != (stop_at < 4 ? stop_at + 1 : 4) ||
+          const bool several = c.p > 1000 || c.p == 90;  // these vectors are updated by several workgroups
+          if (rc != 0 || shared != 0 || off_turn != 0 || updates != (several ? 4 * max_cg : 0) || steps != stop_at || grads != (stop_at < 4 ? stop_at + 1 : 4) ||
               (thin && max_cg == 3 && directions != 2 * stop_at)) {
-            std::printf("n %ld p %d C %d path %d cg %d stop %d: rc %d shared %d steps %d grads %d directions %d\n", (long)c.n, c.p, c.C, c.path, max_cg,
-                        stop_at, rc, shared, steps, grads, directions);
+            std::printf("n %ld p %d C %d path %d cg %d stop %d: rc %d shared %d steps %d grads %d directions %d updates %d, %d off their turn\n", (long)c.n, c.p, c.C,
+                        c.path, max_cg, stop_at, rc, shared, steps, grads, directions, updates, off_turn);
             return 1;
           }
         }
