@@ -14,9 +14,12 @@
 // pointers; a workgroup owns the rows that start in its window: rows of fewer than 48 entries go to 16 lanes each, others to single waves, long
 // ones are shared by its four waves and combined in LDS in wave order.  A row longer than a window is cut where the windows are: every one
 // it reaches over sums its share (the windows inside such a row have no rows of their own), and whichever arrives last adds the shares in their
-// order; where the caller's memory has no room for the shares, one workgroup does both.  Before, one workgroup took such a row whole, 0.9 us for 240 entries, while the others had long ended: columns of the 60000 x 9000 counts
-// of the tests' kind (200 a row, C = 28) 241 us for the product with A^T, 62 for the one with A.  The order of additions depends on the
-// matrix only: results are reproducible bit for bit.
+// order; where the caller's memory has no room for the shares, one workgroup does both.  Before, one workgroup took such a row whole, 0.9 us for
+// 240 entries, while the others had long ended: columns of the 60000 x 9000 counts of the benchmark's kind (200 a row, C = 28) 241 us for the
+// product with A^T, 62 for the one with A.  The order of additions depends on the matrix only: results are reproducible bit for bit.
+// What each of the forms gives, the others in place (us a Hessian-vector product, without and with): cutting 2012 and 1938 at 40628 x 279998, C = 20, 385 and 274 at
+// 60000 x 9000, C = 28; 16 lanes for short rows 105 and 71 at 50000 x 200000, C = 4 (30 a row), but 65 and 67 at 6000 x 4000, C = 20, where few rows are short;
+// windows by size 48 and 31 at 2000 x 2000, C = 3, 80 and 67 at 6000 x 4000.
 #include "nadmm_internal.h"
 #include "nadmm_mfma.h"
 
@@ -265,8 +268,9 @@ __device__ __forceinline__ int64_t lane_of(int64_t x, int i) {
 }
 
 // NPER of the NOPS operands are multiplied together, the others by further workgroups (blockIdx.y).
-// 5 to 7 quads: a wave more per SIMD than the compiler would leave room for (60000 x 9000, 200 a row, C = 28: 304 -> 294 us a Hessian-vector product;
-// fewer or more quads, or two operands, are slower with that, 2 to 25 %)
+// 5 to 7 quads: a wave more per SIMD than the compiler would leave room for, at 1 to 2 spilled registers with 6 and 7 (6000 x 4000, 400 a row, C = 20: 70 -> 67 us a
+// Hessian-vector product; 40000 x 100000, 300 a row, C = 20: 291 -> 296; 60000 x 9000, C = 28, and 40628 x 279998, C = 20: within 1 %; fewer or more quads, or
+// two operands, are slower with that, 2 to 25 %)
 // SHARED: rows as long as a window are shared by the workgroups of the windows they reach over.  Without room for the shares the one in whose
 // window such a row starts takes all of it, window by window and in the same order of additions: the results are the same bit for bit.
 template <int NQ, int NPER, int NOPS, bool SHARED>

@@ -344,8 +344,8 @@ __global__ void state_init_kernel(DevState* st, const int32_t* outer_flag) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   st->loss = 0.0; st->gg = 0.0; st->rr = 0.0; st->gg_cg = 0.0; st->loss_new = 0.0; st->loss_initial = 0.0;
   st->alpha = 0.f;
-  st->cg_go = 0; st->cg_ok = 1; st->cg_alpha = 0.f; st->rr_prev = 0.0;
   st->newton_even = st->newton_odd = outer_flag ? *outer_flag : 1; st->cg_active = st->newton_even; st->cg_iters = 0; st->armijo_ok = 1; st->ls_evals = 0;
+  st->cg_go = 0; st->cg_ok = 1; st->cg_alpha = 0.f; st->rr_prev = 0.0;
   nadmm_stats* s = &st->stats;
   s->newton_iters = 0; s->cg_iters_total = 0; s->ls_evals_total = 0; s->armijo_failed = 0;
   s->loss_initial = 0.0; s->loss_final = 0.0; s->grad_norm_final = 0.0;

@@ -649,8 +649,8 @@ def test_wide_single_pass(n, p, C, pad):
     assert it.item() == it_ref and rel_l2(host(p_out), p_ref) <= TOL_ITERATE
 
 
-# 17 to 32 free classes from 97 columns on: 4 to 9 column steps for eight waves, so that some hold none; fewer than 7 steps take two sweeps from
-# 12289 rows on.  Four waves form the probabilities of a tile (with X): tiles of 1 to 16 rows, one and two blocks of classes, extra classes.
+# 17 to 32 free classes from 97 columns on: 4 to 9 column steps for eight waves, of which some hold none with 4 to 7; fewer than 7 steps take two sweeps
+# from 12289 rows on.  Four waves form the probabilities of a tile (with X): tiles of 1 to 16 rows, one and two blocks of classes, extra classes.
 @pytest.mark.parametrize("pad", [0, 1])
 @pytest.mark.parametrize("n,p,C", [(1, 97, 18), (33, 100, 20), (257, 128, 33), (4099, 129, 21), (12288, 190, 19), (12289, 190, 19), (300, 192, 26), (70, 193, 18),
                                    (12300, 200, 33), (530, 224, 20), (47, 256, 25), (1030, 257, 19), (31, 288, 33)])
