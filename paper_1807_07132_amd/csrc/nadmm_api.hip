@@ -404,7 +404,7 @@ ReduceArgs reduce_args(const nadmm_problem* prob, const Layout& L, void* ws, int
   r.scale = prob->loss_scale;
   r.kind = kind;
   r.V = XorV;
-  r.X = XorV;
+  r.X = kind == 0 ? nullptr : XorV;
   r.z = prob->d_z;
   r.y = prob->d_y;
   r.lambda = prob->lambda;

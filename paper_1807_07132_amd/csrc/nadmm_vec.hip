@@ -17,11 +17,13 @@ constexpr int kTail = 1024;
 // cross-lane shuffles of a double is twelve trips through the LDS pipe, one after the other).
 __device__ __forceinline__ double wave_sum(double v) { return mfma_detail::wave64_sum(v); }
 
-// Sum over the whole workgroup (fixed order); result valid in every thread.
+// Sum over the whole workgroup (fixed order); result valid in every thread.  THREADS: their number where it is a constant (blockDim.x lies behind
+// the arguments; where nothing else has fetched its line, waiting for it takes 0.15 us: 1665 x 17, C = 30, 21 CG iterations 306.9 us, 303.2 without).
+template <int THREADS = 0>
 __device__ __forceinline__ double block_sum(double v, double* sm /* >= 17 doubles */) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nw = (blockDim.x + 63) >> 6;
+  const int nw = THREADS > 0 ? THREADS / 64 : (blockDim.x + 63) >> 6;
   __syncthreads();  // previous users of sm are done
   if (lane == 0) sm[wave] = v;
   __syncthreads();
@@ -99,7 +101,7 @@ __device__ __forceinline__ void newton_head_body(const NewtonHeadArgs& a);  // d
 // FINISH: launched with one workgroup more, which finishes the objective after a gradient pass or does the work of
 // newton_head_kernel beside the first reduction of a CG solve (an instantiation of its own: that workgroup's registers
 // would cost the plain kernel its occupancy on long vectors).  STEP: with the sums of r_dot (an instantiation of
-// its own, and r_dot the last of the arguments: as a condition inside and in the middle of them every gradient took 0.2 us more).
+// its own: as a condition inside every gradient took 0.2 us more).
 template <bool FINISH, bool STEP = false>
 __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
   if (FINISH && blockIdx.x == gridDim.x - 1) {  // the workgroup beyond the last 32 elements
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(256) void reduce_out_kernel(const ReduceArgs a) {
     prod = mfma_detail::half32_sum(prod);
     if (el == 0) first[blockIdx.x] = prod;
     if constexpr (STEP) {
-      const int n = gridDim.x;
+      const int n = (int)((a.d + 31) >> 5);  // workgroups
       const double rv = ok ? (double)lin2 : 0.0, t = ok ? (double)out - (double)linear_factor(a.lambda, a.rho, a.rho_scale) * rv : 0.0;
       const double rt = mfma_detail::half32_sum(rv * t), tt = mfma_detail::half32_sum(t * t), rr = mfma_detail::half32_sum(rv * rv);
       if (el == 0) {
@@ -454,39 +456,31 @@ __device__ __forceinline__ void pack_element(float* __restrict__ pack, int pack_
 // C = 20: 159 -> 139 us; 3000 x 4000, C = 10: 231 -> 215; on 3000 sparse rows of 200 entries, p = 2500, C = 6: 157 -> 137.
 __global__ __launch_bounds__(kCgThreads) void cg_step_kernel(const CgUpdateArgs a) {
   __shared__ double sm[5 * (kCgThreads / 64)];
-  int64_t base = (int64_t)blockIdx.x * kCgChunk;
+  const int64_t base = (int64_t)blockIdx.x * kCgChunk;
   float x[kCgPerThread], pe[kCgPerThread], re[kCgPerThread], y[kCgPerThread];
-  auto request = [&]() {
 #pragma unroll
-    for (int u = 0; u < kCgPerThread; ++u) {
-      const int64_t e = base + threadIdx.x + u * kCgThreads, ec = e < a.d ? e : a.d - 1;
-      x[u] = a.dvec[ec];
-      pe[u] = a.pdir[ec];
-      re[u] = a.r[ec];
-      y[u] = a.q[ec];
-    }
-  };
-  request();
+  for (int u = 0; u < kCgPerThread; ++u) {
+    const int64_t e = base + threadIdx.x + u * kCgThreads, ec = e < a.d ? e : a.d - 1;
+    x[u] = a.dvec[ec];
+    pe[u] = a.pdir[ec];
+    re[u] = a.r[ec];
+    y[u] = a.q[ec];
+  }
   const CgStep s = cg_step_scalars<kCgThreads>(a, sm);
   if (!s.go) return;
-  while (true) {
 #pragma unroll
-    for (int u = 0; u < kCgPerThread; ++u) {
-      const int64_t e = base + threadIdx.x + u * kCgThreads;
-      if (e < a.d) {
-        const float r = fmaf(-s.al, y[u], re[u]);
-        a.r_out[e] = r;
-        a.pdir[e] = fmaf(s.al, x[u], pe[u]);
-        if (!s.stop) {
-          const float d = fmaf(s.be, x[u], r);
-          a.dvec[e] = d;
-          if (a.pack != nullptr) pack_element(a.pack, a.pack_ld, a.NC, e, d);
-        }
+  for (int u = 0; u < kCgPerThread; ++u) {
+    const int64_t e = base + threadIdx.x + u * kCgThreads;
+    if (e < a.d) {
+      const float r = fmaf(-s.al, y[u], re[u]);
+      a.r_out[e] = r;
+      a.pdir[e] = fmaf(s.al, x[u], pe[u]);
+      if (!s.stop) {
+        const float d = fmaf(s.be, x[u], r);
+        a.dvec[e] = d;
+        if (a.pack != nullptr) pack_element(a.pack, a.pack_ld, a.NC, e, d);
       }
     }
-    base += (int64_t)gridDim.x * kCgChunk;
-    if (base >= a.d) break;
-    request();
   }
 }
 
@@ -617,7 +611,7 @@ __global__ __launch_bounds__(kTail) void cg_reduce_update_kernel(const ReduceArg
     dv = dv_in;
     qv = fmaf(ra.lambda + rho_, dv, ra.scale * s2);
   }
-  const double dq = block_sum((double)dv * (double)qv, sm);
+  const double dq = block_sum<kTail>((double)dv * (double)qv, sm);
   if (!(dq > 0.0) || !isfinite(dq)) {  // no positive curvature: keep the current iterate
     __syncthreads();
     if (t == 0) st->cg_active = 0;
@@ -625,7 +619,7 @@ __global__ __launch_bounds__(kTail) void cg_reduce_update_kernel(const ReduceArg
   }
   const float al = (float)(rr / dq);
   const float rn = mine ? fmaf(-al, qv, r_in) : 0.f;
-  const double rr_new = block_sum((double)rn * (double)rn, sm);
+  const double rr_new = block_sum<kTail>((double)rn * (double)rn, sm);
   const bool stop = sqrt(rr_new) <= (double)a.tol * sqrt(gg);
   const float be = (float)(rr_new / rr);
   if (mine) {
@@ -1166,10 +1160,11 @@ hipError_t launch_reduce_out(const ReduceArgs& a, hipStream_t st) {
   if (a.has_head != 0 && (a.kind != 0 || a.d > kReduceFinishMax || a.lf_loss_out != nullptr || a.head.st == nullptr ||
                           a.head.gg_part == nullptr || a.head.pen_part == nullptr))
     return hipErrorInvalidValue;
-  if (a.r_dot != nullptr && (a.kind != 0 || a.has_head != 0 || a.d > kWideFrom || a.dot_part == nullptr)) return hipErrorInvalidValue;
+  const bool step = a.kind == 0 && a.r_dot != nullptr;
+  if (step && (a.has_head != 0 || a.d > kWideFrom || a.dot_part == nullptr)) return hipErrorInvalidValue;
   if (a.d > kWideFrom) hipLaunchKernelGGL(reduce_out_wide_kernel, dim3(blocks), dim3(256), 0, st, a);
   else if (a.lf_loss_out != nullptr || a.has_head != 0) hipLaunchKernelGGL(reduce_out_kernel<true>, dim3(blocks + 1), dim3(256), 0, st, a);
-  else if (a.r_dot != nullptr) hipLaunchKernelGGL((reduce_out_kernel<false, true>), dim3(blocks), dim3(256), 0, st, a);
+  else if (step) hipLaunchKernelGGL((reduce_out_kernel<false, true>), dim3(blocks), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(reduce_out_kernel<false>, dim3(blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }
