@@ -92,7 +92,9 @@ def run_step(L, slot, r, d, pdir, q, sums, ndot, p, NC, tol, lam, rho, scale, rr
 
 # p, NC, sums, wide: one element, parts of a workgroup's 2048, several workgroups, up to the last length; more sums than threads read at once
 SHAPES = [(1, 1, 1, False), (255, 1, 8, False), (2048, 1, 64, False), (683, 3, 1023, False), (65535, 2, 4096, False), (131072, 1, 4096, False),
-          (1000, 2, 63, True), (3072, 9, 864, True), (1500, 19, 891, True), (2048, 32, 2048, True)]
+          (1000, 2, 63, True), (3072, 9, 864, True), (1500, 19, 891, True), (2048, 32, 2048, True),
+          # one free class: 16-byte pieces of the vectors, the last one of 4, 1, 2 and 3 elements
+          (3072, 1, 96, True), (961, 1, 31, True), (1810, 1, 57, True), (2051, 1, 65, True)]
 
 
 @pytest.mark.parametrize("p,NC,ndot,wide", SHAPES)
@@ -138,7 +140,7 @@ def test_norm_of_the_new_residual(shim, p, NC, ndot, wide, cancel):
     assert rel_l2(t["d"], fma.astype(np.float64)) <= 1e-7
 
 
-@pytest.mark.parametrize("p,NC,ndot,wide", [(2049, 1, 65, False), (3072, 9, 864, True)])
+@pytest.mark.parametrize("p,NC,ndot,wide", [(2049, 1, 65, False), (3072, 9, 864, True), (1810, 1, 57, True)])
 @pytest.mark.parametrize("dq,active", [(0.0, 1), (-1.0, 1), (float("nan"), 1), (float("inf"), 1), (1.0, 0)])
 def test_update_that_is_not_made(shim, p, NC, ndot, wide, dq, active):
     """No positive curvature, or CG has stopped before: the iterate stays, the other slot says that CG has stopped."""

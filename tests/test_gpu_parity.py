@@ -697,7 +697,7 @@ def test_wide_cg_on_long_vectors(n, p, C, tol):
 
 # Iterations behind the one that met the tolerance leave everything as it is, however many there are (the update's state alternates between
 # two slots): one launch (general kernels, wide rows, sparse storage) and two, and a gradient of zero, where no iteration is made.
-@pytest.mark.parametrize("n,p,C,path", [(60, 1000, 6, 1), (300, 1100, 4, 4), (300, 2740, 10, 4), (24, 131073, 2, 1), (60, 2000, 3, 5)])
+@pytest.mark.parametrize("n,p,C,path", [(60, 1000, 6, 1), (300, 1100, 4, 4), (300, 1103, 2, 4), (300, 2740, 10, 4), (24, 131073, 2, 1), (60, 2000, 3, 5)])
 def test_cg_iterations_behind_the_last(n, p, C, path):
     w = workloads.generic(n, p, C, seed=n + p, x_std=0.5 / math.sqrt(p), mean=True)
     op = oracle_problem(w)
