@@ -413,8 +413,8 @@ constexpr int kCgChunk = kCgThreads * kCgPerThread;
 // Up to here the update is one launch.  What it costs against two is what each workgroup does for itself, 4 sums over d / 32 values and in the
 // worst case (cg_step_scalars) one over the vectors.  10 iterations with two launches and with one: wide rows, d = 27648: 349 and 320 us, 64512:
 // 586 and 549, 76000: 656 and 620, 114000: 832 and 796; sparse rows, 52500: 426 and 387, 126000: 470 and 437, 240000: 528 and 515.
-// An iteration whose sums cancel takes the kernel 6.9 us for 5.0 at 8192 unknowns, 12.4 for 5.7 at 27648, 22.1 for 6.2 at 65536 and 37.6 for 7.4 at 131072
-// (two launches: 9.3 at 27648, 10.9 at 131072, and a gap).  It takes 10^7 and more off the terms at once, as when CG has as many iterations as the data
+// An iteration whose sums cancel takes the kernel (launches one after the other on the same vectors) 5.7 us for 4.1 at 8192 unknowns, 9.6 for 4.8 at 27648,
+// 16.9 for 5.3 at 65536 and 28.6 for 6.1 at 131072 (two launches in a solve: 9.3 at 27648, 10.9 at 131072, and a gap).  It takes 10^7 and more off the terms at once, as when CG has as many iterations as the data
 // have directions (2 sparse rows, 131072 unknowns: about three of ten iterations, 436 us in all, 30 of them for each of the three).
 constexpr int64_t kCgStepMax = 131072;
 
