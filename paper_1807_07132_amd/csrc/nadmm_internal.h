@@ -66,11 +66,15 @@ struct DevState {
   int32_t cg_ok;    //   0 if the first kernel met non-positive curvature
   float cg_alpha;   //   step length of this CG iteration
   int32_t newton_odd;
+  int32_t pad_[2];  // one slot of cgs to a cache line: a kernel reads one while a workgroup of it writes the other
   double rr_prev;   //   ||r||^2 before this CG iteration
   CgSlot cgs[2];    // CG updates that several workgroups make (CgPend, cg_step_scalars)
   float cg_alphas[kCgHist];  // deferred CG update: step length of every iteration taken (p = sum_k alpha_k d_k)
   nadmm_stats stats;  // copied to the host at the end of nadmm_local_newton
 };
+
+static_assert(offsetof(DevState, cgs) / 128 == (offsetof(DevState, cgs) + sizeof(CgSlot) - 1) / 128 && (offsetof(DevState, cgs) + sizeof(CgSlot)) % 128 == 0,
+              "the slots' lines");
 
 // Iteration `iter` of Algorithm 3 is entered if its word is not 0.  Its head leaves in the other word whether the iteration goes on,
 // and the next iteration is entered by that.  A kernel that makes the head beside other work goes by the first word in all its
