@@ -25,12 +25,12 @@ LG_PER_STEP = 100
 # names the summary it comes from and the digest of the kernel sources it was measured with: if the sources of
 # that kernel path have changed since, the line reports traffic = null instead of a stale figure.
 MEASURED_HV_TRAFFIC = {
-    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "150190013db7"),
-    ("tall_binary_1375000x28_C2", 3): (154.2e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "f3e80051f4d0"),
-    ("wide_50000x3072_C10", 4): (684.6e6, "profiles/hessvec_wide_50000x3072_C10.md", "68a2f1e3807a"),
-    ("large_multiclass_250000x2000_C20", 4): (2184.5e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "68a2f1e3807a"),
+    ("image_like_60000x784_C10", 2): (207.1e6, "profiles/hessvec_fused_image_like_60000x784_C10.md", "e4e4b54a7cac"),
+    ("tall_binary_1375000x28_C2", 3): (154.2e6, "profiles/hessvec_thin_tall_binary_1375000x28_C2.md", "944e43d4a08d"),
+    ("wide_50000x3072_C10", 4): (684.6e6, "profiles/hessvec_wide_50000x3072_C10.md", "f4d0e57d35c7"),
+    ("large_multiclass_250000x2000_C20", 4): (2184.9e6, "profiles/hessvec_wide_large_multiclass_250000x2000_C20.md", "f4d0e57d35c7"),
     # sparse storage: bytes between the L2 caches and the memory side, most of them operand rows served by the Infinity Cache
-    ("e18_like_40628x279998_C20_sparse", 5): (12585.3e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "bc1a3b831845"),
+    ("e18_like_40628x279998_C20_sparse", 5): (12585.7e6, "profiles/hessvec_sparse_e18_like_40628x279998_C20.md", "38d598144758"),
 }
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1807_07132_amd", "csrc")
 PATH_SOURCES = {1: ["nadmm_generic.hip"], 2: ["nadmm_fused.hip", "nadmm_narrow.hip"], 3: ["nadmm_thin.hip", "nadmm_thin_block.hip"],

@@ -35,7 +35,7 @@
  *         (p <= 64) or 49152;
  *       p <= 960 and C-1 <= 16: the single-pass matrix-core kernel, 55-60 % of the HBM roofline with aligned rows;
  *       p <= 3072 and C-1 <= 16, or p <= 2048 and up to 32 free classes: a single-pass kernel for wide rows, 35-51 % (CG at
- *         50000 x 3072, C = 10: 51 %, stand-alone product 40 %; 250000 x 2000, C = 20: 44 and 35 %).  Two sweeps, about 30 %: everything
+ *         50000 x 3072, C = 10: 51 %, stand-alone product 41 %; 250000 x 2000, C = 20: 44 and 35 %).  Two sweeps, about 30 %: everything
  *         wider and, with 17 and more free classes, up to 192 columns and more than 12288 rows; from 20 free classes on X and V together,
  *         and sweeps with X on many rows of more than 1536 columns (n > 22528, 4096 from 25 on);
  *       any other row stride (lda >= p) and a d_A that is only 4-byte aligned take variants of the same kernels that
